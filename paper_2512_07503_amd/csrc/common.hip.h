@@ -59,9 +59,8 @@ template <> struct Layout<float> {
     // one (page, kv head) block of keys / values, logical [page_tokens][hd]
     static SJD_HD size_t k_index(int t, int j, int hd) { return (size_t)t * hd + j; }
     static SJD_HD size_t v_index(int t, int j, int hd) { return (size_t)t * hd + j; }
-    // queries of one (sequence, branch, head): logical [L][hd]
+    // queries: tiles of 32 rows of one segment, [tile][head][32][hd]; element of row i (of the tile) of a head
     static SJD_HD size_t q_index(int i, int j, int hd) { return (size_t)i * hd + j; }
-    static SJD_HD size_t q_elems(int L, int hd) { return (size_t)L * hd; }
 };
 
 template <> struct Layout<bf16_t> {
@@ -87,12 +86,11 @@ template <> struct Layout<bf16_t> {
         size_t frag = ((size_t)(t >> 5) * 2 + ((t >> 4) & 1)) * (hd >> 5) + (j >> 5);
         return (frag * 64 + (g << 5) + (j & 31)) * 8 + e;
     }
-    // queries: operand with rows (columns of the transposed product) = window index, k = head dimension
-    // [i/32][j/16][lane = 32*((j%16)/8) + i%32][j%8]
+    // queries: tiles of 32 rows of one segment, [tile][head][32 * hd]; a tile of a head is an operand with rows (columns
+    // of the transposed product) = row i of the tile, k = head dimension: [j/16][lane = 32*((j%16)/8) + i][j%8]
     static SJD_HD size_t q_index(int i, int j, int hd) {
-        return ((((size_t)(i >> 5) * (hd >> 4) + (j >> 4)) * 64) + (((j >> 3) & 1) << 5) + (i & 31)) * 8 + (j & 7);
+        return ((size_t)(j >> 4) * 64 + (((j >> 3) & 1) << 5) + i) * 8 + (j & 7);
     }
-    static SJD_HD size_t q_elems(int L, int hd) { return (size_t)ceil_div(L, 32) * 32 * hd; }
 };
 
 // ---------------------------------------------------------------------------------------------

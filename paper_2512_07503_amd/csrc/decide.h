@@ -53,21 +53,39 @@ struct SamplingParams {
     int32_t init_mode, row_width;  // Sec. 4.2 initialisation of new slots (see sjd_sampling)
 };
 
-// Rows of the forward: token and position per GEMM row, cache length and active rows per segment
+// Rows of a forward: token and position per GEMM row, cache length and active rows per segment
 // (segment = sequence * 2 + branch).
+// A decoding step gives every segment L consecutive rows (row m: segment m / L, window index m % L), idle ones included,
+// and the pointers of the second group are NULL.  A prefill forward packs the prompts' rows without gaps, whatever
+// their lengths: segment s has rows [seg_row0[s], seg_row0[s] + seg_n[s]).
 struct RowMap {
-    int32_t *row_tok;  // [S*2*L]  token id, -1 = inactive row
-    int32_t *row_pos;  // [S*2*L]
-    int32_t *seg_kv;   // [S*2]
-    int32_t *seg_n;    // [S*2]
+    const int32_t *row_tok;  // [rows]      token id, -1 = inactive row
+    const int32_t *row_pos;  // [rows]
+    const int32_t *seg_kv;   // [segments]  cached positions before this forward's rows
+    const int32_t *seg_n;    // [segments]  active rows
+    const int32_t *row_seg;  // [rows]      packed rows: the row's segment
+    const int32_t *seg_row0; // [segments]  ... a segment's first row
+    const int32_t *seg_q0;   // [segments]  ... its first tile of 32 queries in the attention's query buffer
 };
+// segment and index within the segment of row m (L rows per segment unless packed), and its segment's first query tile
+__host__ __device__ inline void row_place(const RowMap &rm, int L, int m, int &seg, int &i_win, int &q_tile0) {
+    if (rm.row_seg) {
+        seg = rm.row_seg[m];
+        i_win = m - rm.seg_row0[seg];
+        q_tile0 = rm.seg_q0[seg];
+    } else {
+        seg = m / L;
+        i_win = m % L;
+        q_tile0 = seg * ((L + 31) / 32);
+    }
+}
 
 hipError_t launch_init_window(hipStream_t st, const DecideState &d, const SamplingParams &sp, int n_seqs, int max_seqs,
                               const int32_t *prompt_last /*[S][2]*/, const int32_t *prompt_len /*[S][2]*/,
                               const int32_t *n_image /*[S]*/);
-hipError_t launch_stage_window(hipStream_t st, const DecideState &d, const RowMap &rm, int n_seqs);
-hipError_t launch_stage_prompt(hipStream_t st, const RowMap &rm, const int32_t *prompt /*[S][2][max_prompt]*/,
-                               const int32_t *prompt_len, int max_prompt, int chunk, int L, int n_seqs);
+// writes the row map of a decoding step; row_tok, row_pos [n_seqs * 2 * L], seg_kv, seg_n [n_seqs * 2]
+hipError_t launch_stage_window(hipStream_t st, const DecideState &d, int32_t *row_tok, int32_t *row_pos, int32_t *seg_kv,
+                               int32_t *seg_n, int n_seqs);
 // logits: [n_seqs][2][L][V]; z (may be NULL): the guided logits [n_seqs][L][V] already combined by the vocabulary head,
 // read instead of the logits
 hipError_t launch_sample_rows(hipStream_t st, const DecideState &d, const SamplingParams &sp, const float *logits,

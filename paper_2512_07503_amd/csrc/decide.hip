@@ -505,32 +505,17 @@ __global__ void init_window_kernel(DecideState d, uint64_t seed, int n_seqs, con
 }
 
 // Rows of the coming forward over the window; also advances the step counter.
-__global__ void stage_window_kernel(DecideState d, RowMap rm, int n_seqs) {
+__global__ void stage_window_kernel(DecideState d, int32_t *row_tok, int32_t *row_pos, int32_t *seg_kv, int32_t *seg_n, int n_seqs) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m == 0) *d.step += 1u;
     if (m >= n_seqs * 2 * d.L) return;
     const int k = m % d.L, seg = m / d.L, s = seg >> 1;
     const int Le = d.Le[s];
     const int kv = d.kv_len[seg];
-    rm.row_tok[m] = k < Le ? (k == 0 ? d.anchor[seg] : d.win_tok[s * d.L + k]) : -1;
-    rm.row_pos[m] = kv + k;
-    if (k == 0) { rm.seg_kv[seg] = kv; rm.seg_n[seg] = Le; }
+    row_tok[m] = k < Le ? (k == 0 ? d.anchor[seg] : d.win_tok[s * d.L + k]) : -1;
+    row_pos[m] = kv + k;
+    if (k == 0) { seg_kv[seg] = kv; seg_n[seg] = Le; }
     if (k == 0 && (seg & 1) == 0) d.acc_len[s] = Le - 1;   // "every draft accepted" until the verification finds a rejection
-}
-
-// Rows of prefill chunk `chunk`: prompt positions chunk*L .. chunk*L + L - 1 of every segment, as far
-// as they lie before the last prompt token.
-__global__ void stage_prompt_kernel(RowMap rm, const int32_t *prompt, const int32_t *prompt_len, int max_prompt, int chunk,
-                                    int L, int n_seqs) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n_seqs * 2 * L) return;
-    const int k = m % L, seg = m / L;
-    const int start = chunk * L;
-    int n = prompt_len[seg] - 1 - start;
-    n = n < 0 ? 0 : (n > L ? L : n);
-    rm.row_tok[m] = k < n ? prompt[(long)seg * max_prompt + start + k] : -1;
-    rm.row_pos[m] = start + k;
-    if (k == 0) { rm.seg_kv[seg] = start; rm.seg_n[seg] = n; }
 }
 
 constexpr int kRefUniform = -1, kRefOneHot = -2, kRefHist0 = -3;  // values of ref_row below 0 (<= -3: kept row -3 - ref)
@@ -931,16 +916,10 @@ hipError_t launch_init_window(hipStream_t st, const DecideState &d, const Sampli
     return hipGetLastError();
 }
 
-hipError_t launch_stage_window(hipStream_t st, const DecideState &d, const RowMap &rm, int n_seqs) {
+hipError_t launch_stage_window(hipStream_t st, const DecideState &d, int32_t *row_tok, int32_t *row_pos, int32_t *seg_kv,
+                               int32_t *seg_n, int n_seqs) {
     const int M = n_seqs * 2 * d.L;
-    stage_window_kernel<<<ceil_div(M, 256), 256, 0, st>>>(d, rm, n_seqs);
-    return hipGetLastError();
-}
-
-hipError_t launch_stage_prompt(hipStream_t st, const RowMap &rm, const int32_t *prompt, const int32_t *prompt_len,
-                               int max_prompt, int chunk, int L, int n_seqs) {
-    const int M = n_seqs * 2 * L;
-    stage_prompt_kernel<<<ceil_div(M, 256), 256, 0, st>>>(rm, prompt, prompt_len, max_prompt, chunk, L, n_seqs);
+    stage_window_kernel<<<ceil_div(M, 256), 256, 0, st>>>(d, row_tok, row_pos, seg_kv, seg_n, n_seqs);
     return hipGetLastError();
 }
 

@@ -9,14 +9,14 @@
 // One wavefront per (row, head): scores into LDS, softmax, then lanes split the head dimension.
 // out_act (GEMM-operand layout [M][H*hd] of T) and / or out_plain ([M][H][hd] fp32) receive the result.
 template <typename T>
-__global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool, const int32_t *__restrict__ row_tok,
-                                           const int32_t *__restrict__ seg_kv, T *__restrict__ out_act,
+__global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool, RowMap rm, T *__restrict__ out_act,
                                            float *__restrict__ out_plain, int L, int H, int Hkv, int hd, float scale) {
     extern __shared__ float smem[];
     float *qs = smem, *sc = smem + hd;
     const int m = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-    const int seg = m / L, i_win = m % L;
-    if (row_tok[m] < 0) {
+    int seg, i_win, q_tile0;
+    row_place(rm, L, m, seg, i_win, q_tile0);
+    if (rm.row_tok[m] < 0) {
         for (int j = lane; j < hd; j += 64) {
             if (out_act) out_act[Layout<T>::a_index(m, h * hd + j, H * hd)] = from_float<T>(0.0f);
             if (out_plain) out_plain[((size_t)m * H + h) * hd + j] = 0.0f;
@@ -24,9 +24,9 @@ __global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool,
         return;
     }
     const int kvh = h / (H / Hkv);
-    const int n_vis = seg_kv[seg] + i_win + 1;
-    const T *qsrc = q + ((size_t)seg * H + h) * Layout<T>::q_elems(L, hd);
-    for (int j = lane; j < hd; j += 64) qs[j] = to_float<T>(qsrc[Layout<T>::q_index(i_win, j, hd)]);
+    const int n_vis = rm.seg_kv[seg] + i_win + 1;
+    const T *qsrc = q + ((size_t)(q_tile0 + (i_win >> 5)) * H + h) * 32 * hd;
+    for (int j = lane; j < hd; j += 64) qs[j] = to_float<T>(qsrc[Layout<T>::q_index(i_win & 31, j, hd)]);
     __syncthreads();
     const size_t blk = (size_t)pool.page_tokens * hd;
     const int32_t *pt = pool.page_table + (size_t)seg * pool.pages_per_seg;
@@ -63,11 +63,10 @@ __global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool,
 }
 
 template <typename T>
-inline hipError_t launch_attention_reference(hipStream_t st, const T *q, const KvPool &pool, const int32_t *row_tok,
-                                             const int32_t *seg_kv, T *out_act, float *out_plain, int M, int L, int H, int Hkv,
-                                             int hd, int max_visible) {
+inline hipError_t launch_attention_reference(hipStream_t st, const T *q, const KvPool &pool, const RowMap &rm, T *out_act,
+                                             float *out_plain, int M, int L, int H, int Hkv, int hd, int max_visible) {
     const size_t smem = sizeof(float) * (size_t)(hd + max_visible);
-    attention_reference_kernel<T><<<dim3(M, H), 64, smem, st>>>(q, pool, row_tok, seg_kv, out_act, out_plain, L, H, Hkv, hd,
+    attention_reference_kernel<T><<<dim3(M, H), 64, smem, st>>>(q, pool, rm, out_act, out_plain, L, H, Hkv, hd,
                                                                 1.0f / sqrtf((float)hd));
     return hipGetLastError();
 }
@@ -87,11 +86,11 @@ __global__ void pack_kv_kernel(const T *__restrict__ ksrc, const T *__restrict__
 
 // plain [n][H][hd] queries of one segment -> attention operand layout
 template <typename T>
-__global__ void pack_q_kernel(const T *__restrict__ src, T *__restrict__ dst, int n, int H, int hd, int L) {
+__global__ void pack_q_kernel(const T *__restrict__ src, T *__restrict__ dst, int n, int H, int hd) {
     const size_t total = (size_t)n * H * hd;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
         const int j = (int)(idx % hd), h = (int)((idx / hd) % H), i = (int)(idx / ((size_t)hd * H));
-        dst[(size_t)h * Layout<T>::q_elems(L, hd) + Layout<T>::q_index(i, j, hd)] = src[idx];
+        dst[((size_t)(i >> 5) * H + h) * 32 * hd + Layout<T>::q_index(i & 31, j, hd)] = src[idx];
     }
 }
 
@@ -111,17 +110,15 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 hw_bf16x2_t __attribute__((ext_vector_type(2)));
 
 struct AttnArgs {
-    const bf16_t *q;       // [segments][H][q_elems(L, hd)]
+    const bf16_t *q;       // [query tiles][H][32 * hd]
     KvPool pool;
-    const int32_t *row_tok;  // [segments * L]
-    const int32_t *seg_kv;   // cached positions per segment
-    const int32_t *seg_n;    // active window rows per segment
+    RowMap rm;               // segments of L rows each, or (one-pass kernel only) packed rows
     float *part_o;           // [segments * H * n_qt * n_chunks][32][hd]
     float *part_ml;          // [segments * H * n_qt * n_chunks][2][32]  (running max, running sum)
     bf16_t *out_act;         // [M][H * hd] GEMM-operand layout
     float *out_plain;        // optional [M][H][hd]
     int L, H, Hkv, hd, chunk, n_chunks;
-    int n_qt;                // query tiles of 32 window rows = ceil(L / 32)
+    int n_qt;                // query tiles of 32 rows per segment = ceil(L / 32) (packed rows: of the longest segment)
     float scale_log2e;       // 1 / sqrt(hd) * log2(e)
 };
 
@@ -132,8 +129,8 @@ template <int HD, int D>
 SJD_D void attention_wave(const AttnArgs &a, int seg, int h, int kvh, int qt, int t_begin, int t_end, int t_stride, int kv, int n_tot, int lane,
                           f32x16 (&o)[HD / 32], float &m_run, float &l_run) {
     constexpr int KF = HD / 16, DB = HD / 32;
-    const u32x4 *qp = reinterpret_cast<const u32x4 *>(a.q + ((size_t)seg * a.H + h) * Layout<bf16_t>::q_elems(a.L, HD)) +
-                      (size_t)qt * KF * 64 + lane;
+    const int q_tile = (a.rm.seg_q0 ? a.rm.seg_q0[seg] : seg * a.n_qt) + qt;
+    const u32x4 *qp = reinterpret_cast<const u32x4 *>(a.q + ((size_t)q_tile * a.H + h) * 32 * HD) + lane;
     u32x4 qf[KF];
 #pragma unroll
     for (int kb = 0; kb < KF; ++kb) qf[kb] = qp[kb * 64];
@@ -258,8 +255,8 @@ __global__ __launch_bounds__(256) void attention_mfma_kernel(AttnArgs a) {
     const int G = a.H / a.Hkv;
     const int c = blockIdx.x, kvh = blockIdx.y, seg = blockIdx.z / a.n_qt, qt = blockIdx.z % a.n_qt;
     const int h = kvh * G + wave;
-    const int n_act = a.seg_n[seg];
-    const int kv = a.seg_kv[seg];
+    const int n_act = a.rm.seg_n[seg];
+    const int kv = a.rm.seg_kv[seg];
     const int n_tot = n_act > 0 ? kv + n_act : 0;
     const int n_vis = min(n_tot, kv + 32 * (qt + 1));  // nothing later is visible to this query tile
     const int t_begin = c * a.chunk;
@@ -294,8 +291,9 @@ __global__ __launch_bounds__(NS * 64) void attention_onepass_kernel(AttnArgs a) 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = blockIdx.x, seg = blockIdx.y, qt = blockIdx.z;
     const int kvh = h / (a.H / a.Hkv);
-    const int n_act = a.seg_n[seg];
-    const int kv = a.seg_kv[seg];
+    const int n_act = a.rm.seg_n[seg];
+    const int kv = a.rm.seg_kv[seg];
+    if (a.rm.seg_row0 && 32 * qt >= n_act) return;   // packed rows: a shorter segment
     const int n_tot = n_act > 0 ? kv + n_act : 0;
     const int n_vis = 32 * qt < n_act ? min(n_tot, kv + 32 * (qt + 1)) : 0;  // nothing later is visible to this query tile
     f32x16 o[DB];
@@ -319,9 +317,9 @@ __global__ __launch_bounds__(NS * 64) void attention_onepass_kernel(AttnArgs a) 
 #pragma unroll
     for (int w = 0; w < NS; ++w) denom += exp2f(ml[w][0][query] - m_use) * ml[w][1][query];
     const float scale = exp2f(m_run - m_use);  // 0 for a wavefront that saw nothing
-    const int m = seg * a.L + 32 * qt + query;
-    const bool row = 32 * qt + query < a.L;
-    const bool active = row && a.row_tok[m] >= 0 && denom > 0.0f;
+    const int m = (a.rm.seg_row0 ? a.rm.seg_row0[seg] : seg * a.L) + 32 * qt + query;
+    const bool row = 32 * qt + query < (a.rm.seg_row0 ? n_act : a.L);   // idle rows of a window are zeroed
+    const bool active = row && a.rm.row_tok[m] >= 0 && denom > 0.0f;
     const float inv = active ? 1.0f / denom : 0.0f;
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
@@ -358,9 +356,9 @@ __global__ __launch_bounds__(64) void attention_combine_kernel(AttnArgs a) {
     const int i_win = 32 * qt + iq;
     if (i_win >= a.L) return;
     const int m = seg * a.L + i_win;
-    const bool active = a.row_tok[m] >= 0;
-    const int kv = a.seg_kv[seg];
-    const int n_vis = min(kv + a.seg_n[seg], kv + 32 * (qt + 1));  // the chunks this row's query tile went through
+    const bool active = a.rm.row_tok[m] >= 0;
+    const int kv = a.rm.seg_kv[seg];
+    const int n_vis = min(kv + a.rm.seg_n[seg], kv + 32 * (qt + 1));  // the chunks this row's query tile went through
     const int nc = active ? (n_vis + a.chunk - 1) / a.chunk : 0;
     const size_t slot0 = (size_t)pair * a.n_chunks;
     const float *ml = a.part_ml + slot0 * 64 + iq;

@@ -64,15 +64,15 @@ struct KvPool {
 // qkv partial sums [splits][M][(H + 2 Hkv) * hd] -> rotated q (attention operand layout, per segment
 // and head), rotated k and v into the KV pages at the row's position.
 template <typename T>
-__global__ void rope_kv_kernel(const float *__restrict__ partial, int splits, int M, const int32_t *__restrict__ row_tok,
-                               const int32_t *__restrict__ row_pos, const float *__restrict__ rope_cos,
+__global__ void rope_kv_kernel(const float *__restrict__ partial, int splits, int M, RowMap rm, const float *__restrict__ rope_cos,
                                const float *__restrict__ rope_sin, T *__restrict__ q_out, KvPool pool, int L, int H,
                                int Hkv, int hd) {
     const int m = blockIdx.x;
-    if (row_tok[m] < 0) return;
-    const int seg = m / L, i_win = m % L, pos = row_pos[m];
+    if (rm.row_tok[m] < 0) return;
+    int seg, i_win, q_tile0;
+    row_place(rm, L, m, seg, i_win, q_tile0);
+    const int pos = rm.row_pos[m];
     const int half = hd >> 1, N = (H + 2 * Hkv) * hd;
-    const size_t qseg = Layout<T>::q_elems(L, hd);
     const int page = pool.page_table[seg * pool.pages_per_seg + pos / pool.page_tokens];
     const int t = pos % pool.page_tokens;
     const size_t blk = (size_t)pool.page_tokens * hd;
@@ -88,9 +88,9 @@ __global__ void rope_kv_kernel(const float *__restrict__ partial, int splits, in
         const float c = rope_cos[(size_t)pos * half + i], s = rope_sin[(size_t)pos * half + i];
         const float r0 = a * c - b * s, r1 = b * c + a * s;
         if (h < H) {
-            T *dst = q_out + ((size_t)seg * H + h) * qseg;
-            dst[Layout<T>::q_index(i_win, i, hd)] = from_float<T>(r0);
-            dst[Layout<T>::q_index(i_win, i + half, hd)] = from_float<T>(r1);
+            T *dst = q_out + ((size_t)(q_tile0 + (i_win >> 5)) * H + h) * 32 * hd;
+            dst[Layout<T>::q_index(i_win & 31, i, hd)] = from_float<T>(r0);
+            dst[Layout<T>::q_index(i_win & 31, i + half, hd)] = from_float<T>(r1);
         } else {
             T *dst = (T *)pool.k + ((size_t)page * Hkv + (h - H)) * blk;
             dst[Layout<T>::k_index(t, i, hd)] = from_float<T>(r0);

@@ -34,7 +34,7 @@ enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_HEAD = 3, EPI_PARTIAL = 4
 // f(row) + g(head dimension), so everything that depends on the row alone is worked out once per row:
 struct QkvRow {
     int pos;    // absolute position (rotary angle), -1 for a row that is not computed
-    int q_off;  // element offset of this row in the query buffer of head 0: sequence segment and window index
+    int q_off;  // element offset of this row in the query buffer for head 0: query tile and row of the tile
     int page;   // KV page of the position
     int k_off;  // row part of the element offset inside a (page, head) block of keys
     int v_off;  // same for values
@@ -63,7 +63,7 @@ struct SkinnyArgs {
     const float2 *row_rot;    // [M][hd / 2] (cos, sin) of the row's position; (1, 0) for rows that are not computed
     bf16_t *q_out;
     KvPool pool;
-    int L, H, Hkv, hd;
+    int H, Hkv, hd;
     // SWIGLU
     bf16_t *h;
     int F;
@@ -123,7 +123,7 @@ SJD_D void qkv_store(const SkinnyArgs &a, const QkvRow &r, int g, int col, float
         v1 = r1;
     }
     if (head < a.H) {
-        bf16_t *dst = a.q_out + (size_t)head * Layout<bf16_t>::q_elems(a.L, a.hd) + r.q_off;
+        bf16_t *dst = a.q_out + (size_t)head * 32 * a.hd + r.q_off;
         dst[Layout<bf16_t>::q_index(0, j0, a.hd)] = float_to_bf16(v0);
         dst[Layout<bf16_t>::q_index(0, j1, a.hd)] = float_to_bf16(v1);
     } else {
@@ -513,7 +513,7 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
 // also writes the row's entry of the tables that every QKV projection of this forward reads: destination offsets
 // (sequence segment, window index, KV page of the position) and the rotary (cos, sin) of the position.
 struct RowTables {
-    const int32_t *row_pos;
+    RowMap rm;
     const float *rope_cos, *rope_sin;   // [max_ctx][hd / 2]
     const int32_t *page_table;
     int pages_per_seg, page_tokens, L, H, hd;
@@ -522,18 +522,18 @@ struct RowTables {
     float *ssq_part;   // [M][ssq_n] sum of squares of the row in slot 0, zeros in the others (may be NULL)
     int ssq_n;
 };
-__global__ void embed_dual_kernel(const bf16_t *__restrict__ emb, const int32_t *__restrict__ row_tok, float *__restrict__ x,
-                                  bf16_t *__restrict__ xb, int d, RowTables t) {
+__global__ void embed_dual_kernel(const bf16_t *__restrict__ emb, float *__restrict__ x, bf16_t *__restrict__ xb, int d, RowTables t) {
     const int m = blockIdx.x;
-    const int tok = row_tok[m];
+    const int tok = t.rm.row_tok[m];
     const int half = t.hd >> 1;
-    const int pos = tok >= 0 ? t.row_pos[m] : -1;
+    const int pos = tok >= 0 ? t.rm.row_pos[m] : -1;
     if (threadIdx.x == 0) {
         QkvRow r;
         r.pos = pos; r.q_off = 0; r.page = 0; r.k_off = 0; r.v_off = 0;
         if (pos >= 0) {
-            const int seg = m / t.L, i_win = m % t.L;
-            r.q_off = seg * t.H * (int)Layout<bf16_t>::q_elems(t.L, t.hd) + (int)Layout<bf16_t>::q_index(i_win, 0, t.hd);
+            int seg, i_win, q_tile0;
+            row_place(t.rm, t.L, m, seg, i_win, q_tile0);
+            r.q_off = (q_tile0 + (i_win >> 5)) * t.H * 32 * t.hd + (int)Layout<bf16_t>::q_index(i_win & 31, 0, t.hd);
             r.page = t.page_table[seg * t.pages_per_seg + pos / t.page_tokens];
             const int tk = pos % t.page_tokens;
             r.k_off = (int)Layout<bf16_t>::k_index(tk, 0, t.hd);

@@ -54,6 +54,21 @@ struct LayerWeights {
     void *wqkv = nullptr, *wo = nullptr, *wgu = nullptr, *wdown = nullptr;
 };
 
+// The rows of one forward: a decoding step's (L per segment) or a packed piece of the prompts (L = 0).
+struct FwdRows {
+    int M = 0, n_segs = 0;
+    int L = 0;       // rows per segment; 0: packed
+    int n_qt = 0;    // query tiles of 32 rows of the longest segment
+    RowMap rm{};
+};
+
+// Rows of a prefill forward at most.  A prompt's forward is as wide as the prompts allow, not as the window: 120 prompt
+// tokens with a window of 1 used to be 119 forwards of two rows (131 ms on the 36 x 1280 shape, 2.1 ms as one forward of
+// 238).  2 000-token prompts on the 8 x 4096 shape with 14336-wide MLPs, rows per forward 64 / 1024 / 2048 / 4096: 62.8 /
+// 16.1 / 14.4 / 14.0 ms; from 2048 on the buffers only grow.  The reference kernels re-read a weight every 8 rows whatever
+// the forward's size: 512 rows fill the chip.
+constexpr int kPrefillRows = 2048, kPrefillRowsGeneric = 512;
+
 }  // namespace
 
 struct sjd_ctx {
@@ -108,9 +123,15 @@ struct sjd_ctx {
     bool keep_logits = false;
     void *xn = nullptr, *q = nullptr, *attn = nullptr, *h = nullptr;
     size_t partial_elems = 0;
-    RowMap rm{};
+    int32_t *win_row_tok = nullptr, *win_row_pos = nullptr, *win_seg_kv = nullptr, *win_seg_n = nullptr;  // a step's row map
     DecideState ds{};
-    int32_t *prompt_dev = nullptr, *prompt_len_dev = nullptr, *prompt_last_dev = nullptr, *n_image_dev = nullptr;
+    // what a prefill sends to the device, in one copy: the page table, the sequences' scalars, the packed rows and the
+    // segment tables of every prefill forward
+    int32_t *pre_dev = nullptr;
+    size_t pre_elems = 0;
+    std::vector<int32_t> pre_host;         // its source: stays until the copy has run
+    int pre_rows = 0;                      // rows of a prefill forward at most
+    int max_rows = 0;                      // rows the forward's buffers are sized for
     sjd_step_result *res_host = nullptr;
     std::vector<void *> allocations;
     Tracer tracer;
@@ -220,50 +241,49 @@ int run_gemm<bf16_t>(sjd_ctx *c, int cls, const bf16_t *A, const bf16_t *W, floa
 }
 
 // ---------------------------------------------------------------------------------------- attention
-template <typename T> int run_attention(sjd_ctx *c, const KvPool &pool, int M);
+template <typename T> int run_attention(sjd_ctx *c, const KvPool &pool, const FwdRows &fr);
 
-template <> int run_attention<float>(sjd_ctx *c, const KvPool &pool, int M) {
-    SJD_LAUNCH(c, KC_ATTENTION, launch_attention_reference<float>(c->stream, (const float *)c->q, pool, c->rm.row_tok, c->rm.seg_kv,
-                                                                  (float *)c->attn, nullptr, M, c->L, c->md.n_heads,
-                                                                  c->md.n_kv_heads, c->hd, c->max_visible));
+template <> int run_attention<float>(sjd_ctx *c, const KvPool &pool, const FwdRows &fr) {
+    SJD_LAUNCH(c, KC_ATTENTION, launch_attention_reference<float>(c->stream, (const float *)c->q, pool, fr.rm, (float *)c->attn, nullptr,
+                                                                  fr.M, fr.L, c->md.n_heads, c->md.n_kv_heads, c->hd, c->max_visible));
     return SJD_OK;
 }
 
-template <> int run_attention<bf16_t>(sjd_ctx *c, const KvPool &pool, int M) {
+template <> int run_attention<bf16_t>(sjd_ctx *c, const KvPool &pool, const FwdRows &fr) {
     if (!c->attn_mfma) {
-        SJD_LAUNCH(c, KC_ATTENTION, launch_attention_reference<bf16_t>(c->stream, (const bf16_t *)c->q, pool, c->rm.row_tok,
-                                                                       c->rm.seg_kv, (bf16_t *)c->attn, nullptr, M, c->L,
-                                                                       c->md.n_heads, c->md.n_kv_heads, c->hd, c->max_visible));
+        SJD_LAUNCH(c, KC_ATTENTION, launch_attention_reference<bf16_t>(c->stream, (const bf16_t *)c->q, pool, fr.rm, (bf16_t *)c->attn,
+                                                                       nullptr, fr.M, fr.L, c->md.n_heads, c->md.n_kv_heads, c->hd,
+                                                                       c->max_visible));
         return SJD_OK;
     }
     AttnArgs a;
     a.q = (const bf16_t *)c->q;
     a.pool = pool;
-    a.row_tok = c->rm.row_tok;
-    a.seg_kv = c->rm.seg_kv;
-    a.seg_n = c->rm.seg_n;
+    a.rm = fr.rm;
     a.part_o = c->part_o;
     a.part_ml = c->part_ml;
     a.out_act = (bf16_t *)c->attn;
     a.out_plain = nullptr;
-    a.L = c->L; a.H = c->md.n_heads; a.Hkv = c->md.n_kv_heads; a.hd = c->hd;
+    a.L = fr.L; a.H = c->md.n_heads; a.Hkv = c->md.n_kv_heads; a.hd = c->hd;
     a.chunk = c->attn_chunk;
     a.n_chunks = c->attn_nchunks;
-    a.n_qt = ceil_div(c->L, 32);
+    a.n_qt = fr.n_qt;
     a.scale_log2e = (float)(1.4426950408889634 / sqrt((double)c->hd));
-    SJD_LAUNCH(c, KC_ATTENTION, launch_attention_mfma(c->stream, a, M / c->L, c->attn_onepass));
+    // packed prompt rows: a workgroup per (query tile, head) is plenty of them, whatever the context
+    SJD_LAUNCH(c, KC_ATTENTION, launch_attention_mfma(c->stream, a, fr.n_segs, c->attn_onepass || fr.L == 0));
     return SJD_OK;
 }
 
 // ------------------------------------------------------------------------------------------ forward
-// Runs the rows described by c->rm through the model.  Keys and values of active rows are written to
-// their pages; with_head also produces fp32 logits [M][V_s].
-template <typename T> int forward(sjd_ctx *c, bool with_head) {
+// Runs the rows of fr through the model.  Keys and values of active rows are written to their pages; with_head also
+// produces fp32 logits [M][V_s].  Without the head the forward ends with the last layer's keys and values: nothing reads
+// what its attention and MLP would add to the rows.
+template <typename T> int forward(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     const sjd_model_desc &md = c->md;
-    const int M = c->n_seqs * 2 * c->L, d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd, F = md.d_ff;
+    const int M = fr.M, d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd, F = md.d_ff;
     const int Nqkv = (H + 2 * Hkv) * hd;
     hipStream_t st = c->stream;
-    SJD_LAUNCH(c, KC_EMBED, after([&] { embed_kernel<T><<<M, 256, 0, st>>>((const T *)c->tok_emb, c->rm.row_tok, c->x, d); }));
+    SJD_LAUNCH(c, KC_EMBED, after([&] { embed_kernel<T><<<M, 256, 0, st>>>((const T *)c->tok_emb, fr.rm.row_tok, c->x, d); }));
     int down_splits = 0;
     for (int l = 0; l < md.n_layers; ++l) {
         const LayerWeights &lw = c->layers[l];
@@ -282,10 +302,11 @@ template <typename T> int forward(sjd_ctx *c, bool with_head) {
         int rc = run_gemm<T>(c, KC_GEMM_QKV, (const T *)c->xn, (const T *)lw.wqkv, c->partial, M, Nqkv, d, 0, &splits);
         if (rc) return rc;
         SJD_LAUNCH(c, KC_ROPE_KV, after([&] {
-                       rope_kv_kernel<T><<<M, 256, 0, st>>>(c->partial, splits, M, c->rm.row_tok, c->rm.row_pos, c->rope_cos,
-                                                            c->rope_sin, (T *)c->q, pool, c->L, H, Hkv, hd);
+                       rope_kv_kernel<T><<<M, 256, 0, st>>>(c->partial, splits, M, fr.rm, c->rope_cos, c->rope_sin, (T *)c->q, pool, fr.L,
+                                                            H, Hkv, hd);
                    }));
-        if ((rc = run_attention<T>(c, pool, M))) return rc;
+        if (!with_head && l + 1 == md.n_layers) return SJD_OK;
+        if ((rc = run_attention<T>(c, pool, fr))) return rc;
         rc = run_gemm<T>(c, KC_GEMM_O, (const T *)c->attn, (const T *)lw.wo, c->partial, M, d, H * hd, 0, &splits);
         if (rc) return rc;
         SJD_LAUNCH(c, KC_ADDNORM, after([&] {
@@ -309,11 +330,38 @@ template <typename T> int forward(sjd_ctx *c, bool with_head) {
     return SJD_OK;
 }
 
+// Many rows: LDS-staged 256 x 128 tiles (the projections are a dense contraction there, not a weight stream), provided
+// the model is wide enough for 256 x 128 tiles to fill the chip (QKV: >= 96 tiles); a narrow model with a long window
+// keeps the row-group kernels, which give it more workgroups.
+bool tile_forward(const sjd_ctx *c, int M) {
+    return M >= TILE_M && !(c->md.kernel_flags & SJD_KERNELS_ROWGROUPS) &&
+           ((c->md.kernel_flags & SJD_KERNELS_TILES) ||
+            ceil_div((c->md.n_heads + 2 * c->md.n_kv_heads) * (c->hd / 64) * 2, 4) * ceil_div(M, TILE_M) >= 96);
+}
+int resid_nbw(int d) { return ceil_div(d, 32) >= 128 ? 2 : 1; }   // column blocks per workgroup of an output / down projection
+bool resid_r2(const sjd_ctx *c, int M, int groups) {
+    return M > 32 && 2 * ceil_div(M, 64) * 8 * ceil_div(groups, 8) <= c->n_cus && !(c->md.kernel_flags & SJD_NO_ROW_SPLIT);
+}
+// Splits of K of an output / down projection of M rows (their partial sums are added by resid_reduce_kernel).
+int resid_splits(const sjd_ctx *c, int M, int K) {
+    const int d = c->md.d_model, KB = K / 16;
+    int ks = 1;
+    if (tile_forward(c, M)) {
+        ks = std::min(8, std::max(1, c->n_cus / (ceil_div(ceil_div(d, 64) * 2, 4) * ceil_div(M, TILE_M))));
+    } else {
+        const int nbw = resid_nbw(d), groups = ceil_div(ceil_div(d, 32), nbw), mt = M <= 32 || resid_r2(c, M, groups) ? 1 : 2;
+        if ((double)(nbw * 32 + mt * 32) * K * 2.0 <= 512e3) return 1;   // a workgroup's share is small: the whole of K
+        ks = std::min(8, std::max(1, c->n_cus / (groups * ceil_div(M, 64))));
+    }
+    while (ks > 1 && KB / ks < 32) --ks;
+    return ceil_div(KB, ceil_div(KB, ks));
+}
+
 // Small-M bf16 path: five kernels per layer (QKV+RoPE+KV write, attention, out+residual, gate/up+SwiGLU,
 // down+residual); c->xn holds the bf16 copy of the residual stream.
-int forward_fused(sjd_ctx *c, bool with_head) {
+int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     const sjd_model_desc &md = c->md;
-    const int M = c->n_seqs * 2 * c->L, d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd, F = md.d_ff;
+    const int M = fr.M, d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd, F = md.d_ff;
     // up to 64 rows: one row group; more: row groups of 64 over the same weights, the last one as ragged as it comes (the
     // activation buffers hold whole groups; rows past M are computed from whatever they hold and never stored)
     const int m_groups = ceil_div(M, 64);
@@ -322,11 +370,11 @@ int forward_fused(sjd_ctx *c, bool with_head) {
     hipStream_t st = c->stream;
     SJD_LAUNCH(c, KC_EMBED, after([&] {
                    RowTables rt;
-                   rt.row_pos = c->rm.row_pos; rt.rope_cos = c->rope_cos; rt.rope_sin = c->rope_sin;
+                   rt.rm = fr.rm; rt.rope_cos = c->rope_cos; rt.rope_sin = c->rope_sin;
                    rt.page_table = c->page_table; rt.pages_per_seg = c->pps; rt.page_tokens = c->pt;
-                   rt.L = c->L; rt.H = H; rt.hd = hd; rt.meta = c->row_meta; rt.rot = c->row_rot;
+                   rt.L = fr.L; rt.H = H; rt.hd = hd; rt.meta = c->row_meta; rt.rot = c->row_rot;
                    rt.ssq_part = c->row_ssq; rt.ssq_n = ceil_div(d, 256);
-                   embed_dual_kernel<<<M, 256, 0, st>>>((const bf16_t *)c->tok_emb, c->rm.row_tok, c->x, (bf16_t *)c->xn, d, rt);
+                   embed_dual_kernel<<<M, 256, 0, st>>>((const bf16_t *)c->tok_emb, c->x, (bf16_t *)c->xn, d, rt);
                }));
     SkinnyArgs a;
     memset(&a, 0, sizeof a);
@@ -338,12 +386,12 @@ int forward_fused(sjd_ctx *c, bool with_head) {
     a.k_rot = (md.kernel_flags & SJD_NO_K_ROTATION) ? 0 : 1;
     a.row_rot = c->row_rot;
     a.q_out = (bf16_t *)c->q;
-    a.L = c->L; a.H = H; a.Hkv = Hkv; a.hd = hd; a.F = F;
+    a.H = H; a.Hkv = Hkv; a.hd = hd; a.F = F;
     a.x = c->x;
     a.xb = (bf16_t *)c->xn;
     a.h = (bf16_t *)c->h;
     a.logits = c->logits;
-    const int nbw_d = ceil_div(d, 32) >= 128 ? 2 : 1;
+    const int nbw_d = resid_nbw(d);
     a.part = c->skinny_part;
     auto whole_k = [&]() { a.ksplit = 1; a.kb_per_split = a.KB; };
     auto no_room = [&]() { sjd_set_error(c->err, "split-K workspace too small"); return SJD_EINVAL; };
@@ -352,11 +400,7 @@ int forward_fused(sjd_ctx *c, bool with_head) {
     // shapes' gate/up and head) a CU's outstanding misses are the limit either way, the second wavefront of a SIMD
     // only queues behind the first, and 4 win by the cheaper LDS reduction.
     auto nw_for = [](int groups) { return groups >= 200 ? 4 : 8; };
-    // many rows: LDS-staged 256 x 128 tiles (the projections are a dense contraction there, not a weight stream)
-    // ... provided the model is wide enough for 256 x 128 tiles to fill the chip (QKV: >= 96 tiles); a narrow model
-    // with a long window keeps the row-group kernels, which give it more workgroups
-    const bool tile = M >= TILE_M && !(md.kernel_flags & SJD_KERNELS_ROWGROUPS) &&
-                      ((md.kernel_flags & SJD_KERNELS_TILES) || ceil_div((H + 2 * Hkv) * (hd / 64) * 2, 4) * ceil_div(M, TILE_M) >= 96);
+    const bool tile = tile_forward(c, M);
     // output / down projection: x += A W^T.  One kernel when a workgroup's share is small, else K split over
     // grid.y with the partial sums added by resid_reduce_kernel after the kernel boundary.
     // Every few-row projection launch carries extra workgroups that touch the weights of the projection after it,
@@ -367,17 +411,14 @@ int forward_fused(sjd_ctx *c, bool with_head) {
     // More than 32 rows and so few column groups that a workgroup per group and 32-row tile still finds a CU of its
     // own: row groups of 32 rows instead of 64 (all row groups of a column group on one XCD, whose L2 serves the
     // later readers of the weights).  Each workgroup pulls half the activations, twice as many CUs work.
-    auto rows2_for = [&](int groups) {
-        return MT == 2 && 2 * m_groups * 8 * ceil_div(groups, 8) <= n_cus && !(md.kernel_flags & SJD_NO_ROW_SPLIT);
-    };
+    auto rows2_for = [&](int groups) { return resid_r2(c, M, groups); };
     // computing workgroups of a launch over `groups` column groups
     auto compute_wgs = [&](int groups, bool r2, int row_split) {
         if (r2) return 2 * m_groups * 8 * ceil_div(groups, 8);
         if (row_split == 2) return 16 * ceil_div(groups, 8);
         return m_groups > 1 ? m_groups * 8 * ceil_div(groups, 8) : groups;
     };
-    const int mt_resid = rows2_for(groups_d) ? 1 : MT;   // 32-row tiles per workgroup of an output / down projection
-    auto resid_whole = [&](int K) { return (double)(nbw_d * 32 + mt_resid * 32) * K * 2.0 <= 512e3; };
+    auto resid_whole = [&](int K) { return resid_splits(c, M, K) == 1; };
     auto warm = [&](int cur_groups, const Proj &nx) {
         a.pf_wgs = 0;
         if (!c->l2_warm || tile || !nx.whole || !nx.W) return;
@@ -396,12 +437,12 @@ int forward_fused(sjd_ctx *c, bool with_head) {
     // that order); call after warm(): takes what is left of the CUs.
     auto warm_kv = [&](int cur_groups, const KvPool &pool) {
         a.kv_wgs = 0;
-        if (!c->l2_warm || tile || m_groups > 1 || !c->attn_mfma || !c->attn_onepass || c->L > 32) return;
-        const size_t kv_bytes = (size_t)(M / c->L) * Hkv * md.max_ctx * hd * 2 * sizeof(bf16_t);
+        if (!c->l2_warm || tile || m_groups > 1 || !c->attn_mfma || !c->attn_onepass || fr.L < 1 || fr.L > 32) return;
+        const size_t kv_bytes = (size_t)fr.n_segs * Hkv * md.max_ctx * hd * 2 * sizeof(bf16_t);
         const int room = (n_cus - cur_groups - a.pf_wgs) / 8 * 8;
         a.kv_wgs = std::max(0, std::min(room, (int)((kv_bytes / (48 << 10) + 7) / 8 * 8)));
-        a.kv_pairs = (M / c->L) * H;
-        a.kv_seg_kv = c->rm.seg_kv;
+        a.kv_pairs = fr.n_segs * H;
+        a.kv_seg_kv = fr.rm.seg_kv;
         a.kv_pool = pool;
         a.pf_sink = c->pf_sink;
     };
@@ -422,11 +463,9 @@ int forward_fused(sjd_ctx *c, bool with_head) {
         a.pf_wgs = 0;
         a.row_ssq_part = nullptr;
         if (tile) {
-            const int n_blocks = ceil_div(d, 64) * 2, wgs = ceil_div(n_blocks, 4) * ceil_div(M, TILE_M);
-            int ks = std::min(8, std::max(1, n_cus / wgs));
-            while (ks > 1 && a.KB / ks < 32) --ks;
-            a.kb_per_split = ceil_div(a.KB, ks);
-            a.ksplit = ceil_div(a.KB, a.kb_per_split);
+            const int n_blocks = ceil_div(d, 64) * 2;
+            a.ksplit = resid_splits(c, M, K);
+            a.kb_per_split = ceil_div(a.KB, a.ksplit);
             if (a.ksplit == 1) {
                 SJD_LAUNCH(c, cls, launch_tile<EPI_RESID>(st, a, n_blocks, tile_rows, mixed_ok));
                 ssq_ready = false;
@@ -442,13 +481,7 @@ int forward_fused(sjd_ctx *c, bool with_head) {
             return SJD_OK;
         }
         const int groups = ceil_div(ceil_div(d, 32), nbw_d);
-        const double wg_bytes = (double)(nbw_d * 32 + mt_resid * 32) * K * 2.0;
-        int ks = 1;
-        if (wg_bytes > 512e3) {
-            ks = std::min(8, std::max(1, n_cus / (groups * m_groups)));
-            while (ks > 1 && a.KB / ks < 32) --ks;
-        }
-        if (ks == 1) {
+        if (resid_splits(c, M, K) == 1) {
             whole_k();
             a.row_split = row_split_for(groups);
             const bool r2 = rows2_for(groups);
@@ -462,8 +495,8 @@ int forward_fused(sjd_ctx *c, bool with_head) {
             a.m_groups = m_groups;
             return SJD_OK;
         }
-        a.kb_per_split = ceil_div(a.KB, ks);
-        a.ksplit = ceil_div(a.KB, a.kb_per_split);
+        a.ksplit = resid_splits(c, M, K);
+        a.kb_per_split = ceil_div(a.KB, a.ksplit);
         if ((size_t)a.ksplit * M * d > c->skinny_part_elems) return no_room();
         SJD_LAUNCH(c, cls, launch_skinny<EPI_PARTIAL>(st, a, MT, groups, nbw_d, nw_for(groups * a.ksplit)));
         const int ksplit = a.ksplit;
@@ -492,14 +525,15 @@ int forward_fused(sjd_ctx *c, bool with_head) {
             const bool r2 = rows2_for(groups_qkv);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
             const int n_compute = compute_wgs(groups_qkv, r2, a.row_split);
-            warm(n_compute, Proj{lw.wo, groups_d, nbw_d, H * hd / 16, resid_whole(H * hd)});
+            warm(n_compute, with_head || l + 1 < md.n_layers ? Proj{lw.wo, groups_d, nbw_d, H * hd / 16, resid_whole(H * hd)} : none);
             if (l == 0) warm_kv(n_compute, pool);  // later layers: requested by the down projection before them
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_skinny<EPI_QKV>(st, a, r2 ? 1 : MT, groups_qkv, 2, nw_for(groups_qkv)));
             a.pf_wgs = a.kv_wgs = 0;
             a.row_split = 1;
             a.m_groups = m_groups;
         }
-        { int rc = run_attention<bf16_t>(c, pool, M); if (rc) return rc; }
+        if (!with_head && l + 1 == md.n_layers) return SJD_OK;
+        { int rc = run_attention<bf16_t>(c, pool, fr); if (rc) return rc; }
         { int rc = resid(KC_GEMM_O, c->attn, lw.wo, H * hd, Proj{lw.wgu, F / 32, 2, d / 16, true}, nullptr); if (rc) return rc; }
         a.A = (const bf16_t *)c->xn; a.W = (const bf16_t *)lw.wgu; a.KB = d / 16;
         if (tile) {
@@ -560,9 +594,9 @@ int forward_fused(sjd_ctx *c, bool with_head) {
     return SJD_OK;
 }
 
-int forward_any(sjd_ctx *c, bool with_head) {
-    if (c->fused) return forward_fused(c, with_head);
-    return c->md.dtype == SJD_F32 ? forward<float>(c, with_head) : forward<bf16_t>(c, with_head);
+int forward_any(sjd_ctx *c, const FwdRows &fr, bool with_head) {
+    if (c->fused) return forward_fused(c, fr, with_head);
+    return c->md.dtype == SJD_F32 ? forward<float>(c, fr, with_head) : forward<bf16_t>(c, fr, with_head);
 }
 
 // ------------------------------------------------------------------------------------------ create
@@ -664,16 +698,22 @@ int copy_weights_fused(sjd_ctx *c, const sjd_weights *w) {
 
 template <typename T> int alloc_buffers(sjd_ctx *c) {
     const sjd_model_desc &md = c->md;
-    const int S = c->S, L = c->L, M = S * 2 * L, d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd, F = md.d_ff;
+    const int S = c->S, L = c->L, d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd, F = md.d_ff;
     const int Nqkv = (H + 2 * Hkv) * hd;
     int rc;
+    // Rows of a forward: S * 2 windows, or as much of the prompts as one prefill forward takes (whole 32-row tiles)
+    const size_t prompt_rows = (size_t)S * 2 * (md.max_ctx - 1);
+    c->pre_rows = (int)std::min<size_t>(c->fused ? kPrefillRows : kPrefillRowsGeneric, (prompt_rows + 31) / 32 * 32);
+    const int M = c->max_rows = std::max(S * 2 * L, c->pre_rows);
     // KV pages
     c->pps = ceil_div(md.max_ctx, c->pt);
     c->n_pages = S * 2 * c->pps;
     c->pool_layer_bytes = (size_t)c->n_pages * Hkv * c->pt * hd * sizeof(T);
     if ((rc = dev_alloc(c, &c->kpool, c->pool_layer_bytes * md.n_layers))) return rc;
     if ((rc = dev_alloc(c, &c->vpool, c->pool_layer_bytes * md.n_layers))) return rc;
-    if ((rc = dev_alloc(c, &c->page_table, (size_t)S * 2 * c->pps * sizeof(int32_t)))) return rc;
+    c->pre_elems = (size_t)S * 2 * c->pps + 5 * (size_t)S + 3 * prompt_rows + (prompt_rows / c->pre_rows + 1) * 8 * (size_t)S;
+    if ((rc = dev_alloc(c, &c->pre_dev, c->pre_elems * sizeof(int32_t)))) return rc;
+    c->page_table = c->pre_dev;
     // workspaces
     if ((rc = dev_alloc(c, &c->x, (size_t)M * d * sizeof(float)))) return rc;
     size_t pe = 0;
@@ -681,28 +721,35 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
     for (auto &s : shapes) {
         size_t need = (size_t)M * s[0];
         if (md.dtype == SJD_BF16 && !(md.kernel_flags & SJD_KERNELS_REFERENCE)) {
-            // worst case over the number of sequences actually decoded (M = n * 2 * L)
-            for (int n = 1; n <= S; ++n) {
-                GemmPlan p = plan_gemm_bf16(n * 2 * L, s[0], s[1], 0);
-                size_t e = (size_t)p.splits * (n * 2 * L) * s[0];
+            // worst case over the number of sequences actually decoded (M = n * 2 * L) and the rows of a prefill forward
+            // (the plan of M rows is that of its 32-row tiles)
+            auto cover = [&](int m) {
+                GemmPlan p = plan_gemm_bf16(m, s[0], s[1], 0);
+                size_t e = (size_t)p.splits * m * s[0];
                 if (e > need) need = e;
-            }
+            };
+            for (int n = 1; n <= S; ++n) cover(n * 2 * L);
+            for (int m = 32; m <= c->pre_rows; m += 32) cover(m);
         }
         if (need > pe) pe = need;
     }
     c->partial_elems = pe;
     if ((rc = dev_alloc(c, &c->partial, pe * sizeof(float)))) return rc;
-    if ((rc = dev_alloc(c, &c->logits, (size_t)M * c->Vs * sizeof(float)))) return rc;
+    if ((rc = dev_alloc(c, &c->logits, (size_t)S * 2 * L * c->Vs * sizeof(float)))) return rc;
     const int Mpad = ceil_div(M, 64) * 64;   // whole 64-row groups: the fused projections read every row of the last one
     if ((rc = dev_alloc(c, &c->xn, Layout<T>::a_elems(Mpad, d) * sizeof(T)))) return rc;
     if ((rc = dev_alloc(c, &c->attn, Layout<T>::a_elems(Mpad, H * hd) * sizeof(T)))) return rc;
     if ((rc = dev_alloc(c, &c->h, Layout<T>::a_elems(Mpad, F) * sizeof(T)))) return rc;
-    if ((rc = dev_alloc(c, &c->q, (size_t)S * 2 * H * Layout<T>::q_elems(L, hd) * sizeof(T)))) return rc;
+    // queries: 32-row tiles of one segment each (packed segments leave a ragged tile each at most)
+    const size_t q_tiles = std::max((size_t)S * 2 * ceil_div(L, 32), (size_t)c->pre_rows / 32 + 2 * (size_t)S);
+    if ((rc = dev_alloc(c, &c->q, q_tiles * H * 32 * hd * sizeof(T)))) return rc;
     if (c->fused) {
         if ((rc = dev_alloc(c, &c->z, (size_t)S * L * c->Vs * sizeof(float)))) return rc;
         // partial tiles of K-split projections: at most 8 splits of the widest projection (2 column blocks, 2 row tiles)
         const int widest = std::max(std::max((H + 2 * Hkv) * (hd / 64), F / 32), ceil_div(c->Vs, 64));
-        c->skinny_part_elems = std::max((size_t)widest * 8 * (2 * 2 * 1024 + 64), (size_t)8 * M * d);
+        c->skinny_part_elems = std::max((size_t)widest * 8 * (2 * 2 * 1024 + 64), (size_t)8 * S * 2 * L * d);
+        for (int m = 1; m <= c->pre_rows; ++m)
+            for (int K : {H * hd, F}) c->skinny_part_elems = std::max(c->skinny_part_elems, (size_t)resid_splits(c, m, K) * m * d);
         if ((rc = dev_alloc(c, &c->skinny_part, c->skinny_part_elems * sizeof(float)))) return rc;
         if ((rc = dev_alloc(c, &c->pf_sink, 256))) return rc;
         if ((rc = dev_alloc(c, &c->row_ssq, (size_t)M * ceil_div(d, 256) * sizeof(float)))) return rc;
@@ -731,10 +778,10 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
 int alloc_state(sjd_ctx *c) {
     const int S = c->S, L = c->L, M = S * 2 * L;
     int rc;
-    if ((rc = dev_alloc(c, &c->rm.row_tok, (size_t)M * 4))) return rc;
-    if ((rc = dev_alloc(c, &c->rm.row_pos, (size_t)M * 4))) return rc;
-    if ((rc = dev_alloc(c, &c->rm.seg_kv, (size_t)S * 2 * 4))) return rc;
-    if ((rc = dev_alloc(c, &c->rm.seg_n, (size_t)S * 2 * 4))) return rc;
+    if ((rc = dev_alloc(c, &c->win_row_tok, (size_t)M * 4))) return rc;
+    if ((rc = dev_alloc(c, &c->win_row_pos, (size_t)M * 4))) return rc;
+    if ((rc = dev_alloc(c, &c->win_seg_kv, (size_t)S * 2 * 4))) return rc;
+    if ((rc = dev_alloc(c, &c->win_seg_n, (size_t)S * 2 * 4))) return rc;
     DecideState &d = c->ds;
     d.L = L; d.V = c->Vs; d.lo = c->md.sample_lo; d.max_img = c->md.max_ctx;
     if ((rc = dev_alloc(c, &d.win_tok, (size_t)S * L * 4))) return rc;
@@ -767,10 +814,6 @@ int alloc_state(sjd_ctx *c) {
     if ((rc = dev_alloc(c, &d.allow_lo, (size_t)S * d.max_img * 4))) return rc;
     if ((rc = dev_alloc(c, &d.allow_hi, (size_t)S * d.max_img * 4))) return rc;
     if ((rc = dev_alloc(c, &d.res, (size_t)S * sizeof(sjd_step_result)))) return rc;
-    if ((rc = dev_alloc(c, &c->prompt_dev, (size_t)S * 2 * c->md.max_ctx * 4))) return rc;
-    if ((rc = dev_alloc(c, &c->prompt_len_dev, (size_t)S * 2 * 4))) return rc;
-    if ((rc = dev_alloc(c, &c->prompt_last_dev, (size_t)S * 2 * 4))) return rc;
-    if ((rc = dev_alloc(c, &c->n_image_dev, (size_t)S * 4))) return rc;
     hipError_t e = hipHostMalloc((void **)&c->res_host, (size_t)S * sizeof(sjd_step_result), hipHostMallocDefault);
     if (e != hipSuccess) { sjd_set_error(c->err, "hipHostMalloc failed: %s", hipGetErrorString(e)); return SJD_ENOMEM; }
     return SJD_OK;
@@ -852,8 +895,14 @@ int finish_step(sjd_ctx *c, sjd_step_result *out) {
 
 // everything one decoding step launches, in stream order (the host reads the verdicts back afterwards)
 int enqueue_step(sjd_ctx *c) {
-    SJD_LAUNCH(c, KC_STAGE, launch_stage_window(c->stream, c->ds, c->rm, c->n_seqs));
-    int rc = forward_any(c, true);
+    SJD_LAUNCH(c, KC_STAGE, launch_stage_window(c->stream, c->ds, c->win_row_tok, c->win_row_pos, c->win_seg_kv, c->win_seg_n, c->n_seqs));
+    FwdRows fr;
+    fr.n_segs = c->n_seqs * 2;
+    fr.L = c->L;
+    fr.M = fr.n_segs * c->L;
+    fr.n_qt = ceil_div(c->L, 32);
+    fr.rm = {c->win_row_tok, c->win_row_pos, c->win_seg_kv, c->win_seg_n, nullptr, nullptr, nullptr};
+    int rc = forward_any(c, fr, true);
     if (rc) return rc;
     return run_decide(c, false);
 }
@@ -866,7 +915,7 @@ void drop_graph(sjd_ctx *c, int g) {
     c->graph_n_seqs[g] = 0;
 }
 
-// one-pass attention for the coming launches iff the longest visible context (cache + rows) is short
+// one-pass attention for a step's launches iff the longest visible context (cache + rows) is short
 void choose_attention(sjd_ctx *c, int max_kv) {
     c->attn_onepass = c->attn_mfma && c->attn_onepass_ok && attention_onepass_pays(max_kv + c->L, c->hd, c->n_seqs * 2 * c->md.n_heads, c->n_cus);
 }
@@ -957,7 +1006,7 @@ int sjd_prefill(sjd_ctx *c, int32_t n_seqs, const int32_t *const *cond_ids, cons
         return SJD_EINVAL;
     }
     if (n_seqs > c->S) { sjd_set_error(c->err, "n_seqs %d > max_seqs %d", n_seqs, c->S); return SJD_ECAPACITY; }
-    int max_prompt = 1;
+    size_t total_rows = 0;   // every prompt token but the last
     for (int s = 0; s < n_seqs; ++s) {
         if (!cond_ids[s] || !uncond_ids[s] || cond_len[s] < 1 || uncond_len[s] < 1 || n_image_tokens[s] < 1) {
             sjd_set_error(c->err, "sequence %d: null prompt, empty prompt or no image tokens", s);
@@ -971,14 +1020,13 @@ int sjd_prefill(sjd_ctx *c, int32_t n_seqs, const int32_t *const *cond_ids, cons
             if (cond_ids[s][i] < 0 || cond_ids[s][i] >= c->md.vocab) { sjd_set_error(c->err, "token id outside the vocabulary"); return SJD_EINVAL; }
         for (int i = 0; i < uncond_len[s]; ++i)
             if (uncond_ids[s][i] < 0 || uncond_ids[s][i] >= c->md.vocab) { sjd_set_error(c->err, "token id outside the vocabulary"); return SJD_EINVAL; }
-        if (cond_len[s] > max_prompt) max_prompt = cond_len[s];
-        if (uncond_len[s] > max_prompt) max_prompt = uncond_len[s];
+        total_rows += (size_t)(cond_len[s] - 1) + (uncond_len[s] - 1);
     }
     c->prefilled = false;
     c->n_seqs = n_seqs;
-    const int L = c->L;
-    // host staging
-    std::vector<int32_t> prompt((size_t)n_seqs * 2 * max_prompt, 0), plen((size_t)n_seqs * 2), plast((size_t)n_seqs * 2);
+    const int n_segs = n_seqs * 2;
+    hipStream_t st = c->stream;
+    SJD_HIP_TRY(c->err, hipStreamSynchronize(st));   // (after a failed call its copy may still be under way)
     std::vector<int32_t> table((size_t)c->S * 2 * c->pps, 0);
     // Pages are handed out round-robin over the segments, so that the pages of one segment are not
     // contiguous in the pool; a segment takes only the pages its prompt + image need.
@@ -995,34 +1043,64 @@ int sjd_prefill(sjd_ctx *c, int32_t n_seqs, const int32_t *const *cond_ids, cons
             for (int seg = 0; seg < n_seqs * 2; ++seg)
                 if (got[seg] < need[seg]) { table[(size_t)seg * c->pps + got[seg]++] = next++; --pending; }
     }
-    for (int s = 0; s < n_seqs; ++s) {
-        const int32_t *ids[2] = {cond_ids[s], uncond_ids[s]};
-        const int len[2] = {cond_len[s], uncond_len[s]};
-        for (int b = 0; b < 2; ++b) {
-            memcpy(&prompt[((size_t)s * 2 + b) * max_prompt], ids[b], sizeof(int32_t) * len[b]);
-            plen[s * 2 + b] = len[b];
-            plast[s * 2 + b] = ids[b][len[b] - 1];
-        }
-    }
-    hipStream_t st = c->stream;
-    SJD_HIP_TRY(c->err, hipMemcpyAsync(c->prompt_dev, prompt.data(), prompt.size() * 4, hipMemcpyHostToDevice, st));
-    SJD_HIP_TRY(c->err, hipMemcpyAsync(c->prompt_len_dev, plen.data(), plen.size() * 4, hipMemcpyHostToDevice, st));
-    SJD_HIP_TRY(c->err, hipMemcpyAsync(c->prompt_last_dev, plast.data(), plast.size() * 4, hipMemcpyHostToDevice, st));
-    SJD_HIP_TRY(c->err, hipMemcpyAsync(c->n_image_dev, n_image_tokens, (size_t)n_seqs * 4, hipMemcpyHostToDevice, st));
-    SJD_HIP_TRY(c->err, hipMemcpyAsync(c->page_table, table.data(), table.size() * 4, hipMemcpyHostToDevice, st));
-    SJD_HIP_TRY(c->err, hipStreamSynchronize(st));  // the host staging vectors may go away on an early return
     c->page_table_host = table;
     c->n_image_host.assign(n_image_tokens, n_image_tokens + n_seqs);
-    c->kv_host.assign((size_t)n_seqs * 2, 0);
-    for (int s = 0; s < n_seqs; ++s) { c->kv_host[s * 2] = cond_len[s] - 1; c->kv_host[s * 2 + 1] = uncond_len[s] - 1; }
-    const int chunks = ceil_div(max_prompt - 1, L);
-    for (int ch = 0; ch < chunks; ++ch) {
-        choose_attention(c, ch * L);
-        SJD_LAUNCH(c, KC_STAGE, launch_stage_prompt(st, c->rm, c->prompt_dev, c->prompt_len_dev, max_prompt, ch, L, n_seqs));
-        int rc = forward_any(c, false);
+    c->kv_host.assign((size_t)n_segs, 0);
+    // The rows of all prompts one after the other, cut into forwards of about equal size (whole tiles of 256 rows while
+    // there are several); a segment may start in one forward and go on in the next.
+    const size_t n_fwd_max = ceil_div_sz(total_rows, c->pre_rows);
+    const int per_fwd = n_fwd_max < 2 ? c->pre_rows : (int)std::min<size_t>(c->pre_rows, ceil_div_sz(ceil_div_sz(total_rows, n_fwd_max), 256) * 256);
+    std::vector<int32_t> &up = c->pre_host;
+    up.assign(table.size() + 5 * (size_t)n_seqs + 3 * total_rows, 0);
+    std::copy(table.begin(), table.end(), up.begin());
+    const size_t o_len = table.size(), o_last = o_len + n_segs, o_img = o_last + n_segs, o_tok = o_img + n_seqs, o_pos = o_tok + total_rows,
+                 o_seg = o_pos + total_rows, o_fwd = o_seg + total_rows;
+    std::vector<FwdRows> fwds;
+    size_t row = 0;
+    for (int seg = 0; seg < n_segs; ++seg) {
+        const int32_t *ids = seg & 1 ? uncond_ids[seg >> 1] : cond_ids[seg >> 1];
+        const int len = seg & 1 ? uncond_len[seg >> 1] : cond_len[seg >> 1];
+        up[o_len + seg] = len;
+        up[o_last + seg] = ids[len - 1];
+        c->kv_host[seg] = len - 1;
+        for (int pos = 0; pos < len - 1;) {
+            if (fwds.empty() || fwds.back().M == per_fwd) {
+                fwds.emplace_back();
+                fwds.back().n_segs = n_segs;
+                up.resize(up.size() + 4 * (size_t)n_segs, 0);
+            }
+            FwdRows &f = fwds.back();
+            const size_t f_row0 = row - f.M;
+            const int n = std::min(len - 1 - pos, per_fwd - f.M);
+            int32_t *tab = &up[o_fwd + (fwds.size() - 1) * 4 * (size_t)n_segs];   // seg_kv, seg_n, seg_row0, seg_q0
+            int q0 = 0;   // the segments of a forward come in order: the next free query tile
+            for (int i = 0; i < seg; ++i) q0 += ceil_div(tab[n_segs + i], 32);
+            tab[seg] = pos;
+            tab[n_segs + seg] = n;
+            tab[2 * n_segs + seg] = (int)(row - f_row0);
+            tab[3 * n_segs + seg] = q0;
+            for (int i = 0; i < n; ++i, ++row, ++pos) {
+                up[o_tok + row] = ids[pos];
+                up[o_pos + row] = pos;
+                up[o_seg + row] = seg;
+            }
+            f.M += n;
+            f.n_qt = std::max(f.n_qt, ceil_div(n, 32));
+        }
+    }
+    std::copy(n_image_tokens, n_image_tokens + n_seqs, up.begin() + o_img);
+    if (up.size() > c->pre_elems) { sjd_set_error(c->err, "prompt staging too small"); return SJD_EINVAL; }   // cannot happen: sized at create
+    SJD_HIP_TRY(c->err, hipMemcpyAsync(c->pre_dev, up.data(), up.size() * 4, hipMemcpyHostToDevice, st));
+    size_t row0 = 0;
+    for (size_t f = 0; f < fwds.size(); ++f) {
+        const int32_t *tab = c->pre_dev + o_fwd + f * 4 * (size_t)n_segs;
+        fwds[f].rm = {c->pre_dev + o_tok + row0, c->pre_dev + o_pos + row0, tab, tab + n_segs, c->pre_dev + o_seg + row0, tab + 2 * n_segs,
+                      tab + 3 * n_segs};
+        row0 += fwds[f].M;
+        int rc = forward_any(c, fwds[f], false);
         if (rc) return rc;
     }
-    SJD_LAUNCH(c, KC_STAGE, launch_init_window(st, c->ds, c->sp, n_seqs, c->S, c->prompt_last_dev, c->prompt_len_dev, c->n_image_dev));
+    SJD_LAUNCH(c, KC_STAGE, launch_init_window(st, c->ds, c->sp, n_seqs, c->S, c->pre_dev + o_last, c->pre_dev + o_len, c->pre_dev + o_img));
     SJD_HIP_TRY(c->err, hipStreamSynchronize(st));
     trace_collect(c);
     c->prefilled = true;
@@ -1065,7 +1143,7 @@ int sjd_debug_step_from_logits(sjd_ctx *c, const float *logits_host, sjd_step_re
     if (!c->prefilled) { sjd_set_error(c->err, "step before sjd_prefill"); return SJD_ESTATE; }
     SJD_HIP_TRY(c->err, hipMemcpyAsync(c->logits, logits_host, (size_t)c->n_seqs * 2 * c->L * c->Vs * sizeof(float),
                                        hipMemcpyHostToDevice, c->stream));
-    SJD_LAUNCH(c, KC_STAGE, launch_stage_window(c->stream, c->ds, c->rm, c->n_seqs));
+    SJD_LAUNCH(c, KC_STAGE, launch_stage_window(c->stream, c->ds, c->win_row_tok, c->win_row_pos, c->win_seg_kv, c->win_seg_n, c->n_seqs));
     int rc = run_decide(c, true);
     if (rc) return rc;
     return finish_step(c, out);

@@ -145,11 +145,11 @@ int op_attention(hipStream_t st, int flags, const void *q, const void *k, const 
     const int n_tok = ctx + n, pages = ceil_div(n_tok, pt);
     KvPool pool;
     T *qp;
-    int32_t *table, *row_tok, *seg_kv;
+    int32_t *table, *row_tok, *seg_kv, *seg_n;
     const size_t pool_bytes = (size_t)pages * Hkv * pt * hd * sizeof(T);
     if (!s.alloc(&pool.k, pool_bytes, st) || !s.alloc(&pool.v, pool_bytes, st) || !s.alloc(&table, (size_t)pages * 4, st) ||
-        !s.alloc(&row_tok, (size_t)n * 4, st) || !s.alloc(&seg_kv, 4, st) ||
-        !s.alloc(&qp, (size_t)H * Layout<T>::q_elems(n, hd) * sizeof(T), st) || !s.events()) {
+        !s.alloc(&row_tok, (size_t)n * 4, st) || !s.alloc(&seg_kv, 4, st) || !s.alloc(&seg_n, 4, st) ||
+        !s.alloc(&qp, (size_t)H * ceil_div(n, 32) * 32 * hd * sizeof(T), st) || !s.events()) {
         sjd_set_error(g_create_error, "allocation failed");
         return SJD_ENOMEM;
     }
@@ -157,30 +157,29 @@ int op_attention(hipStream_t st, int flags, const void *q, const void *k, const 
     for (int i = 0; i < pages; ++i) tab[i] = pages - 1 - i;  // pages deliberately out of order
     OP_TRY(hipMemcpyAsync(table, tab.data(), (size_t)pages * 4, hipMemcpyHostToDevice, st));
     OP_TRY(hipMemcpyAsync(seg_kv, &ctx, 4, hipMemcpyHostToDevice, st));
+    OP_TRY(hipMemcpyAsync(seg_n, &n, 4, hipMemcpyHostToDevice, st));
     OP_TRY(hipStreamSynchronize(st));
     pool.page_table = table;
     pool.pages_per_seg = pages;
     pool.page_tokens = pt;
     pack_kv_kernel<T><<<512, 256, 0, st>>>((const T *)k, (const T *)v, pool, n_tok, Hkv, hd);
     OP_TRY(hipGetLastError());
-    pack_q_kernel<T><<<64, 256, 0, st>>>((const T *)q, qp, n, H, hd, n);
+    pack_q_kernel<T><<<64, 256, 0, st>>>((const T *)q, qp, n, H, hd);
     OP_TRY(hipGetLastError());
     const bool mfma = std::is_same<T, bf16_t>::value && !(flags & SJD_KERNELS_REFERENCE) && attention_mfma_supported(n, H, Hkv, hd, pt);
+    const RowMap rm = {row_tok, nullptr, seg_kv, seg_n, nullptr, nullptr, nullptr};
     AttnArgs a;
     memset(&a, 0, sizeof a);
     if (mfma) {
-        int32_t *seg_n;
         a.chunk = 128;
         a.n_chunks = ceil_div(n_tok, a.chunk);
         a.n_qt = ceil_div(n, 32);
         if (!s.alloc(&a.part_o, (size_t)H * a.n_qt * a.n_chunks * 32 * hd * sizeof(float), st) ||
-            !s.alloc(&a.part_ml, (size_t)H * a.n_qt * a.n_chunks * 64 * sizeof(float), st) || !s.alloc(&seg_n, 4, st)) {
+            !s.alloc(&a.part_ml, (size_t)H * a.n_qt * a.n_chunks * 64 * sizeof(float), st)) {
             sjd_set_error(g_create_error, "allocation failed");
             return SJD_ENOMEM;
         }
-        OP_TRY(hipMemcpyAsync(seg_n, &n, 4, hipMemcpyHostToDevice, st));
-        OP_TRY(hipStreamSynchronize(st));
-        a.q = (const bf16_t *)qp; a.pool = pool; a.row_tok = row_tok; a.seg_kv = seg_kv; a.seg_n = seg_n;
+        a.q = (const bf16_t *)qp; a.pool = pool; a.rm = rm;
         a.out_act = nullptr; a.out_plain = out;
         a.L = n; a.H = H; a.Hkv = Hkv; a.hd = hd;
         a.scale_log2e = (float)(1.4426950408889634 / sqrt((double)hd));
@@ -188,7 +187,7 @@ int op_attention(hipStream_t st, int flags, const void *q, const void *k, const 
     OP_TRY(hipEventRecord(s.ev0, st));
     for (int r = 0; r < repeat; ++r) {
         if (mfma) OP_TRY(launch_attention_mfma(st, a, 1, !(flags & SJD_ATTENTION_CHUNKED) && attention_onepass_pays(n_tok, hd)));
-        else OP_TRY(launch_attention_reference<T>(st, qp, pool, row_tok, seg_kv, (T *)nullptr, out, n, n, H, Hkv, hd, n_tok + 1));
+        else OP_TRY(launch_attention_reference<T>(st, qp, pool, rm, (T *)nullptr, out, n, n, H, Hkv, hd, n_tok + 1));
     }
     OP_TRY(hipEventRecord(s.ev1, st));
     OP_TRY(hipStreamSynchronize(st));

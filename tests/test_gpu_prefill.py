@@ -1,0 +1,46 @@
+"""Prompts of unequal lengths, one-token prompts among them, packed into prefill forwards without gaps: the first steps'
+logits against the oracle, which runs every prompt on its own.  Tolerance of the small stress models: 8e-2 of a row's
+largest |logit| (tests/test_gpu_e2e.py says where it comes from), 1e-4 in fp32."""
+import numpy as np
+import pytest
+
+import workload
+from helpers import gpu_weights, logits_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("name,lens,flags", [
+    ("small_f32", [(1, 1)], 0),                                  # nothing to prefill
+    ("small_f32", [(40, 1), (2, 33), (65, 17)], 0),              # segments that start inside a query tile
+    ("small_f32", [(300, 290)], 0),                              # two forwards of at most 512 rows
+    ("small_bf16", [(200, 31), (97, 300)], 0),                   # generic projections, two forwards
+    ("small_fused64", [(33, 1), (1, 70), (32, 34)], 0),
+    ("small_fused64", [(1500, 1300)], 0),                        # a branch that starts in one forward and goes on in the next
+    ("small_fused64", [(90, 80), (100, 60)], 1),                 # reference kernels
+    ("small_fused64", [(90, 80), (100, 60)], 8),                 # chunked window attention for the steps
+    ("small_fused128", [(257, 1), (129, 70), (31, 32)], 0),
+    ("small_tile", [(400, 399), (127, 2), (258, 130)], 16),      # tile kernels, ragged last tile
+])
+def test_packed_prompts(oracle, name, lens, flags):
+    import paper_2512_07503_amd as sjd
+    cfg = workload.get_config(name)
+    arch, n = cfg["arch"], 40
+    S, L, max_ctx = len(lens), cfg["window"], max(max(p) for p in lens) + n
+    w = workload.make_weights(arch, cfg["seed"], 6.0, cfg["dtype"], std=0.08)
+    rng = np.random.default_rng(5)
+    cond = [rng.integers(0, arch["vocab"], c).astype(np.int32) for c, _ in lens]
+    uncond = [rng.integers(0, arch["vocab"], u).astype(np.int32) for _, u in lens]
+    o = oracle.Oracle(arch, w, L, max_ctx, top_k=cfg["top_k"], seed=3, max_seqs=S)
+    g = sjd.Decoder(arch, gpu_weights(w, cfg["dtype"]), cfg["dtype"], L, max_ctx, max_seqs=S, top_k=cfg["top_k"], seed=3,
+                    kernel_flags=flags | sjd.KEEP_LOGITS)
+    assert o.prefill(cond, uncond, [n] * S) == 0
+    for again in range(2):   # the second prefill of a context starts over
+        assert g.prefill(cond, uncond, [n] * S) == 0
+        les = [g.window(s)[2] for s in range(S)]
+        g.step()
+        if again == 0:
+            want = o.peek_logits()
+        worst = logits_error(g.logits(), want, les)
+        print(name, lens, flags, "logits error abs/rel:", worst)
+        assert worst[0] <= 1e-4 if cfg["dtype"] == "f32" else worst[1] <= 8e-2
