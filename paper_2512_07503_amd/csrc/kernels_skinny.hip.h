@@ -58,6 +58,10 @@ struct SkinnyArgs {
     // by the kernel that produced the rows; NULL: taken from the activation fragments inside the k-loop
     const float *row_ssq_part;
     int row_ssq_n;
+    // RESID: where a kernel leaves such partial sums for the next one (may be NULL), ssq_out_n per row: one per column group
+    // of the row-group kernels, one per wavefront's columns of the LDS kernels
+    float *ssq_out;
+    int ssq_out_n;
     // QKV: per-row tables written once per forward by embed_dual_kernel (no dependent loads in the projections)
     const QkvRow *row_meta;   // [M]
     const float2 *row_rot;    // [M][hd / 2] (cos, sin) of the row's position; (1, 0) for rows that are not computed
@@ -506,6 +510,19 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
             }
             if constexpr (EPI == EPI_QKV) qkv_store(a, qrow[j][hh], g, col, vals[0] * inv, vals[NBW - 1] * inv, rot_c[j][hh], rot_s[j][hh]);
             else skinny_epilogue<EPI, NBW>(a, ks, m, blk0, col, vals, inv, xin);
+            if constexpr (EPI == EPI_RESID) {
+                if (a.ssq_out) {   // the row's columns of this group lie in one half wavefront
+                    float sq = 0.0f;
+#pragma unroll
+                    for (int i = 0; i < NBW; ++i) {
+                        const float f = (blk0 + i) * 32 + col < a.N ? bf16_to_float(float_to_bf16(xin[i] + vals[i])) : 0.0f;
+                        sq = fmaf(f, f, sq);
+                    }
+#pragma unroll
+                    for (int off = 16; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+                    if (col == 0) a.ssq_out[(size_t)m * a.ssq_out_n + blk0 / NBW] = sq;
+                }
+            }
         }
 }
 

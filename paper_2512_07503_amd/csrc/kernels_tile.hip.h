@@ -328,6 +328,24 @@ inline int tile_rows_for(int M, int n_blocks, int ksplit, int n_cus) {
     return cost1 < cost2 ? 128 : 256;
 }
 
+// Time of a launch: 32-wide K stages x the busiest CU's tiles (the column tiles of an XCD run on its CUs only): 0.27 us a
+// 128-row tile (0.40 alone on its CU), 0.45 a 256-row tile, 0.27 per 128 x 128 in a launch of both heights.  Measured on
+// models 1280 to 4096 wide at 260 to 2040 rows.
+inline bool tile_two_heights(int M, int n_blocks, int ksplit, int n_cus) {
+    const int col_tiles = (n_blocks + 3) / 4, rt2 = (M + 255) / 256, rt1 = (M + 127) / 128;
+    return ksplit == 1 && rt1 > rt2 && col_tiles * rt2 > n_cus && col_tiles * rt2 < 2 * n_cus && n_cus / rt2 >= 8 && (col_tiles * rt1) % n_cus != 0;
+}
+inline double tile_us(int M, int n_blocks, int KB, int ksplit, int n_cus) {
+    const int col_tiles = (n_blocks + 3) / 4, rows = tile_rows_for(M, n_blocks, ksplit, n_cus);
+    const double stages = KB / (2.0 * ksplit);
+    if (tile_two_heights(M, n_blocks, ksplit, n_cus)) {
+        const int rt2 = (M + 255) / 256, ct_split = n_cus / rt2 / 8 * 8;
+        return 12.0 + stages * 0.27 * (2.0 * ct_split * rt2 + (double)(col_tiles - ct_split) * ((M + 127) / 128)) / n_cus;
+    }
+    const int per_xcd = (col_tiles + 7) / 8 * ((M + rows - 1) / rows) * ksplit, cus = n_cus >= 8 ? n_cus / 8 : 1, n = (per_xcd + cus - 1) / cus;
+    return 12.0 + stages * (rows == 256 ? 0.45 * n : n == 1 ? 0.40 : 0.27 * n);
+}
+
 // n_blocks = packed 32-column blocks of W.  The K range of a workgroup is a.kb_per_split k-blocks (grid.y = a.ksplit).
 template <int EPI>
 inline hipError_t launch_tile(hipStream_t st, const SkinnyArgs &a, int n_blocks, int tile_rows = 0, bool two_heights = true) {
@@ -345,8 +363,7 @@ inline hipError_t launch_tile(hipStream_t st, const SkinnyArgs &a, int n_blocks,
     const int rt2 = (a.M + 255) / 256, rt1 = (a.M + 127) / 128;
     // (not where 128-row tiles alone give every CU the same number of workgroups: 1024 x 12288 x 4096, three per CU,
     // 120.6 us against 132.7 mixed)
-    if (two_heights && tile_rows_in == 0 && EPI != EPI_HEAD && a.ksplit == 1 && rt1 > rt2 && col_tiles * rt2 > n_cus && col_tiles * rt2 < 2 * n_cus &&
-        n_cus / rt2 >= 8 && (col_tiles * rt1) % n_cus != 0) {
+    if (two_heights && tile_rows_in == 0 && EPI != EPI_HEAD && tile_two_heights(a.M, n_blocks, a.ksplit, n_cus)) {
         const int ct_split = n_cus / rt2 / 8 * 8;
         const int wg_split = ct_split * rt2, wg_rest = 8 * ((col_tiles - ct_split + 7) / 8) * rt1;
         if (ssq_loop) gemm_tile_mixed_kernel<EPI, true><<<dim3(wg_split + wg_rest, 1), 256, 0, st>>>(a, n_blocks, row_tiles32, col_tiles, ct_split, wg_split, rt2, rt1);

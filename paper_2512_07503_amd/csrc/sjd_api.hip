@@ -19,6 +19,7 @@
 #include "kernels_gemm.hip.h"
 #include "kernels_skinny.hip.h"
 #include "kernels_tile.hip.h"
+#include "kernels_lds.hip.h"
 
 void sjd_set_error(char *buf, const char *fmt, ...) {
     if (!buf) return;
@@ -97,7 +98,7 @@ struct sjd_ctx {
     bool attn_onepass = false;             // regime of the launches being enqueued
     std::vector<int32_t> kv_host;          // committed cache positions per segment (sequence * 2 + branch)
     float *part_o = nullptr, *part_ml = nullptr;
-    float *row_ssq = nullptr;              // [M][ceil(d / 256)] partial sums of squares of the residual stream's rows
+    float *row_ssq = nullptr;              // [M][up to ceil(d / 32)] partial sums of squares of the residual stream's rows
     QkvRow *row_meta = nullptr;            // per-row tables of the fused path, rewritten by every forward
     float2 *row_rot = nullptr;
     bool l2_warm = true;                   // projection launches touch the next projection's weights
@@ -330,31 +331,71 @@ template <typename T> int forward(sjd_ctx *c, const FwdRows &fr, bool with_head)
     return SJD_OK;
 }
 
-// Many rows: LDS-staged 256 x 128 tiles (the projections are a dense contraction there, not a weight stream), provided
-// the model is wide enough for 256 x 128 tiles to fill the chip (QKV: >= 96 tiles); a narrow model with a long window
-// keeps the row-group kernels, which give it more workgroups.
-bool tile_forward(const sjd_ctx *c, int M) {
-    return M >= TILE_M && !(c->md.kernel_flags & SJD_KERNELS_ROWGROUPS) &&
-           ((c->md.kernel_flags & SJD_KERNELS_TILES) ||
-            ceil_div((c->md.n_heads + 2 * c->md.n_kv_heads) * (c->hd / 64) * 2, 4) * ceil_div(M, TILE_M) >= 96);
-}
 int resid_nbw(int d) { return ceil_div(d, 32) >= 128 ? 2 : 1; }   // column blocks per workgroup of an output / down projection
-bool resid_r2(const sjd_ctx *c, int M, int groups) {
+// More than 32 rows and so few column groups that a workgroup per group and 32-row tile still finds a CU of its own
+bool rows_of_32(const sjd_ctx *c, int M, int groups) {
     return M > 32 && 2 * ceil_div(M, 64) * 8 * ceil_div(groups, 8) <= c->n_cus && !(c->md.kernel_flags & SJD_NO_ROW_SPLIT);
 }
-// Splits of K of an output / down projection of M rows (their partial sums are added by resid_reduce_kernel).
-int resid_splits(const sjd_ctx *c, int M, int K) {
-    const int d = c->md.d_model, KB = K / 16;
+
+// How a projection runs: row groups (lds < 0) or LDS tiles of shape `lds`; ks: splits of K (output / down projections, whose
+// partial sums resid_reduce_kernel adds); us: its expected time, on which the choice rests.
+struct ProjPlan { int lds, ks; double us; };
+ProjPlan with_lds(const sjd_ctx *c, int M, int n_blocks, int KB, int max_ks, ProjPlan p, double extra_us) {
+    if (M <= 64 || (c->md.kernel_flags & SJD_KERNELS_ROWGROUPS)) return p;
+    for (int cfg = 0; cfg < kLdsTiles; ++cfg)
+        for (int ks = 1; ks <= max_ks; ks *= 2) {
+            if (ks > 1 && KB / ks < 32) continue;
+            const double t = extra_us + lds_us(cfg, M, n_blocks, KB, ks, c->n_cus) + (ks > 1 ? reduce_us(M, c->md.d_model, ks) : 0.0);
+            if (t < p.us) p = {cfg, ks, t};
+        }
+    return p;
+}
+// QKV, gate/up and head: groups of two column blocks, whole K.  (2 us: the sums of squares that the row-group kernel takes
+// from its operands come from the writer of the rows with LDS tiles.)
+ProjPlan norm_plan(const sjd_ctx *c, int M, int groups) {
+    const int d = c->md.d_model, mt = M <= 32 || rows_of_32(c, M, groups) ? 1 : 2;
+    const ProjPlan p = {-1, 1, skinny_us(ceil_div(M, 32 * mt) * groups, (double)(64 + 32 * mt) * d * 2.0, true, c->n_cus)};
+    return with_lds(c, M, groups * 2, d / 16, 1, p, 2.0);
+}
+ProjPlan resid_plan(const sjd_ctx *c, int M, int K) {
+    const int d = c->md.d_model, KB = K / 16, nbw = resid_nbw(d), groups = ceil_div(ceil_div(d, 32), nbw);
+    const int mt = M <= 32 || rows_of_32(c, M, groups) ? 1 : 2;
+    const double wg_bytes = (double)(nbw * 32 + mt * 32) * K * 2.0;
     int ks = 1;
-    if (tile_forward(c, M)) {
-        ks = std::min(8, std::max(1, c->n_cus / (ceil_div(ceil_div(d, 64) * 2, 4) * ceil_div(M, TILE_M))));
-    } else {
-        const int nbw = resid_nbw(d), groups = ceil_div(ceil_div(d, 32), nbw), mt = M <= 32 || resid_r2(c, M, groups) ? 1 : 2;
-        if ((double)(nbw * 32 + mt * 32) * K * 2.0 <= 512e3) return 1;   // a workgroup's share is small: the whole of K
+    if (wg_bytes > 512e3) {   // one workgroup's share is too much for its CU
         ks = std::min(8, std::max(1, c->n_cus / (groups * ceil_div(M, 64))));
+        while (ks > 1 && KB / ks < 32) --ks;
+        ks = ceil_div(KB, ceil_div(KB, ks));
     }
+    const ProjPlan p = {-1, ks, skinny_us(ceil_div(M, 32 * mt) * groups * ks, wg_bytes / ks, false, c->n_cus) + (ks > 1 ? reduce_us(M, d, ks) : 0.0)};
+    return with_lds(c, M, ceil_div(d, 32), KB, 4, p, 0.0);
+}
+
+// The tile kernels (kernels_tile.hip.h): K splits of an output / down projection, and the same estimate for a layer.
+int tile_splits(const sjd_ctx *c, int M, int KB) {
+    int ks = std::min(8, std::max(1, c->n_cus / (ceil_div(ceil_div(c->md.d_model, 64) * 2, 4) * ceil_div(M, TILE_M))));
     while (ks > 1 && KB / ks < 32) --ks;
     return ceil_div(KB, ceil_div(KB, ks));
+}
+double tile_layer_us(const sjd_ctx *c, int M) {
+    const sjd_model_desc &md = c->md;
+    const int d = md.d_model;
+    auto resid = [&](int K) {
+        const int ks = tile_splits(c, M, K / 16);
+        return tile_us(M, ceil_div(d, 64) * 2, K / 16, ks, c->n_cus) + (ks > 1 ? reduce_us(M, d, ks) : 0.0);
+    };
+    return tile_us(M, (md.n_heads + 2 * md.n_kv_heads) * (c->hd / 64) * 2, d / 16, 1, c->n_cus) + tile_us(M, md.d_ff / 32 * 2, d / 16, 1, c->n_cus) +
+           resid(md.n_heads * c->hd) + resid(md.d_ff);
+}
+// From 256 rows on: the tile kernels where their heights fit the rows and the CUs, else the mix of LDS tiles and row groups.
+// Measured, prompts through 6 layers of the 4096-wide shape, ms: 260 rows 1.38 (tile kernels) against 1.19; 700 2.39 / 2.05;
+// 1000 2.62 / 2.87; 1400 4.22 / 3.97; 2040 5.28 / 5.47; 1280-wide, 16 layers: 1000 rows 2.01 / 1.69, 2040 3.18 / 2.71.
+bool tile_forward(const sjd_ctx *c, int M) {
+    if (M < TILE_M || (c->md.kernel_flags & SJD_KERNELS_ROWGROUPS)) return false;
+    if (c->md.kernel_flags & SJD_KERNELS_TILES) return true;
+    const sjd_model_desc &md = c->md;
+    return tile_layer_us(c, M) < norm_plan(c, M, (md.n_heads + 2 * md.n_kv_heads) * (c->hd / 64)).us + norm_plan(c, M, md.d_ff / 32).us +
+                                     resid_plan(c, M, md.n_heads * c->hd).us + resid_plan(c, M, md.d_ff).us;
 }
 
 // Small-M bf16 path: five kernels per layer (QKV+RoPE+KV write, attention, out+residual, gate/up+SwiGLU,
@@ -373,7 +414,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
                    rt.rm = fr.rm; rt.rope_cos = c->rope_cos; rt.rope_sin = c->rope_sin;
                    rt.page_table = c->page_table; rt.pages_per_seg = c->pps; rt.page_tokens = c->pt;
                    rt.L = fr.L; rt.H = H; rt.hd = hd; rt.meta = c->row_meta; rt.rot = c->row_rot;
-                   rt.ssq_part = c->row_ssq; rt.ssq_n = ceil_div(d, 256);
+                   rt.ssq_part = c->row_ssq; rt.ssq_n = 1;
                    embed_dual_kernel<<<M, 256, 0, st>>>((const bf16_t *)c->tok_emb, c->x, (bf16_t *)c->xn, d, rt);
                }));
     SkinnyArgs a;
@@ -411,14 +452,25 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // More than 32 rows and so few column groups that a workgroup per group and 32-row tile still finds a CU of its
     // own: row groups of 32 rows instead of 64 (all row groups of a column group on one XCD, whose L2 serves the
     // later readers of the weights).  Each workgroup pulls half the activations, twice as many CUs work.
-    auto rows2_for = [&](int groups) { return resid_r2(c, M, groups); };
+    auto rows2_for = [&](int groups) { return rows_of_32(c, M, groups); };
     // computing workgroups of a launch over `groups` column groups
     auto compute_wgs = [&](int groups, bool r2, int row_split) {
         if (r2) return 2 * m_groups * 8 * ceil_div(groups, 8);
         if (row_split == 2) return 16 * ceil_div(groups, 8);
         return m_groups > 1 ? m_groups * 8 * ceil_div(groups, 8) : groups;
     };
-    auto resid_whole = [&](int K) { return resid_splits(c, M, K) == 1; };
+    // what the L2 warm-up of the launch before needs to know about a projection: its slabs are column tiles
+    auto proj_of = [&](const void *W, int n_blocks, int KB, int nbw, const ProjPlan &p) {
+        if (p.lds < 0) return Proj{W, ceil_div(n_blocks, nbw), nbw, KB, p.ks == 1};
+        const int tnb = lds_tile(p.lds).tnb;
+        return Proj{W, n_blocks / tnb, tnb, KB, p.ks == 1};   // whole tiles only: a ragged last one ends with the matrix
+    };
+    const int groups_v = ceil_div(ceil_div(c->Vs, 32), 2);
+    ProjPlan plan_head = norm_plan(c, M, groups_v);
+    // windows of 32: the head combines the guidance branches, which needs both row tiles of a sequence in one wavefront
+    const bool want_z = c->z && !(md.kernel_flags & SJD_NO_HEAD_FUSION);
+    if (plan_head.lds >= 0 && want_z && fr.L == 32) plan_head.lds = kLdsTileHeadZ;
+    const ProjPlan plan_qkv = norm_plan(c, M, groups_qkv), plan_o = resid_plan(c, M, H * hd), plan_gu = norm_plan(c, M, F / 32), plan_down = resid_plan(c, M, F);
     auto warm = [&](int cur_groups, const Proj &nx) {
         a.pf_wgs = 0;
         if (!c->l2_warm || tile || !nx.whole || !nx.W) return;
@@ -455,33 +507,49 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // Many-row kernels take the RMSNorm row sums of squares from the kernel that wrote the residual stream (embedding
     // gather or split-K reduction) instead of accumulating them in their k-loops
     const int tile_rows = (md.kernel_flags & SJD_TILES_256_ROWS) ? 256 : 0;  // 0: chosen per launch
-    bool ssq_ready = true;   // the embedding kernel wrote them
-    float *const ssq_out = tile ? c->row_ssq : nullptr;
-    auto use_ssq = [&]() { a.row_ssq_part = tile && ssq_ready ? c->row_ssq : nullptr; a.row_ssq_n = ceil_div(d, 256); };
-    auto resid = [&](int cls, const void *A, const void *W, int K, const Proj &nx, const KvPool *kv_next) -> int {
+    int ssq_n = 1;   // partial sums per row that the last writer left (0: none); the embedding kernel wrote one
+    float *ssq_out = nullptr;   // where the coming output / down projection leaves them: set if its reader takes them
+    auto use_ssq = [&]() { a.row_ssq_part = ssq_n > 0 ? c->row_ssq : nullptr; a.row_ssq_n = ssq_n; };
+    auto reduce = [&]() -> int {
+        SJD_LAUNCH(c, KC_ADDNORM, after([&] {
+                       resid_reduce_kernel<<<dim3(ceil_div(d, 1024), M), 256, 0, st>>>(c->skinny_part, a.ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out);
+                   }));
+        ssq_n = ceil_div(d, 256);
+        return SJD_OK;
+    };
+    auto resid = [&](int cls, const void *A, const void *W, int K, const ProjPlan &plan, const Proj &nx, const KvPool *kv_next) -> int {
         a.A = (const bf16_t *)A; a.W = (const bf16_t *)W; a.KB = K / 16; a.N = d;
         a.pf_wgs = 0;
         a.row_ssq_part = nullptr;
+        a.ssq_out = ssq_out;
+        if (!tile && plan.lds >= 0) {
+            const int nb = ceil_div(d, 32);
+            a.kb_per_split = ceil_div(a.KB, 2 * plan.ks) * 2;
+            a.ksplit = ceil_div(a.KB, a.kb_per_split);
+            if (a.ksplit == 1) {
+                a.ssq_out_n = ssq_n = ceil_div(nb, lds_tile(plan.lds).cb);
+                SJD_LAUNCH(c, cls, launch_lds<EPI_RESID>(st, a, nb, plan.lds));
+                return SJD_OK;
+            }
+            if ((size_t)a.ksplit * M * d > c->skinny_part_elems) return no_room();
+            SJD_LAUNCH(c, cls, launch_lds<EPI_PARTIAL>(st, a, nb, plan.lds));
+            return reduce();
+        }
         if (tile) {
             const int n_blocks = ceil_div(d, 64) * 2;
-            a.ksplit = resid_splits(c, M, K);
+            a.ksplit = tile_splits(c, M, a.KB);
             a.kb_per_split = ceil_div(a.KB, a.ksplit);
             if (a.ksplit == 1) {
                 SJD_LAUNCH(c, cls, launch_tile<EPI_RESID>(st, a, n_blocks, tile_rows, mixed_ok));
-                ssq_ready = false;
+                ssq_n = 0;
                 return SJD_OK;
             }
             if ((size_t)a.ksplit * M * d > c->skinny_part_elems) return no_room();
             SJD_LAUNCH(c, cls, launch_tile<EPI_PARTIAL>(st, a, n_blocks, tile_rows, mixed_ok));
-            const int ksplit = a.ksplit;
-            SJD_LAUNCH(c, KC_ADDNORM, after([&] {
-                           resid_reduce_kernel<<<dim3(ceil_div(d, 1024), M), 256, 0, st>>>(c->skinny_part, ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out);
-                       }));
-            ssq_ready = true;
-            return SJD_OK;
+            return reduce();
         }
         const int groups = ceil_div(ceil_div(d, 32), nbw_d);
-        if (resid_splits(c, M, K) == 1) {
+        if (plan.ks == 1) {
             whole_k();
             a.row_split = row_split_for(groups);
             const bool r2 = rows2_for(groups);
@@ -489,22 +557,21 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             const int n_compute = compute_wgs(groups, r2, a.row_split);
             warm(n_compute, nx);
             if (kv_next) warm_kv(n_compute, *kv_next);
+            a.ssq_out_n = ssq_n = groups;
             SJD_LAUNCH(c, cls, launch_skinny<EPI_RESID>(st, a, r2 ? 1 : MT, groups, nbw_d, nw_for(groups)));
             a.pf_wgs = a.kv_wgs = 0;
             a.row_split = 1;
             a.m_groups = m_groups;
             return SJD_OK;
         }
-        a.ksplit = resid_splits(c, M, K);
+        a.ksplit = plan.ks;
         a.kb_per_split = ceil_div(a.KB, a.ksplit);
         if ((size_t)a.ksplit * M * d > c->skinny_part_elems) return no_room();
         SJD_LAUNCH(c, cls, launch_skinny<EPI_PARTIAL>(st, a, MT, groups, nbw_d, nw_for(groups * a.ksplit)));
-        const int ksplit = a.ksplit;
-        SJD_LAUNCH(c, KC_ADDNORM, after([&] {
-                       resid_reduce_kernel<<<dim3(ceil_div(d, 1024), M), 256, 0, st>>>(c->skinny_part, ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out);
-                   }));
-        return SJD_OK;
+        return reduce();
     };
+    const Proj proj_o0 = proj_of(nullptr, groups_d * nbw_d, H * hd / 16, nbw_d, plan_o), proj_down0 = proj_of(nullptr, groups_d * nbw_d, F / 16, nbw_d, plan_down);
+    auto with_w = [](Proj p, const void *W) { p.W = W; return p; };
     for (int l = 0; l < md.n_layers; ++l) {
         const LayerWeights &lw = c->layers[l];
         KvPool pool;
@@ -519,13 +586,17 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             whole_k();
             use_ssq();
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_tile<EPI_QKV>(st, a, (H + 2 * Hkv) * (hd / 64) * 2, tile_rows, mixed_ok));
+        } else if (plan_qkv.lds >= 0) {
+            whole_k();
+            use_ssq();
+            SJD_LAUNCH(c, KC_GEMM_QKV, launch_lds<EPI_QKV>(st, a, groups_qkv * 2, plan_qkv.lds));
         } else {
             whole_k();
             a.row_split = row_split_for(groups_qkv);
             const bool r2 = rows2_for(groups_qkv);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
             const int n_compute = compute_wgs(groups_qkv, r2, a.row_split);
-            warm(n_compute, with_head || l + 1 < md.n_layers ? Proj{lw.wo, groups_d, nbw_d, H * hd / 16, resid_whole(H * hd)} : none);
+            warm(n_compute, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
             if (l == 0) warm_kv(n_compute, pool);  // later layers: requested by the down projection before them
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_skinny<EPI_QKV>(st, a, r2 ? 1 : MT, groups_qkv, 2, nw_for(groups_qkv)));
             a.pf_wgs = a.kv_wgs = 0;
@@ -534,43 +605,48 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         }
         if (!with_head && l + 1 == md.n_layers) return SJD_OK;
         { int rc = run_attention<bf16_t>(c, pool, fr); if (rc) return rc; }
-        { int rc = resid(KC_GEMM_O, c->attn, lw.wo, H * hd, Proj{lw.wgu, F / 32, 2, d / 16, true}, nullptr); if (rc) return rc; }
+        ssq_out = tile || plan_gu.lds >= 0 ? c->row_ssq : nullptr;
+        { int rc = resid(KC_GEMM_O, c->attn, lw.wo, H * hd, plan_o, proj_of(lw.wgu, F / 32 * 2, d / 16, 2, plan_gu), nullptr); if (rc) return rc; }
         a.A = (const bf16_t *)c->xn; a.W = (const bf16_t *)lw.wgu; a.KB = d / 16;
         if (tile) {
             whole_k();
             use_ssq();
             SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_tile<EPI_SWIGLU>(st, a, F / 32 * 2, tile_rows, mixed_ok));
+        } else if (plan_gu.lds >= 0) {
+            whole_k();
+            use_ssq();
+            SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_lds<EPI_SWIGLU>(st, a, F / 32 * 2, plan_gu.lds));
         } else {
             whole_k();
             a.row_split = row_split_for(F / 32);
             const bool r2 = rows2_for(F / 32);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
             const int n_compute = compute_wgs(F / 32, r2, a.row_split);
-            warm(n_compute, Proj{lw.wdown, groups_d, nbw_d, F / 16, resid_whole(F)});
+            warm(n_compute, with_w(proj_down0, lw.wdown));
             if (mixed_ok && skinny_mixed_applies(a, F / 32, 2, nw_for(F / 32))) SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_skinny_mixed<EPI_SWIGLU>(st, a, MT, F / 32));
             else SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_skinny<EPI_SWIGLU>(st, a, r2 ? 1 : MT, F / 32, 2, nw_for(F / 32)));
             a.pf_wgs = 0;
             a.row_split = 1;
             a.m_groups = m_groups;
         }
-        const Proj after_down = l + 1 < md.n_layers ? Proj{c->layers[l + 1].wqkv, groups_qkv, 2, d / 16, true}
-                                : with_head         ? Proj{c->lm_head, ceil_div(ceil_div(c->Vs, 32), 2), 2, d / 16, true}
+        const Proj after_down = l + 1 < md.n_layers ? proj_of(c->layers[l + 1].wqkv, groups_qkv * 2, d / 16, 2, plan_qkv)
+                                : with_head         ? proj_of(c->lm_head, groups_v * 2, d / 16, 2, plan_head)
                                                     : none;
         KvPool pool_next = pool;
         pool_next.k = (char *)c->kpool + c->pool_layer_bytes * (l + 1);
         pool_next.v = (char *)c->vpool + c->pool_layer_bytes * (l + 1);
-        { int rc = resid(KC_GEMM_DOWN, c->h, lw.wdown, F, after_down, l + 1 < md.n_layers ? &pool_next : nullptr); if (rc) return rc; }
+        ssq_out = tile || (l + 1 < md.n_layers ? plan_qkv : plan_head).lds >= 0 ? c->row_ssq : nullptr;
+        { int rc = resid(KC_GEMM_DOWN, c->h, lw.wdown, F, plan_down, after_down, l + 1 < md.n_layers ? &pool_next : nullptr); if (rc) return rc; }
     }
     if (with_head) {
         a.A = (const bf16_t *)c->xn; a.W = (const bf16_t *)c->lm_head; a.KB = d / 16; a.N = c->Vs;
         // Guidance fused into the head where a position's conditional and unconditional rows meet in one thread of the
         // epilogue: windows of 32 (row tiles alternate conditional / unconditional) and one sequence with a window of 16
-        const int groups_v = ceil_div(ceil_div(c->Vs, 32), 2);
         const bool head_mixed = !tile && mixed_ok && skinny_mixed_applies(a, groups_v, 2, nw_for(groups_v));
         const bool head_r2 = !tile && !head_mixed && rows2_for(groups_v);
         int z_mode = 0;
-        if (c->z && !(md.kernel_flags & SJD_NO_HEAD_FUSION)) {
-            if (c->L == 32 && (tile || (MT == 2 && !head_r2))) z_mode = 1;
+        if (want_z) {
+            if (c->L == 32 && (tile || plan_head.lds >= 0 || (MT == 2 && !head_r2))) z_mode = 1;
             else if (c->L == 16 && M == 32 && !tile) z_mode = 2;
         }
         a.z_out = c->z; a.z_mode = z_mode; a.cfg_scale = c->sp.cfg_scale; a.inv_t = c->sp.inv_temperature;
@@ -580,6 +656,10 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             whole_k();
             use_ssq();
             SJD_LAUNCH(c, KC_GEMM_HEAD, launch_tile<EPI_HEAD>(st, a, ceil_div(c->Vs, 64) * 2, z_mode ? 256 : tile_rows));
+        } else if (plan_head.lds >= 0) {
+            whole_k();
+            use_ssq();
+            SJD_LAUNCH(c, KC_GEMM_HEAD, launch_lds<EPI_HEAD>(st, a, groups_v * 2, plan_head.lds));
         } else {
             whole_k();
             if (head_mixed) SJD_LAUNCH(c, KC_GEMM_HEAD, launch_skinny_mixed<EPI_HEAD>(st, a, MT, groups_v));
@@ -736,7 +816,7 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
     c->partial_elems = pe;
     if ((rc = dev_alloc(c, &c->partial, pe * sizeof(float)))) return rc;
     if ((rc = dev_alloc(c, &c->logits, (size_t)S * 2 * L * c->Vs * sizeof(float)))) return rc;
-    const int Mpad = ceil_div(M, 64) * 64;   // whole 64-row groups: the fused projections read every row of the last one
+    const int Mpad = ceil_div(M, 64) * 64;   // whole 64-row groups: the row-group projections read every row of the last one
     if ((rc = dev_alloc(c, &c->xn, Layout<T>::a_elems(Mpad, d) * sizeof(T)))) return rc;
     if ((rc = dev_alloc(c, &c->attn, Layout<T>::a_elems(Mpad, H * hd) * sizeof(T)))) return rc;
     if ((rc = dev_alloc(c, &c->h, Layout<T>::a_elems(Mpad, F) * sizeof(T)))) return rc;
@@ -749,10 +829,10 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
         const int widest = std::max(std::max((H + 2 * Hkv) * (hd / 64), F / 32), ceil_div(c->Vs, 64));
         c->skinny_part_elems = std::max((size_t)widest * 8 * (2 * 2 * 1024 + 64), (size_t)8 * S * 2 * L * d);
         for (int m = 1; m <= c->pre_rows; ++m)
-            for (int K : {H * hd, F}) c->skinny_part_elems = std::max(c->skinny_part_elems, (size_t)resid_splits(c, m, K) * m * d);
+            for (int K : {H * hd, F}) c->skinny_part_elems = std::max(c->skinny_part_elems, (size_t)std::max(resid_plan(c, m, K).ks, m < TILE_M ? 1 : tile_splits(c, m, K / 16)) * m * d);
         if ((rc = dev_alloc(c, &c->skinny_part, c->skinny_part_elems * sizeof(float)))) return rc;
         if ((rc = dev_alloc(c, &c->pf_sink, 256))) return rc;
-        if ((rc = dev_alloc(c, &c->row_ssq, (size_t)M * ceil_div(d, 256) * sizeof(float)))) return rc;
+        if ((rc = dev_alloc(c, &c->row_ssq, (size_t)M * ceil_div(d, 32) * sizeof(float)))) return rc;
         if ((rc = dev_alloc(c, &c->row_meta, (size_t)M * sizeof(QkvRow)))) return rc;
         if ((rc = dev_alloc(c, &c->row_rot, (size_t)M * (hd / 2) * sizeof(float2)))) return rc;
         c->l2_warm = !(md.kernel_flags & SJD_NO_L2_WARM);
