@@ -6,7 +6,19 @@
 #include "kernels_forward.hip.h"
 
 // ------------------------------------------------------------------------------------ reference
-// One wavefront per (row, head): scores into LDS, softmax, then lanes split the head dimension.
+// One wavefront per (row, head): scores into LDS, softmax, then lanes split the head dimension.  Every sum runs in the order
+// of its index (dimensions, tokens; the fp32 forward runs on this kernel).  Bound by latency: keys come four dimensions at a
+// time, values eight tokens at a time, page by page instead of a table lookup and two divisions per token.  32 rows x 4 heads
+// of 64, 50 tokens: 15.1 -> 9.8 us between events.
+SJD_D void load4(const float *p, float (&v)[4]) {
+    const float4 x = *reinterpret_cast<const float4 *>(p);
+    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+}
+SJD_D void load4(const bf16_t *p, float (&v)[4]) {
+    const uint2 x = *reinterpret_cast<const uint2 *>(p);
+    v[0] = __builtin_bit_cast(float, x.x << 16); v[1] = __builtin_bit_cast(float, x.x & 0xFFFF0000u);
+    v[2] = __builtin_bit_cast(float, x.y << 16); v[3] = __builtin_bit_cast(float, x.y & 0xFFFF0000u);
+}
 // out_act (GEMM-operand layout [M][H*hd] of T) and / or out_plain ([M][H][hd] fp32) receive the result.
 template <typename T>
 __global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool, RowMap rm, T *__restrict__ out_act,
@@ -35,7 +47,17 @@ __global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool,
         const T *kb = (const T *)pool.k + ((size_t)pt[t / pool.page_tokens] * Hkv + kvh) * blk;
         const int tt = t % pool.page_tokens;
         float s = 0.0f;
-        for (int j = 0; j < hd; ++j) s = fmaf(qs[j], to_float<T>(kb[Layout<T>::k_index(tt, j, hd)]), s);
+        if ((hd & 7) == 0) {   // 4 dimensions of a token are contiguous and aligned in both layouts
+#pragma unroll 4
+            for (int j = 0; j < hd; j += 4) {
+                float kv[4];
+                load4(kb + Layout<T>::k_index(tt, j, hd), kv);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = fmaf(qs[j + e], kv[e], s);
+            }
+        } else {
+            for (int j = 0; j < hd; ++j) s = fmaf(qs[j], to_float<T>(kb[Layout<T>::k_index(tt, j, hd)]), s);
+        }
         s *= scale;
         sc[t] = s;
         mx = fmaxf(mx, s);
@@ -52,9 +74,18 @@ __global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool,
     const float inv = 1.0f / sum;
     for (int j = lane; j < hd; j += 64) {
         float acc = 0.0f;
-        for (int t = 0; t < n_vis; ++t) {
-            const T *vb = (const T *)pool.v + ((size_t)pt[t / pool.page_tokens] * Hkv + kvh) * blk;
-            acc = fmaf(sc[t], to_float<T>(vb[Layout<T>::v_index(t % pool.page_tokens, j, hd)]), acc);
+        for (int t0 = 0, pg = 0; t0 < n_vis; t0 += pool.page_tokens, ++pg) {
+            const T *vb = (const T *)pool.v + ((size_t)pt[pg] * Hkv + kvh) * blk;
+            const int n = min(pool.page_tokens, n_vis - t0);
+            int tt = 0;
+            for (; tt + 8 <= n; tt += 8) {
+                float vv[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) vv[u] = to_float<T>(vb[Layout<T>::v_index(tt + u, j, hd)]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc = fmaf(sc[t0 + tt + u], vv[u], acc);
+            }
+            for (; tt < n; ++tt) acc = fmaf(sc[t0 + tt], to_float<T>(vb[Layout<T>::v_index(tt, j, hd)]), acc);
         }
         acc *= inv;
         if (out_act) out_act[Layout<T>::a_index(m, h * hd + j, H * hd)] = from_float<T>(acc);
