@@ -53,13 +53,14 @@ enum {
     SJD_KERNELS_REFERENCE = 1, /* use the plain (non-MFMA) GEMM and attention kernels */
     SJD_NO_GRAPH = 2,          /* never capture the step into a HIP graph: launch its
                                 * kernels one by one                                   */
-    SJD_KERNELS_ROWGROUPS = 4, /* bf16, >= 256 rows: keep the 64-row-group streaming projection
+    SJD_KERNELS_ROWGROUPS = 4, /* bf16, > 64 rows: keep the 64-row-group streaming projection
                                 * kernels instead of the LDS-staged tile kernels       */
     SJD_ATTENTION_CHUNKED = 8, /* bf16: always split the context over workgroups and merge
                                 * in a second kernel, also where one workgroup per head
-                                * would do (short contexts)                            */
-    SJD_KERNELS_TILES = 16,    /* bf16, >= 256 rows: the tile kernels also for models too
-                                * narrow to fill the chip with 256 x 128 tiles         */
+                                * would do (short contexts); steps only, a prefill always
+                                * runs one workgroup per head and 32 prompt rows       */
+    SJD_KERNELS_TILES = 16,    /* bf16, >= 256 rows: the tile kernels also where smaller
+                                * tiles or row groups are expected to be faster        */
     SJD_NO_L2_WARM = 32,       /* bf16, <= 64 rows: projection launches carry no extra
                                 * workgroups that touch the next launch's weights and
                                 * key/value pages into L2 (same results either way)    */
