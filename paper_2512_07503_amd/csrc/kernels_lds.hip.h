@@ -47,8 +47,9 @@ template <int NL> SJD_D void wait_stages(int stages) {
     }
 }
 
+// (two wavefronts per SIMD at least: the LDS of the larger shapes admits two workgroups per CU, their registers must too)
 template <int TMT, int TNB, int WM, int WN, int S, int EPI>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_lds_kernel(SkinnyArgs a, int n_blocks, int col_tiles, int row_tiles) {
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SkinnyArgs a, int n_blocks, int col_tiles, int row_tiles) {
     constexpr int NW = WM * WN, RT = TMT / WM, CB = TNB / WN;   // wavefronts; MFMA tiles of a wavefront: RT x CB
     constexpr int FR = 2 * (TMT + TNB);                         // fragments of a stage
     constexpr int NL = FR / NW;                                 // ... that a wavefront fetches
@@ -171,12 +172,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds_kernel(SkinnyArgs a, in
         if constexpr (kNorm) {
             // 1 / rms: the row's partial sums of squares, even ones in the lower half wavefront, odd ones in the upper
             const int m = (rt * TMT + wm * RT + j) * 32 + (lane & 31);
-            float t = 0.0f;
-            if (m < a.M) {
-                const float *p = a.row_ssq_part + (size_t)m * a.row_ssq_n;
-#pragma unroll 8
-                for (int c = lane >> 5; c < a.row_ssq_n; c += 2) t += p[c];
-            }
+            float t = m < a.M ? row_ssq_sum(a, m, lane >> 5, 2) : 0.0f;
             t += __shfl_xor(t, 32, 64);
             inv[j] = 1.0f / sqrtf(t / (float)(KB * 16) + a.eps);
         }
@@ -281,7 +277,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds_kernel(SkinnyArgs a, in
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float gt = acc[j][i][4 * q + e] * inv[j], up = acc[j][i + 1][4 * q + e] * inv[j];
-                            s[e] = __fdividef(gt, 1.0f + __expf(-gt)) * up;   // hardware exp2 and reciprocal: rounded to bf16 next
+                            s[e] = silu(gt) * up;
                         }
                         *reinterpret_cast<uint2 *>(a.h + Layout<bf16_t>::a_index(m, ((blk0 + i) >> 1) * 32 + 8 * q + h4, a.F)) = pack_bf16x4(s[0], s[1], s[2], s[3]);
                     }
@@ -297,7 +293,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds_kernel(SkinnyArgs a, in
                         if (n < a.N) xin[i][q] = *reinterpret_cast<const float4 *>(a.x + (size_t)m * a.N + n);
                     }
 #pragma unroll
-                for (int i = 0; i < CB; ++i)
+                for (int i = 0; i < CB; ++i) {
+                    float4 gn[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) gn[q] = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+                    if (a.gain && (blk0 + i) * 32 < a.N) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) gn[q] = *reinterpret_cast<const float4 *>(a.gain + (blk0 + i) * 32 + 8 * q + h4);
+                    }
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int n = (blk0 + i) * 32 + 8 * q + h4;
@@ -305,12 +308,16 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds_kernel(SkinnyArgs a, in
                         float4 v = xin[i][q];
                         v.x += acc[j][i][4 * q]; v.y += acc[j][i][4 * q + 1]; v.z += acc[j][i][4 * q + 2]; v.w += acc[j][i][4 * q + 3];
                         *reinterpret_cast<float4 *>(a.x + (size_t)m * a.N + n) = v;
-                        const uint2 b = pack_bf16x4(v.x, v.y, v.z, v.w);
+                        const float4 g = gn[q];
+                        const uint2 b = pack_bf16x4(v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w);
                         *reinterpret_cast<uint2 *>(a.xb + Layout<bf16_t>::a_index(m, n, a.N)) = b;
-                        const float f0 = __builtin_bit_cast(float, b.x << 16), f1 = __builtin_bit_cast(float, b.x & 0xFFFF0000u);
-                        const float f2 = __builtin_bit_cast(float, b.y << 16), f3 = __builtin_bit_cast(float, b.y & 0xFFFF0000u);
-                        sq += (f0 * f0 + f1 * f1) + (f2 * f2 + f3 * f3);
+                        if (!a.gain) {   // the squares of what the copy holds
+                            v.x = __builtin_bit_cast(float, b.x << 16); v.y = __builtin_bit_cast(float, b.x & 0xFFFF0000u);
+                            v.z = __builtin_bit_cast(float, b.y << 16); v.w = __builtin_bit_cast(float, b.y & 0xFFFF0000u);
+                        }
+                        sq += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
                     }
+                }
             } else {   // EPI_PARTIAL, EPI_HEAD: fp32 rows of N
                 float *row = EPI == EPI_PARTIAL ? a.part + ((size_t)ks * a.M + m) * a.N : a.logits + (size_t)m * a.N;
 #pragma unroll
@@ -332,7 +339,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds_kernel(SkinnyArgs a, in
         if constexpr (EPI == EPI_RESID) {
             // sum of squares of this wavefront's columns of the row, for the next projection's norm
             sq += __shfl_xor(sq, 32, 64);
-            if (a.ssq_out && lane < 32 && m < a.M && blk0 * 32 < a.N) a.ssq_out[(size_t)m * a.ssq_out_n + blk0 / CB] = sq;
+            if (a.ssq_out && lane < 32 && m < a.M && blk0 * 32 < a.N) a.ssq_out[(size_t)(blk0 / CB) * a.M + m] = sq;
         }
     }
 }

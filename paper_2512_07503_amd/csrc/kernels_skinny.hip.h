@@ -14,10 +14,17 @@
 //   PARTIAL plain fp32 partial sums [ksplit][M][N] of a K range (grid.y = ksplit); resid_reduce_kernel adds them
 //           up after the kernel boundary.  Used when one workgroup per column group would have to pull more
 //           than ~0.5 MB through its CU (wide K, M = 64): splitting K also splits the activation re-reads.
-// RMSNorm is folded in: the gain is multiplied into the weights when they are packed, the input is
-// the raw residual stream in bf16, its per-row sum of squares is accumulated from the very A fragments
-// the MFMA consumes, and the row scale 1/rms is applied to the accumulators (it commutes with the
-// contraction).
+// RMSNorm is folded in, in one of two ways; the row scale 1/rms is applied to the accumulators in both (it commutes
+// with the contraction):
+//   gains in the weights   the gain is multiplied into the weights when they are packed, the input is the raw
+//                          residual stream in bf16, and its per-row sum of squares is accumulated from the very A
+//                          fragments the MFMA consumes
+//   gains in the rows      the weights stay the caller's bf16 values; the kernel that writes the residual stream
+//                          multiplies the next norm's gain into its bf16 copy before the one rounding and leaves sums
+//                          of squares of the fp32 stream (SkinnyArgs::gain, ssq_out, row_ssq_part)
+// Gains drawn from U(0.5, 1.5), relative error of the logits against double precision, 2 layers of 1280 with 500 rows:
+// 7.7e-3 with the gains rounded into the weights, 6.7e-3 with the gains in the rows.  The context says which
+// (sjd_ctx::fold_gain).
 #pragma once
 #include <algorithm>
 
@@ -54,14 +61,17 @@ struct SkinnyArgs {
     float *x;          // [M][N] fp32 residual stream, updated in place
     bf16_t *xb;        // the same in bf16, fragment-major [M][N]
     int N;             // also the logits row length for HEAD
-    // Many-row kernels: per-row sums of squares of the (bf16) input rows, as row_ssq_n partial sums per row written
-    // by the kernel that produced the rows; NULL: taken from the activation fragments inside the k-loop
+    // Per-row sums of squares of the input rows, as row_ssq_n partial sums per row written by the kernel that produced the
+    // rows, [row_ssq_n][M] (neighbouring lanes read neighbouring rows); NULL: taken from the activation fragments
+    // inside the k-loop
     const float *row_ssq_part;
     int row_ssq_n;
-    // RESID: where a kernel leaves such partial sums for the next one (may be NULL), ssq_out_n per row: one per column group
-    // of the row-group kernels, one per wavefront's columns of the LDS kernels
+    // RESID: where a kernel leaves such partial sums for the next one (may be NULL): one per column group of the row-group
+    // kernels, one per wavefront's columns of the LDS kernels, one per pair of column blocks of the tile kernels
     float *ssq_out;
-    int ssq_out_n;
+    // Gains in the rows: RESID multiplies gain[n] (the next norm's) into the bf16 copy of the stream, and takes ssq_out from
+    // the fp32 stream; NULL: the gains are in the weights
+    const float *gain;
     // QKV: per-row tables written once per forward by embed_dual_kernel (no dependent loads in the projections)
     const QkvRow *row_meta;   // [M]
     const float2 *row_rot;    // [M][hd / 2] (cos, sin) of the row's position; (1, 0) for rows that are not computed
@@ -151,12 +161,33 @@ SJD_D float guided_z(float val_c, float inv_c, float val_u, float inv_u, float s
     return __fmul_rn(__fmaf_rn(s, __fsub_rn(lc, lu), lu), inv_t);
 }
 
+// Row m's partial sums of squares c0, c0 + step, ..., added in this order; eight loads are in flight
+SJD_D float row_ssq_sum(const SkinnyArgs &a, int m, int c0, int step) {
+    float t = 0.0f;
+    for (int c = c0; c < a.row_ssq_n; c += 8 * step) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = a.row_ssq_part[(size_t)min(c + u * step, a.row_ssq_n - 1) * a.M + m];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t += c + u * step < a.row_ssq_n ? v[u] : 0.0f;
+    }
+    return t;
+}
+
+// Hardware exp2 and reciprocal (1 ulp each).  What it feeds is rounded to bf16 next: for gates and ups of standard deviation
+// 0.3 to 30 the rounded product is off by 1.66e-3 (2-norm, against double precision) either way, equal in seven digits with
+// expf and a true division, which cost 2 to 3 us per launch of 500 rows and 6912 columns.
+SJD_D float silu(float g) { return __fdividef(g, 1.0f + __expf(-g)); }
+
+// the value of the residual stream whose square the next norm sums: the fp32 stream, or what its bf16 copy holds
+SJD_D float ssq_value(const SkinnyArgs &a, float v) { return a.gain ? v : bf16_to_float(float_to_bf16(v)); }
+
 // One output element pair of the projection epilogues: row m, column `col` of NBW consecutive column blocks
 // (val[i] = block blk0 + i), inv = 1 / rms of row m (1 where the epilogue does not normalise).
-// xin: the residual-stream values x[m][n_i] (RESID only; the caller loads them, early if it can).
+// xin: the residual-stream values x[m][n_i], gn: gain[n_i] or 1 (RESID only; the caller loads them, early if it can).
 template <int EPI, int NBW>
 SJD_D void skinny_epilogue(const SkinnyArgs &a, int ks, int m, int blk0, int col, const float (&val)[NBW], float inv,
-                           const float (&xin)[NBW]) {
+                           const float (&xin)[NBW], const float (&gn)[NBW]) {
     if constexpr (EPI == EPI_PARTIAL) {
 #pragma unroll
         for (int i = 0; i < NBW; ++i) {
@@ -170,7 +201,7 @@ SJD_D void skinny_epilogue(const SkinnyArgs &a, int ks, int m, int blk0, int col
             if (n < a.N) {
                 const float nv = xin[i] + val[i];
                 a.x[(size_t)m * a.N + n] = nv;
-                a.xb[Layout<bf16_t>::a_index(m, n, a.N)] = float_to_bf16(nv);
+                a.xb[Layout<bf16_t>::a_index(m, n, a.N)] = float_to_bf16(nv * gn[i]);
             }
         }
     } else if constexpr (EPI == EPI_HEAD) {
@@ -186,8 +217,7 @@ SJD_D void skinny_epilogue(const SkinnyArgs &a, int ks, int m, int blk0, int col
         for (int i = 0; i < NBW; i += 2) {
             const float gt = val[i] * inv, up = val[i + 1] * inv;
             const int n = ((blk0 + i) >> 1) * 32 + col;
-            // hardware exp2 and reciprocal (1 ulp each): the result is rounded to bf16 next
-            if (n < a.F) a.h[Layout<bf16_t>::a_index(m, n, a.F)] = float_to_bf16(__fdividef(gt, 1.0f + __expf(-gt)) * up);
+            if (n < a.F) a.h[Layout<bf16_t>::a_index(m, n, a.F)] = float_to_bf16(silu(gt) * up);
         }
     } else {
         static_assert(EPI != EPI_QKV, "the QKV epilogue is qkv_row + qkv_rotation + qkv_store, called by the kernels");
@@ -315,6 +345,13 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
     // up with elements e = t, t + 64 NW, ... of every tile (see the reduction below).
     constexpr int EPT = 1024 / (NW * 64);  // elements per thread per tile
     [[maybe_unused]] float xpre[MT][NBW][EPT];
+    float gpre[NBW];   // the next norm's gains of this thread's columns
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) {
+        gpre[i] = 1.0f;
+        if constexpr (EPI == EPI_RESID)
+            if (const int n = (blk0 + i) * 32 + (lane & 31); a.gain && n < a.N) gpre[i] = a.gain[n];
+    }
     [[maybe_unused]] QkvRow qrow[MT][EPT];
     [[maybe_unused]] float rot_c[MT][EPT], rot_s[MT][EPT];
     if (EPI == EPI_RESID || EPI == EPI_QKV) {
@@ -428,7 +465,11 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
     if (kNorm) {
 #pragma unroll
         for (int j = 0; j < MT; ++j) {
-            const float t = ssq[j] + __shfl_xor(ssq[j], 32, 64);
+            float t = ssq[j] + __shfl_xor(ssq[j], 32, 64);
+            if (a.row_ssq_part) {   // from the writer of the rows: wavefront w adds its partial sums w, w + NW, ...
+                const int m = m_base + j * 32 + (lane & 31);
+                t = m < a.M ? row_ssq_sum(a, m, wave, NW) : 0.0f;
+            }
             if (lane < 32) ssq_lds[wave][j][lane] = t;
         }
     }
@@ -509,18 +550,18 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
                 xin[i] = EPI == EPI_RESID ? xpre[j][i][hh] : 0.0f;
             }
             if constexpr (EPI == EPI_QKV) qkv_store(a, qrow[j][hh], g, col, vals[0] * inv, vals[NBW - 1] * inv, rot_c[j][hh], rot_s[j][hh]);
-            else skinny_epilogue<EPI, NBW>(a, ks, m, blk0, col, vals, inv, xin);
+            else skinny_epilogue<EPI, NBW>(a, ks, m, blk0, col, vals, inv, xin, gpre);
             if constexpr (EPI == EPI_RESID) {
                 if (a.ssq_out) {   // the row's columns of this group lie in one half wavefront
                     float sq = 0.0f;
 #pragma unroll
                     for (int i = 0; i < NBW; ++i) {
-                        const float f = (blk0 + i) * 32 + col < a.N ? bf16_to_float(float_to_bf16(xin[i] + vals[i])) : 0.0f;
+                        const float f = (blk0 + i) * 32 + col < a.N ? ssq_value(a, xin[i] + vals[i]) : 0.0f;
                         sq = fmaf(f, f, sq);
                     }
 #pragma unroll
                     for (int off = 16; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-                    if (col == 0) a.ssq_out[(size_t)m * a.ssq_out_n + blk0 / NBW] = sq;
+                    if (col == 0) a.ssq_out[(size_t)(blk0 / NBW) * a.M + m] = sq;
                 }
             }
         }
@@ -536,8 +577,8 @@ struct RowTables {
     int pages_per_seg, page_tokens, L, H, hd;
     QkvRow *meta;
     float2 *rot;
-    float *ssq_part;   // [M][ssq_n] sum of squares of the row in slot 0, zeros in the others (may be NULL)
-    int ssq_n;
+    float *ssq_part;   // [M] sum of squares of the row
+    const float *gain; // [d] multiplied into the bf16 copy (may be NULL)
 };
 __global__ void embed_dual_kernel(const bf16_t *__restrict__ emb, float *__restrict__ x, bf16_t *__restrict__ xb, int d, RowTables t) {
     const int m = blockIdx.x;
@@ -566,14 +607,12 @@ __global__ void embed_dual_kernel(const bf16_t *__restrict__ emb, float *__restr
         const bf16_t v = tok >= 0 ? emb[(size_t)tok * d + i] : (bf16_t)0;
         const float f = bf16_to_float(v);
         x[(size_t)m * d + i] = f;
-        xb[Layout<bf16_t>::a_index(m, i, d)] = v;
+        xb[Layout<bf16_t>::a_index(m, i, d)] = t.gain ? float_to_bf16(f * t.gain[i]) : v;
         sq = fmaf(f, f, sq);
     }
-    if (t.ssq_part) {
-        __shared__ float scratch[17];
-        const float total = block_sum_f32(sq, scratch);
-        for (int c = threadIdx.x; c < t.ssq_n; c += blockDim.x) t.ssq_part[(size_t)m * t.ssq_n + c] = c == 0 ? total : 0.0f;
-    }
+    __shared__ float scratch[17];
+    const float total = block_sum_f32(sq, scratch);
+    if (threadIdx.x == 0) t.ssq_part[m] = total;
 }
 
 // Weight re-layout for the fused path.  dst block (group * nbw + i) of 32 rows <- source rows given by
@@ -611,13 +650,13 @@ __global__ void pack_weight_fused_kernel(const bf16_t *__restrict__ s0, const bf
     }
 }
 
-// x[m][n] += sum_ks part[ks][m][n];  xb = bf16(x) in GEMM-operand layout.
+// x[m][n] += sum_ks part[ks][m][n];  xb = bf16(x), or bf16(x * gain) where gain is given, in GEMM-operand layout.
 // One wavefront per (row, 256 columns): a lane takes four consecutive columns (16-byte loads of the stream and of every
 // partial sum, one 8-byte store of the four bf16, which are neighbours in the operand layout), and the chunk's sum of
 // squares is a wavefront reduction: no barrier.  grid (ceil(N / 1024), M), 256 threads.
-// ssq_part (may be NULL): [M][ceil(N / 256)] sums of squares of the bf16 values written per chunk.
+// ssq_part (may be NULL): [ceil(N / 256)][M] sums of squares per chunk, of the bf16 values written or (with gain) of x.
 __global__ __launch_bounds__(256) void resid_reduce_kernel(const float *__restrict__ part, int ksplit, int M, int N, float *__restrict__ x,
-                                                           bf16_t *__restrict__ xb, float *__restrict__ ssq_part) {
+                                                           bf16_t *__restrict__ xb, float *__restrict__ ssq_part, const float *__restrict__ gain) {
     const int m = blockIdx.y, chunk = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n_chunks = (N + 255) >> 8, n = chunk * 256 + lane * 4;
     float sq = 0.0f;
@@ -629,27 +668,33 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(const float *__restri
             v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
         }
         *reinterpret_cast<float4 *>(x + idx) = v;
-        const bf16_t b0 = float_to_bf16(v.x), b1 = float_to_bf16(v.y), b2 = float_to_bf16(v.z), b3 = float_to_bf16(v.w);
+        float4 o = v;
+        if (gain) {
+            const float4 g = *reinterpret_cast<const float4 *>(gain + n);
+            o.x *= g.x; o.y *= g.y; o.z *= g.z; o.w *= g.w;
+        }
+        const bf16_t b0 = float_to_bf16(o.x), b1 = float_to_bf16(o.y), b2 = float_to_bf16(o.z), b3 = float_to_bf16(o.w);
         uint2 packed;
         packed.x = (uint32_t)b0 | ((uint32_t)b1 << 16);
         packed.y = (uint32_t)b2 | ((uint32_t)b3 << 16);
         *reinterpret_cast<uint2 *>(xb + Layout<bf16_t>::a_index(m, n, N)) = packed;   // n % 4 == 0: one 8-element group
-        const float f0 = bf16_to_float(b0), f1 = bf16_to_float(b1), f2 = bf16_to_float(b2), f3 = bf16_to_float(b3);
-        sq = (f0 * f0 + f1 * f1) + (f2 * f2 + f3 * f3);
+        if (!gain) v = make_float4(bf16_to_float(b0), bf16_to_float(b1), bf16_to_float(b2), bf16_to_float(b3));
+        sq = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
     } else {
         for (int nn = n; nn < n + 4 && nn < N; ++nn) {
             const size_t idx = (size_t)m * N + nn;
             float v = x[idx];
             for (int k = 0; k < ksplit; ++k) v += part[(size_t)k * M * N + idx];
             x[idx] = v;
-            const bf16_t b = float_to_bf16(v);
+            const bf16_t b = float_to_bf16(gain ? v * gain[nn] : v);
             xb[Layout<bf16_t>::a_index(m, nn, N)] = b;
-            sq += bf16_to_float(b) * bf16_to_float(b);
+            const float f = gain ? v : bf16_to_float(b);
+            sq += f * f;
         }
     }
     if (ssq_part) {
         for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-        if (lane == 0 && chunk < n_chunks) ssq_part[(size_t)m * n_chunks + chunk] = sq;
+        if (lane == 0 && chunk < n_chunks) ssq_part[(size_t)chunk * M + m] = sq;
     }
 }
 

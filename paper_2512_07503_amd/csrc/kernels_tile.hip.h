@@ -179,9 +179,7 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
     } else if (kNorm) {
         // row tid of the tile: its partial sums of squares in their fixed order
         const int m = rt * TM + tid;
-        float t = 0.0f;
-        if (tid < TM && m < a.M)
-            for (int c = 0; c < a.row_ssq_n; ++c) t += a.row_ssq_part[(size_t)m * a.row_ssq_n + c];
+        const float t = tid < TM && m < a.M ? row_ssq_sum(a, m, 0, 1) : 0.0f;
         if (tid < TM) ssq_lds[tid / (32 * RT)][(tid >> 5) % RT][tid & 31] = 1.0f / sqrtf(t * inv_k + a.eps);
         __syncthreads();
     }
@@ -227,6 +225,12 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
             for (int p = 0; p < 2; ++p) {
                 const int g = ct * 2 + p;
                 if (g * 2 >= n_blocks) continue;  // past the last column pair
+                float gn[2] = {1.0f, 1.0f};
+                if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        if (const int n = (g * 2 + i) * 32 + col; a.gain && n < a.N) gn[i] = a.gain[n];
+                }
 #pragma unroll
                 for (int v0 = 0; v0 < 16; v0 += 4) {
                     const int row0 = 2 * v0 + 4 * (lane >> 5), m0 = rt * TM + (wave * RT + j) * 32 + row0;
@@ -248,7 +252,20 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
                         if (m0 + u >= a.M) continue;
                         const float inv = kNorm ? ssq_lds[wave][j][row0 + u] : 1.0f;
                         const float vals[2] = {acc[j][p * 2][v0 + u], acc[j][p * 2 + 1][v0 + u]};
-                        skinny_epilogue<EPI, 2>(a, ks, m0 + u, g * 2, col, vals, inv, xin[u]);
+                        skinny_epilogue<EPI, 2>(a, ks, m0 + u, g * 2, col, vals, inv, xin[u], gn);
+                        if constexpr (EPI == EPI_RESID) {
+                            if (a.ssq_out) {   // the row's columns of this pair lie in one half wavefront
+                                float sq = 0.0f;
+#pragma unroll
+                                for (int i = 0; i < 2; ++i) {
+                                    const float f = (g * 2 + i) * 32 + col < a.N ? ssq_value(a, xin[u][i] + vals[i]) : 0.0f;
+                                    sq = fmaf(f, f, sq);
+                                }
+#pragma unroll
+                                for (int off = 16; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+                                if (col == 0) a.ssq_out[(size_t)g * a.M + m0 + u] = sq;
+                            }
+                        }
                     }
                 }
             }

@@ -98,14 +98,15 @@ struct sjd_ctx {
     bool attn_onepass = false;             // regime of the launches being enqueued
     std::vector<int32_t> kv_host;          // committed cache positions per segment (sequence * 2 + branch)
     float *part_o = nullptr, *part_ml = nullptr;
-    float *row_ssq = nullptr;              // [M][up to ceil(d / 32)] partial sums of squares of the residual stream's rows
+    float *row_ssq = nullptr;              // [up to ceil(d / 32)][M] partial sums of squares of the residual stream's rows
     QkvRow *row_meta = nullptr;            // per-row tables of the fused path, rewritten by every forward
     float2 *row_rot = nullptr;
     bool l2_warm = true;                   // projection launches touch the next projection's weights
     uint32_t *pf_sink = nullptr;
     float *skinny_part = nullptr;          // partial tiles of K-split fused projections
     size_t skinny_part_elems = 0;
-    bool fused = false;  // small-M path: fused projection kernels, RMSNorm gains folded into the weights
+    bool fused = false;  // bf16 path of fused projection kernels
+    bool fold_gain = false;  // ... with the RMSNorm gains multiplied into the packed weights, else into the rows
     // weights (owned)
     void *tok_emb = nullptr, *lm_head = nullptr;
     float *final_norm = nullptr;
@@ -414,7 +415,8 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
                    rt.rm = fr.rm; rt.rope_cos = c->rope_cos; rt.rope_sin = c->rope_sin;
                    rt.page_table = c->page_table; rt.pages_per_seg = c->pps; rt.page_tokens = c->pt;
                    rt.L = fr.L; rt.H = H; rt.hd = hd; rt.meta = c->row_meta; rt.rot = c->row_rot;
-                   rt.ssq_part = c->row_ssq; rt.ssq_n = 1;
+                   rt.ssq_part = c->row_ssq;
+                   rt.gain = c->layers[0].attn_norm;
                    embed_dual_kernel<<<M, 256, 0, st>>>((const bf16_t *)c->tok_emb, c->x, (bf16_t *)c->xn, d, rt);
                }));
     SkinnyArgs a;
@@ -510,9 +512,11 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     int ssq_n = 1;   // partial sums per row that the last writer left (0: none); the embedding kernel wrote one
     float *ssq_out = nullptr;   // where the coming output / down projection leaves them: set if its reader takes them
     auto use_ssq = [&]() { a.row_ssq_part = ssq_n > 0 ? c->row_ssq : nullptr; a.row_ssq_n = ssq_n; };
+    // The row-group kernels sum the squares of their operands, which are the stream only while the gains are in the weights
+    auto skinny_ssq = [&]() { if (!c->fold_gain) use_ssq(); };
     auto reduce = [&]() -> int {
         SJD_LAUNCH(c, KC_ADDNORM, after([&] {
-                       resid_reduce_kernel<<<dim3(ceil_div(d, 1024), M), 256, 0, st>>>(c->skinny_part, a.ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out);
+                       resid_reduce_kernel<<<dim3(ceil_div(d, 1024), M), 256, 0, st>>>(c->skinny_part, a.ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out, a.gain);
                    }));
         ssq_n = ceil_div(d, 256);
         return SJD_OK;
@@ -527,7 +531,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             a.kb_per_split = ceil_div(a.KB, 2 * plan.ks) * 2;
             a.ksplit = ceil_div(a.KB, a.kb_per_split);
             if (a.ksplit == 1) {
-                a.ssq_out_n = ssq_n = ceil_div(nb, lds_tile(plan.lds).cb);
+                ssq_n = ceil_div(nb, lds_tile(plan.lds).cb);
                 SJD_LAUNCH(c, cls, launch_lds<EPI_RESID>(st, a, nb, plan.lds));
                 return SJD_OK;
             }
@@ -540,8 +544,10 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             a.ksplit = tile_splits(c, M, a.KB);
             a.kb_per_split = ceil_div(a.KB, a.ksplit);
             if (a.ksplit == 1) {
+                // gains in the weights: the next tile kernel sums the squares of its operands
+                ssq_n = c->fold_gain ? 0 : n_blocks / 2;
+                if (c->fold_gain) a.ssq_out = nullptr;
                 SJD_LAUNCH(c, cls, launch_tile<EPI_RESID>(st, a, n_blocks, tile_rows, mixed_ok));
-                ssq_n = 0;
                 return SJD_OK;
             }
             if ((size_t)a.ksplit * M * d > c->skinny_part_elems) return no_room();
@@ -557,7 +563,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             const int n_compute = compute_wgs(groups, r2, a.row_split);
             warm(n_compute, nx);
             if (kv_next) warm_kv(n_compute, *kv_next);
-            a.ssq_out_n = ssq_n = groups;
+            ssq_n = groups;
             SJD_LAUNCH(c, cls, launch_skinny<EPI_RESID>(st, a, r2 ? 1 : MT, groups, nbw_d, nw_for(groups)));
             a.pf_wgs = a.kv_wgs = 0;
             a.row_split = 1;
@@ -592,6 +598,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_lds<EPI_QKV>(st, a, groups_qkv * 2, plan_qkv.lds));
         } else {
             whole_k();
+            skinny_ssq();
             a.row_split = row_split_for(groups_qkv);
             const bool r2 = rows2_for(groups_qkv);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
@@ -605,7 +612,8 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         }
         if (!with_head && l + 1 == md.n_layers) return SJD_OK;
         { int rc = run_attention<bf16_t>(c, pool, fr); if (rc) return rc; }
-        ssq_out = tile || plan_gu.lds >= 0 ? c->row_ssq : nullptr;
+        ssq_out = tile || plan_gu.lds >= 0 || !c->fold_gain ? c->row_ssq : nullptr;
+        a.gain = lw.mlp_norm;
         { int rc = resid(KC_GEMM_O, c->attn, lw.wo, H * hd, plan_o, proj_of(lw.wgu, F / 32 * 2, d / 16, 2, plan_gu), nullptr); if (rc) return rc; }
         a.A = (const bf16_t *)c->xn; a.W = (const bf16_t *)lw.wgu; a.KB = d / 16;
         if (tile) {
@@ -618,6 +626,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_lds<EPI_SWIGLU>(st, a, F / 32 * 2, plan_gu.lds));
         } else {
             whole_k();
+            skinny_ssq();
             a.row_split = row_split_for(F / 32);
             const bool r2 = rows2_for(F / 32);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
@@ -635,7 +644,8 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         KvPool pool_next = pool;
         pool_next.k = (char *)c->kpool + c->pool_layer_bytes * (l + 1);
         pool_next.v = (char *)c->vpool + c->pool_layer_bytes * (l + 1);
-        ssq_out = tile || (l + 1 < md.n_layers ? plan_qkv : plan_head).lds >= 0 ? c->row_ssq : nullptr;
+        ssq_out = tile || (l + 1 < md.n_layers ? plan_qkv : plan_head).lds >= 0 || !c->fold_gain ? c->row_ssq : nullptr;
+        a.gain = l + 1 < md.n_layers ? c->layers[l + 1].attn_norm : c->final_norm;
         { int rc = resid(KC_GEMM_DOWN, c->h, lw.wdown, F, plan_down, after_down, l + 1 < md.n_layers ? &pool_next : nullptr); if (rc) return rc; }
     }
     if (with_head) {
@@ -662,6 +672,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             SJD_LAUNCH(c, KC_GEMM_HEAD, launch_lds<EPI_HEAD>(st, a, groups_v * 2, plan_head.lds));
         } else {
             whole_k();
+            skinny_ssq();
             if (head_mixed) SJD_LAUNCH(c, KC_GEMM_HEAD, launch_skinny_mixed<EPI_HEAD>(st, a, MT, groups_v));
             else {
                 const bool r2 = head_r2;
@@ -729,8 +740,8 @@ template <typename T> int copy_weights(sjd_ctx *c, const sjd_weights *w) {
     return SJD_OK;
 }
 
-// Weights of the fused small-M path: gains folded in, QKV rows in (head, rotary pair) order, gate and up
-// interleaved by blocks of 32.
+// Weights of the fused path: gains folded in or kept beside (the context's pointers to them stay NULL where they are in the
+// weights), QKV rows in (head, rotary pair) order, gate and up interleaved by blocks of 32.
 int copy_weights_fused(sjd_ctx *c, const sjd_weights *w) {
     typedef bf16_t T;
     const sjd_model_desc &md = c->md;
@@ -746,12 +757,23 @@ int copy_weights_fused(sjd_ctx *c, const sjd_weights *w) {
     auto pack = [&](T *dst, const void *s0, const void *s1, const void *s2, int n0, int n1, int N, int K, const void *g,
                     PackMap pm) -> int {
         if (!s0 || (n0 < N && !s1) || (n1 < N && !s2)) { sjd_set_error(c->err, "null weight pointer"); return SJD_EINVAL; }
-        if (g) to_float_kernel<T><<<ceil_div(K, 256), 256, 0, st>>>((const T *)g, gain, K);
-        pack_weight_fused_kernel<<<2048, 256, 0, st>>>((const T *)s0, (const T *)s1, (const T *)s2, n0, n1, g ? gain : nullptr, dst,
+        const bool fold = g && c->fold_gain;
+        if (fold) to_float_kernel<T><<<ceil_div(K, 256), 256, 0, st>>>((const T *)g, gain, K);
+        pack_weight_fused_kernel<<<2048, 256, 0, st>>>((const T *)s0, (const T *)s1, (const T *)s2, n0, n1, fold ? gain : nullptr, dst,
                                                        N, K, pm);
         return hipGetLastError() == hipSuccess ? SJD_OK : SJD_EDEVICE;
     };
+    float *gains = nullptr;   // final, then attention and MLP norm of every layer
+    if (!c->fold_gain && (rc = dev_alloc(c, &gains, (size_t)d * (1 + 2 * md.n_layers) * sizeof(float), false))) return rc;
+    auto keep_gain = [&](const void *src, float **dst) -> int {
+        if (c->fold_gain) return SJD_OK;
+        to_float_kernel<T><<<ceil_div(d, 256), 256, 0, st>>>((const T *)src, gains, d);
+        *dst = gains;
+        gains += d;
+        return hipGetLastError() == hipSuccess ? SJD_OK : SJD_EDEVICE;
+    };
     const PackMap ident{0, hd, F}, qkvmap{1, hd, F}, gumap{2, hd, F};
+    if ((rc = keep_gain(w->final_norm, &c->final_norm))) return rc;
     T *head;
     if ((rc = dev_alloc(c, &head, Layout<T>::w_elems(ceil_div(c->Vs, 64) * 64, d) * sizeof(T)))) return rc;
     if ((rc = pack(head, (const T *)w->lm_head + (size_t)md.sample_lo * d, nullptr, nullptr, c->Vs, c->Vs, c->Vs, d, w->final_norm, ident)))
@@ -762,6 +784,7 @@ int copy_weights_fused(sjd_ctx *c, const sjd_weights *w) {
     for (int l = 0; l < md.n_layers; ++l) {
         LayerWeights &lw = c->layers[l];
         if (!w->attn_norm[l] || !w->mlp_norm[l]) { sjd_set_error(c->err, "null weight pointer"); return SJD_EINVAL; }
+        if ((rc = keep_gain(w->attn_norm[l], &lw.attn_norm)) || (rc = keep_gain(w->mlp_norm[l], &lw.mlp_norm))) return rc;
         T *qkv, *o, *gu, *down;
         if ((rc = dev_alloc(c, &qkv, Layout<T>::w_elems(Nqkv, d) * sizeof(T)))) return rc;
         if ((rc = pack(qkv, w->wq[l], w->wk[l], w->wv[l], H * hd, (H + Hkv) * hd, Nqkv, d, w->attn_norm[l], qkvmap))) return rc;
@@ -1061,6 +1084,9 @@ int sjd_create(const sjd_model_desc *desc, const sjd_weights *weights, const sjd
     // shape measured 5.9 -> 3.9 ms at 500 rows and 5.4 -> 1.9 ms at 192.
     c->fused = !f32 && !(desc->kernel_flags & SJD_KERNELS_REFERENCE) && c->hd % 64 == 0 &&
                desc->d_model % 32 == 0 && desc->d_ff % 32 == 0;
+    // Windows that fill one row group or whole ones have the gains in the weights: their row-group kernels need no sums of
+    // squares from the kernel before.  All others keep the caller's weights as they are, as the generic GEMMs did for them.
+    c->fold_gain = c->S * 2 * c->L <= 64 || (2 * c->L) % 64 == 0;
     rc = f32 ? copy_weights<float>(c, weights) : (c->fused ? copy_weights_fused(c, weights) : copy_weights<bf16_t>(c, weights));
     if (!rc) rc = f32 ? alloc_buffers<float>(c) : alloc_buffers<bf16_t>(c);
     if (!rc) rc = alloc_state(c);

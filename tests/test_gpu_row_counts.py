@@ -27,3 +27,38 @@ def test_rows_that_fill_no_tile(oracle, name, n_seqs, window):
         worst, steps = _lockstep(o, g, n_seqs, 200, tol_rel=8e-2)
         assert [len(g.tokens(s)) for s in range(n_seqs)] == n
         print(name, n_seqs, window, flags, "steps", steps, "worst logits error abs/rel:", worst)
+
+
+@pytest.mark.parametrize("name,n_seqs,window,prompt,flags", [
+    ("small_fused64", 3, 16, 13, 0),      # 96 rows; a prompt forward of 72
+    ("small_fused64", 3, 16, 8, 0),       # ... of 42: row groups of 32 rows within a context of wider steps
+    ("small_fused64", 1, 33, 25, 4),      # 66 rows in row groups
+    ("small_fused64", 1, 150, 140, 0),    # 300 rows, 278 prompt rows
+    ("small_fused64", 1, 150, 140, 16),   # ... through the tile kernels, whole K
+    ("small_fused128", 3, 41, 70, 0),     # 246 rows, 414 prompt rows
+    ("small_tile", 5, 27, 60, 16),        # 270 rows, ragged column tiles
+])
+def test_norm_gains_cost_no_precision(oracle, name, n_seqs, window, prompt, flags):
+    """Norm gains drawn from U(0.5, 1.5), on contexts that once ran the generic GEMMs with the caller's bf16 weights and the
+    gains applied in fp32: the error of the first step's logits against double precision (2-norm) is no larger than that
+    of the reference kernels, which still do that.  Both sides round at the same number of places (a projection's operand
+    once, after the gain), but for the attention probabilities, which the MFMA kernels have always rounded: one of some ten
+    roundings a layer, up to 1.05 on the ratio.  Gains rounded into the weights are a second rounding of every product of
+    the projections behind a norm, about half of what reaches the logits: sqrt(1.4) = 1.18 (1.15 - 1.22 measured).  The
+    bound lies between; three weight sets a case, so that the ratio scatters by a percent or two."""
+    import numpy as np
+    cfg = workload.get_config(name)
+    sq = np.zeros((2, 2))
+    for i, f in [(i, f) for i in range(3) for f in (flags, 1)]:
+        cfg["seed"] = 100 + i
+        o, g, cond, uncond, n = make_pair(oracle, cfg, window=window, n_image=window + 20, n_seqs=n_seqs, prompt_len=prompt,
+                                          kernel_flags=f, head_alpha=6.0, std=0.05, random_gains=True)
+        want = o.peek_logits().astype(np.float64)
+        g.step()
+        got = g.logits().astype(np.float64)
+        assert np.isfinite(got).all()
+        sq[int(f == 1)] += ((got - want) ** 2).sum(), (want ** 2).sum()
+        o.close(), g.close()
+    err = np.sqrt(sq[:, 0] / sq[:, 1])
+    print(name, n_seqs, window, prompt, flags, "relative error, reference kernels, ratio:", err, err[0] / err[1])
+    assert err[0] <= 1.08 * err[1]
