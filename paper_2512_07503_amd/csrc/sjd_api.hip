@@ -819,25 +819,24 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
     c->page_table = c->pre_dev;
     // workspaces
     if ((rc = dev_alloc(c, &c->x, (size_t)M * d * sizeof(float)))) return rc;
-    size_t pe = 0;
-    const int shapes[4][2] = {{Nqkv, d}, {d, H * hd}, {2 * F, d}, {d, F}};
-    for (auto &s : shapes) {
-        size_t need = (size_t)M * s[0];
-        if (md.dtype == SJD_BF16 && !(md.kernel_flags & SJD_KERNELS_REFERENCE)) {
-            // worst case over the number of sequences actually decoded (M = n * 2 * L) and the rows of a prefill forward
-            // (the plan of M rows is that of its 32-row tiles)
-            auto cover = [&](int m) {
-                GemmPlan p = plan_gemm_bf16(m, s[0], s[1], 0);
-                size_t e = (size_t)p.splits * m * s[0];
-                if (e > need) need = e;
-            };
-            for (int n = 1; n <= S; ++n) cover(n * 2 * L);
-            for (int m = 32; m <= c->pre_rows; m += 32) cover(m);
+    if (!c->fused) {   // the generic path's GEMM outputs, with their K splits
+        const int shapes[4][2] = {{Nqkv, d}, {d, H * hd}, {2 * F, d}, {d, F}};
+        for (auto &s : shapes) {
+            size_t need = (size_t)M * s[0];
+            if (md.dtype == SJD_BF16 && !(md.kernel_flags & SJD_KERNELS_REFERENCE)) {
+                // worst case over the number of sequences actually decoded (M = n * 2 * L) and the rows of a prefill forward
+                // (the plan of M rows is that of its 32-row tiles)
+                auto cover = [&](int m) {
+                    GemmPlan p = plan_gemm_bf16(m, s[0], s[1], 0);
+                    need = std::max(need, (size_t)p.splits * m * s[0]);
+                };
+                for (int n = 1; n <= S; ++n) cover(n * 2 * L);
+                for (int m = 32; m <= c->pre_rows; m += 32) cover(m);
+            }
+            c->partial_elems = std::max(c->partial_elems, need);
         }
-        if (need > pe) pe = need;
+        if ((rc = dev_alloc(c, &c->partial, c->partial_elems * sizeof(float)))) return rc;
     }
-    c->partial_elems = pe;
-    if ((rc = dev_alloc(c, &c->partial, pe * sizeof(float)))) return rc;
     if ((rc = dev_alloc(c, &c->logits, (size_t)S * 2 * L * c->Vs * sizeof(float)))) return rc;
     const int Mpad = ceil_div(M, 64) * 64;   // whole 64-row groups: the row-group projections read every row of the last one
     if ((rc = dev_alloc(c, &c->xn, Layout<T>::a_elems(Mpad, d) * sizeof(T)))) return rc;
@@ -848,11 +847,15 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
     if ((rc = dev_alloc(c, &c->q, q_tiles * H * 32 * hd * sizeof(T)))) return rc;
     if (c->fused) {
         if ((rc = dev_alloc(c, &c->z, (size_t)S * L * c->Vs * sizeof(float)))) return rc;
-        // partial tiles of K-split projections: at most 8 splits of the widest projection (2 column blocks, 2 row tiles)
-        const int widest = std::max(std::max((H + 2 * Hkv) * (hd / 64), F / 32), ceil_div(c->Vs, 64));
-        c->skinny_part_elems = std::max((size_t)widest * 8 * (2 * 2 * 1024 + 64), (size_t)8 * S * 2 * L * d);
-        for (int m = 1; m <= c->pre_rows; ++m)
-            for (int K : {H * hd, F}) c->skinny_part_elems = std::max(c->skinny_part_elems, (size_t)std::max(resid_plan(c, m, K).ks, m < TILE_M ? 1 : tile_splits(c, m, K / 16)) * m * d);
+        // partial sums of the output and down projections where they split K, over the rows a step or a prefill forward can have
+        auto cover = [&](int m) {
+            for (int K : {H * hd, F}) {
+                const int ks = std::max(resid_plan(c, m, K).ks, m < TILE_M ? 1 : tile_splits(c, m, K / 16));
+                if (ks > 1) c->skinny_part_elems = std::max(c->skinny_part_elems, (size_t)ks * m * d);
+            }
+        };
+        for (int n = 1; n <= S; ++n) cover(n * 2 * L);
+        for (int m = 1; m <= c->pre_rows; ++m) cover(m);
         if ((rc = dev_alloc(c, &c->skinny_part, c->skinny_part_elems * sizeof(float)))) return rc;
         if ((rc = dev_alloc(c, &c->pf_sink, 256))) return rc;
         if ((rc = dev_alloc(c, &c->row_ssq, (size_t)M * ceil_div(d, 32) * sizeof(float)))) return rc;
