@@ -57,8 +57,8 @@ enum {
                                 * kernels instead of the LDS-staged tile kernels       */
     SJD_ATTENTION_CHUNKED = 8, /* bf16: always split the context over workgroups and merge
                                 * in a second kernel, also where one workgroup per head
-                                * would do (short contexts); steps only, a prefill always
-                                * runs one workgroup per head and 32 prompt rows       */
+                                * would do (short contexts); a prefill then runs window by
+                                * window instead of packing the prompts' rows          */
     SJD_KERNELS_TILES = 16,    /* bf16, >= 256 rows: the tile kernels also where smaller
                                 * tiles or row groups are expected to be faster        */
     SJD_NO_L2_WARM = 32,       /* bf16, <= 64 rows: projection launches carry no extra

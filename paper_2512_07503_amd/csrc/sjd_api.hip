@@ -55,7 +55,8 @@ struct LayerWeights {
     void *wqkv = nullptr, *wo = nullptr, *wgu = nullptr, *wdown = nullptr;
 };
 
-// The rows of one forward: a decoding step's (L per segment) or a packed piece of the prompts (L = 0).
+// The rows of one forward: a decoding step's (L per segment; prompts in the same form where the context asks for the
+// chunked attention) or a packed piece of the prompts (L = 0).
 struct FwdRows {
     int M = 0, n_segs = 0;
     int L = 0;       // rows per segment; 0: packed
@@ -814,7 +815,9 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
     c->pool_layer_bytes = (size_t)c->n_pages * Hkv * c->pt * hd * sizeof(T);
     if ((rc = dev_alloc(c, &c->kpool, c->pool_layer_bytes * md.n_layers))) return rc;
     if ((rc = dev_alloc(c, &c->vpool, c->pool_layer_bytes * md.n_layers))) return rc;
-    c->pre_elems = (size_t)S * 2 * c->pps + 5 * (size_t)S + 3 * prompt_rows + (prompt_rows / c->pre_rows + 1) * 8 * (size_t)S;
+    const size_t packed = 3 * prompt_rows + (prompt_rows / c->pre_rows + 1) * 8 * (size_t)S;
+    const size_t windows = md.kernel_flags & SJD_ATTENTION_CHUNKED ? (size_t)ceil_div(md.max_ctx - 1, L) * 4 * S * (L + 1) : 0;
+    c->pre_elems = (size_t)S * 2 * c->pps + 5 * (size_t)S + std::max(packed, windows);
     if ((rc = dev_alloc(c, &c->pre_dev, c->pre_elems * sizeof(int32_t)))) return rc;
     c->page_table = c->pre_dev;
     // workspaces
@@ -1155,58 +1158,86 @@ int sjd_prefill(sjd_ctx *c, int32_t n_seqs, const int32_t *const *cond_ids, cons
     c->page_table_host = table;
     c->n_image_host.assign(n_image_tokens, n_image_tokens + n_seqs);
     c->kv_host.assign((size_t)n_segs, 0);
-    // The rows of all prompts one after the other, cut into forwards of about equal size (whole tiles of 256 rows while
-    // there are several); a segment may start in one forward and go on in the next.
-    const size_t n_fwd_max = ceil_div_sz(total_rows, c->pre_rows);
-    const int per_fwd = n_fwd_max < 2 ? c->pre_rows : (int)std::min<size_t>(c->pre_rows, ceil_div_sz(ceil_div_sz(total_rows, n_fwd_max), 256) * 256);
     std::vector<int32_t> &up = c->pre_host;
-    up.assign(table.size() + 5 * (size_t)n_seqs + 3 * total_rows, 0);
+    up.assign(table.size() + 5 * (size_t)n_seqs, 0);
     std::copy(table.begin(), table.end(), up.begin());
-    const size_t o_len = table.size(), o_last = o_len + n_segs, o_img = o_last + n_segs, o_tok = o_img + n_seqs, o_pos = o_tok + total_rows,
-                 o_seg = o_pos + total_rows, o_fwd = o_seg + total_rows;
-    std::vector<FwdRows> fwds;
-    size_t row = 0;
+    const size_t o_len = table.size(), o_last = o_len + n_segs, o_img = o_last + n_segs;
+    auto prompt = [&](int seg) { return seg & 1 ? uncond_ids[seg >> 1] : cond_ids[seg >> 1]; };
+    auto prompt_len = [&](int seg) { return seg & 1 ? uncond_len[seg >> 1] : cond_len[seg >> 1]; };
+    int max_len = 1;
     for (int seg = 0; seg < n_segs; ++seg) {
-        const int32_t *ids = seg & 1 ? uncond_ids[seg >> 1] : cond_ids[seg >> 1];
-        const int len = seg & 1 ? uncond_len[seg >> 1] : cond_len[seg >> 1];
-        up[o_len + seg] = len;
-        up[o_last + seg] = ids[len - 1];
-        c->kv_host[seg] = len - 1;
-        for (int pos = 0; pos < len - 1;) {
-            if (fwds.empty() || fwds.back().M == per_fwd) {
-                fwds.emplace_back();
-                fwds.back().n_segs = n_segs;
-                up.resize(up.size() + 4 * (size_t)n_segs, 0);
-            }
-            FwdRows &f = fwds.back();
-            const size_t f_row0 = row - f.M;
-            const int n = std::min(len - 1 - pos, per_fwd - f.M);
-            int32_t *tab = &up[o_fwd + (fwds.size() - 1) * 4 * (size_t)n_segs];   // seg_kv, seg_n, seg_row0, seg_q0
-            int q0 = 0;   // the segments of a forward come in order: the next free query tile
-            for (int i = 0; i < seg; ++i) q0 += ceil_div(tab[n_segs + i], 32);
-            tab[seg] = pos;
-            tab[n_segs + seg] = n;
-            tab[2 * n_segs + seg] = (int)(row - f_row0);
-            tab[3 * n_segs + seg] = q0;
-            for (int i = 0; i < n; ++i, ++row, ++pos) {
-                up[o_tok + row] = ids[pos];
-                up[o_pos + row] = pos;
-                up[o_seg + row] = seg;
-            }
-            f.M += n;
-            f.n_qt = std::max(f.n_qt, ceil_div(n, 32));
-        }
+        up[o_len + seg] = prompt_len(seg);
+        up[o_last + seg] = prompt(seg)[prompt_len(seg) - 1];
+        c->kv_host[seg] = prompt_len(seg) - 1;
+        max_len = std::max(max_len, prompt_len(seg));
     }
     std::copy(n_image_tokens, n_image_tokens + n_seqs, up.begin() + o_img);
+    std::vector<FwdRows> fwds;
+    if (c->attn_mfma && (c->md.kernel_flags & SJD_ATTENTION_CHUNKED)) {
+        // the chunk kernels take windows of L rows per segment, as in a step
+        const int L = c->L, M = n_segs * L;
+        for (int start = 0; start < max_len - 1; start += L) {
+            const size_t o = up.size();
+            up.resize(o + 2 * (size_t)M + 2 * n_segs, 0);
+            int32_t *tok = &up[o], *pos = tok + M, *kv = pos + M, *n = kv + n_segs;
+            for (int seg = 0; seg < n_segs; ++seg) {
+                kv[seg] = start;
+                n[seg] = std::min(std::max(prompt_len(seg) - 1 - start, 0), L);
+                for (int i = 0; i < L; ++i) {
+                    tok[seg * L + i] = i < n[seg] ? prompt(seg)[start + i] : -1;
+                    pos[seg * L + i] = start + i;
+                }
+            }
+            FwdRows f;
+            f.M = M; f.n_segs = n_segs; f.L = L; f.n_qt = ceil_div(L, 32);
+            const int32_t *dev = c->pre_dev + o;
+            f.rm = {dev, dev + M, dev + 2 * (size_t)M, dev + 2 * (size_t)M + n_segs, nullptr, nullptr, nullptr};
+            fwds.push_back(f);
+        }
+    } else {
+        // The rows of all prompts one after the other, cut into forwards of about equal size (whole tiles of 256 rows while
+        // there are several); a segment may start in one forward and go on in the next.
+        const size_t n_fwd_max = ceil_div_sz(total_rows, c->pre_rows);
+        const int per_fwd = n_fwd_max < 2 ? c->pre_rows : (int)std::min<size_t>(c->pre_rows, ceil_div_sz(ceil_div_sz(total_rows, n_fwd_max), 256) * 256);
+        const size_t o_tok = up.size(), o_pos = o_tok + total_rows, o_seg = o_pos + total_rows;
+        up.resize(o_seg + total_rows, 0);
+        size_t row = 0, o_tab = 0;
+        int q_next = 0;   // next free query tile of the forward
+        for (int seg = 0; seg < n_segs; ++seg) {
+            const int len = prompt_len(seg);
+            for (int pos = 0; pos < len - 1;) {
+                if (fwds.empty() || fwds.back().M == per_fwd) {
+                    o_tab = up.size();   // seg_kv, seg_n, seg_row0, seg_q0
+                    up.resize(o_tab + 4 * (size_t)n_segs, 0);
+                    FwdRows f;
+                    f.n_segs = n_segs;
+                    const int32_t *dev = c->pre_dev, *tab = dev + o_tab;
+                    f.rm = {dev + o_tok + row, dev + o_pos + row, tab, tab + n_segs, dev + o_seg + row, tab + 2 * n_segs, tab + 3 * n_segs};
+                    fwds.push_back(f);
+                    q_next = 0;
+                }
+                FwdRows &f = fwds.back();
+                const int n = std::min(len - 1 - pos, per_fwd - f.M);
+                int32_t *tab = &up[o_tab];
+                tab[seg] = pos;
+                tab[n_segs + seg] = n;
+                tab[2 * n_segs + seg] = f.M;
+                tab[3 * n_segs + seg] = q_next;
+                for (int i = 0; i < n; ++i, ++row, ++pos) {
+                    up[o_tok + row] = prompt(seg)[pos];
+                    up[o_pos + row] = pos;
+                    up[o_seg + row] = seg;
+                }
+                f.M += n;
+                f.n_qt = std::max(f.n_qt, ceil_div(n, 32));
+                q_next += ceil_div(n, 32);
+            }
+        }
+    }
     if (up.size() > c->pre_elems) { sjd_set_error(c->err, "prompt staging too small"); return SJD_EINVAL; }   // cannot happen: sized at create
     SJD_HIP_TRY(c->err, hipMemcpyAsync(c->pre_dev, up.data(), up.size() * 4, hipMemcpyHostToDevice, st));
-    size_t row0 = 0;
-    for (size_t f = 0; f < fwds.size(); ++f) {
-        const int32_t *tab = c->pre_dev + o_fwd + f * 4 * (size_t)n_segs;
-        fwds[f].rm = {c->pre_dev + o_tok + row0, c->pre_dev + o_pos + row0, tab, tab + n_segs, c->pre_dev + o_seg + row0, tab + 2 * n_segs,
-                      tab + 3 * n_segs};
-        row0 += fwds[f].M;
-        int rc = forward_any(c, fwds[f], false);
+    for (const FwdRows &f : fwds) {
+        int rc = forward_any(c, f, false);
         if (rc) return rc;
     }
     SJD_LAUNCH(c, KC_STAGE, launch_init_window(st, c->ds, c->sp, n_seqs, c->S, c->pre_dev + o_last, c->pre_dev + o_len, c->pre_dev + o_img));

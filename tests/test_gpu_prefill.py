@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
     ("small_fused64", [(33, 1), (1, 70), (32, 34)], 0),
     ("small_fused64", [(1500, 1300)], 0),                        # a branch that starts in one forward and goes on in the next
     ("small_fused64", [(90, 80), (100, 60)], 1),                 # reference kernels
-    ("small_fused64", [(90, 80), (100, 60)], 8),                 # chunked window attention for the steps
+    ("small_fused64", [(90, 80), (100, 60)], 8),                 # chunked attention, window by window, in a row group
+    ("small_fused128", [(257, 1), (129, 70), (31, 32)], 8),      # ... 192 rows, segments that end in different windows
+    ("small_bf16", [(200, 31)], 8),                              # ... generic projections
     ("small_fused128", [(257, 1), (129, 70), (31, 32)], 0),
     ("small_tile", [(400, 399), (127, 2), (258, 130)], 16),      # tile kernels, ragged last tile
 ])
@@ -44,3 +46,18 @@ def test_packed_prompts(oracle, name, lens, flags):
         worst = logits_error(g.logits(), want, les)
         print(name, lens, flags, "logits error abs/rel:", worst)
         assert worst[0] <= 1e-4 if cfg["dtype"] == "f32" else worst[1] <= 8e-2
+
+
+@pytest.mark.parametrize("flags,forwards", [(0, 1), (8, 5)])
+def test_chunked_attention_serves_the_prompts_too(flags, forwards):
+    """SJD_ATTENTION_CHUNKED always splits the context over workgroups: with it, 79 prompt rows run as five windows of 16
+    (every layer but the last attends), without it as one packed forward."""
+    import paper_2512_07503_amd as sjd
+    cfg = workload.get_config("small_fused64")
+    w = workload.make_weights(cfg["arch"], cfg["seed"], 6.0, cfg["dtype"], std=0.08)
+    ids = np.arange(80, dtype=np.int32)
+    g = sjd.Decoder(cfg["arch"], gpu_weights(w, cfg["dtype"]), cfg["dtype"], 16, 120, kernel_flags=flags)
+    g.trace(True)
+    assert g.prefill([ids], [ids], [40]) == 0
+    t = g.trace_read()
+    assert t["embed"][0] == forwards and t["window_attention"][0] == forwards * (cfg["arch"]["n_layers"] - 1)
