@@ -60,10 +60,12 @@ def assert_same_state(o, g, n_seqs, where=""):
 
 
 def logits_error(got, want, Le_rows):
-    """max abs difference and max over rows of max|d| / max|want| on the active rows."""
+    """max abs difference and max over rows of max|d| / max|want| on the active rows, which must be finite (max() passes
+    over a NaN)."""
     worst_abs, worst_rel = 0.0, 0.0
     for s, le in enumerate(Le_rows):
         for b in range(2):
+            assert np.isfinite(got[s, b, :le]).all() and np.isfinite(want[s, b, :le]).all(), (s, b)
             for k in range(le):
                 d = np.abs(got[s, b, k] - want[s, b, k]).max()
                 worst_abs = max(worst_abs, float(d))
