@@ -61,3 +61,64 @@ def test_chunked_attention_serves_the_prompts_too(flags, forwards):
     assert g.prefill([ids], [ids], [40]) == 0
     t = g.trace_read()
     assert t["embed"][0] == forwards and t["window_attention"][0] == forwards * (cfg["arch"]["n_layers"] - 1)
+
+
+def _cache_rows(g, arch, pt, n_prompt):
+    """Keys and values of every prompt position from a snapshot taken before the first step: per segment [layers][2][positions]
+    [kv heads * hd].  The pages are the snapshot's tail, [layer][keys, values][segment][page of the segment], a page
+    [kv heads][pt * hd] in the attention's operand layouts (csrc/common.hip.h, Layout<bf16_t>)."""
+    hkv, hd, nl = arch["n_kv_heads"], arch["d_model"] // arch["n_heads"], arch["n_layers"]
+    pages = [-(-n // pt) for n in n_prompt]
+    raw = g.snapshot()
+    blk = hkv * pt * hd
+    vals = raw[raw.size - nl * 2 * sum(pages) * blk * 2:].copy().view(np.uint16).astype(np.uint32) << 16
+    vals = vals.view(np.float32).reshape(nl, 2, sum(pages), hkv, pt * hd)
+    t, j = np.arange(pt)[:, None], np.arange(hd)[None, :]
+    k_idx = (((t >> 5) * (hd >> 4) + (j >> 4)) * 64 + (((j >> 3) & 1) << 5) + (t & 31)) * 8 + (j & 7)
+    grp, e = ((t >> 2) & 1), ((t >> 3) & 1) * 4 + (t & 3)
+    v_idx = ((((t >> 5) * 2 + ((t >> 4) & 1)) * (hd >> 5) + (j >> 5)) * 64 + (grp << 5) + (j & 31)) * 8 + e
+    out, p0 = [], 0
+    for n, np_ in zip(n_prompt, pages):
+        seg = vals[:, :, p0:p0 + np_]
+        kv = np.stack([seg[:, 0][..., k_idx], seg[:, 1][..., v_idx]], 1)       # [layers][2][pages][kv heads][pt][hd]
+        kv = kv.transpose(0, 1, 2, 4, 3, 5).reshape(nl, 2, np_ * pt, hkv * hd)
+        out.append(kv[:, :, :n])
+        p0 += np_
+    return out
+
+
+@pytest.mark.parametrize("name,lens,flags", [
+    ("small_fused64", [(33, 1), (1, 70), (32, 34)], 0),
+    ("small_fused64", [(1500, 1300)], 0),                        # a branch cut between two forwards
+    ("small_fused64", [(90, 80), (100, 60)], 8),                 # window by window
+    ("small_fused128", [(257, 1), (129, 70), (31, 32)], 0),
+    ("small_tile", [(400, 399), (127, 2), (258, 130)], 16),
+])
+def test_every_cached_position(name, lens, flags):
+    """Keys and values of every prompt position, layer by layer, against the reference kernels' (which cut the prompts at 512
+    rows).  A position that holds another's row differs by about sqrt(2) of its 2-norm, a missing one by 1.  Roundings of these
+    wide-weight models move a logit by up to 6e-2 of its row's maximum, i.e. 0.2 of the rms at a maximum of 3 to 4 sigma: the
+    2-norm of a row, a mean over its elements, stays below that."""
+    import paper_2512_07503_amd as sjd
+    cfg = workload.get_config(name)
+    arch, n, pt = cfg["arch"], 40, 64
+    S, L, max_ctx = len(lens), cfg["window"], max(max(p) for p in lens) + n
+    w = gpu_weights(workload.make_weights(arch, cfg["seed"], 6.0, cfg["dtype"], std=0.08), cfg["dtype"])
+    rng = np.random.default_rng(7)
+    cond = [rng.integers(0, arch["vocab"], c).astype(np.int32) for c, _ in lens]
+    uncond = [rng.integers(0, arch["vocab"], u).astype(np.int32) for _, u in lens]
+    got = []
+    for f in (flags, 1):
+        g = sjd.Decoder(arch, w, cfg["dtype"], L, max_ctx, max_seqs=S, top_k=cfg["top_k"], seed=3, kernel_flags=f, kv_page_tokens=pt)
+        assert g.prefill(cond, uncond, [n] * S) == 0
+        got.append(_cache_rows(g, arch, pt, [x - 1 for p in lens for x in p]))
+        g.close()
+    worst = 0.0
+    for a, b in zip(*got):
+        if a.shape[2]:
+            assert np.isfinite(a).all()
+            size = np.linalg.norm(b, axis=-1)
+            assert (size > 0).all()
+            worst = max(worst, float((np.linalg.norm(a - b, axis=-1) / size).max()))
+    print(name, lens, flags, "worst relative difference of a position's keys or values", worst)
+    assert worst < 0.2
