@@ -16,7 +16,7 @@
 // What bounds it: a workgroup alone on its CU is bound by the chain wait - barrier - LDS reads - MFMAs of a stage (0.22 us for
 // 64 x 64, 0.42 us for 192 x 128, the same for 3 to 16 stages in flight: not by memory latency), several side by side by
 // LDS traffic and the 40-45 GB/s at which a CU draws a mix of HBM and L2 lines.  Hence small tiles while a launch has fewer
-// workgroups than CUs, larger ones (fewer bytes per MFMA) as rows are added; lds_us() holds the measured rates.
+// workgroups than CUs, larger ones (fewer bytes per MFMA) as rows are added; lds_us() (plans.h) holds the measured rates.
 // Against the row-group kernels, which split K over the wavefronts of a 64-row workgroup: 4096-wide, 192 rows: QKV
 // 68.6 -> 43.3 us, gate/up 97.8 -> 60.3, down 65 -> 41 with its reduction, head (65 536 ids) 263 -> 135; 1280-wide, 500 rows:
 // gate/up 35.9 -> 18.1, QKV 24.2 -> 15.6, down 27.2 -> 24.2.
@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "kernels_skinny.hip.h"
+#include "plans.h"
 
 typedef __attribute__((address_space(3))) void lds_ptr_t;
 typedef const __attribute__((address_space(1))) void glb_ptr_t;
@@ -344,19 +345,6 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SkinnyArgs a,
     }
 }
 
-// Tile shapes (TMT, TNB, WM, WN, S).  The last one is the head's where a wavefront has to hold a conditional and an
-// unconditional row tile.
-#define SJD_LDS_TILES(X) X(0, 2, 2, 2, 1, 6) X(1, 4, 2, 4, 1, 6) X(2, 4, 4, 4, 2, 5) X(3, 6, 4, 2, 2, 4) X(4, 4, 4, 2, 2, 4)
-constexpr int kLdsTiles = 4, kLdsTileHeadZ = 4;
-struct LdsTile { int tmt, tnb, cb; double t1, t2, tn; };
-// t1, t2, tn: microseconds per pipeline stage of a CU with one workgroup, with two, and per workgroup of more.  Measured on
-// models 768 to 4096 wide at 118 to 2040 rows, weights from HBM.
-inline LdsTile lds_tile(int cfg) {
-    static const LdsTile t[5] = {{2, 2, 2, 0.22, 0.33, 0.14}, {4, 2, 2, 0.27, 0.45, 0.19}, {4, 4, 2, 0.38, 0.56, 0.30}, {6, 4, 2, 0.42, 0.72, 0.37},
-                                 {4, 4, 2, 0.40, 0.62, 0.33}};
-    return t[cfg];
-}
-
 // a.ksplit K ranges of a.kb_per_split (even) k-blocks.
 template <int EPI>
 inline hipError_t launch_lds(hipStream_t st, const SkinnyArgs &a, int n_blocks, int cfg) {
@@ -375,17 +363,3 @@ inline hipError_t launch_lds(hipStream_t st, const SkinnyArgs &a, int n_blocks, 
 #undef SJD_LDS_ONE
     return hipErrorInvalidValue;
 }
-
-// Time of an LDS-tile launch: stages x the busiest CU's workgroups (the column tiles of an XCD run on its CUs only).
-inline double lds_us(int cfg, int M, int n_blocks, int KB, int ks, int n_cus) {
-    const LdsTile t = lds_tile(cfg);
-    const int wgs_xcd = ceil_div(ceil_div(n_blocks, t.tnb), 8) * ceil_div(M, 32 * t.tmt) * ks;
-    const int n = ceil_div(wgs_xcd, std::max(1, n_cus / 8));
-    return 4.0 + (double)ceil_div(KB, 2 * ks) * (n == 1 ? t.t1 : n == 2 ? t.t2 : n * t.tn);
-}
-// ... of a row-group launch (kernels_skinny.hip.h): a CU moves 52 GB/s of weights and activations
-inline double skinny_us(int wgs, double wg_bytes, bool norm, int n_cus) {
-    return 5.0 + ceil_div(wgs, n_cus) * wg_bytes / 52e3 + (norm ? 2.5 : 0.0);
-}
-// ... and of the kernel that adds ks partial sums of M rows of d columns
-inline double reduce_us(int M, int d, int ks) { return std::max(6.7, 3.0 + (ks + 2.0) * M * d * 4.0 / 5e6); }

@@ -28,8 +28,8 @@
 // CUs leave room for.
 #pragma once
 #include "kernels_skinny.hip.h"
+#include "plans.h"
 
-constexpr int TILE_M = 256, TILE_N = 128;
 constexpr int TILE_KS = 1;    // k-steps (of 16) per pipeline stage, i.e. per workgroup barrier
 #ifndef SJD_TILE_RING
 #define SJD_TILE_RING 4
@@ -330,37 +330,6 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_mixed_kernel(SkinnyArgs a, i
                                                                 int row_tiles2, int row_tiles1) {
     if ((int)blockIdx.x < wg_split) tile_body<EPI, SSQ_LOOP, 2, TILE_KS, TILE_RING>(a, blockIdx.x, blockIdx.y, n_blocks, row_tiles32, ct_split, row_tiles2, 0);
     else tile_body<EPI, SSQ_LOOP, 1, TILE_KS, TILE_RING>(a, blockIdx.x - wg_split, blockIdx.y, n_blocks, row_tiles32, col_tiles - ct_split, row_tiles1, ct_split);
-}
-
-// Rows per workgroup tile for n_blocks column blocks over M rows.  256 rows (two 32-row tiles per wavefront) need
-// the fewest operand bytes per MFMA: 0.75 KiB against 1.25 KiB for 128 rows, whose weight fragments alone would
-// take the whole LDS bandwidth at full MFMA rate.  128 rows are chosen where they spread the work better: when
-// 256-row tiles would not even fill the CUs, or when the most loaded CU (a launch takes as long as that one)
-// gets less work - ceil(workgroups / CUs) tiles of 256 rows against as many half-size ones.
-inline int tile_rows_for(int M, int n_blocks, int ksplit, int n_cus) {
-    const int col_tiles = (n_blocks + 3) / 4;
-    const long wg2 = (long)col_tiles * ((M + 255) / 256) * ksplit, wg1 = (long)col_tiles * ((M + 127) / 128) * ksplit;
-    if (wg2 < n_cus) return 128;
-    const long cost2 = 2 * ((wg2 + n_cus - 1) / n_cus), cost1 = (wg1 + n_cus - 1) / n_cus;
-    return cost1 < cost2 ? 128 : 256;
-}
-
-// Time of a launch: 32-wide K stages x the busiest CU's tiles (the column tiles of an XCD run on its CUs only): 0.27 us a
-// 128-row tile (0.40 alone on its CU), 0.45 a 256-row tile, 0.27 per 128 x 128 in a launch of both heights.  Measured on
-// models 1280 to 4096 wide at 260 to 2040 rows.
-inline bool tile_two_heights(int M, int n_blocks, int ksplit, int n_cus) {
-    const int col_tiles = (n_blocks + 3) / 4, rt2 = (M + 255) / 256, rt1 = (M + 127) / 128;
-    return ksplit == 1 && rt1 > rt2 && col_tiles * rt2 > n_cus && col_tiles * rt2 < 2 * n_cus && n_cus / rt2 >= 8 && (col_tiles * rt1) % n_cus != 0;
-}
-inline double tile_us(int M, int n_blocks, int KB, int ksplit, int n_cus) {
-    const int col_tiles = (n_blocks + 3) / 4, rows = tile_rows_for(M, n_blocks, ksplit, n_cus);
-    const double stages = KB / (2.0 * ksplit);
-    if (tile_two_heights(M, n_blocks, ksplit, n_cus)) {
-        const int rt2 = (M + 255) / 256, ct_split = n_cus / rt2 / 8 * 8;
-        return 12.0 + stages * 0.27 * (2.0 * ct_split * rt2 + (double)(col_tiles - ct_split) * ((M + 127) / 128)) / n_cus;
-    }
-    const int per_xcd = (col_tiles + 7) / 8 * ((M + rows - 1) / rows) * ksplit, cus = n_cus >= 8 ? n_cus / 8 : 1, n = (per_xcd + cus - 1) / cus;
-    return 12.0 + stages * (rows == 256 ? 0.45 * n : n == 1 ? 0.40 : 0.27 * n);
 }
 
 // n_blocks = packed 32-column blocks of W.  The K range of a workgroup is a.kb_per_split k-blocks (grid.y = a.ksplit).

@@ -106,6 +106,7 @@ struct sjd_ctx {
     uint32_t *pf_sink = nullptr;
     float *skinny_part = nullptr;          // partial tiles of K-split fused projections
     size_t skinny_part_elems = 0;
+    ProjShape shape{};   // what the choice of the fused projections' kernels depends on
     bool fused = false;  // bf16 path of fused projection kernels
     bool fold_gain = false;  // ... with the RMSNorm gains multiplied into the packed weights, else into the rows
     // weights (owned)
@@ -333,73 +334,6 @@ template <typename T> int forward(sjd_ctx *c, const FwdRows &fr, bool with_head)
     return SJD_OK;
 }
 
-int resid_nbw(int d) { return ceil_div(d, 32) >= 128 ? 2 : 1; }   // column blocks per workgroup of an output / down projection
-// More than 32 rows and so few column groups that a workgroup per group and 32-row tile still finds a CU of its own
-bool rows_of_32(const sjd_ctx *c, int M, int groups) {
-    return M > 32 && 2 * ceil_div(M, 64) * 8 * ceil_div(groups, 8) <= c->n_cus && !(c->md.kernel_flags & SJD_NO_ROW_SPLIT);
-}
-
-// How a projection runs: row groups (lds < 0) or LDS tiles of shape `lds`; ks: splits of K (output / down projections, whose
-// partial sums resid_reduce_kernel adds); us: its expected time, on which the choice rests.
-struct ProjPlan { int lds, ks; double us; };
-ProjPlan with_lds(const sjd_ctx *c, int M, int n_blocks, int KB, int max_ks, ProjPlan p, double extra_us) {
-    if (M <= 64 || (c->md.kernel_flags & SJD_KERNELS_ROWGROUPS)) return p;
-    for (int cfg = 0; cfg < kLdsTiles; ++cfg)
-        for (int ks = 1; ks <= max_ks; ks *= 2) {
-            if (ks > 1 && KB / ks < 32) continue;
-            const double t = extra_us + lds_us(cfg, M, n_blocks, KB, ks, c->n_cus) + (ks > 1 ? reduce_us(M, c->md.d_model, ks) : 0.0);
-            if (t < p.us) p = {cfg, ks, t};
-        }
-    return p;
-}
-// QKV, gate/up and head: groups of two column blocks, whole K.  (2 us: the sums of squares that the row-group kernel takes
-// from its operands come from the writer of the rows with LDS tiles.)
-ProjPlan norm_plan(const sjd_ctx *c, int M, int groups) {
-    const int d = c->md.d_model, mt = M <= 32 || rows_of_32(c, M, groups) ? 1 : 2;
-    const ProjPlan p = {-1, 1, skinny_us(ceil_div(M, 32 * mt) * groups, (double)(64 + 32 * mt) * d * 2.0, true, c->n_cus)};
-    return with_lds(c, M, groups * 2, d / 16, 1, p, 2.0);
-}
-ProjPlan resid_plan(const sjd_ctx *c, int M, int K) {
-    const int d = c->md.d_model, KB = K / 16, nbw = resid_nbw(d), groups = ceil_div(ceil_div(d, 32), nbw);
-    const int mt = M <= 32 || rows_of_32(c, M, groups) ? 1 : 2;
-    const double wg_bytes = (double)(nbw * 32 + mt * 32) * K * 2.0;
-    int ks = 1;
-    if (wg_bytes > 512e3) {   // one workgroup's share is too much for its CU
-        ks = std::min(8, std::max(1, c->n_cus / (groups * ceil_div(M, 64))));
-        while (ks > 1 && KB / ks < 32) --ks;
-        ks = ceil_div(KB, ceil_div(KB, ks));
-    }
-    const ProjPlan p = {-1, ks, skinny_us(ceil_div(M, 32 * mt) * groups * ks, wg_bytes / ks, false, c->n_cus) + (ks > 1 ? reduce_us(M, d, ks) : 0.0)};
-    return with_lds(c, M, ceil_div(d, 32), KB, 4, p, 0.0);
-}
-
-// The tile kernels (kernels_tile.hip.h): K splits of an output / down projection, and the same estimate for a layer.
-int tile_splits(const sjd_ctx *c, int M, int KB) {
-    int ks = std::min(8, std::max(1, c->n_cus / (ceil_div(ceil_div(c->md.d_model, 64) * 2, 4) * ceil_div(M, TILE_M))));
-    while (ks > 1 && KB / ks < 32) --ks;
-    return ceil_div(KB, ceil_div(KB, ks));
-}
-double tile_layer_us(const sjd_ctx *c, int M) {
-    const sjd_model_desc &md = c->md;
-    const int d = md.d_model;
-    auto resid = [&](int K) {
-        const int ks = tile_splits(c, M, K / 16);
-        return tile_us(M, ceil_div(d, 64) * 2, K / 16, ks, c->n_cus) + (ks > 1 ? reduce_us(M, d, ks) : 0.0);
-    };
-    return tile_us(M, (md.n_heads + 2 * md.n_kv_heads) * (c->hd / 64) * 2, d / 16, 1, c->n_cus) + tile_us(M, md.d_ff / 32 * 2, d / 16, 1, c->n_cus) +
-           resid(md.n_heads * c->hd) + resid(md.d_ff);
-}
-// From 256 rows on: the tile kernels where their heights fit the rows and the CUs, else the mix of LDS tiles and row groups.
-// Measured, prompts through 6 layers of the 4096-wide shape, ms: 260 rows 1.38 (tile kernels) against 1.19; 700 2.39 / 2.05;
-// 1000 2.62 / 2.87; 1400 4.22 / 3.97; 2040 5.28 / 5.47; 1280-wide, 16 layers: 1000 rows 2.01 / 1.69, 2040 3.18 / 2.71.
-bool tile_forward(const sjd_ctx *c, int M) {
-    if (M < TILE_M || (c->md.kernel_flags & SJD_KERNELS_ROWGROUPS)) return false;
-    if (c->md.kernel_flags & SJD_KERNELS_TILES) return true;
-    const sjd_model_desc &md = c->md;
-    return tile_layer_us(c, M) < norm_plan(c, M, (md.n_heads + 2 * md.n_kv_heads) * (c->hd / 64)).us + norm_plan(c, M, md.d_ff / 32).us +
-                                     resid_plan(c, M, md.n_heads * c->hd).us + resid_plan(c, M, md.d_ff).us;
-}
-
 // Small-M bf16 path: five kernels per layer (QKV+RoPE+KV write, attention, out+residual, gate/up+SwiGLU,
 // down+residual); c->xn holds the bf16 copy of the residual stream.
 int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
@@ -444,7 +378,9 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // shapes' gate/up and head) a CU's outstanding misses are the limit either way, the second wavefront of a SIMD
     // only queues behind the first, and 4 win by the cheaper LDS reduction.
     auto nw_for = [](int groups) { return groups >= 200 ? 4 : 8; };
-    const bool tile = tile_forward(c, M);
+    const bool want_z = c->z && !(md.kernel_flags & SJD_NO_HEAD_FUSION);
+    const ForwardPlan plan = forward_plan(c->shape, M, want_z && fr.L == 32);
+    const bool tile = plan.tile;
     // output / down projection: x += A W^T.  One kernel when a workgroup's share is small, else K split over
     // grid.y with the partial sums added by resid_reduce_kernel after the kernel boundary.
     // Every few-row projection launch carries extra workgroups that touch the weights of the projection after it,
@@ -455,7 +391,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // More than 32 rows and so few column groups that a workgroup per group and 32-row tile still finds a CU of its
     // own: row groups of 32 rows instead of 64 (all row groups of a column group on one XCD, whose L2 serves the
     // later readers of the weights).  Each workgroup pulls half the activations, twice as many CUs work.
-    auto rows2_for = [&](int groups) { return rows_of_32(c, M, groups); };
+    auto rows2_for = [&](int groups) { return rows_of_32(c->shape, M, groups); };
     // computing workgroups of a launch over `groups` column groups
     auto compute_wgs = [&](int groups, bool r2, int row_split) {
         if (r2) return 2 * m_groups * 8 * ceil_div(groups, 8);
@@ -468,12 +404,8 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         const int tnb = lds_tile(p.lds).tnb;
         return Proj{W, n_blocks / tnb, tnb, KB, p.ks == 1};   // whole tiles only: a ragged last one ends with the matrix
     };
-    const int groups_v = ceil_div(ceil_div(c->Vs, 32), 2);
-    ProjPlan plan_head = norm_plan(c, M, groups_v);
-    // windows of 32: the head combines the guidance branches, which needs both row tiles of a sequence in one wavefront
-    const bool want_z = c->z && !(md.kernel_flags & SJD_NO_HEAD_FUSION);
-    if (plan_head.lds >= 0 && want_z && fr.L == 32) plan_head.lds = kLdsTileHeadZ;
-    const ProjPlan plan_qkv = norm_plan(c, M, groups_qkv), plan_o = resid_plan(c, M, H * hd), plan_gu = norm_plan(c, M, F / 32), plan_down = resid_plan(c, M, F);
+    const int groups_v = c->shape.head_groups();
+    const ProjPlan &plan_qkv = plan.qkv, &plan_o = plan.o, &plan_gu = plan.gate_up, &plan_down = plan.down, &plan_head = plan.head;
     auto warm = [&](int cur_groups, const Proj &nx) {
         a.pf_wgs = 0;
         if (!c->l2_warm || tile || !nx.whole || !nx.W) return;
@@ -542,7 +474,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         }
         if (tile) {
             const int n_blocks = ceil_div(d, 64) * 2;
-            a.ksplit = tile_splits(c, M, a.KB);
+            a.ksplit = tile_splits(c->shape, M, a.KB);
             a.kb_per_split = ceil_div(a.KB, a.ksplit);
             if (a.ksplit == 1) {
                 // gains in the weights: the next tile kernel sums the squares of its operands
@@ -853,7 +785,7 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
         // partial sums of the output and down projections where they split K, over the rows a step or a prefill forward can have
         auto cover = [&](int m) {
             for (int K : {H * hd, F}) {
-                const int ks = std::max(resid_plan(c, m, K).ks, m < TILE_M ? 1 : tile_splits(c, m, K / 16));
+                const int ks = std::max(resid_plan(c->shape, m, K).ks, m < TILE_M ? 1 : tile_splits(c->shape, m, K / 16));
                 if (ks > 1) c->skinny_part_elems = std::max(c->skinny_part_elems, (size_t)ks * m * d);
             }
         };
@@ -1080,6 +1012,7 @@ int sjd_create(const sjd_model_desc *desc, const sjd_weights *weights, const sjd
         }
         (void)hipGetLastError();
     }
+    c->shape = {desc->d_model, desc->n_heads, desc->n_kv_heads, desc->d_ff, c->Vs, c->n_cus, desc->kernel_flags};
     c->keep_logits = (desc->kernel_flags & SJD_KEEP_LOGITS) != 0;
     const bool f32 = desc->dtype == SJD_F32;
     c->use_graph = !(desc->kernel_flags & SJD_NO_GRAPH) && hip_stream != nullptr;  // the default stream cannot be captured

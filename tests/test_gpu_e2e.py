@@ -68,8 +68,8 @@ def test_small_models_step_by_step(oracle, name, flags):
                                                    ("small_fused64", None, None, 1), ("small_f32", 1, None, None),
                                                    ("small_f32", None, float("inf"), None), ("small_f32", None, None, 1),
                                                    ("small_sub", 2, 0.0, None),
-                                                   # windows longer than one 32-row attention tile: 48 (generic GEMMs),
-                                                   # 64 (two row groups of the fused projections)
+                                                   # windows longer than one 32-row attention tile: 48 (96 rows, a row
+                                                   # group and a half), 64 (two row groups)
                                                    ("small_fused64", 48, None, None), ("small_fused64", 64, None, None),
                                                    # 33..64 rows: two row groups of 32 per column group (24: 48 rows,
                                                    # the second group half empty)
@@ -91,8 +91,8 @@ def test_decoding_modes_step_by_step(oracle, name, window, tau, top_k):
 
 @pytest.mark.parametrize("name,window", [("small_fused64", 250), ("small_fused64", 256), ("small_f32", 250)])
 def test_paper_sized_window_step_by_step(oracle, name, window):
-    """The largest window the paper uses (250, its 24 x 24-token model; Sec. 5.1) on a 320-token image: 500 rows take the
-    generic projections (not a multiple of 64), 256 the fused row groups; eight query tiles in the attention."""
+    """The largest window the paper uses (250, its 24 x 24-token model; Sec. 5.1) on a 320-token image: 500 rows end inside
+    a row tile and keep the norm gains out of the weights, 512 fill whole row groups; eight query tiles in the attention."""
     cfg = workload.get_config(name)
     o, g, cond, uncond, n_img = make_pair(oracle, cfg, window=window, n_image=320, head_alpha=6.0, std=0.08)
     f32 = cfg["dtype"] == "f32"
@@ -118,7 +118,7 @@ def test_context_grows_past_the_one_workgroup_attention(oracle, name, prompt, fl
                                                        ("small_fused64", 3, 8, 0), ("small_fused64", 4, 16, 0)])
 def test_several_sequences_in_the_row_groups(oracle, name, n_seqs, window, flags):
     """Sequences of different lengths share a forward: 2 x 16-token windows fill two row groups of 32 rows (one of 64
-    with flag 128), 3 x 8 leave the second group half empty, 4 x 16 = 128 rows take the generic GEMMs; each sequence
+    with flag 128), 3 x 8 leave the second group half empty, 4 x 16 = 128 rows fill two groups of 64; each sequence
     keeps its own accept length and page table."""
     cfg = workload.get_config(name)
     n_image = [40, 23, 31, 12][:n_seqs]
@@ -207,9 +207,12 @@ def _shape_weights(name, layers, random_gains):
     ("cfg2", 2, 64, 3, 1, 0, None), ("cfg2", 2, 64, 3, 1, 0, 12), ("cfg2", 2, 64, 2, 1, 512, None),
     # ... one group per workgroup; 64-row groups; chunk + merge attention
     ("cfg3", 2, 64, 3, 1, 0, None), ("cfg3", 2, 64, 2, 1, 256, None), ("cfg3", 2, 64, 2, 1, 128, None), ("cfg3", 2, 64, 3, 1, 8, None),
-    # 3 and 5 sequences on the tile kernels (192 and 320 rows; at 320 the gate/up launch mixes 256-row and 128-row
-    # tiles); 256-row workgroup tiles only; one tile height per launch
-    ("cfg4", 2, 64, 3, 3, 0, None), ("cfg4", 2, 64, 2, 5, 0, None), ("cfg4", 2, 64, 2, 5, 64, None), ("cfg4", 2, 64, 2, 5, 256, None)])
+    # 3 and 5 sequences: 192 and 320 rows through LDS tiles; the same 320 through the tile kernels, whose gate/up launch
+    # mixes 256-row and 128-row tiles; 256-row workgroup tiles only; one tile height per launch
+    ("cfg4", 2, 64, 3, 3, 0, None), ("cfg4", 2, 64, 2, 5, 0, None), ("cfg4", 2, 64, 2, 5, 16, None), ("cfg4", 2, 64, 2, 5, 16 + 64, None),
+    ("cfg4", 2, 64, 2, 5, 16 + 256, None),
+    # 7 sequences: 448 rows, the tile kernels by choice (tests/test_plan_choice.py holds these cases to their kernels)
+    ("cfg4", 2, 64, 1, 7, 0, None)])
 def test_benchmark_shapes_bf16(oracle, name, layers, prompt, steps, S, flags, window):
     """The benchmark shapes: full depth at short context for configs[1]; the 7B-class widths, heads, GQA, vocabulary
     sub-range and batch on depth-reduced twins (a full-depth fp64 CPU forward of those takes hours)."""

@@ -1,0 +1,57 @@
+"""The choice of projection kernels (csrc/plans.h): the GPU tests that are there for certain kernels reach them."""
+import plan_choice
+import workload
+
+EPILOGUE = dict(qkv="QKV", gate_up="SWIGLU", head="HEAD")
+
+
+def _pairs(plan, with_head):
+    """(epilogue, LDS tile shape or -1) of the launches of a forward that does not run through the tile kernels."""
+    out = set()
+    for proj in ("qkv", "out", "gate_up", "down") + (("head",) if with_head else ()):
+        shape, ks = plan[proj]
+        out.add((EPILOGUE.get(proj, "RESID" if ks == 1 else "PARTIAL"), shape))
+    return out
+
+
+def test_the_lds_tile_cases_reach_every_shape_and_epilogue():
+    import test_gpu_lds_tiles as t
+    queries, heads = [], []
+    for d, h, kv, ff, ids, window, lens in t.CASES:
+        a, rows = t.case_arch(d, h, kv, ff, ids), len(lens) * 2 * window
+        queries += [(a, rows, window, 0), (a, rows, window, 2048), (a, sum(c + u - 2 for c, u in lens), 0, 0)]
+        heads += [True, True, False]
+    reached = set()
+    for plan, head in zip(plan_choice.choose(queries), heads):
+        if not plan["tile"]:
+            reached |= _pairs(plan, head)
+    shapes = {(e, s) for e in ("QKV", "SWIGLU", "RESID", "PARTIAL", "HEAD") for s in range(4)} | {("HEAD", 4)}
+    assert shapes <= reached, shapes - reached
+    # the fused head's shape is compared with two of the others: windows of 32 with and without it
+    fused = [(p[0]["head"][0], p[1]["head"][0]) for p in zip(*[iter(plan_choice.choose([q for q in queries if q[2] == 32]))] * 2) if p[0]["head"][0] >= 0]
+    assert {f for f, _ in fused} == {4} and len({g for _, g in fused}) >= 3, fused
+
+
+def test_the_benchmark_shape_cases_reach_the_tile_kernels():
+    arch = workload.get_config("cfg4")["arch"]
+
+    def plan(seqs, flags):
+        return plan_choice.choose([(arch, seqs * 64, 32, flags)])[0]
+    assert not plan(3, 0)["tile"] and not plan(5, 0)["tile"]
+    p = plan(5, 16)
+    assert p["tile"] and p["two_heights"]["gate_up"] and 128 in p["tile_rows"].values()
+    p = plan(7, 0)
+    assert p["tile"] and p["two_heights"]["gate_up"] and p["tile_splits"]["down"] > 1
+    assert plan(8, 0)["tile"]                 # the benchmark's throughput batch
+    assert not plan(8, 4)["tile"]             # row groups only
+    import test_gpu_e2e as e
+    marks = [m for m in e.test_benchmark_shapes_bf16.pytestmark if m.name == "parametrize"][0]
+    cases = {(c[4], c[5]) for c in marks.args[1] if c[0] == "cfg4"}
+    assert {(3, 0), (5, 0), (5, 16), (5, 16 + 64), (5, 16 + 256), (7, 0)} <= cases
+
+
+def test_few_rows_and_the_row_group_flag_keep_the_row_groups():
+    arch = workload.get_config("cfg1")["arch"]
+    for rows, flags in ((32, 0), (64, 0), (500, 4)):
+        p = plan_choice.choose([(arch, rows, 0, flags)])[0]
+        assert not p["tile"] and all(p[n][0] == -1 for n in ("qkv", "out", "gate_up", "down", "head"))
