@@ -180,7 +180,7 @@ SJD_D float row_ssq_sum(const SkinnyArgs &a, int m, int c0, int step) {
 SJD_D float silu(float g) { return __fdividef(g, 1.0f + __expf(-g)); }
 
 // the value of the residual stream whose square the next norm sums: the fp32 stream, or what its bf16 copy holds
-SJD_D float ssq_value(const SkinnyArgs &a, float v) { return a.gain ? v : bf16_to_float(float_to_bf16(v)); }
+template <bool ROWS> SJD_D float ssq_value(float v) { return ROWS ? v : bf16_to_float(float_to_bf16(v)); }
 
 // One output element pair of the projection epilogues: row m, column `col` of NBW consecutive column blocks
 // (val[i] = block blk0 + i), inv = 1 / rms of row m (1 where the epilogue does not normalise).
@@ -266,10 +266,11 @@ SJD_D void l2_warm_kv(const SkinnyArgs &a, int id, int first_id, int tid, int th
     if (sink == 0x9e3779b9u) *a.pf_sink = sink;
 }
 
-template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT>
+template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT, bool ROWS>
 SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0);
 
-template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT = false>
+// ROWS: the norm gains are in the rows (QKV, SWIGLU, HEAD: sums of squares from row_ssq_part; RESID: gain, ssq_out)
+template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT, bool ROWS>
 __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs a) {
     const int tid = threadIdx.x;
     // computing workgroups come first: one per column group, or (row_split 2) two, listed per XCD like row groups
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs a) {
         half = (blockIdx.x >> 3) & 1;
         if (g >= a.groups) return;
     }
-    skinny_body<MT, NBW, NW, DEPTH, EPI, SPLIT>(a, g, mg, half, g * NBW);
+    skinny_body<MT, NBW, NW, DEPTH, EPI, SPLIT, ROWS>(a, g, mg, half, g * NBW);
 }
 
 // Workgroups of two widths in one launch, for more than 256 column groups of two blocks (gate/up and vocabulary
@@ -307,19 +308,20 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs a) {
 // activations)) while the others idle half the time.  Here the first n_heavy workgroups take two consecutive groups
 // (4 blocks: one pass over the activations for both) and the others one, n_heavy + (groups - 2 n_heavy) workgroups in
 // all: 256 for up to 512 groups.  The register count admits one workgroup per CU, so each CU gets one.
-template <int MT, int NW, int DEPTH, int EPI>
+template <int MT, int NW, int DEPTH, int EPI, bool ROWS>
 __global__ __launch_bounds__(NW * 64) void gemm_skinny_mixed_kernel(SkinnyArgs a) {
     static_assert(EPI == EPI_SWIGLU || EPI == EPI_HEAD, "epilogues that take any even number of blocks");
     const int w = blockIdx.x;
     // (the wide body's ring has 3/4 of the slots: 6 fragments per slot instead of 4, more bytes in flight all the same)
-    if (w < a.n_heavy) skinny_body<MT, 4, NW, DEPTH * 3 / 4, EPI, false>(a, 2 * w, 0, 0, 4 * w);
-    else skinny_body<MT, 2, NW, DEPTH, EPI, false>(a, a.n_heavy + w, 0, 0, 2 * (a.n_heavy + w));
+    if (w < a.n_heavy) skinny_body<MT, 4, NW, DEPTH * 3 / 4, EPI, false, ROWS>(a, 2 * w, 0, 0, 4 * w);
+    else skinny_body<MT, 2, NW, DEPTH, EPI, false, ROWS>(a, a.n_heavy + w, 0, 0, 2 * (a.n_heavy + w));
 }
 
 // The workgroup's work: column blocks [blk0, blk0 + NBW) (column group g of the QKV epilogue), row group mg.
-template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT>
+template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT, bool ROWS>
 SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
     constexpr bool kNorm = EPI != EPI_RESID && EPI != EPI_PARTIAL;
+    constexpr bool kSsqLoop = kNorm && !ROWS;   // sums of squares from the operands
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the k-loop control flow scalar
     const bool a_lane = !SPLIT || ((lane >> 4) & 1) == half;  // SPLIT false: a constant, the loads below stay unconditional
@@ -349,8 +351,8 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
 #pragma unroll
     for (int i = 0; i < NBW; ++i) {
         gpre[i] = 1.0f;
-        if constexpr (EPI == EPI_RESID)
-            if (const int n = (blk0 + i) * 32 + (lane & 31); a.gain && n < a.N) gpre[i] = a.gain[n];
+        if constexpr (EPI == EPI_RESID && ROWS)
+            if (const int n = (blk0 + i) * 32 + (lane & 31); n < a.N) gpre[i] = a.gain[n];
     }
     [[maybe_unused]] QkvRow qrow[MT][EPT];
     [[maybe_unused]] float rot_c[MT][EPT], rot_s[MT][EPT];
@@ -408,7 +410,7 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
             for (int j = 0; j < MT; ++j) {
                 const u32x4 araw = aq[s][j];
                 const bf16x8 av = __builtin_bit_cast(bf16x8, araw);
-                if (kNorm) {
+                if (kSsqLoop) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const uint32_t pr = araw[e];
@@ -465,8 +467,10 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
     if (kNorm) {
 #pragma unroll
         for (int j = 0; j < MT; ++j) {
-            float t = ssq[j] + __shfl_xor(ssq[j], 32, 64);
-            if (a.row_ssq_part) {   // from the writer of the rows: wavefront w adds its partial sums w, w + NW, ...
+            float t;
+            if constexpr (kSsqLoop) {
+                t = ssq[j] + __shfl_xor(ssq[j], 32, 64);
+            } else {   // from the writer of the rows: wavefront w adds its partial sums w, w + NW, ...
                 const int m = m_base + j * 32 + (lane & 31);
                 t = m < a.M ? row_ssq_sum(a, m, wave, NW) : 0.0f;
             }
@@ -556,7 +560,7 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
                     float sq = 0.0f;
 #pragma unroll
                     for (int i = 0; i < NBW; ++i) {
-                        const float f = (blk0 + i) * 32 + col < a.N ? ssq_value(a, xin[i] + vals[i]) : 0.0f;
+                        const float f = (blk0 + i) * 32 + col < a.N ? ssq_value<ROWS>(xin[i] + vals[i]) : 0.0f;
                         sq = fmaf(f, f, sq);
                     }
 #pragma unroll
@@ -650,11 +654,13 @@ __global__ void pack_weight_fused_kernel(const bf16_t *__restrict__ s0, const bf
     }
 }
 
-// x[m][n] += sum_ks part[ks][m][n];  xb = bf16(x), or bf16(x * gain) where gain is given, in GEMM-operand layout.
+// x[m][n] += sum_ks part[ks][m][n];  xb = bf16(x), or (ROWS: the norm gains are in the rows) bf16(x * gain), in GEMM-operand
+// layout.
 // One wavefront per (row, 256 columns): a lane takes four consecutive columns (16-byte loads of the stream and of every
 // partial sum, one 8-byte store of the four bf16, which are neighbours in the operand layout), and the chunk's sum of
 // squares is a wavefront reduction: no barrier.  grid (ceil(N / 1024), M), 256 threads.
-// ssq_part (may be NULL): [ceil(N / 256)][M] sums of squares per chunk, of the bf16 values written or (with gain) of x.
+// ssq_part (may be NULL): [ceil(N / 256)][M] sums of squares per chunk, of the bf16 values written or (ROWS) of x.
+template <bool ROWS>
 __global__ __launch_bounds__(256) void resid_reduce_kernel(const float *__restrict__ part, int ksplit, int M, int N, float *__restrict__ x,
                                                            bf16_t *__restrict__ xb, float *__restrict__ ssq_part, const float *__restrict__ gain) {
     const int m = blockIdx.y, chunk = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -669,7 +675,7 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(const float *__restri
         }
         *reinterpret_cast<float4 *>(x + idx) = v;
         float4 o = v;
-        if (gain) {
+        if (ROWS) {
             const float4 g = *reinterpret_cast<const float4 *>(gain + n);
             o.x *= g.x; o.y *= g.y; o.z *= g.z; o.w *= g.w;
         }
@@ -678,7 +684,7 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(const float *__restri
         packed.x = (uint32_t)b0 | ((uint32_t)b1 << 16);
         packed.y = (uint32_t)b2 | ((uint32_t)b3 << 16);
         *reinterpret_cast<uint2 *>(xb + Layout<bf16_t>::a_index(m, n, N)) = packed;   // n % 4 == 0: one 8-element group
-        if (!gain) v = make_float4(bf16_to_float(b0), bf16_to_float(b1), bf16_to_float(b2), bf16_to_float(b3));
+        if (!ROWS) v = make_float4(bf16_to_float(b0), bf16_to_float(b1), bf16_to_float(b2), bf16_to_float(b3));
         sq = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
     } else {
         for (int nn = n; nn < n + 4 && nn < N; ++nn) {
@@ -686,9 +692,9 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(const float *__restri
             float v = x[idx];
             for (int k = 0; k < ksplit; ++k) v += part[(size_t)k * M * N + idx];
             x[idx] = v;
-            const bf16_t b = float_to_bf16(gain ? v * gain[nn] : v);
+            const bf16_t b = float_to_bf16(ROWS ? v * gain[nn] : v);
             xb[Layout<bf16_t>::a_index(m, nn, N)] = b;
-            const float f = gain ? v : bf16_to_float(b);
+            const float f = ROWS ? v : bf16_to_float(b);
             sq += f * f;
         }
     }
@@ -698,7 +704,7 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(const float *__restri
     }
 }
 
-template <int EPI, int NW>
+template <int EPI, int NW, bool ROWS>
 inline hipError_t launch_skinny_nw(hipStream_t st, const SkinnyArgs &a_in, int MT, int groups, int nbw) {
     constexpr int DEPTH = SJD_SKINNY_DEPTH;
     SkinnyArgs a = a_in;
@@ -709,15 +715,15 @@ inline hipError_t launch_skinny_nw(hipStream_t st, const SkinnyArgs &a_in, int M
     const dim3 grid(n_compute + a.pf_wgs + a.kv_wgs, a.ksplit);
     constexpr bool kPair = EPI == EPI_QKV || EPI == EPI_SWIGLU;  // epilogues that need two column blocks
     if (nbw == 2) {
-        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, true><<<grid, NW * 64, 0, st>>>(a);
-        else if (MT == 1) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI><<<grid, NW * 64, 0, st>>>(a);
-        else gemm_skinny_kernel<2, 2, NW, DEPTH, EPI><<<grid, NW * 64, 0, st>>>(a);
+        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, true, ROWS><<<grid, NW * 64, 0, st>>>(a);
+        else if (MT == 1) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, false, ROWS><<<grid, NW * 64, 0, st>>>(a);
+        else gemm_skinny_kernel<2, 2, NW, DEPTH, EPI, false, ROWS><<<grid, NW * 64, 0, st>>>(a);
     } else {
         if (kPair) return hipErrorInvalidValue;
         constexpr int E1 = kPair ? EPI_RESID : EPI;
-        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, true><<<grid, NW * 64, 0, st>>>(a);
-        else if (MT == 1) gemm_skinny_kernel<1, 1, NW, DEPTH, E1><<<grid, NW * 64, 0, st>>>(a);
-        else gemm_skinny_kernel<2, 1, NW, DEPTH, E1><<<grid, NW * 64, 0, st>>>(a);
+        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, true, ROWS><<<grid, NW * 64, 0, st>>>(a);
+        else if (MT == 1) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, false, ROWS><<<grid, NW * 64, 0, st>>>(a);
+        else gemm_skinny_kernel<2, 1, NW, DEPTH, E1, false, ROWS><<<grid, NW * 64, 0, st>>>(a);
     }
     return hipGetLastError();
 }
@@ -736,13 +742,23 @@ inline hipError_t launch_skinny_mixed(hipStream_t st, const SkinnyArgs &a_in, in
     a.pf_wgs = a.kv_wgs = 0;
     a.n_heavy = std::min(groups / 2, groups - a.n_cus);
     const int light = groups - 2 * a.n_heavy;
-    if (MT == 1) gemm_skinny_mixed_kernel<1, 4, DEPTH, EPI><<<a.n_heavy + light, 256, 0, st>>>(a);
-    else gemm_skinny_mixed_kernel<2, 4, DEPTH, EPI><<<a.n_heavy + light, 256, 0, st>>>(a);
+    const int wgs = a.n_heavy + light;
+    if (a.row_ssq_part) {
+        if (MT == 1) gemm_skinny_mixed_kernel<1, 4, DEPTH, EPI, true><<<wgs, 256, 0, st>>>(a);
+        else gemm_skinny_mixed_kernel<2, 4, DEPTH, EPI, true><<<wgs, 256, 0, st>>>(a);
+    } else {
+        if (MT == 1) gemm_skinny_mixed_kernel<1, 4, DEPTH, EPI, false><<<wgs, 256, 0, st>>>(a);
+        else gemm_skinny_mixed_kernel<2, 4, DEPTH, EPI, false><<<wgs, 256, 0, st>>>(a);
+    }
     return hipGetLastError();
 }
 
-// nw = wavefronts per workgroup (4 or 8), the caller's choice.
+// nw = wavefronts per workgroup (4 or 8), the caller's choice.  With the gains in the rows a kernel of its own: the test for it
+// inside cost 0.5 % of a 32-row step, whose 144 projection launches are all prologue and epilogue.
 template <int EPI>
 inline hipError_t launch_skinny(hipStream_t st, const SkinnyArgs &a, int MT, int groups, int nbw, int nw = 8) {
-    return nw == 4 ? launch_skinny_nw<EPI, 4>(st, a, MT, groups, nbw) : launch_skinny_nw<EPI, 8>(st, a, MT, groups, nbw);
+    if constexpr (EPI != EPI_PARTIAL)
+        if (EPI == EPI_RESID ? a.gain != nullptr : a.row_ssq_part != nullptr)
+            return nw == 4 ? launch_skinny_nw<EPI, 4, true>(st, a, MT, groups, nbw) : launch_skinny_nw<EPI, 8, true>(st, a, MT, groups, nbw);
+    return nw == 4 ? launch_skinny_nw<EPI, 4, false>(st, a, MT, groups, nbw) : launch_skinny_nw<EPI, 8, false>(st, a, MT, groups, nbw);
 }

@@ -42,6 +42,7 @@ template <int EPI, bool SSQ_LOOP, int RT, int KS, int D>
 SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_blocks, int row_tiles32, int col_tiles, int row_tiles, int ct0) {
     constexpr bool kNorm = EPI != EPI_RESID && EPI != EPI_PARTIAL;
     constexpr bool kSsqLoop = kNorm && SSQ_LOOP;  // else the rows' sums of squares come from the kernel that wrote the rows
+    constexpr bool kRows = EPI == EPI_RESID && !SSQ_LOOP;  // ... which this is: gains in the rows, sums of squares to ssq_out
     constexpr int U = D % 2 == 0 ? D : 2 * D;  // unroll: ring slot and LDS buffer of an iteration are compile-time
     constexpr int TM = 128 * RT;              // rows of the workgroup's tile: wavefront w owns rows [32 RT w, 32 RT (w + 1))
     const int tid = threadIdx.x, lane = tid & 63;
@@ -226,10 +227,10 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
                 const int g = ct * 2 + p;
                 if (g * 2 >= n_blocks) continue;  // past the last column pair
                 float gn[2] = {1.0f, 1.0f};
-                if constexpr (EPI == EPI_RESID) {
+                if constexpr (kRows) {
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
-                        if (const int n = (g * 2 + i) * 32 + col; a.gain && n < a.N) gn[i] = a.gain[n];
+                        if (const int n = (g * 2 + i) * 32 + col; n < a.N) gn[i] = a.gain[n];
                 }
 #pragma unroll
                 for (int v0 = 0; v0 < 16; v0 += 4) {
@@ -253,18 +254,16 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
                         const float inv = kNorm ? ssq_lds[wave][j][row0 + u] : 1.0f;
                         const float vals[2] = {acc[j][p * 2][v0 + u], acc[j][p * 2 + 1][v0 + u]};
                         skinny_epilogue<EPI, 2>(a, ks, m0 + u, g * 2, col, vals, inv, xin[u], gn);
-                        if constexpr (EPI == EPI_RESID) {
-                            if (a.ssq_out) {   // the row's columns of this pair lie in one half wavefront
-                                float sq = 0.0f;
+                        if constexpr (kRows) {   // the row's columns of this pair lie in one half wavefront
+                            float sq = 0.0f;
 #pragma unroll
-                                for (int i = 0; i < 2; ++i) {
-                                    const float f = (g * 2 + i) * 32 + col < a.N ? ssq_value(a, xin[u][i] + vals[i]) : 0.0f;
-                                    sq = fmaf(f, f, sq);
-                                }
-#pragma unroll
-                                for (int off = 16; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-                                if (col == 0) a.ssq_out[(size_t)g * a.M + m0 + u] = sq;
+                            for (int i = 0; i < 2; ++i) {
+                                const float f = (g * 2 + i) * 32 + col < a.N ? xin[u][i] + vals[i] : 0.0f;
+                                sq = fmaf(f, f, sq);
                             }
+#pragma unroll
+                            for (int off = 16; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+                            if (col == 0) a.ssq_out[(size_t)g * a.M + m0 + u] = sq;
                         }
                     }
                 }
@@ -342,7 +341,7 @@ inline hipError_t launch_tile(hipStream_t st, const SkinnyArgs &a, int n_blocks,
     const int row_tiles32 = (a.M + 31) / 32, row_tiles = (a.M + tile_rows - 1) / tile_rows, col_tiles = (n_blocks + 3) / 4;
     const dim3 grid(8 * ((col_tiles + 7) / 8) * row_tiles, a.ksplit);
     constexpr bool kNorm = EPI != EPI_RESID && EPI != EPI_PARTIAL;
-    const bool ssq_loop = !(kNorm && a.row_ssq_part);
+    const bool ssq_loop = kNorm ? !a.row_ssq_part : EPI == EPI_RESID ? !a.gain : true;
     // Between one and two 256-row tiles per CU: one 256-row tile on every CU, the other column tiles as 128-row tiles
     // beside them (measured at 512 x 22016 x 4096: 95.5 us against 108.0 with 128-row tiles and 126 with 256-row tiles)
     const int n_cus = a.n_cus > 0 ? a.n_cus : 256;

@@ -449,7 +449,9 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     auto skinny_ssq = [&]() { if (!c->fold_gain) use_ssq(); };
     auto reduce = [&]() -> int {
         SJD_LAUNCH(c, KC_ADDNORM, after([&] {
-                       resid_reduce_kernel<<<dim3(ceil_div(d, 1024), M), 256, 0, st>>>(c->skinny_part, a.ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out, a.gain);
+                       const dim3 grid(ceil_div(d, 1024), M);
+                       if (a.gain) resid_reduce_kernel<true><<<grid, 256, 0, st>>>(c->skinny_part, a.ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out, a.gain);
+                       else resid_reduce_kernel<false><<<grid, 256, 0, st>>>(c->skinny_part, a.ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out, nullptr);
                    }));
         ssq_n = ceil_div(d, 256);
         return SJD_OK;
@@ -479,7 +481,6 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             if (a.ksplit == 1) {
                 // gains in the weights: the next tile kernel sums the squares of its operands
                 ssq_n = c->fold_gain ? 0 : n_blocks / 2;
-                if (c->fold_gain) a.ssq_out = nullptr;
                 SJD_LAUNCH(c, cls, launch_tile<EPI_RESID>(st, a, n_blocks, tile_rows, mixed_ok));
                 return SJD_OK;
             }
