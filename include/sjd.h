@@ -168,7 +168,13 @@ int sjd_create(const sjd_model_desc *desc, const sjd_weights *weights, const sjd
  * arrays are HOST arrays of length n_seqs, read during the call only.  Every
  * prompt token but the last is run through the model into the KV cache; the
  * last one becomes the first window input; the L-1 drafts are drawn uniformly.
- * May be called again to start new decodes.  Errors: SJD_EINVAL (null, length
+ * May be called again to start new decodes.
+ * Which kernels run the rows, and so the order of bf16 sums, follows from how
+ * many rows a forward has (the batch size; in a prefill the prompts' total
+ * length) and from the longest cached context: in bf16 a sequence's logits agree
+ * to rounding, not bit for bit, between batches of other sizes or prompt
+ * lengths, and with a fixed seed its tokens may differ.  In fp32 they do not
+ * depend on its neighbours.  Errors: SJD_EINVAL (null, length
  * < 1, id outside the vocabulary), SJD_ECAPACITY (n_seqs > max_seqs or
  * prompt + image tokens > max_ctx; nothing is enqueued), SJD_EDEVICE. */
 int sjd_prefill(sjd_ctx *ctx, int32_t n_seqs, const int32_t *const *cond_ids, const int32_t *cond_len,

@@ -122,3 +122,30 @@ def test_every_cached_position(name, lens, flags):
             worst = max(worst, float((np.linalg.norm(a - b, axis=-1) / size).max()))
     print(name, lens, flags, "worst relative difference of a position's keys or values", worst)
     assert worst < 0.2
+
+
+def test_neighbours_do_not_change_a_sequence():
+    """Sequence 0 beside prompts of other lengths: fp32 sums keep their order whatever the rows of a forward, so its logits
+    and tokens are the same bits; bf16 ones follow the number of rows and agree to rounding (8e-2, as above)."""
+    import paper_2512_07503_amd as sjd
+    for name in ("small_f32", "small_fused64"):
+        cfg = workload.get_config(name)
+        arch, L = cfg["arch"], cfg["window"]
+        w = gpu_weights(workload.make_weights(arch, cfg["seed"], 6.0, cfg["dtype"], std=0.08), cfg["dtype"])
+        rng = np.random.default_rng(9)
+        mine = [rng.integers(0, arch["vocab"], 70).astype(np.int32) for _ in range(2)]
+        runs = []
+        for other in (3, 41, 600):
+            mate = [rng.integers(0, arch["vocab"], other).astype(np.int32) for _ in range(2)]
+            g = sjd.Decoder(arch, w, cfg["dtype"], L, 700, max_seqs=2, top_k=cfg["top_k"], seed=3, kernel_flags=sjd.KEEP_LOGITS)
+            assert g.prefill([mine[0], mate[0]], [mine[1], mate[1]], [30, 30]) == 0
+            g.step()
+            logits = g.logits()[0]
+            g.decode()
+            runs.append((logits, g.tokens(0).copy()))
+            g.close()
+        for logits, tokens in runs[1:]:
+            if cfg["dtype"] == "f32":
+                assert np.array_equal(logits, runs[0][0]) and np.array_equal(tokens, runs[0][1])
+            else:
+                assert logits_error(logits[None], runs[0][0][None], [L])[1] <= 8e-2
