@@ -348,7 +348,7 @@ def main():
                     help="also run one plain 256 MiB device copy (reference dispatch for scaling rocprofv3 byte counters)")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
-        print("bench.py: this build runs on ONE GPU; sequences are independent and would shard by prompt with no "
+        print("bench.py: the library runs on ONE GPU; sequences are independent and would shard by prompt with no "
               "communication, but no multi-GPU path exists here. Run with --gpus 1.", file=sys.stderr)
         sys.exit(2)
 

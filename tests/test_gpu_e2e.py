@@ -1,7 +1,7 @@
 """Whole decoding path on the GPU against the oracle: forward logits within tolerance at every step, decisions
 bit-exact on the GPU's own logits, and the whole token sequence identical in fp32 mode.
 
-Tolerances (the benchmark spec): fp32 mode max-abs 1e-4 on the logits; bf16 mode 3e-2 of the row's largest
+Tolerances: fp32 mode max-abs 1e-4 on the logits; bf16 mode 3e-2 of the row's largest
 |logit| (weights are identical bf16 values on both sides; the GPU also rounds GEMM inputs and the KV cache to bf16)."""
 import numpy as np
 import pytest
@@ -150,7 +150,7 @@ def test_spatial_initialisation_step_by_step(oracle, name, mode, row_width, tau)
 
 
 def test_cfg0_whole_sequence_identity(oracle):
-    """configs[0] in fp32: the GPU decode and the oracle decode, each on its own forward, give the same 256 tokens."""
+    """cfg0 in fp32: the GPU decode and the oracle decode, each on its own forward, give the same 256 tokens."""
     cfg = workload.get_config("cfg0")
     o, g, cond, uncond, n_img = make_pair(oracle, cfg)
     ho = o.decode()
@@ -214,7 +214,7 @@ def _shape_weights(name, layers, random_gains):
     # 7 sequences: 448 rows, the tile kernels by choice (tests/test_plan_choice.py holds these cases to their kernels)
     ("cfg4", 2, 64, 1, 7, 0, None)])
 def test_benchmark_shapes_bf16(oracle, name, layers, prompt, steps, S, flags, window):
-    """The benchmark shapes: full depth at short context for configs[1]; the 7B-class widths, heads, GQA, vocabulary
+    """The benchmark shapes: full depth at short context for cfg1; the 7B-class widths, heads, GQA, vocabulary
     sub-range and batch on depth-reduced twins (a full-depth fp64 CPU forward of those takes hours)."""
     cfg = workload.get_config(name)
     w = _shape_weights(name, layers, bool(flags & (1 << 20)))
