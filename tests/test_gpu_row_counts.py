@@ -62,3 +62,36 @@ def test_norm_gains_cost_no_precision(oracle, name, n_seqs, window, prompt, flag
     err = np.sqrt(sq[:, 0] / sq[:, 1])
     print(name, n_seqs, window, prompt, flags, "relative error, reference kernels, ratio:", err, err[0] / err[1])
     assert err[0] <= 1.08 * err[1]
+
+
+@pytest.mark.parametrize("n_seqs,flags", [(1, 0), (1, 128), (1, 256), (2, 0), (2, 128), (2, 256), (2, 512), (3, 0)])
+def test_fewer_sequences_than_the_context_holds(n_seqs, flags):
+    """A context for three 16-token windows (96 rows: norm gains in the rows) with one or two of them in use: 32 and 64 rows,
+    whose projections run as 16-row halves, 32- and 64-row groups and, with more than 256 column groups (8 256-wide MLP, 17 000
+    ids), as workgroups of two widths; flags 128, 256 and 512 take the other kernels.  Against float64, bound as in
+    tests/test_gpu_lds_tiles.py; gains from U(0.5, 1.5)."""
+    import numpy as np
+    import torch
+    import paper_2512_07503_amd as sjd
+    from test_gpu_lds_tiles import _forward64, _weights, case_arch
+    arch, window, n = case_arch(256, 4, 2, 8256, 17000), 16, 40
+    w = _weights(arch, 13)
+    for name in ("attn_norm", "mlp_norm"):
+        w[name] = [(torch.rand(256, device="cuda") + 0.5).to(torch.bfloat16) for _ in w[name]]
+    w["final_norm"] = (torch.rand(256, device="cuda") + 0.5).to(torch.bfloat16)
+    rng = np.random.default_rng(4)
+    cond = [rng.integers(0, arch["vocab"], c).astype(np.int32) for c in (20, 9, 31)[:n_seqs]]
+    uncond = [rng.integers(0, arch["vocab"], c).astype(np.int32) for c in (14, 20, 1)[:n_seqs]]
+    g = sjd.Decoder(arch, w, "bf16", window, 80, max_seqs=3, top_k=200, seed=5, kernel_flags=flags | sjd.KEEP_LOGITS)
+    for again in range(2):   # the second time over the first one's buffers, replaying its graph
+        assert g.prefill(cond, uncond, [n] * n_seqs) == 0
+        windows = [g.window(s)[0] for s in range(n_seqs)]
+        g.step()
+        out = g.logits().astype(np.float64)
+        assert np.isfinite(out).all()
+        for s in range(n_seqs):
+            for b, p in enumerate((cond[s], uncond[s])):
+                want = _forward64(arch, w, np.concatenate([p, windows[s][1:]]), window)
+                err = np.linalg.norm(out[s, b] - want) / np.linalg.norm(want)
+                print(n_seqs, flags, "sequence", s, "branch", b, "relative error of the logits", err)
+                assert err < 1.5e-2
