@@ -10,7 +10,9 @@ BUILD = os.path.join(HERE, "_build")
 
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
           # packed-fp32 code generation is switched off (hipcc's host pass warns that it does not know the feature)
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          # leading scalar arguments of a kernel arrive in registers instead of through a load
+          "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 # (source, extra flags): the decision stage is specified bit for bit and must not contract a*b+c
 UNITS = [("decide.hip", ["-ffp-contract=off"]), ("sjd_api.hip", [])]
 

@@ -50,7 +50,8 @@ template <int NL> SJD_D void wait_stages(int stages) {
 
 // (two wavefronts per SIMD at least: the LDS of the larger shapes admits two workgroups per CU, their registers must too)
 template <int TMT, int TNB, int WM, int WN, int S, int EPI>
-__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SkinnyArgs a, int n_blocks, int col_tiles, int row_tiles) {
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARAMS, int col_tiles, int row_tiles, SkinnyArgs a) {
+    SJD_TILE_TAKE(a);
     constexpr int NW = WM * WN, RT = TMT / WM, CB = TNB / WN;   // wavefronts; MFMA tiles of a wavefront: RT x CB
     constexpr int FR = 2 * (TMT + TNB);                         // fragments of a stage
     constexpr int NL = FR / NW;                                 // ... that a wavefront fetches
@@ -356,7 +357,7 @@ inline hipError_t launch_lds(hipStream_t st, const SkinnyArgs &a, int n_blocks, 
         if (cfg == I) {                                                                                                        \
             const int col_tiles = ceil_div(n_blocks, TNB), row_tiles = ceil_div(a.M, 32 * TMT);                                \
             const dim3 grid(8 * ceil_div(col_tiles, 8) * row_tiles, a.ksplit);                                                 \
-            gemm_lds_kernel<TMT, TNB, WM, WN, S, EPI><<<grid, WM * WN * 64, 0, st>>>(a, n_blocks, col_tiles, row_tiles);       \
+            gemm_lds_kernel<TMT, TNB, WM, WN, S, EPI><<<grid, WM * WN * 64, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);       \
             return hipGetLastError();                                                                                          \
         }
     SJD_LDS_TILES(SJD_LDS_ONE)

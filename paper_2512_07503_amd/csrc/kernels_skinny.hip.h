@@ -110,6 +110,20 @@ struct SkinnyArgs {
     const int32_t *kv_seg_kv;   // [segments] tokens in the cache before this forward's rows
 };
 
+// The arguments that the first loads of a projection kernel need, as leading scalars: the compiler has those put into registers
+// ahead of the wavefront's start (-amdgpu-kernarg-preload-count), the rest of SkinnyArgs is read from memory meanwhile.
+// Read from memory they cost every launch 0.5 to 0.8 us ahead of its first operand (in-kernel stamps): 36 layers of 1280, window
+// 16: 1.192 -> 1.098 ms a step; window 250: 2.69 -> 2.59; 4096-wide layers 1 % (a launch is 13 to 40 us there).
+#define SJD_HOT_PARAMS const bf16_t *hot_A, const bf16_t *hot_W, int hot_M, int hot_KB, int hot_kb_per_split, int hot_groups, int hot_m_groups, int hot_k_rot, int hot_pf_wgs, int hot_kv_wgs
+#define SJD_HOT_PASS(a) (a).A, (a).W, (a).M, (a).KB, (a).kb_per_split, (a).groups, (a).m_groups, (a).k_rot, (a).pf_wgs, (a).kv_wgs
+#define SJD_HOT_TAKE(a) \
+    (a).A = hot_A; (a).W = hot_W; (a).M = hot_M; (a).KB = hot_KB; (a).kb_per_split = hot_kb_per_split; \
+    (a).groups = hot_groups; (a).m_groups = hot_m_groups; (a).k_rot = hot_k_rot; (a).pf_wgs = hot_pf_wgs; (a).kv_wgs = hot_kv_wgs
+// ... and of the kernels for more rows (n_blocks: packed 32-column blocks of W)
+#define SJD_TILE_PARAMS const bf16_t *hot_A, const bf16_t *hot_W, int hot_M, int hot_KB, int hot_kb_per_split, int n_blocks
+#define SJD_TILE_PASS(a) (a).A, (a).W, (a).M, (a).KB, (a).kb_per_split, n_blocks
+#define SJD_TILE_TAKE(a) (a).A = hot_A; (a).W = hot_W; (a).M = hot_M; (a).KB = hot_KB; (a).kb_per_split = hot_kb_per_split
+
 SJD_D QkvRow qkv_row(const SkinnyArgs &a, int m) { return a.row_meta[m]; }
 // Column group g = (head, sub-block of 32 dimensions); v0 / v1 are dimensions j0 = 32 sub + col and j0 + hd / 2 of
 // that head (a rotary pair): rotate q and k, then queries to the attention operand layout, keys / values into
@@ -271,7 +285,8 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0);
 
 // ROWS: the norm gains are in the rows (QKV, SWIGLU, HEAD: sums of squares from row_ssq_part; RESID: gain, ssq_out)
 template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT, bool ROWS>
-__global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs a) {
+__global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SJD_HOT_PARAMS, SkinnyArgs a) {
+    SJD_HOT_TAKE(a);
     const int tid = threadIdx.x;
     // computing workgroups come first: one per column group, or (row_split 2) two, listed per XCD like row groups
     const int n_compute = SPLIT ? 16 * ((a.groups + 7) / 8) : a.m_groups > 1 ? 8 * ((a.groups + 7) / 8) * a.m_groups : a.groups;
@@ -309,7 +324,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SkinnyArgs a) {
 // (4 blocks: one pass over the activations for both) and the others one, n_heavy + (groups - 2 n_heavy) workgroups in
 // all: 256 for up to 512 groups.  The register count admits one workgroup per CU, so each CU gets one.
 template <int MT, int NW, int DEPTH, int EPI, bool ROWS>
-__global__ __launch_bounds__(NW * 64) void gemm_skinny_mixed_kernel(SkinnyArgs a) {
+__global__ __launch_bounds__(NW * 64) void gemm_skinny_mixed_kernel(SJD_HOT_PARAMS, SkinnyArgs a) {
+    SJD_HOT_TAKE(a);
     static_assert(EPI == EPI_SWIGLU || EPI == EPI_HEAD, "epilogues that take any even number of blocks");
     const int w = blockIdx.x;
     // (the wide body's ring has 3/4 of the slots: 6 fragments per slot instead of 4, more bytes in flight all the same)
@@ -342,44 +358,46 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
         return (size_t)(kb_lo + wave + (r >= n_it ? r - n_it : r) * NW);
     };
 
-    // What the epilogue will need from memory is requested now, ahead of the weight stream, so that its latency
-    // is not paid after the last MFMA: residual values (RESID), row destination and rotation (QKV).  Thread t ends
+    // What the epilogue will need from memory is requested behind the first fragments of the weight stream, so that its
+    // latency is not paid after the last MFMA: residual values (RESID), row destination and rotation (QKV).  Thread t ends
     // up with elements e = t, t + 64 NW, ... of every tile (see the reduction below).
     constexpr int EPT = 1024 / (NW * 64);  // elements per thread per tile
     [[maybe_unused]] float xpre[MT][NBW][EPT];
     float gpre[NBW];   // the next norm's gains of this thread's columns
-#pragma unroll
-    for (int i = 0; i < NBW; ++i) {
-        gpre[i] = 1.0f;
-        if constexpr (EPI == EPI_RESID && ROWS)
-            if (const int n = (blk0 + i) * 32 + (lane & 31); n < a.N) gpre[i] = a.gain[n];
-    }
     [[maybe_unused]] QkvRow qrow[MT][EPT];
     [[maybe_unused]] float rot_c[MT][EPT], rot_s[MT][EPT];
-    if (EPI == EPI_RESID || EPI == EPI_QKV) {
+    auto request_epilogue = [&]() {
 #pragma unroll
-        for (int j = 0; j < MT; ++j)
+        for (int i = 0; i < NBW; ++i) {
+            gpre[i] = 1.0f;
+            if constexpr (EPI == EPI_RESID && ROWS)
+                if (const int n = (blk0 + i) * 32 + (lane & 31); n < a.N) gpre[i] = a.gain[n];
+        }
+        if (EPI == EPI_RESID || EPI == EPI_QKV) {
 #pragma unroll
-            for (int hh = 0; hh < EPT; ++hh) {
-                const int v = wave + NW * hh;
-                const int m = m_base + j * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                if (EPI == EPI_RESID) {
+            for (int j = 0; j < MT; ++j)
 #pragma unroll
-                    for (int i = 0; i < NBW; ++i) {
-                        const int n = (blk0 + i) * 32 + (lane & 31);
-                        xpre[j][i][hh] = m < a.M && n < a.N && (!SPLIT || ((m >> 4) & 1) == half) ? a.x[(size_t)m * a.N + n] : 0.0f;
-                    }
-                } else {
-                    qrow[j][hh].pos = -1;
-                    rot_c[j][hh] = 1.0f;
-                    rot_s[j][hh] = 0.0f;
-                    if (m < a.M && (!SPLIT || ((m >> 4) & 1) == half)) {
-                        qrow[j][hh] = qkv_row(a, m);
-                        qkv_rotation(a, m, g, lane & 31, rot_c[j][hh], rot_s[j][hh]);
+                for (int hh = 0; hh < EPT; ++hh) {
+                    const int v = wave + NW * hh;
+                    const int m = m_base + j * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                    if (EPI == EPI_RESID) {
+#pragma unroll
+                        for (int i = 0; i < NBW; ++i) {
+                            const int n = (blk0 + i) * 32 + (lane & 31);
+                            xpre[j][i][hh] = m < a.M && n < a.N && (!SPLIT || ((m >> 4) & 1) == half) ? a.x[(size_t)m * a.N + n] : 0.0f;
+                        }
+                    } else {
+                        qrow[j][hh].pos = -1;
+                        rot_c[j][hh] = 1.0f;
+                        rot_s[j][hh] = 0.0f;
+                        if (m < a.M && (!SPLIT || ((m >> 4) & 1) == half)) {
+                            qrow[j][hh] = qkv_row(a, m);
+                            qkv_rotation(a, m, g, lane & 31, rot_c[j][hh], rot_s[j][hh]);
+                        }
                     }
                 }
-            }
-    }
+        }
+    };
 
     f32x16 acc[MT][NBW];
 #pragma unroll
@@ -404,6 +422,8 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
 #pragma unroll
             for (int j = 0; j < MT; ++j) aq[s][j] = a_lane ? Ap[((size_t)j * KB + kb) * 64] : u32x4{0u, 0u, 0u, 0u};
         }
+        __builtin_amdgcn_sched_barrier(0);
+        request_epilogue();
         __builtin_amdgcn_sched_barrier(0);
         auto consume = [&](int s) {
 #pragma unroll
@@ -457,6 +477,8 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
 #pragma unroll
         for (int s = 0; s < DEPTH; ++s)
             if (it0 + DEPTH + s < n_it) consume(s);
+    } else {
+        request_epilogue();
     }
 
     // ---- sum the NW partial tiles through LDS; thread t ends up with elements e = t and t + 512 of every
@@ -715,15 +737,15 @@ inline hipError_t launch_skinny_nw(hipStream_t st, const SkinnyArgs &a_in, int M
     const dim3 grid(n_compute + a.pf_wgs + a.kv_wgs, a.ksplit);
     constexpr bool kPair = EPI == EPI_QKV || EPI == EPI_SWIGLU;  // epilogues that need two column blocks
     if (nbw == 2) {
-        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, true, ROWS><<<grid, NW * 64, 0, st>>>(a);
-        else if (MT == 1) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, false, ROWS><<<grid, NW * 64, 0, st>>>(a);
-        else gemm_skinny_kernel<2, 2, NW, DEPTH, EPI, false, ROWS><<<grid, NW * 64, 0, st>>>(a);
+        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, true, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
+        else if (MT == 1) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, false, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
+        else gemm_skinny_kernel<2, 2, NW, DEPTH, EPI, false, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
     } else {
         if (kPair) return hipErrorInvalidValue;
         constexpr int E1 = kPair ? EPI_RESID : EPI;
-        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, true, ROWS><<<grid, NW * 64, 0, st>>>(a);
-        else if (MT == 1) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, false, ROWS><<<grid, NW * 64, 0, st>>>(a);
-        else gemm_skinny_kernel<2, 1, NW, DEPTH, E1, false, ROWS><<<grid, NW * 64, 0, st>>>(a);
+        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, true, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
+        else if (MT == 1) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, false, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
+        else gemm_skinny_kernel<2, 1, NW, DEPTH, E1, false, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
     }
     return hipGetLastError();
 }
@@ -744,11 +766,11 @@ inline hipError_t launch_skinny_mixed(hipStream_t st, const SkinnyArgs &a_in, in
     const int light = groups - 2 * a.n_heavy;
     const int wgs = a.n_heavy + light;
     if (a.row_ssq_part) {
-        if (MT == 1) gemm_skinny_mixed_kernel<1, 4, DEPTH, EPI, true><<<wgs, 256, 0, st>>>(a);
-        else gemm_skinny_mixed_kernel<2, 4, DEPTH, EPI, true><<<wgs, 256, 0, st>>>(a);
+        if (MT == 1) gemm_skinny_mixed_kernel<1, 4, DEPTH, EPI, true><<<wgs, 256, 0, st>>>(SJD_HOT_PASS(a), a);
+        else gemm_skinny_mixed_kernel<2, 4, DEPTH, EPI, true><<<wgs, 256, 0, st>>>(SJD_HOT_PASS(a), a);
     } else {
-        if (MT == 1) gemm_skinny_mixed_kernel<1, 4, DEPTH, EPI, false><<<wgs, 256, 0, st>>>(a);
-        else gemm_skinny_mixed_kernel<2, 4, DEPTH, EPI, false><<<wgs, 256, 0, st>>>(a);
+        if (MT == 1) gemm_skinny_mixed_kernel<1, 4, DEPTH, EPI, false><<<wgs, 256, 0, st>>>(SJD_HOT_PASS(a), a);
+        else gemm_skinny_mixed_kernel<2, 4, DEPTH, EPI, false><<<wgs, 256, 0, st>>>(SJD_HOT_PASS(a), a);
     }
     return hipGetLastError();
 }

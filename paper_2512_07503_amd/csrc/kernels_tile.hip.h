@@ -314,7 +314,9 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
 }
 
 template <int EPI, bool SSQ_LOOP = true, int RT = 2, int KS = TILE_KS, int D = TILE_RING>
-__global__ __launch_bounds__(256, RT == 2 ? 2 : 3) void gemm_tile_kernel(SkinnyArgs a, int n_blocks, int row_tiles32, int col_tiles, int row_tiles) {
+__global__ __launch_bounds__(256, RT == 2 ? 2 : 3) void gemm_tile_kernel(SJD_TILE_PARAMS, int col_tiles, int row_tiles, SkinnyArgs a) {
+    SJD_TILE_TAKE(a);
+    const int row_tiles32 = (a.M + 31) / 32;
     tile_body<EPI, SSQ_LOOP, RT, KS, D>(a, blockIdx.x, blockIdx.y, n_blocks, row_tiles32, col_tiles, row_tiles, 0);
 }
 
@@ -325,8 +327,10 @@ __global__ __launch_bounds__(256, RT == 2 ? 2 : 3) void gemm_tile_kernel(SkinnyA
 // 256-row body admits two workgroups per CU, whatever their height).  wg_split is a multiple of 8, so both lists keep
 // the workgroup id -> XCD correspondence of tile_body.
 template <int EPI, bool SSQ_LOOP>
-__global__ __launch_bounds__(256, 2) void gemm_tile_mixed_kernel(SkinnyArgs a, int n_blocks, int row_tiles32, int col_tiles, int ct_split, int wg_split,
-                                                                int row_tiles2, int row_tiles1) {
+__global__ __launch_bounds__(256, 2) void gemm_tile_mixed_kernel(SJD_TILE_PARAMS, int col_tiles, int ct_split, int wg_split, int row_tiles2, int row_tiles1,
+                                                                SkinnyArgs a) {
+    SJD_TILE_TAKE(a);
+    const int row_tiles32 = (a.M + 31) / 32;
     if ((int)blockIdx.x < wg_split) tile_body<EPI, SSQ_LOOP, 2, TILE_KS, TILE_RING>(a, blockIdx.x, blockIdx.y, n_blocks, row_tiles32, ct_split, row_tiles2, 0);
     else tile_body<EPI, SSQ_LOOP, 1, TILE_KS, TILE_RING>(a, blockIdx.x - wg_split, blockIdx.y, n_blocks, row_tiles32, col_tiles - ct_split, row_tiles1, ct_split);
 }
@@ -338,7 +342,7 @@ inline hipError_t launch_tile(hipStream_t st, const SkinnyArgs &a, int n_blocks,
     if (a.M <= 0 || n_blocks <= 0 || a.KB <= 0 || a.ksplit < 1 || (size_t)a.kb_per_split * a.ksplit < (size_t)a.KB) return hipErrorInvalidValue;
     if (EPI != EPI_PARTIAL && a.ksplit != 1) return hipErrorInvalidValue;
     if (tile_rows == 0) tile_rows = tile_rows_for(a.M, n_blocks, a.ksplit, a.n_cus > 0 ? a.n_cus : 256);
-    const int row_tiles32 = (a.M + 31) / 32, row_tiles = (a.M + tile_rows - 1) / tile_rows, col_tiles = (n_blocks + 3) / 4;
+    const int row_tiles = (a.M + tile_rows - 1) / tile_rows, col_tiles = (n_blocks + 3) / 4;
     const dim3 grid(8 * ((col_tiles + 7) / 8) * row_tiles, a.ksplit);
     constexpr bool kNorm = EPI != EPI_RESID && EPI != EPI_PARTIAL;
     const bool ssq_loop = kNorm ? !a.row_ssq_part : EPI == EPI_RESID ? !a.gain : true;
@@ -351,16 +355,16 @@ inline hipError_t launch_tile(hipStream_t st, const SkinnyArgs &a, int n_blocks,
     if (two_heights && tile_rows_in == 0 && EPI != EPI_HEAD && tile_two_heights(a.M, n_blocks, a.ksplit, n_cus)) {
         const int ct_split = n_cus / rt2 / 8 * 8;
         const int wg_split = ct_split * rt2, wg_rest = 8 * ((col_tiles - ct_split + 7) / 8) * rt1;
-        if (ssq_loop) gemm_tile_mixed_kernel<EPI, true><<<dim3(wg_split + wg_rest, 1), 256, 0, st>>>(a, n_blocks, row_tiles32, col_tiles, ct_split, wg_split, rt2, rt1);
-        else gemm_tile_mixed_kernel<EPI, false><<<dim3(wg_split + wg_rest, 1), 256, 0, st>>>(a, n_blocks, row_tiles32, col_tiles, ct_split, wg_split, rt2, rt1);
+        if (ssq_loop) gemm_tile_mixed_kernel<EPI, true><<<dim3(wg_split + wg_rest, 1), 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, ct_split, wg_split, rt2, rt1, a);
+        else gemm_tile_mixed_kernel<EPI, false><<<dim3(wg_split + wg_rest, 1), 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, ct_split, wg_split, rt2, rt1, a);
         return hipGetLastError();
     }
     if (tile_rows == 128) {
-        if (ssq_loop) gemm_tile_kernel<EPI, true, 1><<<grid, 256, 0, st>>>(a, n_blocks, row_tiles32, col_tiles, row_tiles);
-        else gemm_tile_kernel<EPI, false, 1><<<grid, 256, 0, st>>>(a, n_blocks, row_tiles32, col_tiles, row_tiles);
+        if (ssq_loop) gemm_tile_kernel<EPI, true, 1><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
+        else gemm_tile_kernel<EPI, false, 1><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
     } else {
-        if (ssq_loop) gemm_tile_kernel<EPI, true, 2><<<grid, 256, 0, st>>>(a, n_blocks, row_tiles32, col_tiles, row_tiles);
-        else gemm_tile_kernel<EPI, false, 2><<<grid, 256, 0, st>>>(a, n_blocks, row_tiles32, col_tiles, row_tiles);
+        if (ssq_loop) gemm_tile_kernel<EPI, true, 2><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
+        else gemm_tile_kernel<EPI, false, 2><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
     }
     return hipGetLastError();
 }
