@@ -359,9 +359,11 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
     };
 
     // What the epilogue will need from memory is requested behind the first fragments of the weight stream, so that its
-    // latency is not paid after the last MFMA: residual values (RESID), row destination and rotation (QKV).  Thread t ends
-    // up with elements e = t, t + 64 NW, ... of every tile (see the reduction below).
-    constexpr int EPT = 1024 / (NW * 64);  // elements per thread per tile
+    // latency is not paid after the last MFMA: residual values (RESID), row destination and rotation (QKV).
+    // a tile's accumulators that hold this workgroup's rows (rows 0..15 are registers 0..7), of which a thread adds EPT:
+    // element hh of thread t is register v_of(hh) of lane t % 64
+    constexpr int NV = SPLIT ? 8 : 16, EPT = NV / NW;
+    auto v_of = [&](int hh) { return (SPLIT ? 8 * half : 0) + wave + NW * hh; };
     [[maybe_unused]] float xpre[MT][NBW][EPT];
     float gpre[NBW];   // the next norm's gains of this thread's columns
     [[maybe_unused]] QkvRow qrow[MT][EPT];
@@ -378,19 +380,19 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
             for (int j = 0; j < MT; ++j)
 #pragma unroll
                 for (int hh = 0; hh < EPT; ++hh) {
-                    const int v = wave + NW * hh;
+                    const int v = v_of(hh);
                     const int m = m_base + j * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
                     if (EPI == EPI_RESID) {
 #pragma unroll
                         for (int i = 0; i < NBW; ++i) {
                             const int n = (blk0 + i) * 32 + (lane & 31);
-                            xpre[j][i][hh] = m < a.M && n < a.N && (!SPLIT || ((m >> 4) & 1) == half) ? a.x[(size_t)m * a.N + n] : 0.0f;
+                            xpre[j][i][hh] = m < a.M && n < a.N ? a.x[(size_t)m * a.N + n] : 0.0f;
                         }
                     } else {
                         qrow[j][hh].pos = -1;
                         rot_c[j][hh] = 1.0f;
                         rot_s[j][hh] = 0.0f;
-                        if (m < a.M && (!SPLIT || ((m >> 4) & 1) == half)) {
+                        if (m < a.M) {
                             qrow[j][hh] = qkv_row(a, m);
                             qkv_rotation(a, m, g, lane & 31, rot_c[j][hh], rot_s[j][hh]);
                         }
@@ -481,10 +483,13 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
         request_epilogue();
     }
 
-    // ---- sum the NW partial tiles through LDS; thread t ends up with elements e = t and t + 512 of every
-    //      tile: accumulator register v = e / 64 of lane l = e % 64, i.e. row 8 (v / 4) + 4 (l / 32) + v % 4,
+    // ---- sum the NW partial tiles through LDS, a row tile's NBW blocks at a time: every wavefront leaves its accumulators as
+    //      vectors of the EPT elements that one thread adds (64 KiB with 8 wavefronts and two blocks, and it is these bytes
+    //      that the step's time is, not the barriers; a register at a time and a block at a time it took 1.4 us of a launch's
+    //      5.2 at 32 rows: 36 layers of 1280, window 16, 1.098 -> 1.063 ms a step, 192 rows 1.81 -> 1.78).  Accumulator register v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
     //      column l % 32.
-    __shared__ float red[NW][16][64];
+    typedef float red_t __attribute__((ext_vector_type(EPT)));
+    __shared__ red_t red[NW][NBW][NW][64];
     __shared__ float ssq_lds[NW][MT][32];
     if (kNorm) {
 #pragma unroll
@@ -501,22 +506,32 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
     }
     float out[MT][NBW][EPT];
 #pragma unroll
-    for (int j = 0; j < MT; ++j)
+    for (int j = 0; j < MT; ++j) {
+        if (j > 0) __syncthreads();   // the row tile before has been read
+#pragma unroll
+        for (int i = 0; i < NBW; ++i)
+#pragma unroll
+            for (int r = 0; r < NW; ++r) {
+                red_t e;
+#pragma unroll
+                for (int hh = 0; hh < EPT; ++hh) {
+                    const int v = r + NW * hh;
+                    e[hh] = SPLIT && half ? acc[j][i][(SPLIT ? 8 : 0) + v] : acc[j][i][v];
+                }
+                red[wave][i][r][lane] = e;
+            }
+        __syncthreads();
 #pragma unroll
         for (int i = 0; i < NBW; ++i) {
-            __syncthreads();
+            red_t t;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[j][i][v];
-            __syncthreads();
+            for (int hh = 0; hh < EPT; ++hh) t[hh] = 0.0f;
 #pragma unroll
-            for (int hh = 0; hh < EPT; ++hh) {
-                const int v = wave + NW * hh;
-                float s = 0.0f;
+            for (int w = 0; w < NW; ++w) t += red[w][i][wave][lane];
 #pragma unroll
-                for (int w = 0; w < NW; ++w) s += red[w][v][lane];
-                out[j][i][hh] = s;
-            }
+            for (int hh = 0; hh < EPT; ++hh) out[j][i][hh] = t[hh];
         }
+    }
 
     const int col = lane & 31;
     if constexpr (EPI == EPI_HEAD) {
@@ -532,7 +547,7 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
             constexpr int HP = MT == 2 ? EPT : EPT / 2;   // positions per thread and column block
 #pragma unroll
             for (int hp = 0; hp < HP; ++hp) {
-                const int v = wave + NW * hp;
+                const int v = v_of(hp);
                 const int row = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
                 const int jc = 0, ju = MT == 2 ? 1 : 0, hc = hp, hu = MT == 2 ? hp : hp + EPT / 2;
                 const int row_u = MT == 2 ? row : row + 16;
@@ -558,10 +573,10 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
     for (int j = 0; j < MT; ++j)
 #pragma unroll
         for (int hh = 0; hh < EPT; ++hh) {
-            const int v = wave + NW * hh;
+            const int v = v_of(hh);
             const int row = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
             const int m = m_base + j * 32 + row;
-            if (m >= a.M || (SPLIT && (row >> 4) != half)) continue;
+            if (m >= a.M) continue;
             float inv = 1.0f;
             if (kNorm) {
                 float t = 0.0f;
