@@ -156,9 +156,10 @@ struct AttnArgs {
 // One wavefront's pass over the 32-token blocks t_begin, t_begin + t_stride, ... < t_end of (segment seg, query
 // head h, query tile qt): leaves the unnormalised O^T in o, the running maximum (base-2 logits) in m_run and this
 // lane's half of the running sum in l_run; window row = 32 qt + lane % 32.
+// first_page: pages of the first D blocks.
 template <int HD, int D>
 SJD_D void attention_wave(const AttnArgs &a, int seg, int h, int kvh, int qt, int t_begin, int t_end, int t_stride, int kv, int n_tot, int lane,
-                          f32x16 (&o)[HD / 32], float &m_run, float &l_run) {
+                          const int (&first_page)[D], f32x16 (&o)[HD / 32], float &m_run, float &l_run) {
     constexpr int KF = HD / 16, DB = HD / 32;
     const int q_tile = (a.rm.seg_q0 ? a.rm.seg_q0[seg] : seg * a.n_qt) + qt;
     const u32x4 *qp = reinterpret_cast<const u32x4 *>(a.q + ((size_t)q_tile * a.H + h) * 32 * HD) + lane;
@@ -169,12 +170,12 @@ SJD_D void attention_wave(const AttnArgs &a, int seg, int h, int kvh, int qt, in
     const int32_t *pt = a.pool.page_table + (size_t)seg * a.pool.pages_per_seg;
     const int ptok = a.pool.page_tokens;
     const size_t blk = (size_t)ptok * HD;  // elements of one (page, kv head) block
-    auto kfrag = [&](int t0) {            // first fragment of the 32-token block starting at t0
-        return reinterpret_cast<const u32x4 *>((const bf16_t *)a.pool.k + ((size_t)pt[t0 / ptok] * a.Hkv + kvh) * blk) +
+    auto kfrag = [&](int t0, int page) {  // first fragment of the 32-token block starting at t0
+        return reinterpret_cast<const u32x4 *>((const bf16_t *)a.pool.k + ((size_t)page * a.Hkv + kvh) * blk) +
                (size_t)((t0 % ptok) >> 5) * KF * 64 + lane;
     };
-    auto vfrag = [&](int t0) {
-        return reinterpret_cast<const u32x4 *>((const bf16_t *)a.pool.v + ((size_t)pt[t0 / ptok] * a.Hkv + kvh) * blk) +
+    auto vfrag = [&](int t0, int page) {
+        return reinterpret_cast<const u32x4 *>((const bf16_t *)a.pool.v + ((size_t)page * a.Hkv + kvh) * blk) +
                (size_t)((t0 % ptok) >> 5) * 2 * DB * 64 + lane;
     };
 
@@ -193,13 +194,14 @@ SJD_D void attention_wave(const AttnArgs &a, int seg, int h, int kvh, int qt, in
     // and pays the memory latency once.
     u32x4 kf[D][KF], vf[D][2 * DB];
     const int n_blk = (t_end - t_begin + t_stride - 1) / t_stride;
-    auto load_k = [&](int s, int b) {
-        const u32x4 *kp = kfrag(t_begin + b * t_stride);
+    auto page_of = [&](int b) { return pt[(t_begin + b * t_stride) / ptok]; };
+    auto load_k = [&](int s, int b, int page) {
+        const u32x4 *kp = kfrag(t_begin + b * t_stride, page);
 #pragma unroll
         for (int kb = 0; kb < KF; ++kb) kf[s][kb] = kp[kb * 64];
     };
-    auto load_v = [&](int s, int b) {
-        const u32x4 *vp = vfrag(t_begin + b * t_stride);
+    auto load_v = [&](int s, int b, int page) {
+        const u32x4 *vp = vfrag(t_begin + b * t_stride, page);
 #pragma unroll
         for (int f = 0; f < 2 * DB; ++f) vf[s][f] = vp[f * 64];
     };
@@ -213,7 +215,8 @@ SJD_D void attention_wave(const AttnArgs &a, int seg, int h, int kvh, int qt, in
 #pragma unroll
         for (int kb = 0; kb < KF; ++kb)
             sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s][kb]), __builtin_bit_cast(bf16x8, qf[kb]), sc, 0, 0, 0);
-        if (next >= 0) load_k(s, next);
+        const int next_page = next >= 0 ? page_of(next) : 0;
+        if (next >= 0) load_k(s, next, next_page);
         __builtin_amdgcn_sched_barrier(0);
         // The softmax arithmetic below is what bounds a short-context workgroup (all of a head's blocks run on one
         // CU), so it is kept lean and branch-free: one compare per score for the causal / length mask, raw
@@ -255,14 +258,14 @@ SJD_D void attention_wave(const AttnArgs &a, int seg, int h, int kvh, int qt, in
             o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[s][db]), __builtin_bit_cast(bf16x8, p0), o[db], 0, 0, 0);
             o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[s][DB + db]), __builtin_bit_cast(bf16x8, p1), o[db], 0, 0, 0);
         }
-        if (next >= 0) load_v(s, next);
+        if (next >= 0) load_v(s, next, next_page);
         __builtin_amdgcn_sched_barrier(0);
     };
 #pragma unroll
     for (int s = 0; s < D; ++s)
         if (s < n_blk) {
-            load_k(s, s);
-            load_v(s, s);
+            load_k(s, s, first_page[s]);
+            load_v(s, s, first_page[s]);
         }
     __builtin_amdgcn_sched_barrier(0);
     int b0 = 0;
@@ -293,9 +296,13 @@ __global__ __launch_bounds__(256) void attention_mfma_kernel(AttnArgs a) {
     const int t_begin = c * a.chunk;
     if (t_begin >= n_vis || 32 * qt >= n_act) return;
     const int t_end = t_begin + a.chunk < n_vis ? t_begin + a.chunk : n_vis;
+    constexpr int D = HD <= 64 ? 3 : 2;
+    int pages[D];
+#pragma unroll
+    for (int s = 0; s < D; ++s) pages[s] = a.pool.page_table[(size_t)seg * a.pool.pages_per_seg + min((t_begin + 32 * s) / a.pool.page_tokens, a.pool.pages_per_seg - 1)];
     f32x16 o[DB];
     float m_run, l_run;
-    attention_wave<HD, (HD <= 64 ? 3 : 2)>(a, seg, h, kvh, qt, t_begin, t_end, 32, kv, n_tot, lane, o, m_run, l_run);
+    attention_wave<HD, D>(a, seg, h, kvh, qt, t_begin, t_end, 32, kv, n_tot, lane, pages, o, m_run, l_run);
     const int query = lane & 31;
     l_run += __shfl_xor(l_run, 32, 64);
     const size_t slot = (((size_t)seg * a.H + h) * a.n_qt + qt) * a.n_chunks + c;
@@ -314,27 +321,39 @@ __global__ __launch_bounds__(256) void attention_mfma_kernel(AttnArgs a) {
 // the whole softmax.  Its NS wavefronts take the 32-token blocks round-robin, then merge through LDS:
 // out = sum_w 2^(m_w - m) O_w / sum_w 2^(m_w - m) l_w, written straight into the next GEMM's operand layout.
 // No partial results go to HBM and no second kernel is launched.
+// The merge moves NS x 32 x HD floats through LDS, two blocks of 32 dimensions at a time (64 KiB with 8 wavefronts), as the
+// quads of accumulators that a thread adds and stores: 8 bytes of the operand layout at a time.  Only wavefronts that had a
+// block take part.
+// (seg_n, seg_kv, page_table, pages_per_seg: as leading scalars they are in registers when a wavefront starts, so that the
+// segment's lengths, its first pages and the rest of the arguments are on their way together; the keys follow one round trip
+// later instead of three.)
 template <int HD, int NS>
-__global__ __launch_bounds__(NS * 64) void attention_onepass_kernel(AttnArgs a) {
-    constexpr int DB = HD / 32, EPT = 16 / NS;
-    static_assert(16 % NS == 0, "NS must divide 16");
+__global__ __launch_bounds__(NS * 64) void attention_onepass_kernel(const int32_t *seg_n, const int32_t *seg_kv, const int32_t *page_table,
+                                                                    int pages_per_seg, int page_tokens, AttnArgs a) {
+    constexpr int DB = HD / 32, D = HD <= 64 ? 3 : 1;
+    constexpr int QD = NS / 4;        // a block of dimensions has 4 quads per lane: blocks that the workgroup merges at a time
+    static_assert(NS % 4 == 0 && DB % QD == 0, "whole quads per thread");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = blockIdx.x, seg = blockIdx.y, qt = blockIdx.z;
+    const int n_act = seg_n[seg];
+    const int kv = seg_kv[seg];
+    int pages[D];   // (entries past the segment's context are valid page ids that are not used)
+#pragma unroll
+    for (int s = 0; s < D; ++s) pages[s] = page_table[(size_t)seg * pages_per_seg + min((32 * wave + 32 * NS * s) / page_tokens, pages_per_seg - 1)];
     const int kvh = h / (a.H / a.Hkv);
-    const int n_act = a.rm.seg_n[seg];
-    const int kv = a.rm.seg_kv[seg];
     if (a.rm.seg_row0 && 32 * qt >= n_act) return;   // packed rows: a shorter segment
     const int n_tot = n_act > 0 ? kv + n_act : 0;
     const int n_vis = 32 * qt < n_act ? min(n_tot, kv + 32 * (qt + 1)) : 0;  // nothing later is visible to this query tile
+    const int n_waves = min(NS, (n_vis + 31) >> 5);                           // wavefronts with a block of their own
     f32x16 o[DB];
     float m_run, l_run;
-    attention_wave<HD, (HD <= 64 ? 3 : 1)>(a, seg, h, kvh, qt, 32 * wave, n_vis, 32 * NS, kv, n_tot, lane, o, m_run, l_run);
+    attention_wave<HD, D>(a, seg, h, kvh, qt, 32 * wave, n_vis, 32 * NS, kv, n_tot, lane, pages, o, m_run, l_run);
     const int query = lane & 31;
     l_run += __shfl_xor(l_run, 32, 64);
 
     __shared__ float ml[NS][2][32];
-    __shared__ float red[NS][16][64];
+    __shared__ f32x4 red[NS][QD][4][64];
     if (lane < 32) {
         ml[wave][0][query] = m_run;
         ml[wave][1][query] = l_run;
@@ -353,22 +372,31 @@ __global__ __launch_bounds__(NS * 64) void attention_onepass_kernel(AttnArgs a) 
     const bool active = row && a.rm.row_tok[m] >= 0 && denom > 0.0f;
     const float inv = active ? 1.0f / denom : 0.0f;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
+    for (int d0 = 0; d0 < DB; d0 += QD) {
+        if (d0 > 0) __syncthreads();
+        if (wave < n_waves)
+#pragma unroll
+            for (int u = 0; u < QD; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    red[wave][u][q][lane] = f32x4{o[d0 + u][4 * q] * scale, o[d0 + u][4 * q + 1] * scale, o[d0 + u][4 * q + 2] * scale, o[d0 + u][4 * q + 3] * scale};
         __syncthreads();
+        const int u = wave >> 2, q = wave & 3;
+        f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int w = 0; w < n_waves; ++w) t += red[w][u][q][lane];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) red[wave][v][lane] = o[db][v] * scale;
-        __syncthreads();
+        for (int e = 0; e < 4; ++e) t[e] = active ? t[e] * inv : 0.0f;  // 0 * inf (an idle row's garbage) must not become NaN
+        const int j = (d0 + u) * 32 + 8 * q + 4 * (lane >> 5);   // this thread's four dimensions
+        if (row) {
+            if (a.out_act) {
+                uint2 b;
+                b.x = (uint32_t)float_to_bf16(t[0]) | ((uint32_t)float_to_bf16(t[1]) << 16);
+                b.y = (uint32_t)float_to_bf16(t[2]) | ((uint32_t)float_to_bf16(t[3]) << 16);
+                *reinterpret_cast<uint2 *>(a.out_act + Layout<bf16_t>::a_index(m, h * HD + j, a.H * HD)) = b;
+            }
+            if (a.out_plain) {
 #pragma unroll
-        for (int hh = 0; hh < EPT; ++hh) {
-            const int v = wave + NS * hh;
-            float t = 0.0f;
-#pragma unroll
-            for (int w = 0; w < NS; ++w) t += red[w][v][lane];
-            t = active ? t * inv : 0.0f;  // 0 * inf (an idle row's garbage) must not become NaN
-            const int j = db * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            if (row) {
-                if (a.out_act) a.out_act[Layout<bf16_t>::a_index(m, h * HD + j, a.H * HD)] = float_to_bf16(t);
-                if (a.out_plain) a.out_plain[((size_t)m * a.H + h) * HD + j] = t;
+                for (int e = 0; e < 4; ++e) a.out_plain[((size_t)m * a.H + h) * HD + j + e] = t[e];
             }
         }
     }
@@ -441,11 +469,16 @@ inline bool attention_onepass_pays(int max_tokens, int hd, int pairs = 0, int n_
 }
 
 // n_segments segments of L rows each.  onepass: contexts short enough for one workgroup per (segment, head).
-inline hipError_t launch_attention_mfma(hipStream_t st, const AttnArgs &a, int n_segments, bool onepass = false) {
+inline hipError_t launch_attention_mfma(hipStream_t st, const AttnArgs &a, int n_segments, bool onepass = false, int n_cus = 256) {
     if (onepass) {
         const dim3 grid(a.H, n_segments, a.n_qt);
-        if (a.hd == 64) attention_onepass_kernel<64, 8><<<grid, 512, 0, st>>>(a);
-        else attention_onepass_kernel<128, 8><<<grid, 512, 0, st>>>(a);
+        const auto run = [&](auto kernel, int ns) { kernel<<<grid, 64 * ns, 0, st>>>(a.rm.seg_n, a.rm.seg_kv, a.pool.page_table, a.pool.pages_per_seg, a.pool.page_tokens, a); };
+        // A workgroup of 8 wavefronts has a CU to itself (174 registers).  Where there are more of them than CUs, 4 wavefronts each let
+        // two run side by side, if the heads are 64 wide: 320 workgroups of 250-row windows 11.8 -> 10.4 us, 960 of six
+        // prompts 13.5 -> 12.0, but 240 8.2 -> 9.3, and with 128-wide heads 512 10.5 -> 12.3, 1 800 of 2 000 tokens 80 -> 102.
+        if (a.hd == 64 && (long)a.H * n_segments * a.n_qt > n_cus) run(attention_onepass_kernel<64, 4>, 4);
+        else if (a.hd == 64) run(attention_onepass_kernel<64, 8>, 8);
+        else run(attention_onepass_kernel<128, 8>, 8);
         return hipGetLastError();
     }
     dim3 grid(a.n_chunks, a.Hkv, n_segments * a.n_qt);

@@ -274,7 +274,7 @@ template <> int run_attention<bf16_t>(sjd_ctx *c, const KvPool &pool, const FwdR
     a.n_qt = fr.n_qt;
     a.scale_log2e = (float)(1.4426950408889634 / sqrt((double)c->hd));
     // packed prompt rows: a workgroup per (query tile, head) is plenty of them, whatever the context
-    SJD_LAUNCH(c, KC_ATTENTION, launch_attention_mfma(c->stream, a, fr.n_segs, c->attn_onepass || fr.L == 0));
+    SJD_LAUNCH(c, KC_ATTENTION, launch_attention_mfma(c->stream, a, fr.n_segs, c->attn_onepass || fr.L == 0, c->n_cus));
     return SJD_OK;
 }
 

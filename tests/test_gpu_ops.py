@@ -153,3 +153,10 @@ def test_window_attention_fp32(sjd, n, ctx, H, Hkv, hd):
                                                    (250, 300, 4, 2, 128, 8), (40, 0, 2, 2, 64, 0), (33, 31, 2, 1, 128, 8)])
 def test_window_attention_bf16(sjd, n, ctx, H, Hkv, hd, flags):
     _attention_case(sjd, n, ctx, H, Hkv, hd, "bf16", flags=flags)
+
+
+# 64-wide heads and more (head, query tile) workgroups than CUs: four wavefronts a workgroup, of which the first query tiles use
+# fewer; one block past the ring of three, ragged last tiles, grouped heads
+@pytest.mark.parametrize("n,ctx,H,Hkv", [(33, 31, 129, 129), (65, 0, 88, 22), (250, 385, 40, 20), (1, 700, 260, 65)])
+def test_window_attention_more_workgroups_than_cus(sjd, n, ctx, H, Hkv):
+    _attention_case(sjd, n, ctx, H, Hkv, 64, "bf16")
