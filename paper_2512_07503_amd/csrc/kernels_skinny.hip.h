@@ -67,7 +67,7 @@ struct SkinnyArgs {
     const float *row_ssq_part;
     int row_ssq_n;
     // RESID: where a kernel leaves such partial sums for the next one (may be NULL): one per column group of the row-group
-    // kernels, one per wavefront's columns of the LDS kernels, one per pair of column blocks of the tile kernels
+    // kernels, one per wavefront's columns of the LDS kernels, one per column tile of the tile kernels
     float *ssq_out;
     // Gains in the rows: RESID multiplies gain[n] (the next norm's) into the bf16 copy of the stream, and takes ssq_out from
     // the fp32 stream; NULL: the gains are in the weights

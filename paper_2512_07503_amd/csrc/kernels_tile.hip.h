@@ -16,8 +16,8 @@
 //
 // Epilogues and operand layouts are those of the small-row kernel (skinny_epilogue): column blocks (0, 1) and
 // (2, 3) of a tile are rotary / gate-up pairs.  RMSNorm row sums of squares come from the kernel that wrote the
-// rows (partial sums per row, added in a fixed order by the epilogue) when it provides them, else from the
-// activation fragments as they are consumed - which costs a third of the loop's issue slots.
+// rows (partial sums per row, added in a fixed order by the epilogue): taken from the activation fragments as they are
+// consumed they cost a third of the loop's issue slots.
 //
 // What bounds it (measured): replaying only the loop's global loads takes 80 % of the kernel's time whatever the
 // depth of the ring - all workgroups of an XCD ask its L2 for the same few lines at the same time (a k-step's
@@ -38,11 +38,9 @@ constexpr int TILE_RING = SJD_TILE_RING;  // stages of global loads in flight pe
 
 // The work of one workgroup: tile (column tile ct0 + ..., row tile ...) number `wg` of a list of col_tiles x row_tiles
 // tiles that starts at column tile ct0, K range `ks`.
-template <int EPI, bool SSQ_LOOP, int RT, int KS, int D>
+template <int EPI, int RT, int KS, int D>
 SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_blocks, int row_tiles32, int col_tiles, int row_tiles, int ct0) {
     constexpr bool kNorm = EPI != EPI_RESID && EPI != EPI_PARTIAL;
-    constexpr bool kSsqLoop = kNorm && SSQ_LOOP;  // else the rows' sums of squares come from the kernel that wrote the rows
-    constexpr bool kRows = EPI == EPI_RESID && !SSQ_LOOP;  // ... which this is: gains in the rows, sums of squares to ssq_out
     constexpr int U = D % 2 == 0 ? D : 2 * D;  // unroll: ring slot and LDS buffer of an iteration are compile-time
     constexpr int TM = 128 * RT;              // rows of the workgroup's tile: wavefront w owns rows [32 RT w, 32 RT (w + 1))
     const int tid = threadIdx.x, lane = tid & 63;
@@ -84,9 +82,6 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.0f;
-    float ssq[RT];
-#pragma unroll
-    for (int j = 0; j < RT; ++j) ssq[j] = 0.0f;
 
     if (n_it > 0) {
         u32x4 ra[D][KS][RT], rbw[D][KS];
@@ -132,15 +127,6 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
                 for (int j = 0; j < RT; ++j) {
                     const u32x4 araw = valid ? ra[slot][q][j] : zero4;
                     const bf16x8 av = __builtin_bit_cast(bf16x8, araw);
-                    if (kSsqLoop) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const uint32_t pr = araw[e];
-                            const float lo = __builtin_bit_cast(float, pr << 16), hi = __builtin_bit_cast(float, pr & 0xFFFF0000u);
-                            ssq[j] = fmaf(lo, lo, ssq[j]);
-                            ssq[j] = fmaf(hi, hi, ssq[j]);
-                        }
-                    }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bfr[q][i], acc[j][i], 0, 0, 0);
                 }
@@ -170,14 +156,7 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
 
     // 1 / rms of the tile's rows, once per row (ssq_lds holds the factor, not the sum)
     const float inv_k = 1.0f / (float)(KB * 16);
-    if (kSsqLoop) {
-#pragma unroll
-        for (int j = 0; j < RT; ++j) {
-            const float t = ssq[j] + __shfl_xor(ssq[j], 32, 64);
-            if (lane < 32) ssq_lds[wave][j][lane] = 1.0f / sqrtf(t * inv_k + a.eps);
-        }
-        __syncthreads();
-    } else if (kNorm) {
+    if (kNorm) {
         // row tid of the tile: its partial sums of squares in their fixed order
         const int m = rt * TM + tid;
         const float t = tid < TM && m < a.M ? row_ssq_sum(a, m, 0, 1) : 0.0f;
@@ -221,13 +200,16 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
         // short bodies: straight from the accumulators, four rows at a time (the residual values of all four are
         // requested before the first is used)
 #pragma unroll
-        for (int j = 0; j < RT; ++j)
+        for (int j = 0; j < RT; ++j) {
+            [[maybe_unused]] float sq[16];   // RESID: squares of this lane's columns of the accumulators' rows
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sq[v] = 0.0f;
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 const int g = ct * 2 + p;
                 if (g * 2 >= n_blocks) continue;  // past the last column pair
                 float gn[2] = {1.0f, 1.0f};
-                if constexpr (kRows) {
+                if (EPI == EPI_RESID && a.gain) {
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
                         if (const int n = (g * 2 + i) * 32 + col; n < a.N) gn[i] = a.gain[n];
@@ -254,20 +236,34 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
                         const float inv = kNorm ? ssq_lds[wave][j][row0 + u] : 1.0f;
                         const float vals[2] = {acc[j][p * 2][v0 + u], acc[j][p * 2 + 1][v0 + u]};
                         skinny_epilogue<EPI, 2>(a, ks, m0 + u, g * 2, col, vals, inv, xin[u], gn);
-                        if constexpr (kRows) {   // the row's columns of this pair lie in one half wavefront
-                            float sq = 0.0f;
+                        if constexpr (EPI == EPI_RESID) {
 #pragma unroll
                             for (int i = 0; i < 2; ++i) {
-                                const float f = (g * 2 + i) * 32 + col < a.N ? xin[u][i] + vals[i] : 0.0f;
-                                sq = fmaf(f, f, sq);
+                                const float nv = xin[u][i] + vals[i], f = (g * 2 + i) * 32 + col >= a.N ? 0.0f : a.gain ? nv : ssq_value<false>(nv);
+                                sq[v0 + u] = fmaf(f, f, sq[v0 + u]);
                             }
-#pragma unroll
-                            for (int off = 16; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-                            if (col == 0) a.ssq_out[(size_t)g * a.M + m0 + u] = sq;
                         }
                     }
                 }
             }
+            if constexpr (EPI == EPI_RESID) {
+                // A row's columns lie in one half wavefront: halving exchanges, after which lane l holds the sum over even or odd
+                // columns of register v = 8 b4 + 4 b3 + 2 b2 + b1 of its half (b: the bits of l).  16 exchanges; row by row they
+                // were 160 in chains of five, 19 us of a 107 us launch (2000 x 4096 x 4096).
+#pragma unroll
+                for (int h = 8; h > 0; h >>= 1) {
+                    const bool upper = lane & (2 * h);
+#pragma unroll
+                    for (int v = 0; v < h; ++v) {
+                        const float keep = upper ? sq[v + h] : sq[v], give = upper ? sq[v] : sq[v + h];
+                        sq[v] = keep + __shfl_xor(give, 2 * h, 64);
+                    }
+                }
+                sq[0] += __shfl_xor(sq[0], 1, 64);
+                const int v = (lane & 31) >> 1, m = rt * TM + (wave * RT + j) * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                if (!(lane & 1) && m < a.M) a.ssq_out[(size_t)ct * a.M + m] = sq[0];
+            }
+        }
         return;
     }
     // QKV: the body is long; unrolled 64 times it would exceed what the compiler unrolls, and a rolled loop cannot
@@ -313,11 +309,11 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
         }
 }
 
-template <int EPI, bool SSQ_LOOP = true, int RT = 2, int KS = TILE_KS, int D = TILE_RING>
+template <int EPI, int RT = 2, int KS = TILE_KS, int D = TILE_RING>
 __global__ __launch_bounds__(256, RT == 2 ? 2 : 3) void gemm_tile_kernel(SJD_TILE_PARAMS, int col_tiles, int row_tiles, SkinnyArgs a) {
     SJD_TILE_TAKE(a);
     const int row_tiles32 = (a.M + 31) / 32;
-    tile_body<EPI, SSQ_LOOP, RT, KS, D>(a, blockIdx.x, blockIdx.y, n_blocks, row_tiles32, col_tiles, row_tiles, 0);
+    tile_body<EPI, RT, KS, D>(a, blockIdx.x, blockIdx.y, n_blocks, row_tiles32, col_tiles, row_tiles, 0);
 }
 
 // Two tile heights in one launch.  256-row tiles move a quarter fewer operand bytes per MFMA than 128-row tiles, but a
@@ -326,26 +322,26 @@ __global__ __launch_bounds__(256, RT == 2 ? 2 : 3) void gemm_tile_kernel(SJD_TIL
 // the remaining column tiles as 128-row tiles, which fill the second slot of the CUs (the register count of the
 // 256-row body admits two workgroups per CU, whatever their height).  wg_split is a multiple of 8, so both lists keep
 // the workgroup id -> XCD correspondence of tile_body.
-template <int EPI, bool SSQ_LOOP>
+template <int EPI>
 __global__ __launch_bounds__(256, 2) void gemm_tile_mixed_kernel(SJD_TILE_PARAMS, int col_tiles, int ct_split, int wg_split, int row_tiles2, int row_tiles1,
                                                                 SkinnyArgs a) {
     SJD_TILE_TAKE(a);
     const int row_tiles32 = (a.M + 31) / 32;
-    if ((int)blockIdx.x < wg_split) tile_body<EPI, SSQ_LOOP, 2, TILE_KS, TILE_RING>(a, blockIdx.x, blockIdx.y, n_blocks, row_tiles32, ct_split, row_tiles2, 0);
-    else tile_body<EPI, SSQ_LOOP, 1, TILE_KS, TILE_RING>(a, blockIdx.x - wg_split, blockIdx.y, n_blocks, row_tiles32, col_tiles - ct_split, row_tiles1, ct_split);
+    if ((int)blockIdx.x < wg_split) tile_body<EPI, 2, TILE_KS, TILE_RING>(a, blockIdx.x, blockIdx.y, n_blocks, row_tiles32, ct_split, row_tiles2, 0);
+    else tile_body<EPI, 1, TILE_KS, TILE_RING>(a, blockIdx.x - wg_split, blockIdx.y, n_blocks, row_tiles32, col_tiles - ct_split, row_tiles1, ct_split);
 }
 
 // n_blocks = packed 32-column blocks of W.  The K range of a workgroup is a.kb_per_split k-blocks (grid.y = a.ksplit).
 template <int EPI>
 inline hipError_t launch_tile(hipStream_t st, const SkinnyArgs &a, int n_blocks, int tile_rows = 0, bool two_heights = true) {
+    constexpr bool kNorm = EPI != EPI_RESID && EPI != EPI_PARTIAL;
+    if ((kNorm && !a.row_ssq_part) || (EPI == EPI_RESID && !a.ssq_out)) return hipErrorInvalidValue;
     const int tile_rows_in = tile_rows;   // 0: the launcher chooses
     if (a.M <= 0 || n_blocks <= 0 || a.KB <= 0 || a.ksplit < 1 || (size_t)a.kb_per_split * a.ksplit < (size_t)a.KB) return hipErrorInvalidValue;
     if (EPI != EPI_PARTIAL && a.ksplit != 1) return hipErrorInvalidValue;
     if (tile_rows == 0) tile_rows = tile_rows_for(a.M, n_blocks, a.ksplit, a.n_cus > 0 ? a.n_cus : 256);
     const int row_tiles = (a.M + tile_rows - 1) / tile_rows, col_tiles = (n_blocks + 3) / 4;
     const dim3 grid(8 * ((col_tiles + 7) / 8) * row_tiles, a.ksplit);
-    constexpr bool kNorm = EPI != EPI_RESID && EPI != EPI_PARTIAL;
-    const bool ssq_loop = kNorm ? !a.row_ssq_part : EPI == EPI_RESID ? !a.gain : true;
     // Between one and two 256-row tiles per CU: one 256-row tile on every CU, the other column tiles as 128-row tiles
     // beside them (measured at 512 x 22016 x 4096: 95.5 us against 108.0 with 128-row tiles and 126 with 256-row tiles)
     const int n_cus = a.n_cus > 0 ? a.n_cus : 256;
@@ -355,16 +351,13 @@ inline hipError_t launch_tile(hipStream_t st, const SkinnyArgs &a, int n_blocks,
     if (two_heights && tile_rows_in == 0 && EPI != EPI_HEAD && tile_two_heights(a.M, n_blocks, a.ksplit, n_cus)) {
         const int ct_split = n_cus / rt2 / 8 * 8;
         const int wg_split = ct_split * rt2, wg_rest = 8 * ((col_tiles - ct_split + 7) / 8) * rt1;
-        if (ssq_loop) gemm_tile_mixed_kernel<EPI, true><<<dim3(wg_split + wg_rest, 1), 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, ct_split, wg_split, rt2, rt1, a);
-        else gemm_tile_mixed_kernel<EPI, false><<<dim3(wg_split + wg_rest, 1), 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, ct_split, wg_split, rt2, rt1, a);
+        gemm_tile_mixed_kernel<EPI><<<dim3(wg_split + wg_rest, 1), 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, ct_split, wg_split, rt2, rt1, a);
         return hipGetLastError();
     }
     if (tile_rows == 128) {
-        if (ssq_loop) gemm_tile_kernel<EPI, true, 1><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
-        else gemm_tile_kernel<EPI, false, 1><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
+        gemm_tile_kernel<EPI, 1><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
     } else {
-        if (ssq_loop) gemm_tile_kernel<EPI, true, 2><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
-        else gemm_tile_kernel<EPI, false, 2><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
+        gemm_tile_kernel<EPI, 2><<<grid, 256, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);
     }
     return hipGetLastError();
 }

@@ -442,9 +442,9 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // Many-row kernels take the RMSNorm row sums of squares from the kernel that wrote the residual stream (embedding
     // gather or split-K reduction) instead of accumulating them in their k-loops
     const int tile_rows = (md.kernel_flags & SJD_TILES_256_ROWS) ? 256 : 0;  // 0: chosen per launch
-    int ssq_n = 1;   // partial sums per row that the last writer left (0: none); the embedding kernel wrote one
+    int ssq_n = 1;   // partial sums per row that the last writer left; the embedding kernel wrote one
     float *ssq_out = nullptr;   // where the coming output / down projection leaves them: set if its reader takes them
-    auto use_ssq = [&]() { a.row_ssq_part = ssq_n > 0 ? c->row_ssq : nullptr; a.row_ssq_n = ssq_n; };
+    auto use_ssq = [&]() { a.row_ssq_part = c->row_ssq; a.row_ssq_n = ssq_n; };
     // The row-group kernels sum the squares of their operands, which are the stream only while the gains are in the weights
     auto skinny_ssq = [&]() { if (!c->fold_gain) use_ssq(); };
     auto reduce = [&]() -> int {
@@ -479,8 +479,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             a.ksplit = tile_splits(c->shape, M, a.KB);
             a.kb_per_split = ceil_div(a.KB, a.ksplit);
             if (a.ksplit == 1) {
-                // gains in the weights: the next tile kernel sums the squares of its operands
-                ssq_n = c->fold_gain ? 0 : n_blocks / 2;
+                ssq_n = ceil_div(n_blocks, 4);
                 SJD_LAUNCH(c, cls, launch_tile<EPI_RESID>(st, a, n_blocks, tile_rows, mixed_ok));
                 return SJD_OK;
             }
