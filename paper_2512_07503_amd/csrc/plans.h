@@ -21,16 +21,19 @@ struct ProjShape {
 
 constexpr int TILE_M = 256;   // rows of the larger tile of kernels_tile.hip.h
 
-// ---- LDS tiles.  Tile shapes (TMT, TNB, WM, WN, S) of kernels_lds.hip.h.  The last one is the head's where a wavefront has
-// to hold a conditional and an unconditional row tile.
-#define SJD_LDS_TILES(X) X(0, 2, 2, 2, 1, 6) X(1, 4, 2, 4, 1, 6) X(2, 4, 4, 4, 2, 5) X(3, 6, 4, 2, 2, 4) X(4, 4, 4, 2, 2, 4)
-constexpr int kLdsTiles = 4, kLdsTileHeadZ = 4;
+// ---- LDS tiles.  Tile shapes (TMT, TNB, WM, WN, S) of kernels_lds.hip.h.  Shape 4 is the head's where a wavefront has to hold a
+// conditional and an unconditional row tile.  Shape 5 (QKV and gate/up) moves the fewest bytes per MFMA but leaves a CU to one
+// workgroup and its epilogue uncovered: it is for launches of one workgroup per CU at most.  2048 x 6144 x 4096 121 -> 107 us in
+// a forward (tile kernels before), 1000 x 12288 x 4096 108 -> 100, 1280 x 12288 135 -> 110, 2040 x 6912 x 1280 48 -> 43; with
+// several per CU it gains nothing (2048 x 28672 x 4096 434 us against 430).
+#define SJD_LDS_TILES(X) X(0, 2, 2, 2, 1, 6) X(1, 4, 2, 4, 1, 6) X(2, 4, 4, 4, 2, 5) X(3, 6, 4, 2, 2, 4) X(4, 4, 4, 2, 2, 4) X(5, 8, 8, 2, 4, 4)
+constexpr int kLdsTiles = 4, kLdsTileHeadZ = 4, kLdsTileBig = 5;
 struct LdsTile { int tmt, tnb, cb; double t1, t2, tn; };
 // t1, t2, tn: microseconds per pipeline stage of a CU with one workgroup, with two, and per workgroup of more.  Measured on
 // models 768 to 4096 wide at 118 to 2040 rows, weights from HBM.
 inline LdsTile lds_tile(int cfg) {
-    static const LdsTile t[5] = {{2, 2, 2, 0.22, 0.33, 0.14}, {4, 2, 2, 0.27, 0.45, 0.19}, {4, 4, 2, 0.38, 0.56, 0.30}, {6, 4, 2, 0.42, 0.72, 0.37},
-                                 {4, 4, 2, 0.40, 0.62, 0.33}};
+    static const LdsTile t[6] = {{2, 2, 2, 0.22, 0.33, 0.14}, {4, 2, 2, 0.27, 0.45, 0.19}, {4, 4, 2, 0.38, 0.56, 0.30}, {6, 4, 2, 0.42, 0.72, 0.37},
+                                 {4, 4, 2, 0.40, 0.62, 0.33}, {8, 8, 2, 0.80, 1e3, 1e3}};
     return t[cfg];
 }
 
@@ -39,7 +42,7 @@ inline double lds_us(int cfg, int M, int n_blocks, int KB, int ks, int n_cus) {
     const LdsTile t = lds_tile(cfg);
     const int wgs_xcd = plan_div(plan_div(n_blocks, t.tnb), 8) * plan_div(M, 32 * t.tmt) * ks;
     const int n = plan_div(wgs_xcd, std::max(1, n_cus / 8));
-    return 4.0 + (double)plan_div(KB, 2 * ks) * (n == 1 ? t.t1 : n == 2 ? t.t2 : n * t.tn);
+    return (cfg == kLdsTileBig ? 8.0 : 4.0) + (double)plan_div(KB, 2 * ks) * (n == 1 ? t.t1 : n == 2 ? t.t2 : n * t.tn);
 }
 // ... of a row-group launch (kernels_skinny.hip.h): a CU moves 52 GB/s of weights and activations
 inline double skinny_us(int wgs, double wg_bytes, bool norm, int n_cus) {
@@ -100,6 +103,12 @@ inline ProjPlan with_lds(const ProjShape &s, int M, int n_blocks, int KB, int ma
         }
     return p;
 }
+// Shape 5 in the place of p where it is expected to be faster (QKV and gate/up only).
+inline ProjPlan with_big(const ProjShape &s, int M, int n_blocks, ProjPlan p) {
+    if (M < TILE_M || (s.kernel_flags & (SJD_KERNELS_ROWGROUPS | SJD_KERNELS_TILES))) return p;
+    const double t = lds_us(kLdsTileBig, M, n_blocks, s.d_model / 16, 1, s.n_cus);
+    return t < p.us ? ProjPlan{kLdsTileBig, 1, t} : p;
+}
 // QKV, gate/up and head: groups of two column blocks, whole K.  (2 us: the sums of squares that the row-group kernel takes
 // from its operands come from the writer of the rows with LDS tiles.)
 inline ProjPlan norm_plan(const ProjShape &s, int M, int groups) {
@@ -147,13 +156,19 @@ inline bool tile_forward(const ProjShape &s, int M) {
 }
 
 struct ForwardPlan {
-    bool tile;                             // every projection through the tile kernels
+    bool tile;                             // every projection through the tile kernels, but QKV or gate/up of LDS tile shape 5
     ProjPlan qkv, o, gate_up, down, head;  // else each its own
 };
 // windows32: windows of 32 whose guidance branches the head combines, which needs both row tiles of a sequence in one wavefront
 inline ForwardPlan forward_plan(const ProjShape &s, int M, bool windows32) {
     ForwardPlan f = {tile_forward(s, M), norm_plan(s, M, s.qkv_groups()), resid_plan(s, M, s.q_dim()), norm_plan(s, M, s.gate_up_groups()),
                      resid_plan(s, M, s.d_ff), norm_plan(s, M, s.head_groups())};
+    if (f.tile) {
+        f.qkv = {-1, 1, tile_us(M, s.qkv_groups() * 2, s.d_model / 16, 1, s.n_cus)};
+        f.gate_up = {-1, 1, tile_us(M, s.gate_up_groups() * 2, s.d_model / 16, 1, s.n_cus)};
+    }
+    f.qkv = with_big(s, M, s.qkv_groups() * 2, f.qkv);
+    f.gate_up = with_big(s, M, s.gate_up_groups() * 2, f.gate_up);
     if (f.head.lds >= 0 && windows32) f.head.lds = kLdsTileHeadZ;
     return f;
 }

@@ -521,7 +521,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         pool.page_tokens = c->pt;
         a.pool = pool;
         a.A = (const bf16_t *)c->xn; a.W = (const bf16_t *)lw.wqkv; a.KB = d / 16;
-        if (tile) {
+        if (tile && plan_qkv.lds < 0) {
             whole_k();
             use_ssq();
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_tile<EPI_QKV>(st, a, (H + 2 * Hkv) * (hd / 64) * 2, tile_rows, mixed_ok));
@@ -549,7 +549,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         a.gain = lw.mlp_norm;
         { int rc = resid(KC_GEMM_O, c->attn, lw.wo, H * hd, plan_o, proj_of(lw.wgu, F / 32 * 2, d / 16, 2, plan_gu), nullptr); if (rc) return rc; }
         a.A = (const bf16_t *)c->xn; a.W = (const bf16_t *)lw.wgu; a.KB = d / 16;
-        if (tile) {
+        if (tile && plan_gu.lds < 0) {
             whole_k();
             use_ssq();
             SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_tile<EPI_SWIGLU>(st, a, F / 32 * 2, tile_rows, mixed_ok));

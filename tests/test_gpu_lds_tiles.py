@@ -113,3 +113,17 @@ def test_against_float64(d, heads, kv, ff, ids, window, lens):
             assert err < 1.5e-2 and row.max() < 4.5e-2
     # windows of 32: the head that combines the branches against the tile shape that it takes otherwise, the same sums
     assert np.abs(out[0] - out[1]).max() <= (1e-5 if window == 32 else 0.0) * np.abs(out[1]).max()
+
+
+# 256 x 256 tiles (QKV or gate/up of prompts whose tiles number at most one per CU), ragged in rows and in columns; same bound
+BIG_CASES = [
+    (2048, 16, 16, 5664, 3001, 33, [(500, 505)]),    # 1003 prompt rows: gate/up, its last column tile two blocks wide
+    (2048, 16, 16, 5664, 3001, 1, [(1000, 1005)]),   # 2003, beside tile kernels: QKV
+    (1280, 20, 20, 6912, 3001, 1, [(480, 480)]),     # 958, 64-wide heads: gate/up
+    (3072, 24, 24, 8224, 3001, 2, [(700, 709)]),     # 1407, beside LDS tiles of other shapes: QKV
+]
+
+
+@pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens", BIG_CASES)
+def test_big_tiles_against_float64(d, heads, kv, ff, ids, window, lens):
+    test_against_float64(d, heads, kv, ff, ids, window, lens)

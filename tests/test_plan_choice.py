@@ -55,3 +55,10 @@ def test_few_rows_and_the_row_group_flag_keep_the_row_groups():
     for rows, flags in ((32, 0), (64, 0), (500, 4)):
         p = plan_choice.choose([(arch, rows, 0, flags)])[0]
         assert not p["tile"] and all(p[n][0] == -1 for n in ("qkv", "out", "gate_up", "down", "head"))
+
+
+def test_the_big_tile_cases_reach_the_256_x_256_tiles():
+    import test_gpu_lds_tiles as t
+    queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, 0) for d, h, kv, ff, ids, _, lens in t.BIG_CASES]
+    got = [(n, p["tile"]) for p in plan_choice.choose(queries) for n in ("qkv", "gate_up") if p[n][0] == 5]
+    assert got == [("gate_up", False), ("qkv", True), ("gate_up", False), ("qkv", False)], got
