@@ -643,13 +643,26 @@ __global__ void embed_dual_kernel(const bf16_t *__restrict__ emb, float *__restr
     for (int j = threadIdx.x; j < half; j += blockDim.x)
         t.rot[(size_t)m * half + j] = pos >= 0 ? make_float2(t.rope_cos[(size_t)pos * half + j], t.rope_sin[(size_t)pos * half + j])
                                                : make_float2(1.0f, 0.0f);
+    // 8 elements a thread (d is a multiple of 32): 16 bytes of the table and of the operand copy, 32 of the stream; element by
+    // element 16 rows of 4096 took 14 us
     float sq = 0.0f;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) {
-        const bf16_t v = tok >= 0 ? emb[(size_t)tok * d + i] : (bf16_t)0;
-        const float f = bf16_to_float(v);
-        x[(size_t)m * d + i] = f;
-        xb[Layout<bf16_t>::a_index(m, i, d)] = t.gain ? float_to_bf16(f * t.gain[i]) : v;
-        sq = fmaf(f, f, sq);
+    for (int i = threadIdx.x * 8; i < d; i += blockDim.x * 8) {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (tok >= 0) v = *reinterpret_cast<const u32x4 *>(emb + (size_t)tok * d + i);
+        float f[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = __builtin_bit_cast(float, e & 1 ? v[e >> 1] & 0xFFFF0000u : v[e >> 1] << 16);
+        float4 *xr = reinterpret_cast<float4 *>(x + (size_t)m * d + i);
+        xr[0] = make_float4(f[0], f[1], f[2], f[3]);
+        xr[1] = make_float4(f[4], f[5], f[6], f[7]);
+        if (t.gain) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[e] = (uint32_t)float_to_bf16(f[2 * e] * t.gain[i + 2 * e]) | ((uint32_t)float_to_bf16(f[2 * e + 1] * t.gain[i + 2 * e + 1]) << 16);
+        }
+        *reinterpret_cast<u32x4 *>(xb + Layout<bf16_t>::a_index(m, i, d)) = v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sq = fmaf(f[e], f[e], sq);
     }
     __shared__ float scratch[17];
     const float total = block_sum_f32(sq, scratch);
