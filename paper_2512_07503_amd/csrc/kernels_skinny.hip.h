@@ -260,21 +260,23 @@ SJD_D void l2_warm_kv(const SkinnyArgs &a, int id, int first_id, int tid, int th
     const int xcd = id & 7, rank = (id - first_id) >> 3, ranks = a.kv_wgs >> 3;
     const int G = a.H / a.Hkv;
     const size_t blk_bytes = (size_t)a.kv_pool.page_tokens * a.hd * sizeof(bf16_t);  // one (page, kv head) block of keys or values
-    const uint32_t blk_lines = (uint32_t)(blk_bytes >> 7), pair_lines = (uint32_t)a.kv_pool.pages_per_seg * 2 * blk_lines;
-    const uint32_t n_pairs = a.kv_pairs > xcd ? (uint32_t)(a.kv_pairs - xcd + 7) >> 3 : 0;  // this XCD's (segment, head) pairs
+    const int blk_lines = (int)(blk_bytes >> 7);
+    const int n_pairs = a.kv_pairs > xcd ? (a.kv_pairs - xcd + 7) >> 3 : 0;  // this XCD's (segment, head) pairs
+    if (n_pairs == 0) return;
+    // `per` workgroups share a pair where there are more of them than pairs; only the pages that exist are walked (over all
+    // pages that a segment may have, 512 pairs of 24 of 2376 tokens kept these workgroups busy for 56 us of a 21 us launch)
+    const int per = ranks > n_pairs ? ranks / n_pairs : 1, teams = ranks / per, sub = rank % per;
     uint32_t sink = 0;
-    // One flat index space over (pair, page, keys | values, line), so that a thread's few lines are independent of
-    // each other: the page count of the segment and the page table entry load side by side, then the line.
+    for (int j = rank / per; j < n_pairs && rank / per < teams; j += teams) {
+        const int p = xcd + 8 * j, seg = p / a.H, kvh = (p % a.H) / G;
+        const int lines = a.kv_seg_kv[seg] / a.kv_pool.page_tokens * 2 * blk_lines;   // per page: its keys, then its values
+        const int32_t *pt = a.kv_pool.page_table + seg * a.kv_pool.pages_per_seg;
+        if (sub == 0 && tid < a.kv_pool.pages_per_seg) sink ^= (uint32_t)pt[tid];   // the table itself, also of a context without a whole page
 #pragma unroll 2
-    for (uint32_t i = rank * threads + tid; i < n_pairs * pair_lines; i += ranks * threads) {
-        const uint32_t j = i / pair_lines, r0 = i - j * pair_lines;
-        const uint32_t pg = r0 / (2 * blk_lines), r = r0 - pg * 2 * blk_lines;
-        const int p = xcd + 8 * (int)j, seg = p / a.H, kvh = (p % a.H) / G;
-        const int pages = a.kv_seg_kv[seg] / a.kv_pool.page_tokens;
-        const int page = a.kv_pool.page_table[seg * a.kv_pool.pages_per_seg + pg];
-        if ((int)pg < pages) {
+        for (int i = sub * threads + tid; i < lines; i += per * threads) {
+            const int pg = i / (2 * blk_lines), r = i - pg * 2 * blk_lines;
             const char *base = r < blk_lines ? (const char *)a.kv_pool.k : (const char *)a.kv_pool.v;
-            sink ^= *reinterpret_cast<const uint32_t *>(base + ((size_t)page * a.Hkv + kvh) * blk_bytes + (size_t)(r % blk_lines) * 128);
+            sink ^= *reinterpret_cast<const uint32_t *>(base + ((size_t)pt[pg] * a.Hkv + kvh) * blk_bytes + (size_t)(r % blk_lines) * 128);
         }
     }
     if (sink == 0x9e3779b9u) *a.pf_sink = sink;
