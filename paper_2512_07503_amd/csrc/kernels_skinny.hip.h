@@ -168,11 +168,14 @@ SJD_D void qkv_store(const SkinnyArgs &a, const QkvRow &r, int g, int col, float
     }
 }
 
-// z = fma(s, l_c - l_u, l_u) / T on logits l = value * (1 / rms), every operation rounded on its own (the decision stage
-// is specified bit for bit on these values, and the compiler may otherwise contract the products into the sums)
+// z = fma(s, l_c - l_u, l_u) / T on logits l = value * (1 / rms), every operation rounded on its own: the decision stage is
+// specified bit for bit on these values.  (By pragma: __fmul_rn and __fsub_rn are plain operators to the compiler, which made
+// fma(value, 1 / rms, -l_u) of them, and now and then a draw took the neighbouring id.)
 SJD_D float guided_z(float val_c, float inv_c, float val_u, float inv_u, float s, float inv_t) {
-    const float lc = __fmul_rn(val_c, inv_c), lu = __fmul_rn(val_u, inv_u);
-    return __fmul_rn(__fmaf_rn(s, __fsub_rn(lc, lu), lu), inv_t);
+#pragma clang fp contract(off)
+    const float lc = val_c * inv_c, lu = val_u * inv_u;
+    const float diff = lc - lu;
+    return __builtin_fmaf(s, diff, lu) * inv_t;
 }
 
 // Row m's partial sums of squares c0, c0 + step, ..., added in this order; eight loads are in flight

@@ -257,6 +257,29 @@ def test_guidance_fused_into_the_head_changes_nothing(oracle, name, window, n_se
     assert all(len(t) == n for t, n in zip(runs[0][1], n_img))
 
 
+@pytest.mark.parametrize("name,n_seqs,flags", [("small_wide_vocab", None, 0), ("small_wide_vocab", 2, 0), ("small_wide_vocab", 4, 0),
+                                               ("small_wide_vocab", 4, 16), ("small_fused64", None, 0), ("small_tile", None, 16)])
+def test_guidance_fused_into_the_head_is_that_of_the_logits(oracle, name, n_seqs, flags):
+    """The rows that a step keeps (ids and weights, every bit) where its head wrote z are those that the decision stage makes
+    of the same step's logits.  (A difference contracted with the product before it passes most comparisons of tokens.)"""
+    cfg = workload.get_config(name)
+    o, g, cond, uncond, n_img = make_pair(oracle, cfg, n_seqs=n_seqs, kernel_flags=flags, head_alpha=6.0, std=0.08)
+    o.close()
+    before = g.snapshot()
+    res = g.step()
+    logits, fused = g.logits(), g.snapshot()
+    g.restore(before)
+    assert g.step_from_logits(logits) == res
+    plain = g.snapshot()
+    # without the cache pages that end a snapshot: only a forward writes the window's keys and values to them
+    arch = cfg["arch"]
+    tokens = [len(p) - 1 + r["n_finalized"] for ps in (cond, uncond) for p, r in zip(ps, res)]
+    pages = sum(-(-t // 64) for t in tokens) * 64 * arch["n_kv_heads"] * (arch["d_model"] // arch["n_heads"]) * 2 * 2 * arch["n_layers"]
+    end = len(plain) - pages
+    assert len(fused) == len(plain) and end > 4 * cfg["top_k"] and np.array_equal(fused[:end], plain[:end])
+    g.close()
+
+
 def test_error_paths_on_device(oracle):
     import paper_2512_07503_amd as sjd
     from helpers import gpu_weights
