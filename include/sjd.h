@@ -21,9 +21,10 @@
  *    pointers are ordinary process memory;
  *  - hip_stream is a hipStream_t passed as void* (NULL = the default stream);
  *    it is borrowed and must outlive the context; all work of a context is
- *    enqueued on it.  On an ordinary stream sjd_step records its launches once
- *    (stream capture, thread-local mode) and replays them as a HIP graph; on
- *    the default stream, which cannot be captured, it launches them one by one;
+ *    enqueued on it.  On an ordinary stream sjd_step records its launches
+ *    beside its first run (stream capture, thread-local mode) and replays them
+ *    as a HIP graph from then on; on the default stream, which cannot be
+ *    captured, it launches them one by one;
  *  - a context is not thread-safe; different contexts are independent.
  */
 #ifndef SJD_H

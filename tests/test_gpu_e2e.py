@@ -257,6 +257,27 @@ def test_guidance_fused_into_the_head_changes_nothing(oracle, name, window, n_se
     assert all(len(t) == n for t, n in zip(runs[0][1], n_img))
 
 
+def test_recorded_steps_of_changing_batches(oracle):
+    """Contexts whose batch grows and shrinks between images record the step anew, beside the first one of each size: verdicts,
+    tokens and logits as without recording, bit for bit."""
+    import paper_2512_07503_amd as sjd
+    cfg = workload.get_config("small_fused64")
+    runs = []
+    for flags in (0, sjd.NO_GRAPH):
+        o, g, cond, uncond, _ = make_pair(oracle, cfg, n_seqs=3, n_image=30, kernel_flags=flags, head_alpha=6.0, std=0.08)
+        o.close()
+        out = []
+        for n in (1, 1, 3, 2, 3):
+            assert g.prefill(cond[:n], uncond[:n], [30] * n) == 0
+            for _ in range(3):
+                out.append((g.step(), g.logits()))
+            out.append((g.decode(1000), np.concatenate([g.tokens(s) for s in range(n)])))
+        g.close()
+        runs.append(out)
+    for (a, x), (b, y) in zip(*runs):
+        assert a == b and np.array_equal(x, y)
+
+
 @pytest.mark.parametrize("name,n_seqs,flags", [("small_wide_vocab", None, 0), ("small_wide_vocab", 2, 0), ("small_wide_vocab", 4, 0),
                                                ("small_wide_vocab", 4, 16), ("small_fused64", None, 0), ("small_tile", None, 16)])
 def test_guidance_fused_into_the_head_is_that_of_the_logits(oracle, name, n_seqs, flags):
