@@ -61,6 +61,16 @@ struct KvPool {
     int pages_per_seg, page_tokens;
 };
 
+// A rotary pair turned by (c, s): v0 c - v1 s and v1 c + v0 s.  Of each sum's two products one is rounded ahead of the sum and the
+// other one within it; which, is said here.  Of the plain expressions the compiler made either, from one kernel instance to the
+// next and from one build to the next, and some keys and queries took the neighbouring bf16.  The row-group projections round
+// v1 c of the second sum (ROUND_V1C), all others v0 s.
+template <bool ROUND_V1C = false> SJD_D void rotate_pair(float &v0, float &v1, float c, float s) {
+    const float r0 = __builtin_fmaf(v0, c, -(v1 * s));
+    v1 = ROUND_V1C ? __builtin_fmaf(v0, s, v1 * c) : __builtin_fmaf(v1, c, v0 * s);
+    v0 = r0;
+}
+
 // qkv partial sums [splits][M][(H + 2 Hkv) * hd] -> rotated q (attention operand layout, per segment
 // and head), rotated k and v into the KV pages at the row's position.
 template <typename T>
@@ -84,9 +94,8 @@ __global__ void rope_kv_kernel(const float *__restrict__ partial, int splits, in
     // q and k: one thread per rotated pair
     for (int idx = threadIdx.x; idx < (H + Hkv) * half; idx += blockDim.x) {
         const int h = idx / half, i = idx % half;
-        const float a = val(h * hd + i), b = val(h * hd + i + half);
-        const float c = rope_cos[(size_t)pos * half + i], s = rope_sin[(size_t)pos * half + i];
-        const float r0 = a * c - b * s, r1 = b * c + a * s;
+        float r0 = val(h * hd + i), r1 = val(h * hd + i + half);
+        rotate_pair(r0, r1, rope_cos[(size_t)pos * half + i], rope_sin[(size_t)pos * half + i]);
         if (h < H) {
             T *dst = q_out + ((size_t)(q_tile0 + (i_win >> 5)) * H + h) * 32 * hd;
             dst[Layout<T>::q_index(i_win & 31, i, hd)] = from_float<T>(r0);

@@ -258,15 +258,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARA
                         }
                         const float4 r0 = rot[4 * q], r1 = rot[4 * q + 1];   // (cos, sin) of 4 consecutive dimensions
                         const float c[4] = {r0.x, r0.z, r1.x, r1.z}, s[4] = {r0.y, r0.w, r1.y, r1.w};
-                        float w0[4], w1[4];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            w0[e] = v0[e] * c[e] - v1[e] * s[e];
-                            w1[e] = v1[e] * c[e] + v0[e] * s[e];
-                        }
+                        for (int e = 0; e < 4; ++e) rotate_pair(v0[e], v1[e], c[e], s[e]);
                         // queries and keys share the form of their row operand: 4 dimensions are 8 contiguous bytes
-                        *reinterpret_cast<uint2 *>(dst + Layout<bf16_t>::q_index(0, j0 + 8 * q, a.hd)) = pack_bf16x4(w0[0], w0[1], w0[2], w0[3]);
-                        *reinterpret_cast<uint2 *>(dst + Layout<bf16_t>::q_index(0, j0 + 8 * q + half, a.hd)) = pack_bf16x4(w1[0], w1[1], w1[2], w1[3]);
+                        *reinterpret_cast<uint2 *>(dst + Layout<bf16_t>::q_index(0, j0 + 8 * q, a.hd)) = pack_bf16x4(v0[0], v0[1], v0[2], v0[3]);
+                        *reinterpret_cast<uint2 *>(dst + Layout<bf16_t>::q_index(0, j0 + 8 * q + half, a.hd)) = pack_bf16x4(v1[0], v1[1], v1[2], v1[3]);
                     }
                 }
             } else if constexpr (EPI == EPI_SWIGLU) {

@@ -140,16 +140,13 @@ SJD_D void qkv_rotation(const SkinnyArgs &a, int m, int g, int col, float &c, fl
         s = cs.y;
     }
 }
+template <bool ROUND_V1C>
 SJD_D void qkv_store(const SkinnyArgs &a, const QkvRow &r, int g, int col, float v0, float v1, float c, float s) {
     if (r.pos < 0) return;
     const int pairs = a.hd >> 6;
     const int head = g / pairs, sub = g % pairs, half = a.hd >> 1;
     const int j0 = sub * 32 + col, j1 = j0 + half;
-    {
-        const float r0 = v0 * c - v1 * s, r1 = v1 * c + v0 * s;
-        v0 = r0;
-        v1 = r1;
-    }
+    rotate_pair<ROUND_V1C>(v0, v1, c, s);
     if (head < a.H) {
         bf16_t *dst = a.q_out + (size_t)head * 32 * a.hd + r.q_off;
         dst[Layout<bf16_t>::q_index(0, j0, a.hd)] = float_to_bf16(v0);
@@ -595,7 +592,7 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
                 vals[i] = out[j][i][hh];
                 xin[i] = EPI == EPI_RESID ? xpre[j][i][hh] : 0.0f;
             }
-            if constexpr (EPI == EPI_QKV) qkv_store(a, qrow[j][hh], g, col, vals[0] * inv, vals[NBW - 1] * inv, rot_c[j][hh], rot_s[j][hh]);
+            if constexpr (EPI == EPI_QKV) qkv_store<true>(a, qrow[j][hh], g, col, vals[0] * inv, vals[NBW - 1] * inv, rot_c[j][hh], rot_s[j][hh]);
             else skinny_epilogue<EPI, NBW>(a, ks, m, blk0, col, vals, inv, xin, gpre);
             if constexpr (EPI == EPI_RESID) {
                 if (a.ssq_out) {   // the row's columns of this group lie in one half wavefront

@@ -303,7 +303,7 @@ SJD_D void tile_body(const SkinnyArgs &a, const int wg, const int ks, int n_bloc
                     const int v = v0 + u;
                     if (m0 + u >= a.M) continue;
                     const float inv = ssq_lds[wave][j][row0 + u];
-                    qkv_store(a, qrow[(wave * RT + j) * 32 + row0 + u], g, col, park[v * 64] * inv, park[(16 + v) * 64] * inv, rc[u], rs[u]);
+                    qkv_store<false>(a, qrow[(wave * RT + j) * 32 + row0 + u], g, col, park[v * 64] * inv, park[(16 + v) * 64] * inv, rc[u], rs[u]);
                 }
             }
         }

@@ -95,3 +95,28 @@ def test_fewer_sequences_than_the_context_holds(n_seqs, flags):
                 err = np.linalg.norm(out[s, b] - want) / np.linalg.norm(want)
                 print(n_seqs, flags, "sequence", s, "branch", b, "relative error of the logits", err)
                 assert err < 1.5e-2
+
+
+@pytest.mark.parametrize("window", [16, 32])
+def test_row_splits_change_no_bit(window):
+    """A 1280-wide model (its MLP narrow enough that K is whole in every projection), 32 rows as two workgroups of 16 a column
+    group against one of 32, and 64 rows as groups of 32 against one of 64 (flag 128; every workgroup walking K from 0): the same
+    sums in the same order, and a rotation whose operations the source fixes, so logits, keys and values agree bit for bit.
+    (Which of the rotation's products was rounded ahead of the sum was once left to the compiler: one key in some 10^5 moves to
+    the next bf16, and the pages hold 24 x 32 x 1280 keys of this step.)"""
+    import numpy as np
+    import paper_2512_07503_amd as sjd
+    from test_gpu_lds_tiles import _weights, case_arch
+    arch = dict(case_arch(1280, 20, 20, 2560, 3001), n_layers=24)
+    w = _weights(arch, 17)
+    runs = []
+    for flags in (sjd.NO_K_ROTATION, sjd.NO_K_ROTATION | sjd.NO_ROW_SPLIT):
+        g = sjd.Decoder(arch, w, "bf16", window, 200, top_k=200, seed=5, kernel_flags=flags | sjd.KEEP_LOGITS)
+        one = [np.array([7], dtype=np.int32)]   # a prompt of one token: no forward before the step
+        assert g.prefill(one, one, [190]) == 0
+        g.step()
+        # the cache pages that end a snapshot: one page of 64 tokens a segment holds the whole window
+        runs.append((g.logits(), g.snapshot()[-2 * arch["n_layers"] * 2 * 64 * 1280 * 2:]))
+        g.close()
+    assert runs[0][0].any() and runs[0][1].any()
+    assert all(np.array_equal(a, b) for a, b in zip(*runs))
