@@ -24,7 +24,7 @@
  *    enqueued on it.  On an ordinary stream sjd_step records its launches
  *    beside its first run (stream capture, thread-local mode) and replays them
  *    as a HIP graph from then on; on the default stream, which cannot be
- *    captured, it launches them one by one;
+ *    captured, or where the recording fails, it launches them one by one;
  *  - a context is not thread-safe; different contexts are independent.
  */
 #ifndef SJD_H
@@ -184,8 +184,10 @@ int sjd_prefill(sjd_ctx *ctx, int32_t n_seqs, const int32_t *const *cond_ids, co
 /* One speculative Jacobi iteration for every unfinished sequence (Sec. 4.1
  * Steps 1-4).  out is a HOST array of n_seqs results.  The call returns after
  * the step has completed on the device.  Sequences that are done are left
- * untouched (n_finalized = 0, done = 1).  Errors: SJD_ESTATE (no prefill),
- * SJD_EINVAL, SJD_EDEVICE. */
+ * untouched (n_finalized = 0, done = 1).  Errors: SJD_ESTATE (no prefill) and
+ * SJD_EINVAL (null argument), before anything ran; SJD_EDEVICE: a launch, the
+ * device or the download of the verdicts failed, and the step may have run in
+ * part or whole: go on from sjd_prefill or sjd_snapshot_restore. */
 int sjd_step(sjd_ctx *ctx, sjd_step_result *out);
 
 /* Frees everything the context owns.  NULL is allowed. */

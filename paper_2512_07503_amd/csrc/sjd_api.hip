@@ -956,18 +956,25 @@ void drop_graph(sjd_ctx *c, int g) {
     c->graph_n_seqs[g] = 0;
 }
 
-// records the launches of a step as graph g
-int record_step(sjd_ctx *c, int g) {
-    SJD_HIP_TRY(c->err, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    const int rc = enqueue_step(c);
+// Records the launches of a step, which have been enqueued already, as graph g; false where that fails.
+bool record_step(sjd_ctx *c, int g) {
     hipGraph_t gr = nullptr;
-    const hipError_t e = hipStreamEndCapture(c->stream, &gr);  // always end the capture, also after a failed launch
-    if (rc) { if (gr) (void)hipGraphDestroy(gr); return rc; }
-    if (e != hipSuccess || !gr) { sjd_set_error(c->err, "stream capture of the step failed: %s", hipGetErrorString(e)); return SJD_EDEVICE; }
+    hipGraphExec_t ex = nullptr;
+    bool ok = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
+    if (ok) {
+        ok = enqueue_step(c) == SJD_OK;
+        ok = hipStreamEndCapture(c->stream, &gr) == hipSuccess && gr && ok;   // always end the capture, also after a failed launch
+        ok = ok && hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0) == hipSuccess;
+    }
+    if (!ok) {
+        if (gr) (void)hipGraphDestroy(gr);
+        (void)hipGetLastError();   // not the error of a launch to come
+        return false;
+    }
     c->graph[g] = gr;
-    SJD_HIP_TRY(c->err, hipGraphInstantiate(&c->graph_exec[g], c->graph[g], nullptr, nullptr, 0));
+    c->graph_exec[g] = ex;
     c->graph_n_seqs[g] = c->n_seqs;
-    return SJD_OK;
+    return true;
 }
 
 // one-pass attention for a step's launches iff the longest visible context (cache + rows) is short
@@ -1211,9 +1218,10 @@ int sjd_step(sjd_ctx *c, sjd_step_result *out) {
             // instantiated ahead of it, its launches kept the device idle for half a millisecond (a new context's first prefill and
             // step, 36 layers of 1280, window 16: 1800 -> 1260 us; with a 120-token prompt, window 32: 4310 -> 3370)
             if ((rc = enqueue_step(c))) return rc;
-            const int recorded = record_step(c, g);
+            const bool recorded = record_step(c, g);
             rc = finish_step(c, out);
-            return rc ? rc : recorded;
+            if (!rc && !recorded) c->use_graph = false;   // the step is the step; those after it are launched one by one
+            return rc;
         }
         SJD_HIP_TRY(c->err, hipGraphLaunch(c->graph_exec[g], c->stream));
     } else if ((rc = enqueue_step(c))) {
