@@ -279,11 +279,27 @@ def test_recorded_steps_of_changing_batches(oracle):
 
 
 @pytest.mark.parametrize("name,n_seqs,flags", [("small_wide_vocab", None, 0), ("small_wide_vocab", 2, 0), ("small_wide_vocab", 4, 0),
-                                               ("small_wide_vocab", 4, 16), ("small_fused64", None, 0), ("small_tile", None, 16)])
+                                               ("small_wide_vocab", 4, 16), ("small_fused64", None, 0), ("small_tile", None, 16),
+                                               # 17 001 sampled ids, 266 column groups: workgroups of two widths
+                                               ("small_wide_vocab 17001", None, 0)])
 def test_guidance_fused_into_the_head_is_that_of_the_logits(oracle, name, n_seqs, flags):
     """The rows that a step keeps (ids and weights, every bit) where its head wrote z are those that the decision stage makes
     of the same step's logits.  (A difference contracted with the product before it passes most comparisons of tokens.)"""
+    import paper_2512_07503_amd as sjd
+    name, *ids = name.split()
     cfg = workload.get_config(name)
+    arch = cfg["arch"]
+    if ids:
+        arch["sample_hi"] = arch["sample_lo"] + int(ids[0])
+        arch["vocab"] = arch["sample_hi"] + 100
+    # that the head writes z here: a context that keeps no logits has none after a step
+    o, g, _, _, _ = make_pair(oracle, cfg, n_seqs=n_seqs, kernel_flags=flags, head_alpha=6.0, std=0.08, drop_logits=True)
+    o.close()
+    g.step()
+    with pytest.raises(sjd.SjdError) as e:
+        g.logits()
+    assert e.value.code == sjd.ESTATE
+    g.close()
     o, g, cond, uncond, n_img = make_pair(oracle, cfg, n_seqs=n_seqs, kernel_flags=flags, head_alpha=6.0, std=0.08)
     o.close()
     before = g.snapshot()
@@ -293,7 +309,6 @@ def test_guidance_fused_into_the_head_is_that_of_the_logits(oracle, name, n_seqs
     assert g.step_from_logits(logits) == res
     plain = g.snapshot()
     # without the cache pages that end a snapshot: only a forward writes the window's keys and values to them
-    arch = cfg["arch"]
     tokens = [len(p) - 1 + r["n_finalized"] for ps in (cond, uncond) for p, r in zip(ps, res)]
     pages = sum(-(-t // 64) for t in tokens) * 64 * arch["n_kv_heads"] * (arch["d_model"] // arch["n_heads"]) * 2 * 2 * arch["n_layers"]
     end = len(plain) - pages

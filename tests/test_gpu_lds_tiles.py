@@ -127,3 +127,17 @@ BIG_CASES = [
 @pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens", BIG_CASES)
 def test_big_tiles_against_float64(d, heads, kv, ff, ids, window, lens):
     test_against_float64(d, heads, kv, ff, ids, window, lens)
+
+
+# Long prompts whose projections run through the tile kernels with K whole: output and down projections of 256-row tiles that
+# leave one partial sum of squares per column tile (32 of them), read by a 256 x 256 QKV and a 256-row gate/up; gains in the
+# weights (window 1) and in the rows (33).  Ragged in rows and in the MLP's columns; same bound.
+WHOLE_K_CASES = [
+    (4096, 32, 8, 5664, 3001, 1, [(1022, 1019)]),    # 2039 prompt rows
+    (4096, 32, 8, 5664, 3001, 33, [(1000, 1003)]),   # 2001
+]
+
+
+@pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens", WHOLE_K_CASES)
+def test_whole_k_tiles_against_float64(d, heads, kv, ff, ids, window, lens):
+    test_against_float64(d, heads, kv, ff, ids, window, lens)

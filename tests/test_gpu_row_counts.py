@@ -37,6 +37,7 @@ def test_rows_that_fill_no_tile(oracle, name, n_seqs, window):
     ("small_fused64", 1, 150, 140, 16),   # ... through the tile kernels, whole K
     ("small_fused128", 3, 41, 70, 0),     # 246 rows, 414 prompt rows
     ("small_tile", 5, 27, 60, 16),        # 270 rows, ragged column tiles
+    ("small_tile", 5, 27, 60, 80),        # ... in tiles of 256 rows
 ])
 def test_norm_gains_cost_no_precision(oracle, name, n_seqs, window, prompt, flags):
     """Norm gains drawn from U(0.5, 1.5), on contexts that once ran the generic GEMMs with the caller's bf16 weights and the

@@ -62,3 +62,11 @@ def test_the_big_tile_cases_reach_the_256_x_256_tiles():
     queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, 0) for d, h, kv, ff, ids, _, lens in t.BIG_CASES]
     got = [(n, p["tile"]) for p in plan_choice.choose(queries) for n in ("qkv", "gate_up") if p[n][0] == 5]
     assert got == [("gate_up", False), ("qkv", True), ("gate_up", False), ("qkv", False)], got
+
+
+def test_the_whole_k_cases_reach_the_tile_kernels_with_256_rows():
+    import test_gpu_lds_tiles as t
+    queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, 0) for d, h, kv, ff, ids, _, lens in t.WHOLE_K_CASES]
+    for p in plan_choice.choose(queries):
+        assert p["tile"] and p["qkv"][0] == 5 and p["gate_up"][0] == -1 and p["tile_splits"] == dict(out=1, down=1)
+        assert all(p["tile_rows"][n] == 256 and not p["two_heights"][n] for n in ("out", "down")), p
