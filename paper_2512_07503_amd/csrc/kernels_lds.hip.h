@@ -48,7 +48,8 @@ template <int NL> SJD_D void wait_stages(int stages) {
     }
 }
 
-// (two wavefronts per SIMD at least: the LDS of the larger shapes admits two workgroups per CU, their registers must too)
+// (two wavefronts per SIMD at least: two workgroups of the four-wavefront shapes share a CU if LDS and registers admit them, and
+// the 256 x 256 shape, whose 128 KiB of LDS admit one workgroup, has eight wavefronts)
 template <int TMT, int TNB, int WM, int WN, int S, int EPI>
 __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARAMS, int col_tiles, int row_tiles, SkinnyArgs a) {
     SJD_TILE_TAKE(a);

@@ -62,12 +62,13 @@ struct SkinnyArgs {
     bf16_t *xb;        // the same in bf16, fragment-major [M][N]
     int N;             // also the logits row length for HEAD
     // Per-row sums of squares of the input rows, as row_ssq_n partial sums per row written by the kernel that produced the
-    // rows, [row_ssq_n][M] (neighbouring lanes read neighbouring rows); NULL: taken from the activation fragments
-    // inside the k-loop
+    // rows, [row_ssq_n][M] (neighbouring lanes read neighbouring rows); NULL (row-group kernels only): taken from the
+    // activation fragments inside the k-loop
     const float *row_ssq_part;
     int row_ssq_n;
-    // RESID: where a kernel leaves such partial sums for the next one (may be NULL): one per column group of the row-group
-    // kernels, one per wavefront's columns of the LDS kernels, one per column tile of the tile kernels
+    // RESID: where a kernel leaves such partial sums for the next one (may be NULL, but not for the tile kernels): one per
+    // column group of the row-group kernels, one per wavefront's columns of the LDS kernels, one per column tile of the tile
+    // kernels
     float *ssq_out;
     // Gains in the rows: RESID multiplies gain[n] (the next norm's) into the bf16 copy of the stream, and takes ssq_out from
     // the fp32 stream; NULL: the gains are in the weights
@@ -486,10 +487,11 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
     }
 
     // ---- sum the NW partial tiles through LDS, a row tile's NBW blocks at a time: every wavefront leaves its accumulators as
-    //      vectors of the EPT elements that one thread adds (64 KiB with 8 wavefronts and two blocks, and it is these bytes
-    //      that the step's time is, not the barriers; a register at a time and a block at a time it took 1.4 us of a launch's
-    //      5.2 at 32 rows: 36 layers of 1280, window 16, 1.098 -> 1.063 ms a step, 192 rows 1.81 -> 1.78).  Accumulator register v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
-    //      column l % 32.
+    //      vectors of the EPT elements that one thread adds (64 KiB with 8 wavefronts and two blocks).  A register at a time
+    //      and a block at a time it took 1.4 us of a launch's 5.2 at 32 rows: 36 layers of 1280, window 16, 1.098 -> 1.063 ms a
+    //      step, 192 rows 1.81 -> 1.78.  LDS is busy for 256 (output, down), 690 (QKV) and 1 330 cycles (gate/up) of a workgroup
+    //      of that step, 0.1 - 0.6 us, without bank conflicts (SQ_LDS_IDX_ACTIVE, SQ_LDS_BANK_CONFLICT).
+    //      Accumulator register v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.
     typedef float red_t __attribute__((ext_vector_type(EPT)));
     __shared__ red_t red[NW][NBW][NW][64];
     __shared__ float ssq_lds[NW][MT][32];
@@ -646,7 +648,7 @@ __global__ void embed_dual_kernel(const bf16_t *__restrict__ emb, float *__restr
         t.rot[(size_t)m * half + j] = pos >= 0 ? make_float2(t.rope_cos[(size_t)pos * half + j], t.rope_sin[(size_t)pos * half + j])
                                                : make_float2(1.0f, 0.0f);
     // 8 elements a thread (d is a multiple of 32): 16 bytes of the table and of the operand copy, 32 of the stream; element by
-    // element 16 rows of 4096 took 14 us
+    // element 16 rows of 4096 took 14 us.  The sum of squares takes a thread's elements in this order, neighbours first.
     float sq = 0.0f;
     for (int i = threadIdx.x * 8; i < d; i += blockDim.x * 8) {
         u32x4 v = {0u, 0u, 0u, 0u};

@@ -23,14 +23,17 @@ constexpr int TILE_M = 256;   // rows of the larger tile of kernels_tile.hip.h
 
 // ---- LDS tiles.  Tile shapes (TMT, TNB, WM, WN, S) of kernels_lds.hip.h.  Shape 4 is the head's where a wavefront has to hold a
 // conditional and an unconditional row tile.  Shape 5 (QKV and gate/up) moves the fewest bytes per MFMA but leaves a CU to one
-// workgroup and its epilogue uncovered: it is for launches of one workgroup per CU at most.  2048 x 6144 x 4096 121 -> 107 us in
-// a forward (tile kernels before), 1000 x 12288 x 4096 108 -> 100, 1280 x 12288 135 -> 110, 2040 x 6912 x 1280 48 -> 43; with
-// several per CU it gains nothing (2048 x 28672 x 4096 434 us against 430).
+// workgroup and its epilogue uncovered: it is for launches of one workgroup per CU at most.  Kernel times in repeated prompt
+// forwards, without -> with it: 2040 x 6144 x 4096 117 -> 101 us (128-row tiles), 900 x 12288 x 4096 110 -> 104 and 1008 x 12288
+// 113 -> 106 (the same), 1280 x 12288 136 -> 113 (192 x 128), 2040 x 6912 x 1280 50 -> 42 (192 x 128); with several per CU it
+// gains nothing (2048 x 28672 x 4096 434 us against 430).
 #define SJD_LDS_TILES(X) X(0, 2, 2, 2, 1, 6) X(1, 4, 2, 4, 1, 6) X(2, 4, 4, 4, 2, 5) X(3, 6, 4, 2, 2, 4) X(4, 4, 4, 2, 2, 4) X(5, 8, 8, 2, 4, 4)
 constexpr int kLdsTiles = 4, kLdsTileHeadZ = 4, kLdsTileBig = 5;
 struct LdsTile { int tmt, tnb, cb; double t1, t2, tn; };
 // t1, t2, tn: microseconds per pipeline stage of a CU with one workgroup, with two, and per workgroup of more.  Measured on
-// models 768 to 4096 wide at 118 to 2040 rows, weights from HBM.
+// models 768 to 4096 wide at 118 to 2040 rows, weights from HBM, before the kernels had their first arguments in registers: launches
+// of up to 500 rows now take 5 to 30 % less than this says (row groups of 126 rows of 1280: 40 %), larger ones are within 13 %
+// (2040 x 3840 x 1280: 15 % more).
 inline LdsTile lds_tile(int cfg) {
     static const LdsTile t[6] = {{2, 2, 2, 0.22, 0.33, 0.14}, {4, 2, 2, 0.27, 0.45, 0.19}, {4, 4, 2, 0.38, 0.56, 0.30}, {6, 4, 2, 0.42, 0.72, 0.37},
                                  {4, 4, 2, 0.40, 0.62, 0.33}, {8, 8, 2, 0.80, 1e3, 1e3}};
@@ -145,7 +148,8 @@ inline double tile_layer_us(const ProjShape &s, int M) {
     return tile_us(M, s.qkv_groups() * 2, d / 16, 1, s.n_cus) + tile_us(M, s.d_ff / 32 * 2, d / 16, 1, s.n_cus) +
            resid(s.q_dim()) + resid(s.d_ff);
 }
-// From 256 rows on: the tile kernels where their heights fit the rows and the CUs, else the mix of LDS tiles and row groups.
+// From 256 rows on: the tile kernels where their heights fit the rows and the CUs, else the mix of LDS tiles and row groups (shape 5
+// apart: it takes its place in either afterwards).
 // Measured, prompts through 6 layers of the 4096-wide shape, ms: 260 rows 1.38 (tile kernels) against 1.19; 700 2.39 / 2.05;
 // 1000 2.62 / 2.87; 1400 4.22 / 3.97; 2040 5.28 / 5.47; 1280-wide, 16 layers: 1000 rows 2.01 / 1.69, 2040 3.18 / 2.71.
 inline bool tile_forward(const ProjShape &s, int M) {

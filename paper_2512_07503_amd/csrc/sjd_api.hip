@@ -439,8 +439,8 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     auto row_split_for = [&](int groups) { return MT == 1 && M > 16 && groups <= 64 && !(md.kernel_flags & SJD_NO_ROW_SPLIT) ? 2 : 1; };
     const Proj none = {nullptr, 0, 0, 0, false};
     const bool mixed_ok = !(md.kernel_flags & SJD_NO_MIXED_WIDTH);
-    // Many-row kernels take the RMSNorm row sums of squares from the kernel that wrote the residual stream (embedding
-    // gather or split-K reduction) instead of accumulating them in their k-loops
+    // LDS-tile and tile kernels (and row groups with the gains in the rows) take the RMSNorm row sums of squares from the kernel
+    // that wrote the residual stream: embedding gather, whole-K output / down projection or split-K reduction
     const int tile_rows = (md.kernel_flags & SJD_TILES_256_ROWS) ? 256 : 0;  // 0: chosen per launch
     int ssq_n = 1;   // partial sums per row that the last writer left; the embedding kernel wrote one
     float *ssq_out = nullptr;   // where the coming output / down projection leaves them: set if its reader takes them
