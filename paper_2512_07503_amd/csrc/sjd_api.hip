@@ -15,6 +15,7 @@
 #include "common.hip.h"
 #include "decide.h"
 #include "kernels_attention.hip.h"
+#include "kernels_f32.hip.h"
 #include "kernels_forward.hip.h"
 #include "kernels_gemm.hip.h"
 #include "kernels_skinny.hip.h"
@@ -334,6 +335,48 @@ template <typename T> int forward(sjd_ctx *c, const FwdRows &fr, bool with_head)
     return SJD_OK;
 }
 
+// fp32 path: five kernels per layer, the same sums bit for bit as forward<float> (nine), which SJD_KERNELS_REFERENCE selects.
+// 2 layers of 256, window 16, a step: 25 launches, now 17.
+int forward_f32(sjd_ctx *c, const FwdRows &fr, bool with_head) {
+    const sjd_model_desc &md = c->md;
+    const int d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd;
+    hipStream_t st = c->stream;
+    SJD_LAUNCH(c, KC_EMBED, after([&] { embed_kernel<float><<<fr.M, 256, 0, st>>>((const float *)c->tok_emb, fr.rm.row_tok, c->x, d); }));
+    F32Args a{};
+    a.M = fr.M;
+    a.eps = md.rms_eps;
+    a.rm = fr.rm;
+    a.rope_cos = c->rope_cos; a.rope_sin = c->rope_sin;
+    a.q_out = (float *)c->q;
+    a.L = fr.L; a.H = H; a.Hkv = Hkv; a.hd = hd;
+    auto gemm = [&](auto epi, int cls, const void *A, const void *W, int N, int K, const float *gain, float *out) -> int {
+        a.N = N; a.K = K; a.gain = gain; a.out = out;
+        SJD_LAUNCH(c, cls, launch_gemm_f32<decltype(epi)::value>(st, (const float *)A, (const float *)W, a));
+        return SJD_OK;
+    };
+    constexpr std::integral_constant<int, F32_QKV> kQkv{};
+    constexpr std::integral_constant<int, F32_RESID> kResid{};
+    constexpr std::integral_constant<int, F32_SWIGLU> kSwiglu{};
+    constexpr std::integral_constant<int, F32_LOGITS> kLogits{};
+    for (int l = 0; l < md.n_layers; ++l) {
+        const LayerWeights &lw = c->layers[l];
+        KvPool &pool = a.pool;
+        pool.k = (char *)c->kpool + c->pool_layer_bytes * l;
+        pool.v = (char *)c->vpool + c->pool_layer_bytes * l;
+        pool.page_table = c->page_table;
+        pool.pages_per_seg = c->pps;
+        pool.page_tokens = c->pt;
+        int rc = gemm(kQkv, KC_GEMM_QKV, c->x, lw.wqkv, (H + 2 * Hkv) * hd, d, lw.attn_norm, nullptr);
+        if (rc) return rc;
+        if (!with_head && l + 1 == md.n_layers) return SJD_OK;
+        if ((rc = run_attention<float>(c, pool, fr))) return rc;
+        if ((rc = gemm(kResid, KC_GEMM_O, c->attn, lw.wo, d, H * hd, nullptr, c->x))) return rc;
+        if ((rc = gemm(kSwiglu, KC_GEMM_GATEUP, c->x, lw.wgu, 2 * md.d_ff, d, lw.mlp_norm, (float *)c->h))) return rc;
+        if ((rc = gemm(kResid, KC_GEMM_DOWN, c->h, lw.wdown, d, md.d_ff, nullptr, c->x))) return rc;
+    }
+    return with_head ? gemm(kLogits, KC_GEMM_HEAD, c->x, c->lm_head, c->Vs, d, c->final_norm, c->logits) : SJD_OK;
+}
+
 // Small-M bf16 path: five kernels per layer (QKV+RoPE+KV write, attention, out+residual, gate/up+SwiGLU,
 // down+residual); c->xn holds the bf16 copy of the residual stream.
 int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
@@ -620,7 +663,8 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
 
 int forward_any(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     if (c->fused) return forward_fused(c, fr, with_head);
-    return c->md.dtype == SJD_F32 ? forward<float>(c, fr, with_head) : forward<bf16_t>(c, fr, with_head);
+    if (c->md.dtype == SJD_F32) return c->md.kernel_flags & SJD_KERNELS_REFERENCE ? forward<float>(c, fr, with_head) : forward_f32(c, fr, with_head);
+    return forward<bf16_t>(c, fr, with_head);
 }
 
 // ------------------------------------------------------------------------------------------ create
@@ -754,7 +798,7 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
     c->page_table = c->pre_dev;
     // workspaces
     if ((rc = dev_alloc(c, &c->x, (size_t)M * d * sizeof(float)))) return rc;
-    if (!c->fused) {   // the generic path's GEMM outputs, with their K splits
+    if (!c->fused && (md.dtype == SJD_BF16 || (md.kernel_flags & SJD_KERNELS_REFERENCE))) {   // the generic path's GEMM outputs, with their K splits
         const int shapes[4][2] = {{Nqkv, d}, {d, H * hd}, {2 * F, d}, {d, F}};
         for (auto &s : shapes) {
             size_t need = (size_t)M * s[0];
