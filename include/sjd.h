@@ -185,9 +185,8 @@ int sjd_prefill(sjd_ctx *ctx, int32_t n_seqs, const int32_t *const *cond_ids, co
  * Steps 1-4).  out is a HOST array of n_seqs results.  The call returns after
  * the step has completed on the device.  Sequences that are done are left
  * untouched (n_finalized = 0, done = 1).  Errors: SJD_ESTATE (no prefill) and
- * SJD_EINVAL (null argument), before anything ran; SJD_EDEVICE: a launch, the
- * device or the download of the verdicts failed, and the step may have run in
- * part or whole: go on from sjd_prefill or sjd_snapshot_restore. */
+ * SJD_EINVAL (null argument), before anything ran; SJD_EDEVICE: a launch or
+ * the device failed, and the step may have run in part or whole: go on from sjd_prefill or sjd_snapshot_restore. */
 int sjd_step(sjd_ctx *ctx, sjd_step_result *out);
 
 /* Frees everything the context owns.  NULL is allowed. */

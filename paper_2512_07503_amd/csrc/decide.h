@@ -44,6 +44,7 @@ struct DecideState {
     // sample_lo); every other id has probability 0 there.  [S][max_img]; the whole range by default.
     int32_t *allow_lo, *allow_hi;
     sjd_step_result *res; // [S]
+    sjd_step_result *res_host; // [S] the same in pinned host memory (every device writes to it directly): no copy behind a step
 };
 
 struct SamplingParams {
@@ -80,12 +81,35 @@ __host__ __device__ inline void row_place(const RowMap &rm, int L, int m, int &s
     }
 }
 
+// A step's rows, worked out from the decoding state by the kernel that gathers their embeddings (one workgroup per row), which
+// writes the row map for the kernels behind it: one launch less a step than a staging kernel of its own.
+struct StageRows {
+    const int32_t *Le, *kv_len, *anchor, *win_tok;   // DecideState; Le NULL: the rows are there already
+    int32_t *acc_len;
+    uint32_t *step;
+    int32_t *row_tok, *row_pos, *seg_kv, *seg_n;     // the row map
+    int L;
+};
+// token (-1: inactive) and position of row m; `write`: this thread writes what the kernels behind read
+__device__ inline void stage_row_of(const StageRows &t, int m, bool write, int &tok, int &pos) {
+    const int k = m % t.L, seg = m / t.L, s = seg >> 1;
+    const int Le = t.Le[s], kv = t.kv_len[seg];
+    tok = k < Le ? (k == 0 ? t.anchor[seg] : t.win_tok[s * t.L + k]) : -1;
+    pos = kv + k;
+    if (!write) return;
+    if (m == 0) *t.step += 1u;
+    t.row_tok[m] = tok;
+    t.row_pos[m] = pos;
+    if (k == 0) { t.seg_kv[seg] = kv; t.seg_n[seg] = Le; }
+    if (k == 0 && (seg & 1) == 0) t.acc_len[s] = Le - 1;   // "every draft accepted" until the verification finds a rejection
+}
+
 hipError_t launch_init_window(hipStream_t st, const DecideState &d, const SamplingParams &sp, int n_seqs, int max_seqs,
                               const int32_t *prompt_last /*[S][2]*/, const int32_t *prompt_len /*[S][2]*/,
                               const int32_t *n_image /*[S]*/);
-// writes the row map of a decoding step; row_tok, row_pos [n_seqs * 2 * L], seg_kv, seg_n [n_seqs * 2]
-hipError_t launch_stage_window(hipStream_t st, const DecideState &d, int32_t *row_tok, int32_t *row_pos, int32_t *seg_kv,
-                               int32_t *seg_n, int n_seqs);
+// writes the row map of a decoding step whose logits are there already; row_tok, row_pos [n_seqs * 2 * L], seg_kv, seg_n [n_seqs * 2]
+StageRows stage_rows(const DecideState &d, int32_t *row_tok, int32_t *row_pos, int32_t *seg_kv, int32_t *seg_n);
+hipError_t launch_stage_window(hipStream_t st, const StageRows &t, int n_seqs);
 // logits: [n_seqs][2][L][V]; z (may be NULL): the guided logits [n_seqs][L][V] already combined by the vocabulary head,
 // read instead of the logits
 hipError_t launch_sample_rows(hipStream_t st, const DecideState &d, const SamplingParams &sp, const float *logits,

@@ -504,18 +504,11 @@ __global__ void init_window_kernel(DecideState d, uint64_t seed, int n_seqs, con
     }
 }
 
-// Rows of the coming forward over the window; also advances the step counter.
-__global__ void stage_window_kernel(DecideState d, int32_t *row_tok, int32_t *row_pos, int32_t *seg_kv, int32_t *seg_n, int n_seqs) {
+// Rows of the coming step over the window; also advances the step counter.
+__global__ void stage_window_kernel(StageRows t, int n_rows) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m == 0) *d.step += 1u;
-    if (m >= n_seqs * 2 * d.L) return;
-    const int k = m % d.L, seg = m / d.L, s = seg >> 1;
-    const int Le = d.Le[s];
-    const int kv = d.kv_len[seg];
-    row_tok[m] = k < Le ? (k == 0 ? d.anchor[seg] : d.win_tok[s * d.L + k]) : -1;
-    row_pos[m] = kv + k;
-    if (k == 0) { seg_kv[seg] = kv; seg_n[seg] = Le; }
-    if (k == 0 && (seg & 1) == 0) d.acc_len[s] = Le - 1;   // "every draft accepted" until the verification finds a rejection
+    int tok, pos;
+    if (m < n_rows) stage_row_of(t, m, true, tok, pos);
 }
 
 constexpr int kRefUniform = -1, kRefOneHot = -2, kRefHist0 = -3;  // values of ref_row below 0 (<= -3: kept row -3 - ref)
@@ -597,7 +590,7 @@ SJD_D uint64_t wave_row_weight(const RowRef &r, int x, int lane) {
 
 // ------------------------------------------------------------------- a11: verification (Eq. 2)
 // One wavefront per draft (4 per block, grid.y = sequence): all drafts are tested in parallel and the first rejection
-// is the minimum over the rejected ones.  stage_window_kernel has set acc_len[s] = Le - 1 (no rejection).
+// is the minimum over the rejected ones.  the staging of the rows has set acc_len[s] = Le - 1 (no rejection).
 __global__ __launch_bounds__(256) void verify_kernel(DecideState d, uint64_t seed, int row_width) {
     const int s = blockIdx.y, L = d.L, lane = threadIdx.x & 63;
     const int k = 1 + blockIdx.x * 4 + (threadIdx.x >> 6);   // draft in slot k against row k - 1
@@ -800,9 +793,12 @@ __global__ void draw_kernel(DecideState d, uint64_t seed, float tau, int rows_pe
 __global__ void commit_kernel(DecideState d, uint64_t seed, int init_mode, int row_width) {
     const int s = blockIdx.x, L = d.L;
     const int Le = d.Le[s];
-    sjd_step_result *res = d.res + s;
+    auto verdict = [&](const sjd_step_result &r) {
+        d.res[s] = r;
+        d.res_host[s] = r;
+    };
     if (Le == 0) {
-        if (threadIdx.x == 0) { res->n_accepted = 0; res->n_finalized = 0; res->reject_index = -1; res->done = 1; }
+        if (threadIdx.x == 0) verdict({0, 0, -1, 1});
         return;
     }
     const uint32_t step = *d.step;
@@ -873,10 +869,7 @@ __global__ void commit_kernel(DecideState d, uint64_t seed, int init_mode, int r
         d.anchor[s * 2] = y;
         d.anchor[s * 2 + 1] = y;
         d.Le[s] = Le2;  // 0 when the image is complete
-        res->n_accepted = a;
-        res->n_finalized = a + 1;
-        res->reject_index = a < Le - 1 ? a + 1 : -1;
-        res->done = remaining == 0 ? 1 : 0;
+        verdict({a, a + 1, a < Le - 1 ? a + 1 : -1, remaining == 0 ? 1 : 0});
     }
 }
 
@@ -916,10 +909,12 @@ hipError_t launch_init_window(hipStream_t st, const DecideState &d, const Sampli
     return hipGetLastError();
 }
 
-hipError_t launch_stage_window(hipStream_t st, const DecideState &d, int32_t *row_tok, int32_t *row_pos, int32_t *seg_kv,
-                               int32_t *seg_n, int n_seqs) {
-    const int M = n_seqs * 2 * d.L;
-    stage_window_kernel<<<ceil_div(M, 256), 256, 0, st>>>(d, row_tok, row_pos, seg_kv, seg_n, n_seqs);
+StageRows stage_rows(const DecideState &d, int32_t *row_tok, int32_t *row_pos, int32_t *seg_kv, int32_t *seg_n) {
+    return {d.Le, d.kv_len, d.anchor, d.win_tok, d.acc_len, d.step, row_tok, row_pos, seg_kv, seg_n, d.L};
+}
+hipError_t launch_stage_window(hipStream_t st, const StageRows &t, int n_seqs) {
+    const int M = n_seqs * 2 * t.L;
+    stage_window_kernel<<<ceil_div(M, 256), 256, 0, st>>>(t, M);
     return hipGetLastError();
 }
 

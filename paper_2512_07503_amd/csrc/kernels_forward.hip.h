@@ -9,9 +9,11 @@
 #include "decide.h"
 
 template <typename T>
-__global__ void embed_kernel(const T *__restrict__ emb, const int32_t *__restrict__ row_tok, float *__restrict__ x, int d) {
+__global__ void embed_kernel(const T *__restrict__ emb, const int32_t *__restrict__ row_tok, float *__restrict__ x, int d, StageRows stage) {
     const int m = blockIdx.x;
-    const int tok = row_tok[m];
+    int tok, pos;
+    if (stage.Le) stage_row_of(stage, m, threadIdx.x == 0, tok, pos);
+    else tok = row_tok[m];
     for (int i = threadIdx.x; i < d; i += blockDim.x) x[(size_t)m * d + i] = tok >= 0 ? to_float<T>(emb[(size_t)tok * d + i]) : 0.0f;
 }
 

@@ -624,12 +624,19 @@ struct RowTables {
     float2 *rot;
     float *ssq_part;   // [M] sum of squares of the row
     const float *gain; // [d] multiplied into the bf16 copy (may be NULL)
+    StageRows stage;
 };
 __global__ void embed_dual_kernel(const bf16_t *__restrict__ emb, float *__restrict__ x, bf16_t *__restrict__ xb, int d, RowTables t) {
     const int m = blockIdx.x;
-    const int tok = t.rm.row_tok[m];
     const int half = t.hd >> 1;
-    const int pos = tok >= 0 ? t.rm.row_pos[m] : -1;
+    int tok, pos;
+    if (t.stage.Le) {
+        stage_row_of(t.stage, m, threadIdx.x == 0, tok, pos);
+    } else {
+        tok = t.rm.row_tok[m];
+        pos = t.rm.row_pos[m];
+    }
+    if (tok < 0) pos = -1;
     if (threadIdx.x == 0) {
         QkvRow r;
         r.pos = pos; r.q_off = 0; r.page = 0; r.k_off = 0; r.v_off = 0;

@@ -63,6 +63,7 @@ struct FwdRows {
     int L = 0;       // rows per segment; 0: packed
     int n_qt = 0;    // query tiles of 32 rows of the longest segment
     RowMap rm{};
+    StageRows stage{};   // a step's rows are worked out by the embedding kernel
 };
 
 // Rows of a prefill forward at most.  A prompt's forward is as wide as the prompts allow, not as the window: 120 prompt
@@ -288,7 +289,7 @@ template <typename T> int forward(sjd_ctx *c, const FwdRows &fr, bool with_head)
     const int M = fr.M, d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd, F = md.d_ff;
     const int Nqkv = (H + 2 * Hkv) * hd;
     hipStream_t st = c->stream;
-    SJD_LAUNCH(c, KC_EMBED, after([&] { embed_kernel<T><<<M, 256, 0, st>>>((const T *)c->tok_emb, fr.rm.row_tok, c->x, d); }));
+    SJD_LAUNCH(c, KC_EMBED, after([&] { embed_kernel<T><<<M, 256, 0, st>>>((const T *)c->tok_emb, fr.rm.row_tok, c->x, d, fr.stage); }));
     int down_splits = 0;
     for (int l = 0; l < md.n_layers; ++l) {
         const LayerWeights &lw = c->layers[l];
@@ -341,7 +342,7 @@ int forward_f32(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     const sjd_model_desc &md = c->md;
     const int d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd;
     hipStream_t st = c->stream;
-    SJD_LAUNCH(c, KC_EMBED, after([&] { embed_kernel<float><<<fr.M, 256, 0, st>>>((const float *)c->tok_emb, fr.rm.row_tok, c->x, d); }));
+    SJD_LAUNCH(c, KC_EMBED, after([&] { embed_kernel<float><<<fr.M, 256, 0, st>>>((const float *)c->tok_emb, fr.rm.row_tok, c->x, d, fr.stage); }));
     F32Args a{};
     a.M = fr.M;
     a.eps = md.rms_eps;
@@ -395,6 +396,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
                    rt.L = fr.L; rt.H = H; rt.hd = hd; rt.meta = c->row_meta; rt.rot = c->row_rot;
                    rt.ssq_part = c->row_ssq;
                    rt.gain = c->layers[0].attn_norm;
+                   rt.stage = fr.stage;
                    embed_dual_kernel<<<M, 256, 0, st>>>((const bf16_t *)c->tok_emb, c->x, (bf16_t *)c->xn, d, rt);
                }));
     SkinnyArgs a;
@@ -899,8 +901,9 @@ int alloc_state(sjd_ctx *c) {
     if ((rc = dev_alloc(c, &d.allow_lo, (size_t)S * d.max_img * 4))) return rc;
     if ((rc = dev_alloc(c, &d.allow_hi, (size_t)S * d.max_img * 4))) return rc;
     if ((rc = dev_alloc(c, &d.res, (size_t)S * sizeof(sjd_step_result)))) return rc;
-    hipError_t e = hipHostMalloc((void **)&c->res_host, (size_t)S * sizeof(sjd_step_result), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void **)&c->res_host, (size_t)S * sizeof(sjd_step_result), hipHostMallocMapped | hipHostMallocCoherent);
     if (e != hipSuccess) { sjd_set_error(c->err, "hipHostMalloc failed: %s", hipGetErrorString(e)); return SJD_ENOMEM; }
+    d.res_host = c->res_host;   // (host and device share the address)
     return SJD_OK;
 }
 
@@ -963,9 +966,7 @@ int run_decide(sjd_ctx *c, bool from_logits) {
 }
 
 int finish_step(sjd_ctx *c, sjd_step_result *out) {
-    SJD_HIP_TRY(c->err, hipMemcpyAsync(c->res_host, c->ds.res, (size_t)c->n_seqs * sizeof(sjd_step_result), hipMemcpyDeviceToHost,
-                                       c->stream));
-    SJD_HIP_TRY(c->err, hipStreamSynchronize(c->stream));
+    SJD_HIP_TRY(c->err, hipStreamSynchronize(c->stream));   // the verdicts are in host memory then
     trace_collect(c);
     bool all = true;
     for (int s = 0; s < c->n_seqs; ++s) {
@@ -980,8 +981,8 @@ int finish_step(sjd_ctx *c, sjd_step_result *out) {
 
 // everything one decoding step launches, in stream order (the host reads the verdicts back afterwards)
 int enqueue_step(sjd_ctx *c) {
-    SJD_LAUNCH(c, KC_STAGE, launch_stage_window(c->stream, c->ds, c->win_row_tok, c->win_row_pos, c->win_seg_kv, c->win_seg_n, c->n_seqs));
     FwdRows fr;
+    fr.stage = stage_rows(c->ds, c->win_row_tok, c->win_row_pos, c->win_seg_kv, c->win_seg_n);
     fr.n_segs = c->n_seqs * 2;
     fr.L = c->L;
     fr.M = fr.n_segs * c->L;
@@ -1280,7 +1281,7 @@ int sjd_debug_step_from_logits(sjd_ctx *c, const float *logits_host, sjd_step_re
     if (!c->prefilled) { sjd_set_error(c->err, "step before sjd_prefill"); return SJD_ESTATE; }
     SJD_HIP_TRY(c->err, hipMemcpyAsync(c->logits, logits_host, (size_t)c->n_seqs * 2 * c->L * c->Vs * sizeof(float),
                                        hipMemcpyHostToDevice, c->stream));
-    SJD_LAUNCH(c, KC_STAGE, launch_stage_window(c->stream, c->ds, c->win_row_tok, c->win_row_pos, c->win_seg_kv, c->win_seg_n, c->n_seqs));
+    SJD_LAUNCH(c, KC_STAGE, launch_stage_window(c->stream, stage_rows(c->ds, c->win_row_tok, c->win_row_pos, c->win_seg_kv, c->win_seg_n), c->n_seqs));
     int rc = run_decide(c, true);
     if (rc) return rc;
     return finish_step(c, out);
