@@ -123,22 +123,42 @@ SJD_D uint64_t block_sum_u64(uint64_t v, uint64_t *scratch /* >= 17 entries */) 
     return scratch[16];
 }
 
-SJD_D uint32_t block_max_u32(uint32_t v, uint32_t *scratch /* >= 17 */) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+// 16 wavefronts; every wavefront reduces the 16 maxima itself (a thread's loop over them was 16 dependent steps and a barrier)
+SJD_D uint32_t block_max_u32(uint32_t v, uint32_t *scratch /* >= 16 */) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int d = 32; d > 0; d >>= 1) {
-        uint32_t o = __shfl_down(v, d, 64);
+        uint32_t o = __shfl_xor(v, d, 64);
         v = o > v ? o : v;
     }
-    __syncthreads();
     if (lane == 0) scratch[wave] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t t = 0;
-        for (int i = 0; i < nw; ++i) t = scratch[i] > t ? scratch[i] : t;
-        scratch[16] = t;
+    v = scratch[lane & 15];
+    for (int d = 8; d > 0; d >>= 1) {
+        uint32_t o = __shfl_xor(v, d, 64);
+        v = o > v ? o : v;
     }
-    __syncthreads();
-    return scratch[16];
+    return v;
+}
+
+// Sum over the 16 wavefronts of wsum[] before this one, and over all of them
+SJD_D uint32_t waves_before(const uint32_t *wsum, int lane, int wave, uint32_t &total) {
+    uint32_t v = wsum[lane & 15];
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+        const uint32_t o = __shfl_up(v, d, 16);
+        if ((lane & 15) >= d) v += o;
+    }
+    total = __shfl(v, 15, 64);
+    return wave ? (uint32_t)__shfl(v, wave - 1, 64) : 0u;
+}
+
+SJD_D uint32_t wave_inclusive_sum(uint32_t v, int lane) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = __shfl_up(v, d, 64);
+        if (lane >= d) v += o;
+    }
+    return v;
 }
 
 // ------------------------------------------------------------------ a10: the sampling distribution
@@ -184,16 +204,11 @@ SJD_D void find_bin(const uint32_t *hist, uint32_t want, uint32_t *wsum /* [16] 
                     uint32_t &before) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t c0 = hist[2 * tid], c1 = hist[2 * tid + 1], mine = c0 + c1;
-    uint32_t incl = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-    }
+    const uint32_t incl = wave_inclusive_sum(mine, lane);
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
-    uint32_t excl = incl - mine;
-    for (int w = 0; w < wave; ++w) excl += wsum[w];
+    uint32_t total;
+    const uint32_t excl = incl - mine + waves_before(wsum, lane, wave, total);
     if (excl < want && want <= excl + mine) {   // exactly one thread
         const bool first = want <= excl + c0;
         out[0] = 2 * tid + (first ? 0 : 1);
@@ -204,6 +219,77 @@ SJD_D void find_bin(const uint32_t *hist, uint32_t want, uint32_t *wsum /* [16] 
     before = out[1];
     __syncthreads();   // out and wsum may be reused
 }
+
+// The `want`-th largest of the block's keys (0: none), NPT a thread; kmax: the largest
+template <int NPT>
+SJD_D uint32_t kth_key(const uint32_t (&key)[NPT], uint32_t want, uint32_t kmax, uint32_t *hist, uint32_t *wsum, uint32_t *sel) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    // round 0: bins of the key distance to the maximum, 2^17 keys each
+    hist[2 * tid] = 0u;
+    hist[2 * tid + 1] = 0u;
+    __syncthreads();
+    uint32_t n_far = 0;   // wave-uniform
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+        const uint32_t b = (kmax - key[i]) >> kBin0Shift;
+        if (key[i] && b < (uint32_t)(kSelBins - 1)) atomicAdd(&hist[b], 1u);
+        // everything further away (half of a row: the negative logits) shares the last bin: counted per wavefront
+        n_far += (uint32_t)__popcll(__ballot(key[i] && b >= (uint32_t)(kSelBins - 1)));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (lane == 0 && n_far) atomicAdd(&hist[kSelBins - 1], n_far);
+    __syncthreads();
+    uint32_t bin, before;
+    find_bin(hist, want, wsum, sel, bin, before);
+    want -= before;                               // rank of the K-th largest among the keys of that bin, from the top
+    uint32_t hi = kmax - (bin << kBin0Shift);     // a bin is a range of keys: (hi - 2^17, hi], the last one [1, hi]
+    uint32_t lo = bin < (uint32_t)(kSelBins - 1) && hi > (1u << kBin0Shift) ? hi - ((1u << kBin0Shift) - 1u) : 1u;
+    // rounds 1+: equal bins over [lo, hi], counted from the top
+    for (int round = 0; round < 4 && lo != hi; ++round) {   // block-uniform; three rounds exhaust 32 bits
+        const uint32_t span = hi - lo;
+        const int width = 32 - __builtin_clz(span);          // bits of span
+        const int shift = width > 11 ? width - 11 : 0;       // (span >> shift) < 2048
+        hist[2 * tid] = 0u;
+        hist[2 * tid + 1] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NPT; ++i)
+            if (key[i] >= lo && key[i] <= hi) atomicAdd(&hist[kSelBins - 1 - ((key[i] - lo) >> shift)], 1u);
+        __syncthreads();
+        find_bin(hist, want, wsum, sel, bin, before);
+        want -= before;
+        const uint32_t nlo = lo + ((uint32_t)(kSelBins - 1 - bin) << shift);
+        uint32_t nhi = nlo + ((1u << shift) - 1u);
+        if (nhi < nlo || nhi > hi) nhi = hi;
+        lo = nlo;
+        hi = nhi;
+    }
+    return lo;
+}
+
+// Slots of the keys at or above `thresh` (1 at least), in the order (i, wavefront, lane): base[i * 16 + wavefront] = slots before
+// that wavefront's i-th keys; returns their number.  Ends with a barrier.
+template <int NPT>
+SJD_D uint32_t ordered_slots(const uint32_t (&key)[NPT], uint32_t thresh, uint32_t *base /* [NPT * 16] */, uint32_t *wsum) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+        const uint32_t c = (uint32_t)__popcll(__ballot(key[i] >= thresh));
+        if (lane == 0) base[i * 16 + wave] = c;
+        __builtin_amdgcn_sched_barrier(0);   // (no masks of several indices at a time: they would not fit the scalar registers)
+    }
+    __syncthreads();
+    const uint32_t mine = tid < NPT * 16 ? base[tid] : 0u;
+    const uint32_t incl = wave_inclusive_sum(mine, lane);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t total;
+    const uint32_t excl = incl - mine + waves_before(wsum, lane, wave, total);
+    if (tid < NPT * 16) base[tid] = excl;
+    __syncthreads();
+    return total;
+}
+SJD_D uint32_t lanes_before(uint64_t mask, int lane) { return (uint32_t)__popcll(mask & ((1ull << lane) - 1ull)); }
 
 template <int VPT>
 __global__ __launch_bounds__(1024) void sample_rows_sparse_kernel(SampleRowsArgs a) {
@@ -232,110 +318,118 @@ __global__ __launch_bounds__(1024) void sample_rows_sparse_kernel(SampleRowsArgs
     // The loads are unconditional (index clamped to the row) and issued in batches: a load under `if (v < V)` is
     // waited for inside its branch, and a thread would pay one memory round trip per element.
     constexpr int kBatch = VPT < 16 ? VPT : 16;
+    // (the row's pointer is uniform: a load then needs one register for its place, not two)
+    auto at = [](const float *row, uint32_t i) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + i * 4u); };
     const float *zrow = a.z_base ? a.z_base + row * V : nullptr;   // block-uniform
+    auto take = [&](int i, float z) {
+        const uint32_t kk = order_key(z);
+        key[i] = (uint32_t)(tid + i * 1024 - alo) < (uint32_t)(ahi - alo) ? kk : 0u;
+        kmax = key[i] > kmax ? key[i] : kmax;
+    };
+    auto place = [&](int i) { const int v = tid + i * 1024; return (uint32_t)(v < V ? v : V - 1); };
+    if (zrow) {   // one uniform branch around all batches: a branch per load would make each wait for its data
 #pragma unroll
-    for (int i0 = 0; i0 < VPT; i0 += kBatch) {
-        float c[kBatch], u[kBatch];
-        if (zrow) {   // one uniform branch around a whole batch: a branch per load would make each wait for its data
+        for (int i0 = 0; i0 < VPT; i0 += kBatch) {
+            float c[kBatch];
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                const int v = tid + (i0 + j) * 1024;
-                c[j] = zrow[v < V ? v : V - 1];
-                u[j] = 0.0f;
-            }
-        } else {
+            for (int j = 0; j < kBatch; ++j) c[j] = at(zrow, place(i0 + j));
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                const int v = tid + (i0 + j) * 1024, vv = v < V ? v : V - 1;
-                c[j] = lc[vv];
-                u[j] = lu[vv];
-            }
+            for (int j = 0; j < kBatch; ++j) take(i0 + j, c[j]);
+            __builtin_amdgcn_sched_barrier(0);   // one batch of loads in flight at a time: the keys need the registers
         }
+    } else {
+        constexpr int kHalf = kBatch / 2;
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const int i = i0 + j, v = tid + i * 1024;
-            const uint32_t kk = order_key(zrow ? c[j] : guided(c[j], u[j], a.cfg_scale, a.inv_t));
-            key[i] = (uint32_t)(v - alo) < (uint32_t)(ahi - alo) ? kk : 0u;
-            kmax = key[i] > kmax ? key[i] : kmax;
+        for (int i0 = 0; i0 < VPT; i0 += kHalf) {
+            float c[kHalf], u[kHalf];
+#pragma unroll
+            for (int j = 0; j < kHalf; ++j) {
+                c[j] = at(lc, place(i0 + j));
+                u[j] = at(lu, place(i0 + j));
+            }
+#pragma unroll
+            for (int j = 0; j < kHalf; ++j) take(i0 + j, guided(c[j], u[j], a.cfg_scale, a.inv_t));
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);   // one batch of loads in flight at a time: the keys need the registers
     }
     kmax = block_max_u32(kmax, scratch32);
     const float m = key_to_float(kmax);
 
-    uint32_t thresh = 1u;   // every candidate
-    if (a.top_k < ahi - alo) {
-        // round 0: bins of the key distance to the maximum, 2^17 keys each
-        hist[2 * tid] = 0u;
-        hist[2 * tid + 1] = 0u;
-        __syncthreads();
-        uint32_t n_far = 0;   // wave-uniform
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-            const uint32_t b = (kmax - key[i]) >> kBin0Shift;
-            if (key[i] && b < (uint32_t)(kSelBins - 1)) atomicAdd(&hist[b], 1u);
-            // everything further away (half of a row: the negative logits) shares the last bin: counted per wavefront
-            n_far += (uint32_t)__popcll(__ballot(key[i] && b >= (uint32_t)(kSelBins - 1)));
-        }
-        if (lane == 0 && n_far) atomicAdd(&hist[kSelBins - 1], n_far);
-        __syncthreads();
-        uint32_t bin, before;
-        find_bin(hist, (uint32_t)a.top_k, wsum, sel, bin, before);
-        uint32_t want = (uint32_t)a.top_k - before;   // rank of the K-th largest among the keys of that bin, from the top
-        uint32_t hi = kmax - (bin << kBin0Shift);     // a bin is a range of keys: (hi - 2^17, hi], the last one [1, hi]
-        uint32_t lo = bin < (uint32_t)(kSelBins - 1) && hi > (1u << kBin0Shift) ? hi - ((1u << kBin0Shift) - 1u) : 1u;
-        // rounds 1+: equal bins over [lo, hi], counted from the top
-        for (int round = 0; round < 4 && lo != hi; ++round) {   // block-uniform; three rounds exhaust 32 bits
-            const uint32_t span = hi - lo;
-            const int width = 32 - __builtin_clz(span);          // bits of span
-            const int shift = width > 11 ? width - 11 : 0;       // (span >> shift) < 2048
+    __shared__ uint32_t base[VPT * 16];
+    // Rows of many ids: the K kept ones are a few percent, and what follows took 64 steps a thread, each with something to do.  The
+    // keys above a bound that 1024 of them (one a thread, spread over the ids) suggest are moved together first, in id order; if
+    // they turn out to be the K largest at least and fit, the rest works on them, six a thread, else on all.  The result is the
+    // same.  The bound: rank 1.5 x K / V of the sample and 12 more, some three standard deviations above what K needs.  32 rows of
+    // 65 536 ids, K = 2000: 46.2 -> 25.4 us a launch; 16 rows of 16 384, K = 1000: 19.0 -> 17.6 (the sums over the wavefronts, which
+    // no longer run one by one, included).
+    if constexpr (VPT >= 16) {
+        constexpr int kCand = 6 * 1024;
+        __shared__ uint32_t cand_key[kCand], cand_id[kCand];
+        const uint32_t rank = (uint32_t)((long)a.top_k * 1536 / (ahi - alo > 0 ? ahi - alo : 1)) + 12u;
+        if (a.top_k < ahi - alo && rank < 256u && alo == 0 && ahi == V) {   // block-uniform
+            const int sid = tid + 1024 * ((tid ^ (tid >> 6)) & (VPT - 1)), sv = sid < V ? sid : V - 1;
+            const uint32_t sample = order_key(zrow ? zrow[sv] : guided(lc[sv], lu[sv], a.cfg_scale, a.inv_t));
             hist[2 * tid] = 0u;
             hist[2 * tid + 1] = 0u;
             __syncthreads();
-#pragma unroll
-            for (int i = 0; i < VPT; ++i)
-                if (key[i] >= lo && key[i] <= hi) atomicAdd(&hist[kSelBins - 1 - ((key[i] - lo) >> shift)], 1u);
+            const uint32_t b = (kmax - sample) >> kBin0Shift;
+            atomicAdd(&hist[b < (uint32_t)(kSelBins - 1) ? b : kSelBins - 1], 1u);
             __syncthreads();
-            find_bin(hist, want, wsum, sel, bin, before);
-            want -= before;
-            const uint32_t nlo = lo + ((uint32_t)(kSelBins - 1 - bin) << shift);
-            uint32_t nhi = nlo + ((1u << shift) - 1u);
-            if (nhi < nlo || nhi > hi) nhi = hi;
-            lo = nlo;
-            hi = nhi;
+            uint32_t bin, before;
+            find_bin(hist, rank, wsum, sel, bin, before);
+            const uint32_t off = (bin + 1u) << kBin0Shift;   // (2048 x 2^17 = 2^28: no overflow)
+            uint32_t bound = bin < (uint32_t)(kSelBins - 1) && kmax > off ? kmax - off + 1u : 1u;   // the bin's lowest key
+            bound = __builtin_amdgcn_readfirstlane(bound);
+            const uint32_t n_cand = ordered_slots(key, bound, base, wsum);
+            asm volatile("" : "+s"(bound));   // (as below: nothing is carried from the counting pass in registers)
+            int tid_again = tid;
+            asm volatile("" : "+v"(tid_again));
+            if (n_cand >= (uint32_t)a.top_k && n_cand <= (uint32_t)kCand) {   // block-uniform
+#pragma unroll
+                for (int i = 0; i < VPT; ++i) {
+                    const bool take = key[i] >= bound;
+                    const uint64_t mask = __ballot(take);
+                    if (take) {
+                        const uint32_t pos = base[i * 16 + wave] + lanes_before(mask, lane);
+                        cand_key[pos] = key[i];
+                        cand_id[pos] = (uint32_t)(tid_again + i * 1024);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __syncthreads();
+                uint32_t ck[6];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) ck[j] = (uint32_t)(tid + j * 1024) < n_cand ? cand_key[tid + j * 1024] : 0u;
+                const uint32_t thresh = kth_key(ck, (uint32_t)a.top_k, kmax, hist, wsum, sel);
+                const uint32_t n_kept = ordered_slots(ck, thresh, base, wsum);
+                if (tid == 0) a.cnt_base[par][row] = (int32_t)n_kept;
+                uint64_t zsum = 0;
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {
+                    const bool keep = ck[j] >= thresh;
+                    const uint64_t mask = __ballot(keep);
+                    if (keep) {
+                        const uint32_t pos = base[j * 16 + wave] + lanes_before(mask, lane);
+                        const float ev = exp_neg(key_to_float(ck[j]) - m);
+                        ids[pos] = (int32_t)cand_id[tid + j * 1024];
+                        e[pos] = ev;
+                        zsum += weight_of(ev);
+                    }
+                }
+                zsum = block_sum_u64(zsum, scratch64);
+                if (tid == 0) a.Z_base[par][row] = zsum;
+                return;
+            }
         }
-        thresh = lo;
     }
 
-    // kept pairs in ascending id order: id = tid + 1024 i, so (i, wave, lane) ascending.  Every wavefront counts its
-    // kept ids per i; a prefix sum over the (i, wave) counts gives each wavefront's first output slot.
-    __shared__ uint32_t base[VPT * 16];
-    {
-        uint32_t count_i = 0;   // lane i of a wavefront ends up with the wavefront's count for index i (VPT <= 64)
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-            const uint32_t c = (uint32_t)__popcll(__ballot(key[i] >= thresh && key[i] != 0u));
-            count_i = lane == i ? c : count_i;
-        }
-        if (lane < VPT) base[lane * 16 + wave] = count_i;
-    }
-    __syncthreads();
-    {
-        const uint32_t mine = tid < VPT * 16 ? base[tid] : 0u;
-        uint32_t incl = mine;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t o = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += o;
-        }
-        if (lane == 63) wsum[wave] = incl;
-        __syncthreads();
-        uint32_t excl = incl - mine;
-        for (int w = 0; w < wave; ++w) excl += wsum[w];
-        if (tid < VPT * 16) base[tid] = excl;
-        if (tid == VPT * 16 - 1) a.cnt_base[par][row] = (int32_t)(excl + mine);
-        __syncthreads();
-    }
+    uint32_t thresh = 1u;   // every candidate
+    if (a.top_k < ahi - alo) thresh = kth_key(key, (uint32_t)a.top_k, kmax, hist, wsum, sel);
+    thresh = __builtin_amdgcn_readfirstlane(thresh);
+
+    // kept pairs in ascending id order: id = tid + 1024 i, so (i, wave, lane) ascending
+    const uint32_t n_kept = ordered_slots(key, thresh, base, wsum);
+    if (tid == 0) a.cnt_base[par][row] = (int32_t)n_kept;
     // (the ballots are taken again rather than kept: VPT 64-bit masks would not fit the scalar registers; the empty
     // asm keeps the compiler from carrying them over from the counting pass)
     asm volatile("" : "+s"(thresh));
@@ -344,10 +438,10 @@ __global__ __launch_bounds__(1024) void sample_rows_sparse_kernel(SampleRowsArgs
     uint64_t zsum = 0;
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
-        const bool keep = key[i] >= thresh && key[i] != 0u;
+        const bool keep = key[i] >= thresh;
         const uint64_t mask = __ballot(keep);
         if (keep) {
-            const uint32_t pos = base[i * 16 + wave] + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+            const uint32_t pos = base[i * 16 + wave] + lanes_before(mask, lane);
             const float ev = exp_neg(key_to_float(key[i]) - m);
             ids[pos] = tid_again + i * 1024;
             e[pos] = ev;
