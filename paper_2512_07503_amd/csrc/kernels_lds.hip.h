@@ -66,7 +66,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARA
     // workgroup id -> tile: all row tiles of a column tile on one XCD (ids go to the 8 XCDs round-robin), whose L2 then
     // fetches the column tile's weights once; the grid is padded to a multiple of 8 column tiles
     const int ct = (blockIdx.x & 7) + 8 * ((int)(blockIdx.x >> 3) / row_tiles), rt = (int)(blockIdx.x >> 3) % row_tiles;
-    if (ct >= col_tiles) return;
+    if (ct >= col_tiles) {
+        // past the padded grid: a workgroup that only touches what the next launch reads (l2_warm_next)
+        const int n_compute = 8 * ((col_tiles + 7) >> 3) * row_tiles;
+        if ((int)blockIdx.x >= n_compute) l2_warm_next(a, blockIdx.x, n_compute, tid, NW * 64);
+        return;
+    }
     const int KB = a.KB, ks = blockIdx.y;
     const int kb_lo = ks * a.kb_per_split;
     const int kb_hi = kb_lo + a.kb_per_split < KB ? kb_lo + a.kb_per_split : KB;
@@ -353,7 +358,7 @@ inline hipError_t launch_lds(hipStream_t st, const SkinnyArgs &a, int n_blocks, 
     if constexpr (I < kLdsTiles || (I == kLdsTileHeadZ ? EPI == EPI_HEAD : EPI == EPI_QKV || EPI == EPI_SWIGLU))               \
         if (cfg == I) {                                                                                                        \
             const int col_tiles = ceil_div(n_blocks, TNB), row_tiles = ceil_div(a.M, 32 * TMT);                                \
-            const dim3 grid(8 * ceil_div(col_tiles, 8) * row_tiles, a.ksplit);                                                 \
+            const dim3 grid(8 * ceil_div(col_tiles, 8) * row_tiles + (a.ksplit == 1 ? a.pf_wgs : 0), a.ksplit);                \
             gemm_lds_kernel<TMT, TNB, WM, WN, S, EPI><<<grid, WM * WN * 64, 0, st>>>(SJD_TILE_PASS(a), col_tiles, row_tiles, a);       \
             return hipGetLastError();                                                                                          \
         }

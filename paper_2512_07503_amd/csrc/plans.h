@@ -29,30 +29,45 @@ constexpr int TILE_M = 256;   // rows of the larger tile of kernels_tile.hip.h
 // gains nothing (2048 x 28672 x 4096 434 us against 430).
 #define SJD_LDS_TILES(X) X(0, 2, 2, 2, 1, 6) X(1, 4, 2, 4, 1, 6) X(2, 4, 4, 4, 2, 5) X(3, 6, 4, 2, 2, 4) X(4, 4, 4, 2, 2, 4) X(5, 8, 8, 2, 4, 4)
 constexpr int kLdsTiles = 4, kLdsTileHeadZ = 4, kLdsTileBig = 5;
-struct LdsTile { int tmt, tnb, cb; double t1, t2, tn; };
-// t1, t2, tn: microseconds per pipeline stage of a CU with one workgroup, with two, and per workgroup of more.  Measured on
-// models 768 to 4096 wide at 118 to 2040 rows, weights from HBM, before the kernels had their first arguments in registers: launches
-// of up to 500 rows now take 5 to 30 % less than this says (row groups of 126 rows of 1280: 40 %), larger ones are within 13 %
-// (2040 x 3840 x 1280: 15 % more).
+// What a projection's epilogue is, as far as its time goes.
+enum PlanEpi { PLAN_QKV = 0, PLAN_SWIGLU = 1, PLAN_RESID = 2, PLAN_PARTIAL = 3 };   // (the head: as SWIGLU)
+
+// The expected times below are fits to launches one after the other over weights from HBM, models of 768, 1280, 2048, 3072 and 4096
+// (grouped heads and not) at 66 to 2040 rows, 4 860 of them; the standard deviation of expected against measured is 5 to 9 % for
+// the row groups and the LDS tiles, 11 % for the tile kernels.
+struct LdsTile { int tmt, tnb, cb; double t1, t2, tn, fixed[4], hbm, tflops; };
+// t1, t2, tn: microseconds per pipeline stage of a CU with one workgroup, with two, and per workgroup of more; fixed: launch,
+// first operands and epilogue; hbm: MB of weights per microsecond that a launch is held to; tflops: what it sustains at most (long
+// launches run into the power limit; short ones, at higher clocks, do not)
 inline LdsTile lds_tile(int cfg) {
-    static const LdsTile t[6] = {{2, 2, 2, 0.22, 0.33, 0.14}, {4, 2, 2, 0.27, 0.45, 0.19}, {4, 4, 2, 0.38, 0.56, 0.30}, {6, 4, 2, 0.42, 0.72, 0.37},
-                                 {4, 4, 2, 0.40, 0.62, 0.33}, {8, 8, 2, 0.80, 1e3, 1e3}};
+    static const LdsTile t[6] = {{2, 2, 2, 0.142, 0.228, 0.109, {4.1, 3.5, 4.4, 4.6}, 3.83, 480}, {4, 2, 2, 0.166, 0.316, 0.167, {4.5, 3.5, 5.9, 5.1}, 4.28, 780},
+                                 {4, 4, 2, 0.240, 0.511, 0.2634, {5.6, 3.9, 6.5, 5.7}, 4.75, 950}, {6, 4, 2, 0.305, 0.608, 0.328, {11.2, 7.8, 13.9, 6.2}, 4.38, 1090},
+                                 {4, 4, 2, 0.240, 0.511, 0.2634, {5.6, 3.9, 6.5, 5.7}, 4.75, 950}, {8, 8, 2, 0.697, 1e3, 1e3, {11.5, 9.6, 0.0, 0.0}, 5.91, 1110}};
     return t[cfg];
 }
 
 // Time of an LDS-tile launch: stages x the busiest CU's workgroups (the column tiles of an XCD run on its CUs only).
-inline double lds_us(int cfg, int M, int n_blocks, int KB, int ks, int n_cus) {
+inline double lds_us(int cfg, PlanEpi epi, int M, int n_blocks, int KB, int ks, int n_cus) {
     const LdsTile t = lds_tile(cfg);
     const int wgs_xcd = plan_div(plan_div(n_blocks, t.tnb), 8) * plan_div(M, 32 * t.tmt) * ks;
     const int n = plan_div(wgs_xcd, std::max(1, n_cus / 8));
-    return (cfg == kLdsTileBig ? 8.0 : 4.0) + (double)plan_div(KB, 2 * ks) * (n == 1 ? t.t1 : n == 2 ? t.t2 : n * t.tn);
+    const double us = t.fixed[epi] + (double)plan_div(KB, 2 * ks) * (n == 1 ? t.t1 : n == 2 ? t.t2 : n * t.tn);
+    return std::max({us, 4.0 + n_blocks * (KB * 1024.0) / (t.hbm * 1e6), t.fixed[epi] + 1024.0 * M * n_blocks * KB / (t.tflops * 1e6)});
 }
-// ... of a row-group launch (kernels_skinny.hip.h): a CU moves 52 GB/s of weights and activations
-inline double skinny_us(int wgs, double wg_bytes, bool norm, int n_cus) {
-    return 5.0 + plan_div(wgs, n_cus) * wg_bytes / 52e3 + (norm ? 2.5 : 0.0);
+// ... of a row-group launch (kernels_skinny.hip.h) over row groups of 32 mt rows and column groups of nbw blocks: a CU moves 65 GB/s
+// of weights and activations, its workgroups but the first cost `more` each on top, and all CUs move 6 TB/s of weights
+inline int skinny_per_cu(int M, int mt, int groups, int ks, int n_cus) {
+    return plan_div(plan_div(groups, 8) * plan_div(M, 32 * mt) * ks, std::max(1, n_cus / 8));
+}
+inline double skinny_us(PlanEpi epi, int M, int mt, int groups, int nbw, int KB, int ks, int n_cus) {
+    static const double fixed[4][2][2] = {{{4.6, 4.6}, {6.9, 6.9}}, {{4.1, 4.1}, {5.6, 5.6}}, {{2.8, 3.9}, {3.5, 5.7}}, {{5.1, 5.1}, {4.7, 6.0}}};   // [epilogue][mt - 1][nbw - 1]
+    static const double more[2][2] = {{0.0, 1.0}, {1.5, 2.4}};
+    const int n = skinny_per_cu(M, mt, groups, ks, n_cus);
+    const double us = fixed[epi][mt - 1][nbw - 1] + (n - 1) * more[mt - 1][nbw - 1] + n * (double)(nbw + mt) * KB / ks * 1024.0 / 65e3;
+    return std::max(us, 4.0 + (double)groups * nbw * KB * 1024.0 / 6e6);
 }
 // ... and of the kernel that adds ks partial sums of M rows of d columns
-inline double reduce_us(int M, int d, int ks) { return std::max(6.7, 3.0 + (ks + 2.0) * M * d * 4.0 / 5e6); }
+inline double reduce_us(int M, int d, int ks) { return 0.3 + (ks + 2.0) * M * d * 4.0 / 3.28e6; }
 
 // ---- tile kernels
 // Rows per workgroup tile for n_blocks column blocks over M rows.  256 rows (two 32-row tiles per wavefront) need
@@ -68,22 +83,22 @@ inline int tile_rows_for(int M, int n_blocks, int ksplit, int n_cus) {
     return cost1 < cost2 ? 128 : 256;
 }
 
-// Time of a launch: 32-wide K stages x the busiest CU's tiles (the column tiles of an XCD run on its CUs only): 0.27 us a
-// 128-row tile (0.40 alone on its CU), 0.45 a 256-row tile, 0.27 per 128 x 128 in a launch of both heights.  Measured on
-// models 1280 to 4096 wide at 260 to 2040 rows.
+// Time of a launch: 32-wide K stages x the busiest CU's tiles (the column tiles of an XCD run on its CUs only): 0.25 us a
+// 128-row tile (0.33 alone on its CU), 0.47 a 256-row tile, 0.25 per 128 x 128 in a launch of both heights.
 inline bool tile_two_heights(int M, int n_blocks, int ksplit, int n_cus) {
     const int col_tiles = (n_blocks + 3) / 4, rt2 = (M + 255) / 256, rt1 = (M + 127) / 128;
     return ksplit == 1 && rt1 > rt2 && col_tiles * rt2 > n_cus && col_tiles * rt2 < 2 * n_cus && n_cus / rt2 >= 8 && (col_tiles * rt1) % n_cus != 0;
 }
-inline double tile_us(int M, int n_blocks, int KB, int ksplit, int n_cus) {
+inline double tile_us(PlanEpi epi, int M, int n_blocks, int KB, int ksplit, int n_cus) {
+    static const double fixed[4] = {16.8, 7.2, 22.1, 5.4};
     const int col_tiles = (n_blocks + 3) / 4, rows = tile_rows_for(M, n_blocks, ksplit, n_cus);
     const double stages = KB / (2.0 * ksplit);
     if (tile_two_heights(M, n_blocks, ksplit, n_cus)) {
         const int rt2 = (M + 255) / 256, ct_split = n_cus / rt2 / 8 * 8;
-        return 12.0 + stages * 0.27 * (2.0 * ct_split * rt2 + (double)(col_tiles - ct_split) * ((M + 127) / 128)) / n_cus;
+        return fixed[epi] + stages * 0.25 * (2.0 * ct_split * rt2 + (double)(col_tiles - ct_split) * ((M + 127) / 128)) / n_cus;
     }
     const int per_xcd = (col_tiles + 7) / 8 * ((M + rows - 1) / rows) * ksplit, cus = n_cus >= 8 ? n_cus / 8 : 1, n = (per_xcd + cus - 1) / cus;
-    return 12.0 + stages * (rows == 256 ? 0.45 * n : n == 1 ? 0.40 : 0.27 * n);
+    return fixed[epi] + stages * (rows == 256 ? 0.465 * n : n == 1 ? 0.328 : 0.25 * n);
 }
 
 // ---- the choice
@@ -93,86 +108,110 @@ inline bool rows_of_32(const ProjShape &s, int M, int groups) {
     return M > 32 && 2 * plan_div(M, 64) * 8 * plan_div(groups, 8) <= s.n_cus && !(s.kernel_flags & SJD_NO_ROW_SPLIT);
 }
 
-// How a projection runs: row groups (lds < 0) or LDS tiles of shape `lds`; ks: splits of K (output / down projections, whose
-// partial sums resid_reduce_kernel adds); us: its expected time, on which the choice rests.
-struct ProjPlan { int lds, ks; double us; };
-inline ProjPlan with_lds(const ProjShape &s, int M, int n_blocks, int KB, int max_ks, ProjPlan p, double extra_us) {
-    if (M <= 64 || (s.kernel_flags & SJD_KERNELS_ROWGROUPS)) return p;
-    for (int cfg = 0; cfg < kLdsTiles; ++cfg)
-        for (int ks = 1; ks <= max_ks; ks *= 2) {
-            if (ks > 1 && KB / ks < 32) continue;
-            const double t = extra_us + lds_us(cfg, M, n_blocks, KB, ks, s.n_cus) + (ks > 1 ? reduce_us(M, s.d_model, ks) : 0.0);
-            if (t < p.us) p = {cfg, ks, t};
-        }
-    return p;
-}
-// Shape 5 in the place of p where it is expected to be faster (QKV and gate/up only).
-inline ProjPlan with_big(const ProjShape &s, int M, int n_blocks, ProjPlan p) {
-    if (M < TILE_M || (s.kernel_flags & (SJD_KERNELS_ROWGROUPS | SJD_KERNELS_TILES))) return p;
-    const double t = lds_us(kLdsTileBig, M, n_blocks, s.d_model / 16, 1, s.n_cus);
-    return t < p.us ? ProjPlan{kLdsTileBig, 1, t} : p;
-}
-// QKV, gate/up and head: groups of two column blocks, whole K.  (2 us: the sums of squares that the row-group kernel takes
-// from its operands come from the writer of the rows with LDS tiles.)
-inline ProjPlan norm_plan(const ProjShape &s, int M, int groups) {
-    const int d = s.d_model, mt = M <= 32 || rows_of_32(s, M, groups) ? 1 : 2;
-    const ProjPlan p = {-1, 1, skinny_us(plan_div(M, 32 * mt) * groups, (double)(64 + 32 * mt) * d * 2.0, true, s.n_cus)};
-    return with_lds(s, M, groups * 2, d / 16, 1, p, 2.0);
-}
-inline ProjPlan resid_plan(const ProjShape &s, int M, int K) {
-    const int d = s.d_model, KB = K / 16, nbw = resid_nbw(d), groups = plan_div(plan_div(d, 32), nbw);
-    const int mt = M <= 32 || rows_of_32(s, M, groups) ? 1 : 2;
-    const double wg_bytes = (double)(nbw * 32 + mt * 32) * K * 2.0;
-    int ks = 1;
-    if (wg_bytes > 512e3) {   // one workgroup's share is too much for its CU
-        ks = std::min(8, std::max(1, s.n_cus / (groups * plan_div(M, 64))));
-        while (ks > 1 && KB / ks < 32) --ks;
-        ks = plan_div(KB, plan_div(KB, ks));
-    }
-    const ProjPlan p = {-1, ks, skinny_us(plan_div(M, 32 * mt) * groups * ks, wg_bytes / ks, false, s.n_cus) + (ks > 1 ? reduce_us(M, d, ks) : 0.0)};
-    return with_lds(s, M, plan_div(d, 32), KB, 4, p, 0.0);
-}
-
-// The tile kernels (kernels_tile.hip.h): K splits of an output / down projection, and the same estimate for a layer.
-inline int tile_splits(const ProjShape &s, int M, int KB) {
+// How a projection runs: row groups (lds < 0, not tile), LDS tiles of shape `lds`, or the tile kernels; ks: splits of
+// K (output / down projections, whose partial sums resid_reduce_kernel adds); us: its expected time, on which the choice rests.
+struct ProjPlan { int lds, ks; double us; bool tile = false; };
+inline int tile_splits(const ProjShape &s, int M, int KB) {   // K splits of an output / down projection through the tile kernels
     int ks = std::min(8, std::max(1, s.n_cus / (plan_div(plan_div(s.d_model, 64) * 2, 4) * plan_div(M, TILE_M))));
     while (ks > 1 && KB / ks < 32) --ks;
     return plan_div(KB, plan_div(KB, ks));
 }
-inline double tile_layer_us(const ProjShape &s, int M) {
-    const int d = s.d_model;
-    auto resid = [&](int K) {
-        const int ks = tile_splits(s, M, K / 16);
-        return tile_us(M, plan_div(d, 64) * 2, K / 16, ks, s.n_cus) + (ks > 1 ? reduce_us(M, d, ks) : 0.0);
-    };
-    return tile_us(M, s.qkv_groups() * 2, d / 16, 1, s.n_cus) + tile_us(M, s.d_ff / 32 * 2, d / 16, 1, s.n_cus) +
-           resid(s.q_dim()) + resid(s.d_ff);
+// The better of p and the kernels for more rows than a row group's
+inline ProjPlan with_tiles(const ProjShape &s, PlanEpi epi, int M, int n_blocks, int KB, ProjPlan p, bool tile_kernels) {
+    if (M <= 64 || (s.kernel_flags & SJD_KERNELS_ROWGROUPS)) return p;
+    // Beyond 512 rows the row groups' many short workgroups take far longer than the bytes they move say (1434 rows of 512, output
+    // projection: 11.3 us, expected 5.8)
+    if (M > 512) p.us = 1e9;
+    const bool resid = epi == PLAN_RESID;
+    auto reduced = [&](int ks) { return ks > 1 ? reduce_us(M, s.d_model, ks) : 0.0; };
+    auto kind = [&](int ks) { return ks > 1 ? PLAN_PARTIAL : epi; };
+    for (int cfg = 0; cfg < kLdsTiles; ++cfg)
+        for (int ks = 1; ks <= (resid ? 4 : 1); ks *= 2) {
+            if (ks > 1 && KB / ks < 32) continue;
+            const double t = lds_us(cfg, kind(ks), M, n_blocks, KB, ks, s.n_cus) + reduced(ks);
+            if (t < p.us) p = {cfg, ks, t};
+        }
+    if (M < TILE_M) return p;
+    const int ks = resid ? tile_splits(s, M, KB) : 1;
+    const double t = tile_us(kind(ks), M, n_blocks, KB, ks, s.n_cus) + reduced(ks);
+    if (tile_kernels && (t < p.us || (s.kernel_flags & SJD_KERNELS_TILES))) p = {-1, ks, t, true};
+    if (!resid && !(s.kernel_flags & SJD_KERNELS_TILES)) {
+        const double big = lds_us(kLdsTileBig, epi, M, n_blocks, KB, 1, s.n_cus);
+        if (big < p.us) p = {kLdsTileBig, 1, big};
+    }
+    return p;
 }
-// From 256 rows on: the tile kernels where their heights fit the rows and the CUs, else the mix of LDS tiles and row groups (shape 5
-// apart: it takes its place in either afterwards).
-// Measured, prompts through 6 layers of the 4096-wide shape, ms: 260 rows 1.38 (tile kernels) against 1.19; 700 2.39 / 2.05;
-// 1000 2.62 / 2.87; 1400 4.22 / 3.97; 2040 5.28 / 5.47; 1280-wide, 16 layers: 1000 rows 2.01 / 1.69, 2040 3.18 / 2.71.
-inline bool tile_forward(const ProjShape &s, int M) {
-    if (M < TILE_M || (s.kernel_flags & SJD_KERNELS_ROWGROUPS)) return false;
-    if (s.kernel_flags & SJD_KERNELS_TILES) return true;
-    return tile_layer_us(s, M) < norm_plan(s, M, s.qkv_groups()).us + norm_plan(s, M, s.d_ff / 32).us +
-                                     resid_plan(s, M, s.q_dim()).us + resid_plan(s, M, s.d_ff).us;
+inline int skinny_mt(const ProjShape &s, int M, int groups) { return M <= 32 || rows_of_32(s, M, groups) ? 1 : 2; }   // 32-row tiles per row group
+// Whether launch p of an output / down projection has CUs to spare for touching the next projection's weights (32 at least; no more
+// weights than the L2s hold)
+inline bool warms(const ProjShape &s, int M, const ProjPlan &p, size_t next_bytes) {
+    if (p.lds >= 0 || p.tile || p.ks > 1 || (s.kernel_flags & SJD_NO_L2_WARM)) return false;
+    const int groups = plan_div(plan_div(s.d_model, 32), resid_nbw(s.d_model));
+    return s.n_cus - 8 * plan_div(groups, 8) * plan_div(M, 32 * skinny_mt(s, M, groups)) >= 32 && next_bytes <= (size_t)24 << 20;
+}
+// QKV, gate/up: groups of two column blocks, whole K.  Row groups of a CU each whose weights the launch before has touched take
+// about 0.85 of the time (LDS tiles gain a tenth or nothing).
+inline ProjPlan norm_plan(const ProjShape &s, PlanEpi epi, int M, int groups, bool tile_kernels, const ProjPlan &before) {
+    const int KB = s.d_model / 16, mt = skinny_mt(s, M, groups);
+    const bool hot = skinny_per_cu(M, mt, groups, 1, s.n_cus) == 1 && warms(s, M, before, (size_t)groups * 64 * s.d_model * 2);
+    const double warm = hot ? 0.85 : 1.0;
+    return with_tiles(s, epi, M, groups * 2, KB, {-1, 1, warm * skinny_us(epi, M, mt, groups, 2, KB, 1, s.n_cus)}, tile_kernels);
+}
+inline ProjPlan resid_plan(const ProjShape &s, int M, int K, bool tile_kernels) {
+    const int d = s.d_model, KB = K / 16, nbw = resid_nbw(d), groups = plan_div(plan_div(d, 32), nbw);
+    int mt = skinny_mt(s, M, groups), ks = 1;
+    if ((double)(nbw + mt) * KB * 1024.0 > 512e3 && (M <= 64 || nbw > 1)) {   // one workgroup's share is too much for its CU
+        mt = M <= 32 ? 1 : 2;
+        ks = std::min(8, std::max(1, s.n_cus / (groups * plan_div(M, 64))));
+        while (ks > 1 && KB / ks < 32) --ks;
+        ks = plan_div(KB, plan_div(KB, ks));
+    }
+    const ProjPlan p = {-1, ks, skinny_us(ks > 1 ? PLAN_PARTIAL : PLAN_RESID, M, mt, groups, nbw, KB, ks, s.n_cus) + (ks > 1 ? reduce_us(M, d, ks) : 0.0)};
+    return with_tiles(s, PLAN_RESID, M, plan_div(d, 32), KB, p, tile_kernels);
+}
+
+// K splits of an output / down projection at most, whatever is chosen
+inline int max_splits(const ProjShape &s, int M, int K) {
+    const int KB = K / 16, groups = plan_div(plan_div(s.d_model, 32), resid_nbw(s.d_model));
+    int ks = KB >= 32 ? std::min(std::min(8, KB / 32), std::max(1, s.n_cus / (groups * plan_div(M, 64)))) : 1;
+    if (M > 64) ks = std::max(ks, KB >= 128 ? 4 : KB >= 64 ? 2 : 1);
+    return M >= TILE_M ? std::max(ks, tile_splits(s, M, KB)) : ks;
 }
 
 struct ForwardPlan {
-    bool tile;                             // every projection through the tile kernels, but QKV or gate/up of LDS tile shape 5
-    ProjPlan qkv, o, gate_up, down, head;  // else each its own
+    bool tile;                             // some projection runs through the tile kernels, and so does the head
+    ProjPlan qkv, o, gate_up, down, head;
 };
 // windows32: windows of 32 whose guidance branches the head combines, which needs both row tiles of a sequence in one wavefront
+inline ForwardPlan layer_plan(const ProjShape &s, int M, bool tile_kernels) {
+    ForwardPlan f{};
+    f.o = resid_plan(s, M, s.q_dim(), tile_kernels);
+    f.down = resid_plan(s, M, s.d_ff, tile_kernels);
+    // Beside a down projection of the tile kernels the output projection takes them too: LDS tiles are the faster launch there
+    // (2048 x 4096 x 4096: 86 us against 99) and the slower layer (two forwards of some 2000 rows, 8 layers of 4096: 15.09 ms
+    // against 15.03), at the power limit, to which their LDS traffic counts.
+    if (f.down.tile && !f.o.tile) f.o = {-1, tile_splits(s, M, s.q_dim() / 16), f.o.us, true};
+    f.qkv = norm_plan(s, PLAN_QKV, M, s.qkv_groups(), tile_kernels, f.down);
+    f.gate_up = norm_plan(s, PLAN_SWIGLU, M, s.gate_up_groups(), tile_kernels, f.o);
+    f.tile = f.qkv.tile || f.o.tile || f.gate_up.tile || f.down.tile;
+    return f;
+}
+inline double layer_us(const ForwardPlan &f) { return f.qkv.us + f.o.us + f.gate_up.us + f.down.us; }
 inline ForwardPlan forward_plan(const ProjShape &s, int M, bool windows32) {
-    ForwardPlan f = {tile_forward(s, M), norm_plan(s, M, s.qkv_groups()), resid_plan(s, M, s.q_dim()), norm_plan(s, M, s.gate_up_groups()),
-                     resid_plan(s, M, s.d_ff), norm_plan(s, M, s.head_groups())};
-    if (f.tile) {
-        f.qkv = {-1, 1, tile_us(M, s.qkv_groups() * 2, s.d_model / 16, 1, s.n_cus)};
-        f.gate_up = {-1, 1, tile_us(M, s.gate_up_groups() * 2, s.d_model / 16, 1, s.n_cus)};
+    // The tile kernels are a third set of kernels for the same rows: only where a layer is expected to gain 2 % by them, which is
+    // where the fits tell the sets apart
+    ForwardPlan f = layer_plan(s, M, (s.kernel_flags & SJD_KERNELS_TILES) != 0);
+    if (M >= TILE_M && !(s.kernel_flags & (SJD_KERNELS_ROWGROUPS | SJD_KERNELS_TILES))) {
+        const ForwardPlan g = layer_plan(s, M, true);
+        if (layer_us(g) < 0.98 * layer_us(f)) f = g;
     }
-    f.qkv = with_big(s, M, s.qkv_groups() * 2, f.qkv);
-    f.gate_up = with_big(s, M, s.gate_up_groups() * 2, f.gate_up);
+    const int groups = s.head_groups(), mt = skinny_mt(s, M, groups);
+    f.head = {-1, 1, skinny_us(PLAN_SWIGLU, M, mt, groups, 2, s.d_model / 16, 1, s.n_cus), f.tile};
+    if (!f.tile && M > 64 && !(s.kernel_flags & SJD_KERNELS_ROWGROUPS))
+        for (int cfg = 0; cfg < kLdsTiles; ++cfg) {
+            const double t = lds_us(cfg, PLAN_SWIGLU, M, groups * 2, s.d_model / 16, 1, s.n_cus);
+            if (t < f.head.us) f.head = {cfg, 1, t};
+        }
     if (f.head.lds >= 0 && windows32) f.head.lds = kLdsTileHeadZ;
     return f;
 }

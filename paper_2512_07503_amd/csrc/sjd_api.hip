@@ -431,7 +431,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // Every few-row projection launch carries extra workgroups that touch the weights of the projection after it,
     // so that those are in the L2 of the XCD that will read them when that launch starts (the launches are short
     // and latency-bound: first touch from HBM costs 2-3x the time of an L2 hit, and the chip is mostly idle).
-    struct Proj { const void *W; int groups, nbw, KB; bool whole; };
+    struct Proj { const void *W; int groups, nbw, KB; bool whole, lds; };
     const int groups_d = ceil_div(ceil_div(d, 32), nbw_d), groups_qkv = (H + 2 * Hkv) * (hd / 64);
     // More than 32 rows and so few column groups that a workgroup per group and 32-row tile still finds a CU of its
     // own: row groups of 32 rows instead of 64 (all row groups of a column group on one XCD, whose L2 serves the
@@ -445,15 +445,21 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     };
     // what the L2 warm-up of the launch before needs to know about a projection: its slabs are column tiles
     auto proj_of = [&](const void *W, int n_blocks, int KB, int nbw, const ProjPlan &p) {
-        if (p.lds < 0) return Proj{W, ceil_div(n_blocks, nbw), nbw, KB, p.ks == 1};
+        if (p.lds < 0) return Proj{W, ceil_div(n_blocks, nbw), nbw, KB, p.ks == 1, false};
         const int tnb = lds_tile(p.lds).tnb;
-        return Proj{W, n_blocks / tnb, tnb, KB, p.ks == 1};   // whole tiles only: a ragged last one ends with the matrix
+        return Proj{W, n_blocks / tnb, tnb, KB, p.ks == 1, true};   // whole tiles only: a ragged last one ends with the matrix
+    };
+    auto compute_wgs_lds = [&](int n_blocks, const ProjPlan &p) {
+        const LdsTile t = lds_tile(p.lds);
+        return 8 * ceil_div(ceil_div(n_blocks, t.tnb), 8) * ceil_div(M, 32 * t.tmt);
     };
     const int groups_v = c->shape.head_groups();
     const ProjPlan &plan_qkv = plan.qkv, &plan_o = plan.o, &plan_gu = plan.gate_up, &plan_down = plan.down, &plan_head = plan.head;
-    auto warm = [&](int cur_groups, const Proj &nx) {
+    // LDS tiles gain about 1 us where their weights are touched ahead, which a launch of less than 12 us loses and more (500
+    // rows of 1280: output projection 11.5 -> 14.8 us, gate/up 15.3 -> 14.0; 948 rows: 18.7 -> 18.2 and 25.0 -> 23.2).
+    auto warm = [&](int cur_groups, double cur_us, const Proj &nx) {
         a.pf_wgs = 0;
-        if (!c->l2_warm || tile || !nx.whole || !nx.W) return;
+        if (!c->l2_warm || tile || !nx.whole || !nx.W || (nx.lds && cur_us < 12.0)) return;
         const uint32_t slab = (uint32_t)nx.nbw * nx.KB * 1024;
         int fit = (int)std::min<size_t>(nx.groups, ((size_t)24 << 20) / slab);   // what the L2s hold beside the current weights
         int wgs = (int)(((size_t)fit * slab / (96 << 10) + 7) / 8 * 8);
@@ -482,7 +488,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // workgroup; the loop is bound by what a CU's L1 delivers).  Measured on the 36 x 1280 shape: output, down and QKV
     // projections (40-60 groups) gain, gate/up (108 groups: too few CUs left for the warm-up workgroups) loses.
     auto row_split_for = [&](int groups) { return MT == 1 && M > 16 && groups <= 64 && !(md.kernel_flags & SJD_NO_ROW_SPLIT) ? 2 : 1; };
-    const Proj none = {nullptr, 0, 0, 0, false};
+    const Proj none = {nullptr, 0, 0, 0, false, false};
     const bool mixed_ok = !(md.kernel_flags & SJD_NO_MIXED_WIDTH);
     // LDS-tile and tile kernels (and row groups with the gains in the rows) take the RMSNorm row sums of squares from the kernel
     // that wrote the residual stream: embedding gather, whole-K output / down projection or split-K reduction
@@ -490,6 +496,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     int ssq_n = 1;   // partial sums per row that the last writer left; the embedding kernel wrote one
     float *ssq_out = nullptr;   // where the coming output / down projection leaves them: set if its reader takes them
     auto use_ssq = [&]() { a.row_ssq_part = c->row_ssq; a.row_ssq_n = ssq_n; };
+    auto takes_ssq = [&](const ProjPlan &p) { return p.tile || p.lds >= 0 || !c->fold_gain; };
     // The row-group kernels sum the squares of their operands, which are the stream only while the gains are in the weights
     auto skinny_ssq = [&]() { if (!c->fold_gain) use_ssq(); };
     auto reduce = [&]() -> int {
@@ -506,22 +513,24 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         a.pf_wgs = 0;
         a.row_ssq_part = nullptr;
         a.ssq_out = ssq_out;
-        if (!tile && plan.lds >= 0) {
+        if (plan.lds >= 0) {
             const int nb = ceil_div(d, 32);
             a.kb_per_split = ceil_div(a.KB, 2 * plan.ks) * 2;
             a.ksplit = ceil_div(a.KB, a.kb_per_split);
             if (a.ksplit == 1) {
                 ssq_n = ceil_div(nb, lds_tile(plan.lds).cb);
+                warm(compute_wgs_lds(nb, plan), plan.us, nx);
                 SJD_LAUNCH(c, cls, launch_lds<EPI_RESID>(st, a, nb, plan.lds));
+                a.pf_wgs = 0;
                 return SJD_OK;
             }
             if ((size_t)a.ksplit * M * d > c->skinny_part_elems) return no_room();
             SJD_LAUNCH(c, cls, launch_lds<EPI_PARTIAL>(st, a, nb, plan.lds));
             return reduce();
         }
-        if (tile) {
+        if (plan.tile) {
             const int n_blocks = ceil_div(d, 64) * 2;
-            a.ksplit = tile_splits(c->shape, M, a.KB);
+            a.ksplit = plan.ks;
             a.kb_per_split = ceil_div(a.KB, a.ksplit);
             if (a.ksplit == 1) {
                 ssq_n = ceil_div(n_blocks, 4);
@@ -539,7 +548,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             const bool r2 = rows2_for(groups);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
             const int n_compute = compute_wgs(groups, r2, a.row_split);
-            warm(n_compute, nx);
+            warm(n_compute, plan.us, nx);
             if (kv_next) warm_kv(n_compute, *kv_next);
             ssq_n = groups;
             SJD_LAUNCH(c, cls, launch_skinny<EPI_RESID>(st, a, r2 ? 1 : MT, groups, nbw_d, nw_for(groups)));
@@ -566,14 +575,16 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         pool.page_tokens = c->pt;
         a.pool = pool;
         a.A = (const bf16_t *)c->xn; a.W = (const bf16_t *)lw.wqkv; a.KB = d / 16;
-        if (tile && plan_qkv.lds < 0) {
+        if (plan_qkv.tile) {
             whole_k();
             use_ssq();
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_tile<EPI_QKV>(st, a, (H + 2 * Hkv) * (hd / 64) * 2, tile_rows, mixed_ok));
         } else if (plan_qkv.lds >= 0) {
             whole_k();
             use_ssq();
+            warm(compute_wgs_lds(groups_qkv * 2, plan_qkv), plan_qkv.us, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_lds<EPI_QKV>(st, a, groups_qkv * 2, plan_qkv.lds));
+            a.pf_wgs = 0;
         } else {
             whole_k();
             skinny_ssq();
@@ -581,7 +592,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             const bool r2 = rows2_for(groups_qkv);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
             const int n_compute = compute_wgs(groups_qkv, r2, a.row_split);
-            warm(n_compute, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
+            warm(n_compute, plan_qkv.us, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
             if (l == 0) warm_kv(n_compute, pool);  // later layers: requested by the down projection before them
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_skinny<EPI_QKV>(st, a, r2 ? 1 : MT, groups_qkv, 2, nw_for(groups_qkv)));
             a.pf_wgs = a.kv_wgs = 0;
@@ -590,18 +601,20 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         }
         if (!with_head && l + 1 == md.n_layers) return SJD_OK;
         { int rc = run_attention<bf16_t>(c, pool, fr); if (rc) return rc; }
-        ssq_out = tile || plan_gu.lds >= 0 || !c->fold_gain ? c->row_ssq : nullptr;
+        ssq_out = takes_ssq(plan_gu) ? c->row_ssq : nullptr;
         a.gain = lw.mlp_norm;
         { int rc = resid(KC_GEMM_O, c->attn, lw.wo, H * hd, plan_o, proj_of(lw.wgu, F / 32 * 2, d / 16, 2, plan_gu), nullptr); if (rc) return rc; }
         a.A = (const bf16_t *)c->xn; a.W = (const bf16_t *)lw.wgu; a.KB = d / 16;
-        if (tile && plan_gu.lds < 0) {
+        if (plan_gu.tile) {
             whole_k();
             use_ssq();
             SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_tile<EPI_SWIGLU>(st, a, F / 32 * 2, tile_rows, mixed_ok));
         } else if (plan_gu.lds >= 0) {
             whole_k();
             use_ssq();
+            warm(compute_wgs_lds(F / 32 * 2, plan_gu), plan_gu.us, with_w(proj_down0, lw.wdown));
             SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_lds<EPI_SWIGLU>(st, a, F / 32 * 2, plan_gu.lds));
+            a.pf_wgs = 0;
         } else {
             whole_k();
             skinny_ssq();
@@ -609,7 +622,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             const bool r2 = rows2_for(F / 32);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
             const int n_compute = compute_wgs(F / 32, r2, a.row_split);
-            warm(n_compute, with_w(proj_down0, lw.wdown));
+            warm(n_compute, plan_gu.us, with_w(proj_down0, lw.wdown));
             if (mixed_ok && skinny_mixed_applies(a, F / 32, 2, nw_for(F / 32))) SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_skinny_mixed<EPI_SWIGLU>(st, a, MT, F / 32));
             else SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_skinny<EPI_SWIGLU>(st, a, r2 ? 1 : MT, F / 32, 2, nw_for(F / 32)));
             a.pf_wgs = 0;
@@ -622,7 +635,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         KvPool pool_next = pool;
         pool_next.k = (char *)c->kpool + c->pool_layer_bytes * (l + 1);
         pool_next.v = (char *)c->vpool + c->pool_layer_bytes * (l + 1);
-        ssq_out = tile || (l + 1 < md.n_layers ? plan_qkv : plan_head).lds >= 0 || !c->fold_gain ? c->row_ssq : nullptr;
+        ssq_out = takes_ssq(l + 1 < md.n_layers ? plan_qkv : plan_head) ? c->row_ssq : nullptr;
         a.gain = l + 1 < md.n_layers ? c->layers[l + 1].attn_norm : c->final_norm;
         { int rc = resid(KC_GEMM_DOWN, c->h, lw.wdown, F, plan_down, after_down, l + 1 < md.n_layers ? &pool_next : nullptr); if (rc) return rc; }
     }
@@ -831,7 +844,7 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
         // partial sums of the output and down projections where they split K, over the rows a step or a prefill forward can have
         auto cover = [&](int m) {
             for (int K : {H * hd, F}) {
-                const int ks = std::max(resid_plan(c->shape, m, K).ks, m < TILE_M ? 1 : tile_splits(c->shape, m, K / 16));
+                const int ks = max_splits(c->shape, m, K);
                 if (ks > 1) c->skinny_part_elems = std::max(c->skinny_part_elems, (size_t)ks * m * d);
             }
         };

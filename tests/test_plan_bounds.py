@@ -1,0 +1,41 @@
+"""The choice of projection kernels (csrc/plans.h), compiled for the host, over widths, MLPs, row counts and kernel flags: the K
+splits stay within what a context's workspace is sized for, no split is empty, and every projection has a kernel."""
+import subprocess
+
+import pytest
+
+import plan_choice
+
+_MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "plans.h"
+int main(int, char **v) {
+    const int d = atoi(v[1]), hd = d % 128 ? 64 : 128, flags[] = {0, SJD_KERNELS_ROWGROUPS, SJD_KERNELS_TILES, SJD_NO_ROW_SPLIT, SJD_NO_L2_WARM};
+    for (int ff : {d / 32 * 32 + 32, 2 * d + 96, 7 * d / 2 / 32 * 32}) for (int kv : {1, 4}) for (int fl : flags) for (int M = 1; M <= 2200; ++M) {
+        if (d / hd % kv) continue;
+        const ProjShape s{d, d / hd, d / hd / kv, ff, 16384, 256, fl};
+        const ForwardPlan f = forward_plan(s, M, M % 64 == 0);
+        for (const ProjPlan *p : {&f.qkv, &f.o, &f.gate_up, &f.down}) {
+            const int K = p == &f.down ? ff : d, KB = K / 16, unit = p->lds >= 0 ? 2 : 1, per = plan_div(KB, unit * p->ks) * unit;
+            if (p->ks < 1 || (p->ks - 1) * per >= KB) { printf("empty split: d %d ff %d M %d flags %d\n", d, ff, M, fl); return 1; }
+            if ((p == &f.o || p == &f.down) ? p->ks > max_splits(s, M, K) : p->ks != 1) { printf("splits: d %d ff %d M %d flags %d\n", d, ff, M, fl); return 1; }
+            if (!(p->us > 0 && p->us < 1e8) || (p->tile && p->lds >= 0) || (p->tile && M < TILE_M) || (p->lds >= 0 && M <= 64)) { printf("kernel: d %d ff %d M %d flags %d\n", d, ff, M, fl); return 1; }
+        }
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plans")
+    (d / "main.cpp").write_text(_MAIN)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", plan_choice.CSRC, str(d / "main.cpp"), "-o", str(d / "main")], check=True)
+    return d / "main"
+
+
+@pytest.mark.parametrize("d", [64, 128, 512, 640, 768, 1280, 2048, 3072, 4096, 5120])
+def test_every_choice_fits(program, d):
+    r = subprocess.run([str(program), str(d)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
