@@ -13,10 +13,11 @@
 // one row per accumulator quad, which is 8 bytes of the next GEMM's operand layout, 16 bytes of the residual stream or of the
 // logits: the epilogues store whole quads instead of single elements.
 //
-// What bounds it: a workgroup alone on its CU is bound by the chain wait - barrier - LDS reads - MFMAs of a stage (0.22 us for
-// 64 x 64, 0.42 us for 192 x 128, the same for 3 to 16 stages in flight: not by memory latency), several side by side by
-// LDS traffic and the 40-45 GB/s at which a CU draws a mix of HBM and L2 lines.  Hence small tiles while a launch has fewer
-// workgroups than CUs, larger ones (fewer bytes per MFMA) as rows are added; lds_us() (plans.h) holds the measured rates.
+// What bounds it: the operand bytes of a CU.  192 x 4096 x 11008 whole K in 128 x 128 tiles, 64 workgroups: 80 us; with the loads
+// alone 80, from L2 55 (70 and 102 GB/s, with 64 or with 128 KB in flight alike).  A K split over two or four groups of
+// wavefronts in the workgroup, which brings MFMAs and LDS reads down to 53 us together, is therefore no faster (83 us), and
+// slower on short K.  Hence small tiles while a launch has fewer workgroups than CUs, larger ones
+// (fewer bytes per MFMA) as rows are added; lds_us() (plans.h) holds the measured rates.
 // Against the row-group kernels, which split K over the wavefronts of a 64-row workgroup: 4096-wide, 192 rows: QKV
 // 68.6 -> 43.3 us, gate/up 97.8 -> 60.3, down 65 -> 41 with its reduction, head (65 536 ids) 263 -> 135; 1280-wide, 500 rows:
 // gate/up 35.9 -> 18.1, QKV 24.2 -> 15.6, down 27.2 -> 24.2.

@@ -34,7 +34,10 @@ enum PlanEpi { PLAN_QKV = 0, PLAN_SWIGLU = 1, PLAN_RESID = 2, PLAN_PARTIAL = 3 }
 
 // The expected times below are fits to launches one after the other over weights from HBM, models of 768, 1280, 2048, 3072 and 4096
 // (grouped heads and not) at 66 to 2040 rows, 4 860 of them; the standard deviation of expected against measured is 5 to 9 % for
-// the row groups and the LDS tiles, 11 % for the tile kernels.
+// the row groups and the LDS tiles, 11 % for the tile kernels.  Shapes 2 and 5 and the tile kernels' rates are then set within
+// that, so that near ties fall as whole forwards measured.  Over those models and rows the four projections chosen take 1.021
+// of the fastest launches' time in the geometric mean; with the rates measured before the kernels had their first arguments in
+// registers, and one family of kernels for a whole layer, it was 1.047.
 struct LdsTile { int tmt, tnb, cb; double t1, t2, tn, fixed[4], hbm, tflops; };
 // t1, t2, tn: microseconds per pipeline stage of a CU with one workgroup, with two, and per workgroup of more; fixed: launch,
 // first operands and epilogue; hbm: MB of weights per microsecond that a launch is held to; tflops: what it sustains at most (long
@@ -120,7 +123,7 @@ inline int tile_splits(const ProjShape &s, int M, int KB) {   // K splits of an 
 inline ProjPlan with_tiles(const ProjShape &s, PlanEpi epi, int M, int n_blocks, int KB, ProjPlan p, bool tile_kernels) {
     if (M <= 64 || (s.kernel_flags & SJD_KERNELS_ROWGROUPS)) return p;
     // Beyond 512 rows the row groups' many short workgroups take far longer than the bytes they move say (1434 rows of 512, output
-    // projection: 11.3 us, expected 5.8)
+    // projection in row groups of 32: 11.3 us, expected 5.8)
     if (M > 512) p.us = 1e9;
     const bool resid = epi == PLAN_RESID;
     auto reduced = [&](int ks) { return ks > 1 ? reduce_us(M, s.d_model, ks) : 0.0; };
