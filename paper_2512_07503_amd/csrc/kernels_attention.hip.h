@@ -7,8 +7,10 @@
 
 // ------------------------------------------------------------------------------------ reference
 // One wavefront per (row, head): scores into LDS, softmax, then lanes split the head dimension.  Every sum runs in the order
-// of its index (dimensions, tokens; the fp32 forward runs on this kernel).  Bound by latency: 64 dimensions of a key and 32
-// tokens' values are in flight together, the first values from ahead of the keys.
+// of its index (dimensions, tokens; the fp32 forward runs on this kernel).  Bound by latency: keys come four dimensions at a
+// time, values eight tokens at a time, page by page instead of a table lookup and two divisions per token.  32 rows x 4 heads
+// of 64, 50 tokens: 15.1 -> 9.8 us between events.  (Not more of them: 64 dimensions and 32 tokens in flight leave a SIMD two
+// wavefronts; 500 rows x 40 heads of 128 over 300 tokens took 1415 us instead of 334 in bf16, 16 x 4 of 64 17.8 instead of 14.4 in fp32.)
 SJD_D void load4(const float *p, float (&v)[4]) {
     const float4 x = *reinterpret_cast<const float4 *>(p);
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
@@ -41,34 +43,14 @@ __global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool,
     __syncthreads();
     const size_t blk = (size_t)pool.page_tokens * hd;
     const int32_t *pt = pool.page_table + (size_t)seg * pool.pages_per_seg;
-    // Dimension j of the values of a block of 32 tokens (a page is whole blocks; tokens past the last repeat it): the first
-    // block is requested ahead of the keys, each next one while the one before is added.
-    auto load_block = [&](int t0, int j, float (&vv)[32]) {
-        const int pg = t0 / pool.page_tokens;
-        const T *vb = (const T *)pool.v + ((size_t)pt[pg] * Hkv + kvh) * blk;
-        const int tt = t0 - pg * pool.page_tokens, last = n_vis - 1 - t0;
-#pragma unroll
-        for (int u = 0; u < 32; ++u) vv[u] = to_float<T>(vb[Layout<T>::v_index(tt + min(u, last), j, hd)]);
-    };
-    float va[32], vb[32];
-    load_block(0, min(lane, hd - 1), va);
     float mx = -INFINITY;
     for (int t = lane; t < n_vis; t += 64) {
         const T *kb = (const T *)pool.k + ((size_t)pt[t / pool.page_tokens] * Hkv + kvh) * blk;
         const int tt = t % pool.page_tokens;
         float s = 0.0f;
         if ((hd & 7) == 0) {   // 4 dimensions of a token are contiguous and aligned in both layouts
-            int j = 0;
-            for (; j + 64 <= hd; j += 64) {   // 16 loads in flight
-                float kv[16][4];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) load4(kb + Layout<T>::k_index(tt, j + 4 * u, hd), kv[u]);
-#pragma unroll
-                for (int u = 0; u < 16; ++u)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) s = fmaf(qs[j + 4 * u + e], kv[u][e], s);
-            }
-            for (; j < hd; j += 4) {
+#pragma unroll 4
+            for (int j = 0; j < hd; j += 4) {
                 float kv[4];
                 load4(kb + Layout<T>::k_index(tt, j, hd), kv);
 #pragma unroll
@@ -93,23 +75,18 @@ __global__ void attention_reference_kernel(const T *__restrict__ q, KvPool pool,
     const float inv = 1.0f / sum;
     for (int j = lane; j < hd; j += 64) {
         float acc = 0.0f;
-        auto add_block = [&](int t0, const float (&vv)[32]) {
-            if (t0 + 32 <= n_vis) {
+        for (int t0 = 0, pg = 0; t0 < n_vis; t0 += pool.page_tokens, ++pg) {
+            const T *vb = (const T *)pool.v + ((size_t)pt[pg] * Hkv + kvh) * blk;
+            const int n = min(pool.page_tokens, n_vis - t0);
+            int tt = 0;
+            for (; tt + 8 <= n; tt += 8) {
+                float vv[8];
 #pragma unroll
-                for (int u = 0; u < 32; ++u) acc = fmaf(sc[t0 + u], vv[u], acc);
-            } else {
+                for (int u = 0; u < 8; ++u) vv[u] = to_float<T>(vb[Layout<T>::v_index(tt + u, j, hd)]);
 #pragma unroll
-                for (int u = 0; u < 32; ++u)
-                    if (t0 + u < n_vis) acc = fmaf(sc[t0 + u], vv[u], acc);
+                for (int u = 0; u < 8; ++u) acc = fmaf(sc[t0 + tt + u], vv[u], acc);
             }
-        };
-        if (j != lane) load_block(0, j, va);
-        for (int t0 = 0; t0 < n_vis; t0 += 64) {
-            if (t0 + 32 < n_vis) load_block(t0 + 32, j, vb);
-            add_block(t0, va);
-            if (t0 + 32 >= n_vis) break;
-            if (t0 + 64 < n_vis) load_block(t0 + 64, j, va);
-            add_block(t0 + 32, vb);
+            for (; tt < n; ++tt) acc = fmaf(sc[t0 + tt], to_float<T>(vb[Layout<T>::v_index(tt, j, hd)]), acc);
         }
         acc *= inv;
         if (out_act) out_act[Layout<T>::a_index(m, h * hd + j, H * hd)] = from_float<T>(acc);
