@@ -6,7 +6,8 @@
 // threads, lanes 32, 16, ..., 1 apart, then the four wavefronts), every element rounded where they round it.
 //
 // Bound: a step of the fp32 model is a chain of short dependent launches (2 layers of 256: 4 us each whatever they do), so what
-// counts is their number, nine a layer before and five now.  The four wavefronts of a workgroup share the sums of squares of their
+// counts is their number, nine a layer before and five now (where results are many, the norm and what follows are on their own again:
+// f32_inside, plans.h).  The four wavefronts of a workgroup share the sums of squares of their
 // eight rows, two rows each: 10 exchanges and a barrier.
 #pragma once
 #include "kernels_attention.hip.h"

@@ -72,6 +72,16 @@ inline double skinny_us(PlanEpi epi, int M, int mt, int groups, int nbw, int KB,
 // ... and of the kernel that adds ks partial sums of M rows of d columns
 inline double reduce_us(int M, int d, int ks) { return 0.3 + (ks + 2.0) * M * d * 4.0 / 3.28e6; }
 
+// ---- fp32
+// Whether an fp32 projection that starts with a norm has it, and what follows, inside (gemm_f32_kernel) or as kernels of their own.  Inside
+// saves two launches (QKV: norm and rotation, gate/up: norm and SwiGLU) or one (the head's norm), and costs every wavefront the norm of its
+// rows and one multiplication more per four, so what it costs grows with the results, M x N.  The lines lie where neither way gains;
+// steps and prompts of 2 layers, us, inside / apart: QKV of 240 rows of 256 91 / 98, 180 of 512 122 / 126 and 240 143 / 140, 60 of 2048
+// 354 / 357 and 118 602 / 583; gate/up of 240 rows of 256 91 / 93 and 512 138 / 134, 180 of 512 122 / 120, 32 of 2048 215 / 225 and 118
+// 602 / 599; head of 4096 ids, 512 wide, 32 rows 159 / 156 and 512 477 / 456, of 16384 ids, 512 rows of 64 307 / 234.
+enum { F32_QKV_INSIDE = 320000, F32_GATE_UP_INSIDE = 480000, F32_HEAD_INSIDE = 160000 };
+inline bool f32_inside(int M, int N, long results) { return (long)M * N <= results; }
+
 // ---- tile kernels
 // Rows per workgroup tile for n_blocks column blocks over M rows.  256 rows (two 32-row tiles per wavefront) need
 // the fewest operand bytes per MFMA: 0.75 KiB against 1.25 KiB for 128 rows, whose weight fragments alone would

@@ -336,8 +336,9 @@ template <typename T> int forward(sjd_ctx *c, const FwdRows &fr, bool with_head)
     return SJD_OK;
 }
 
-// fp32 path: five kernels per layer, the same sums bit for bit as forward<float> (nine), which SJD_KERNELS_REFERENCE selects.
-// 2 layers of 256, window 16, a step: 25 launches, now 17.
+// fp32 path: five kernels per layer, the same sums bit for bit as forward<float> (nine), which SJD_KERNELS_REFERENCE selects; QKV, gate/up
+// and head of more results leave their norm, rotation and SwiGLU to forward<float>'s kernels (f32_inside).
+// 2 layers of 256, window 16, a step: 26 launches, now 16.
 int forward_f32(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     const sjd_model_desc &md = c->md;
     const int d = md.d_model, H = md.n_heads, Hkv = md.n_kv_heads, hd = c->hd;
@@ -350,6 +351,12 @@ int forward_f32(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     a.rope_cos = c->rope_cos; a.rope_sin = c->rope_sin;
     a.q_out = (float *)c->q;
     a.L = fr.L; a.H = H; a.Hkv = Hkv; a.hd = hd;
+    // a projection behind a norm whose element-wise steps run on their own: the norm here, the product into `out`
+    auto apart = [&](int cls, const void *W, int N, const float *gain, float *out) -> int {
+        SJD_LAUNCH(c, KC_ADDNORM, after([&] { addnorm_kernel<float><<<fr.M, 256, 0, st>>>(c->x, nullptr, 0, fr.M, gain, (float *)c->xn, d, md.rms_eps); }));
+        int splits;
+        return run_gemm<float>(c, cls, (const float *)c->xn, (const float *)W, out, fr.M, N, d, 1, &splits);
+    };
     auto gemm = [&](auto epi, int cls, const void *A, const void *W, int N, int K, const float *gain, float *out) -> int {
         a.N = N; a.K = K; a.gain = gain; a.out = out;
         SJD_LAUNCH(c, cls, launch_gemm_f32<decltype(epi)::value>(st, (const float *)A, (const float *)W, a));
@@ -367,15 +374,31 @@ int forward_f32(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         pool.page_table = c->page_table;
         pool.pages_per_seg = c->pps;
         pool.page_tokens = c->pt;
-        int rc = gemm(kQkv, KC_GEMM_QKV, c->x, lw.wqkv, (H + 2 * Hkv) * hd, d, lw.attn_norm, nullptr);
-        if (rc) return rc;
+        const int n_qkv = (H + 2 * Hkv) * hd;
+        int rc;
+        if (f32_inside(fr.M, n_qkv, F32_QKV_INSIDE)) {
+            if ((rc = gemm(kQkv, KC_GEMM_QKV, c->x, lw.wqkv, n_qkv, d, lw.attn_norm, nullptr))) return rc;
+        } else {
+            if ((rc = apart(KC_GEMM_QKV, lw.wqkv, n_qkv, lw.attn_norm, c->partial))) return rc;
+            SJD_LAUNCH(c, KC_ROPE_KV, after([&] {
+                           rope_kv_kernel<float><<<fr.M, 256, 0, st>>>(c->partial, 1, fr.M, fr.rm, c->rope_cos, c->rope_sin, (float *)c->q, pool, fr.L, H,
+                                                                       Hkv, hd);
+                       }));
+        }
         if (!with_head && l + 1 == md.n_layers) return SJD_OK;
         if ((rc = run_attention<float>(c, pool, fr))) return rc;
         if ((rc = gemm(kResid, KC_GEMM_O, c->attn, lw.wo, d, H * hd, nullptr, c->x))) return rc;
-        if ((rc = gemm(kSwiglu, KC_GEMM_GATEUP, c->x, lw.wgu, 2 * md.d_ff, d, lw.mlp_norm, (float *)c->h))) return rc;
+        if (f32_inside(fr.M, 2 * md.d_ff, F32_GATE_UP_INSIDE)) {
+            if ((rc = gemm(kSwiglu, KC_GEMM_GATEUP, c->x, lw.wgu, 2 * md.d_ff, d, lw.mlp_norm, (float *)c->h))) return rc;
+        } else {
+            if ((rc = apart(KC_GEMM_GATEUP, lw.wgu, 2 * md.d_ff, lw.mlp_norm, c->partial))) return rc;
+            SJD_LAUNCH(c, KC_SWIGLU, after([&] { swiglu_kernel<float><<<fr.M, 256, 0, st>>>(c->partial, 1, fr.M, (float *)c->h, md.d_ff); }));
+        }
         if ((rc = gemm(kResid, KC_GEMM_DOWN, c->h, lw.wdown, d, md.d_ff, nullptr, c->x))) return rc;
     }
-    return with_head ? gemm(kLogits, KC_GEMM_HEAD, c->x, c->lm_head, c->Vs, d, c->final_norm, c->logits) : SJD_OK;
+    if (!with_head) return SJD_OK;
+    if (!f32_inside(fr.M, c->Vs, F32_HEAD_INSIDE)) return apart(KC_GEMM_HEAD, c->lm_head, c->Vs, c->final_norm, c->logits);
+    return gemm(kLogits, KC_GEMM_HEAD, c->x, c->lm_head, c->Vs, d, c->final_norm, c->logits);
 }
 
 // Small-M bf16 path: five kernels per layer (QKV+RoPE+KV write, attention, out+residual, gate/up+SwiGLU,
@@ -813,7 +836,9 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
     c->page_table = c->pre_dev;
     // workspaces
     if ((rc = dev_alloc(c, &c->x, (size_t)M * d * sizeof(float)))) return rc;
-    if (!c->fused && (md.dtype == SJD_BF16 || (md.kernel_flags & SJD_KERNELS_REFERENCE))) {   // the generic path's GEMM outputs, with their K splits
+    const bool generic = !c->fused && (md.dtype == SJD_BF16 || (md.kernel_flags & SJD_KERNELS_REFERENCE));
+    const bool f32_apart = md.dtype == SJD_F32 && !(f32_inside(M, Nqkv, F32_QKV_INSIDE) && f32_inside(M, 2 * F, F32_GATE_UP_INSIDE));
+    if (generic || f32_apart) {   // the generic path's GEMM outputs, with their K splits
         const int shapes[4][2] = {{Nqkv, d}, {d, H * hd}, {2 * F, d}, {d, F}};
         for (auto &s : shapes) {
             size_t need = (size_t)M * s[0];
@@ -833,7 +858,8 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
     }
     if ((rc = dev_alloc(c, &c->logits, (size_t)S * 2 * L * c->Vs * sizeof(float)))) return rc;
     const int Mpad = ceil_div(M, 64) * 64;   // whole 64-row groups: the row-group projections read every row of the last one
-    if ((rc = dev_alloc(c, &c->xn, Layout<T>::a_elems(Mpad, d) * sizeof(T)))) return rc;
+    if ((c->fused || generic || f32_apart || !f32_inside(S * 2 * L, c->Vs, F32_HEAD_INSIDE)) &&
+        (rc = dev_alloc(c, &c->xn, Layout<T>::a_elems(Mpad, d) * sizeof(T)))) return rc;
     if ((rc = dev_alloc(c, &c->attn, Layout<T>::a_elems(Mpad, H * hd) * sizeof(T)))) return rc;
     if ((rc = dev_alloc(c, &c->h, Layout<T>::a_elems(Mpad, F) * sizeof(T)))) return rc;
     // queries: 32-row tiles of one segment each (packed segments leave a ragged tile each at most)

@@ -39,3 +39,25 @@ def program(tmp_path_factory):
 def test_every_choice_fits(program, d):
     r = subprocess.run([str(program), str(d)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+def test_which_fp32_projections_have_their_norm_inside(tmp_path):
+    """(QKV, gate/up, head) of a step and (QKV, gate/up) of the prompt: few results inside, many apart, and the GPU cases on both sides."""
+    import test_gpu_f32_fused as t
+    (tmp_path / "main.cpp").write_text("""#include <cstdio>
+#include "plans.h"
+int main() { int M, n, f, v; while (scanf("%d %d %d %d", &M, &n, &f, &v) == 4)
+    printf("%d%d%d\\n", f32_inside(M, n, F32_QKV_INSIDE), f32_inside(M, 2 * f, F32_GATE_UP_INSIDE), f32_inside(M, v, F32_HEAD_INSIDE)); }
+""")
+    subprocess.run(["g++", "-std=c++17", "-I", plan_choice.CSRC, str(tmp_path / "main.cpp"), "-o", str(tmp_path / "main")], check=True)
+
+    def sides(*queries):
+        return subprocess.run([str(tmp_path / "main")], input="\n".join("%d %d %d %d" % q for q in queries), capture_output=True, text=True, check=True).stdout.split()
+    # 62 prompt and 32 step rows of 256; 512 prompt rows of 512 and 2048
+    assert sides((62, 768, 1024, 1), (32, 768, 1024, 4096), (512, 1536, 1440, 1), (512, 6144, 5632, 1)) == ["111", "111", "001", "001"]
+    seen = []
+    for a, window, seqs, prompt in t.CASES[-3:]:
+        n = (a["n_heads"] + 2 * a["n_kv_heads"]) * a["d_model"] // a["n_heads"]
+        step, rows = sides((2 * seqs * window, n, a["d_ff"], a["vocab"]), (min(512, 2 * seqs * (prompt - 1)), n, a["d_ff"], 1))
+        seen.append((step, rows[:2]))
+    assert seen == [("100", "10"), ("111", "01"), ("000", "11")], seen
