@@ -517,7 +517,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // that wrote the residual stream: embedding gather, whole-K output / down projection or split-K reduction
     const int tile_rows = (md.kernel_flags & SJD_TILES_256_ROWS) ? 256 : 0;  // 0: chosen per launch
     int ssq_n = 1;   // partial sums per row that the last writer left; the embedding kernel wrote one
-    float *ssq_out = nullptr;   // where the coming output / down projection leaves them: set if its reader takes them
+    float *ssq_out = nullptr;   // where the coming output / down projection leaves them: set if its reader takes them (tile kernels: always)
     auto use_ssq = [&]() { a.row_ssq_part = c->row_ssq; a.row_ssq_n = ssq_n; };
     auto takes_ssq = [&](const ProjPlan &p) { return p.tile || p.lds >= 0 || !c->fold_gain; };
     // The row-group kernels sum the squares of their operands, which are the stream only while the gains are in the weights
@@ -556,6 +556,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             a.ksplit = plan.ks;
             a.kb_per_split = ceil_div(a.KB, a.ksplit);
             if (a.ksplit == 1) {
+                a.ssq_out = c->row_ssq;   // also where the reader sums for itself: the kernel always leaves them
                 ssq_n = ceil_div(n_blocks, 4);
                 SJD_LAUNCH(c, cls, launch_tile<EPI_RESID>(st, a, n_blocks, tile_rows, mixed_ok));
                 return SJD_OK;

@@ -5,7 +5,9 @@ rows; tests/test_plan_choice.py computes it for CASES and holds them to all shap
 Bound: a projection's operand, the rotated queries and keys, values, probabilities, attention output and hidden activations are
 rounded to bf16 (2^-9 / sqrt(3) = 1.1e-3 in the 2-norm each, the gains where they are in the weights once more), some
 ten independent ones a layer: sqrt(20) x 1.1e-3 = 5e-3 for two layers of projections that neither shrink nor amplify, up to
-twice that where they amplify (0.02 sqrt(d) = 1.28 at 4096); 1.5e-2 leaves half of that again."""
+twice that where they amplify (0.02 sqrt(d) = 1.28 at 4096); 1.5e-2 leaves half of that again.  Wider models have weights of 1.28 / sqrt(d):
+at 16384 with 0.02 a projection amplifies 2.56 times, the attention's scores reach 2.56^2 times a unit normal, whose operands' roundings alone
+move a probability by 6.6 sqrt(2) x 1.1e-3 = 1.0e-2 a layer (2.2e-2 measured over two)."""
 import numpy as np
 import pytest
 
@@ -20,7 +22,7 @@ def _weights(arch, seed):
     q, kv = arch["n_heads"] * hd, arch["n_kv_heads"] * hd
 
     def rnd(*s):
-        return torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16) * 0.02
+        return torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16) * min(0.02, 1.28 / d ** 0.5)
     shapes = dict(wq=(q, d), wk=(kv, d), wv=(kv, d), wo=(d, q), w_gate=(ff, d), w_up=(ff, d), w_down=(d, ff))
     w = {n: [rnd(*s) for _ in range(arch["n_layers"])] for n, s in shapes.items()}
     for n in ("attn_norm", "mlp_norm"):
@@ -126,6 +128,17 @@ BIG_CASES = [
 
 @pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens", BIG_CASES)
 def test_big_tiles_against_float64(d, heads, kv, ff, ids, window, lens):
+    test_against_float64(d, heads, kv, ff, ids, window, lens)
+
+
+# A whole-K output projection of the tile kernels ahead of a gate/up in row groups that sums the squares for itself (gains in the weights)
+TILE_BEFORE_ROW_GROUPS = [
+    (16384, 128, 32, 128, 301, 1, [(250, 244)]),     # 492 prompt rows
+]
+
+
+@pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens", TILE_BEFORE_ROW_GROUPS)
+def test_tile_kernels_before_row_groups_against_float64(d, heads, kv, ff, ids, window, lens):
     test_against_float64(d, heads, kv, ff, ids, window, lens)
 
 

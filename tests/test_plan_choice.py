@@ -70,3 +70,10 @@ def test_the_whole_k_cases_reach_the_tile_kernels_with_256_rows():
     for p in plan_choice.choose(queries):
         assert p["tile"] and p["qkv"][0] == 5 and p["gate_up"][0] == -1 and p["tile_splits"] == dict(out=1, down=1)
         assert all(p["tile_rows"][n] == 256 and not p["two_heights"][n] for n in ("out", "down")), p
+
+
+def test_the_tile_before_row_groups_case_is_one():
+    import test_gpu_lds_tiles as t
+    queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, 0) for d, h, kv, ff, ids, _, lens in t.TILE_BEFORE_ROW_GROUPS]
+    for p in plan_choice.choose(queries):
+        assert p["by_tile"]["out"] and p["out"] == (-1, 1) and not p["by_tile"]["gate_up"] and p["gate_up"][0] == -1, p
