@@ -200,10 +200,6 @@ inline ForwardPlan layer_plan(const ProjShape &s, int M, bool tile_kernels) {
     ForwardPlan f{};
     f.o = resid_plan(s, M, s.q_dim(), tile_kernels);
     f.down = resid_plan(s, M, s.d_ff, tile_kernels);
-    // Beside a down projection of the tile kernels the output projection takes them too: LDS tiles are the faster launch there
-    // (2048 x 4096 x 4096: 86 us against 99) and the slower layer (two forwards of some 2000 rows, 8 layers of 4096: 15.09 ms
-    // against 15.03), at the power limit, to which their LDS traffic counts.
-    if (f.down.tile && !f.o.tile) f.o = {-1, tile_splits(s, M, s.q_dim() / 16), f.o.us, true};
     f.qkv = norm_plan(s, PLAN_QKV, M, s.qkv_groups(), tile_kernels, f.down);
     f.gate_up = norm_plan(s, PLAN_SWIGLU, M, s.gate_up_groups(), tile_kernels, f.o);
     f.tile = f.qkv.tile || f.o.tile || f.gate_up.tile || f.down.tile;
@@ -212,7 +208,7 @@ inline ForwardPlan layer_plan(const ProjShape &s, int M, bool tile_kernels) {
 inline double layer_us(const ForwardPlan &f) { return f.qkv.us + f.o.us + f.gate_up.us + f.down.us; }
 inline ForwardPlan forward_plan(const ProjShape &s, int M, bool windows32) {
     // The tile kernels are a third set of kernels for the same rows: only where a layer is expected to gain 2 % by them, which is
-    // where the fits tell the sets apart
+    // where the fits tell the sets apart (2048 x 6912 beside 1280 wide, 2000 rows: expected 0.4 % less, 8 % more as whole prompts)
     ForwardPlan f = layer_plan(s, M, (s.kernel_flags & SJD_KERNELS_TILES) != 0);
     if (M >= TILE_M && !(s.kernel_flags & (SJD_KERNELS_ROWGROUPS | SJD_KERNELS_TILES))) {
         const ForwardPlan g = layer_plan(s, M, true);

@@ -1,5 +1,5 @@
 """The choice of projection kernels (csrc/plans.h), compiled for the host, over widths, MLPs, row counts and kernel flags: the K
-splits stay within what a context's workspace is sized for, no split is empty, and every projection has a kernel."""
+splits stay within what a context's workspace is sized for, no split is empty, every projection has a kernel and is expected to take that kernel's time."""
 import subprocess
 
 import pytest
@@ -9,13 +9,29 @@ import plan_choice
 _MAIN = r"""
 #include <cstdio>
 #include <cstdlib>
+#include <math.h>
 #include "plans.h"
+// the expected time of the kernels that the plan names (whether the weights are touched ahead: row groups, 0.85)
+static bool own_time(const ProjShape &s, int M, PlanEpi epi, int blocks, int KB, const ProjPlan &p) {
+    const int nbw = epi == PLAN_RESID ? resid_nbw(s.d_model) : 2, groups = plan_div(blocks, nbw);
+    const int mt = p.ks > 1 ? (M <= 32 ? 1 : 2) : skinny_mt(s, M, groups);
+    const PlanEpi e = p.ks > 1 ? PLAN_PARTIAL : epi;
+    const double reduce = p.ks > 1 ? reduce_us(M, s.d_model, p.ks) : 0.0;
+    const double us = (p.tile ? tile_us(e, M, blocks, KB, p.ks, s.n_cus) : p.lds >= 0 ? lds_us(p.lds, e, M, blocks, KB, p.ks, s.n_cus)
+                                                                                   : skinny_us(e, M, mt, groups, nbw, KB, p.ks, s.n_cus)) + reduce;
+    return fabs(p.us - us) < 1e-9 * us || (!p.tile && p.lds < 0 && epi != PLAN_RESID && fabs(p.us - 0.85 * us) < 1e-9 * us);
+}
 int main(int, char **v) {
     const int d = atoi(v[1]), hd = d % 128 ? 64 : 128, flags[] = {0, SJD_KERNELS_ROWGROUPS, SJD_KERNELS_TILES, SJD_NO_ROW_SPLIT, SJD_NO_L2_WARM};
     for (int ff : {d / 32 * 32 + 32, 2 * d + 96, 7 * d / 2 / 32 * 32}) for (int kv : {1, 4}) for (int fl : flags) for (int M = 1; M <= 2200; ++M) {
         if (d / hd % kv) continue;
         const ProjShape s{d, d / hd, d / hd / kv, ff, 16384, 256, fl};
         const ForwardPlan f = forward_plan(s, M, M % 64 == 0);
+        if (!own_time(s, M, PLAN_QKV, s.qkv_groups() * 2, d / 16, f.qkv) || !own_time(s, M, PLAN_RESID, plan_div(d, 32), d / 16, f.o) ||
+            !own_time(s, M, PLAN_SWIGLU, s.gate_up_groups() * 2, d / 16, f.gate_up) || !own_time(s, M, PLAN_RESID, plan_div(d, 32), ff / 16, f.down)) {
+            printf("expected time: d %d ff %d kv %d M %d flags %d\n", d, ff, d / hd / kv, M, fl);
+            return 1;
+        }
         for (const ProjPlan *p : {&f.qkv, &f.o, &f.gate_up, &f.down}) {
             const int K = p == &f.down ? ff : d, KB = K / 16, unit = p->lds >= 0 ? 2 : 1, per = plan_div(KB, unit * p->ks) * unit;
             if (p->ks < 1 || (p->ks - 1) * per >= KB) { printf("empty split: d %d ff %d M %d flags %d\n", d, ff, M, fl); return 1; }
