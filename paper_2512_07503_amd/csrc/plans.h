@@ -132,9 +132,6 @@ inline int tile_splits(const ProjShape &s, int M, int KB) {   // K splits of an 
 // The better of p and the kernels for more rows than a row group's
 inline ProjPlan with_tiles(const ProjShape &s, PlanEpi epi, int M, int n_blocks, int KB, ProjPlan p, bool tile_kernels) {
     if (M <= 64 || (s.kernel_flags & SJD_KERNELS_ROWGROUPS)) return p;
-    // Beyond 512 rows the row groups' many short workgroups take far longer than the bytes they move say (1434 rows of 512, output
-    // projection in row groups of 32: 11.3 us, expected 5.8)
-    if (M > 512) p.us = 1e9;
     const bool resid = epi == PLAN_RESID;
     auto reduced = [&](int ks) { return ks > 1 ? reduce_us(M, s.d_model, ks) : 0.0; };
     auto kind = [&](int ks) { return ks > 1 ? PLAN_PARTIAL : epi; };
@@ -162,15 +159,23 @@ inline bool warms(const ProjShape &s, int M, const ProjPlan &p, size_t next_byte
     const int groups = plan_div(plan_div(s.d_model, 32), resid_nbw(s.d_model));
     return s.n_cus - 8 * plan_div(groups, 8) * plan_div(M, 32 * skinny_mt(s, M, groups)) >= 32 && next_bytes <= (size_t)24 << 20;
 }
+// Row groups as a choice.  Beyond 512 rows and one workgroup per CU their many short workgroups take far longer than the bytes
+// they move say (1434 rows of 512, output projection in row groups of 32: 11.3 us, expected 5.8): not there, except where the flag asks.
+// With a workgroup per CU at most they are the better kernels of narrow models at any number of rows (prompts through 12 layers with LDS
+// tiles in their place: 743 rows of 256 361 -> 422 us, 558 of 512 430 -> 457, 637 of 384 397 -> 412).
+inline ProjPlan row_groups(const ProjShape &s, PlanEpi epi, int M, int mt, int groups, int nbw, int KB, int ks) {
+    if (M > 512 && skinny_per_cu(M, mt, groups, ks, s.n_cus) > 1 && !(s.kernel_flags & SJD_KERNELS_ROWGROUPS)) return {-1, ks, 1e9};
+    return {-1, ks, skinny_us(epi, M, mt, groups, nbw, KB, ks, s.n_cus) + (ks > 1 ? reduce_us(M, s.d_model, ks) : 0.0)};
+}
 // QKV, gate/up: groups of two column blocks, whole K.  Row groups of a CU each whose weights the launch before has touched take
 // about 0.85 of the time (LDS tiles gain a tenth or nothing).
 inline ProjPlan norm_plan(const ProjShape &s, PlanEpi epi, int M, int groups, bool tile_kernels, const ProjPlan &before) {
     const int KB = s.d_model / 16, mt = skinny_mt(s, M, groups);
-    const bool hot = skinny_per_cu(M, mt, groups, 1, s.n_cus) == 1 && warms(s, M, before, (size_t)groups * 64 * s.d_model * 2);
-    const double warm = hot ? 0.85 : 1.0;
-    return with_tiles(s, epi, M, groups * 2, KB, {-1, 1, warm * skinny_us(epi, M, mt, groups, 2, KB, 1, s.n_cus)}, tile_kernels);
+    ProjPlan p = row_groups(s, epi, M, mt, groups, 2, KB, 1);
+    if (skinny_per_cu(M, mt, groups, 1, s.n_cus) == 1 && warms(s, M, before, (size_t)groups * 64 * s.d_model * 2)) p.us *= 0.85;
+    return with_tiles(s, epi, M, groups * 2, KB, p, tile_kernels);
 }
-inline ProjPlan resid_plan(const ProjShape &s, int M, int K, bool tile_kernels) {
+inline ProjPlan resid_row_groups(const ProjShape &s, int M, int K) {
     const int d = s.d_model, KB = K / 16, nbw = resid_nbw(d), groups = plan_div(plan_div(d, 32), nbw);
     int mt = skinny_mt(s, M, groups), ks = 1;
     if ((double)(nbw + mt) * KB * 1024.0 > 512e3 && (M <= 64 || nbw > 1)) {   // one workgroup's share is too much for its CU
@@ -179,8 +184,10 @@ inline ProjPlan resid_plan(const ProjShape &s, int M, int K, bool tile_kernels) 
         while (ks > 1 && KB / ks < 32) --ks;
         ks = plan_div(KB, plan_div(KB, ks));
     }
-    const ProjPlan p = {-1, ks, skinny_us(ks > 1 ? PLAN_PARTIAL : PLAN_RESID, M, mt, groups, nbw, KB, ks, s.n_cus) + (ks > 1 ? reduce_us(M, d, ks) : 0.0)};
-    return with_tiles(s, PLAN_RESID, M, plan_div(d, 32), KB, p, tile_kernels);
+    return row_groups(s, ks > 1 ? PLAN_PARTIAL : PLAN_RESID, M, mt, groups, nbw, KB, ks);
+}
+inline ProjPlan resid_plan(const ProjShape &s, int M, int K, bool tile_kernels) {
+    return with_tiles(s, PLAN_RESID, M, plan_div(s.d_model, 32), K / 16, resid_row_groups(s, M, K), tile_kernels);
 }
 
 // K splits of an output / down projection at most, whatever is chosen

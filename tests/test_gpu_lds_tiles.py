@@ -142,6 +142,18 @@ def test_tile_kernels_before_row_groups_against_float64(d, heads, kv, ff, ids, w
     test_against_float64(d, heads, kv, ff, ids, window, lens)
 
 
+# Narrow models: output and down projections in row groups, a workgroup per CU at most, however many rows
+NARROW_CASES = [
+    (256, 4, 4, 1280, 301, 33, [(380, 365)]),        # 743 prompt rows
+    (512, 8, 2, 1376, 301, 1, [(470, 466)]),         # 934
+]
+
+
+@pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens", NARROW_CASES)
+def test_row_groups_of_many_rows_against_float64(d, heads, kv, ff, ids, window, lens):
+    test_against_float64(d, heads, kv, ff, ids, window, lens)
+
+
 # Long prompts whose projections run through the tile kernels with K whole: output and down projections of 256-row tiles that
 # leave one partial sum of squares per column tile (32 of them), read by a 256 x 256 QKV and a 256-row gate/up; gains in the
 # weights (window 1) and in the rows (33).  Ragged in rows and in the MLP's columns; same bound.

@@ -77,3 +77,12 @@ def test_the_tile_before_row_groups_case_is_one():
     queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, 0) for d, h, kv, ff, ids, _, lens in t.TILE_BEFORE_ROW_GROUPS]
     for p in plan_choice.choose(queries):
         assert p["by_tile"]["out"] and p["out"] == (-1, 1) and not p["by_tile"]["gate_up"] and p["gate_up"][0] == -1, p
+
+
+def test_narrow_models_keep_the_row_groups_at_any_number_of_rows():
+    import test_gpu_lds_tiles as t
+    queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, 0) for d, h, kv, ff, ids, _, lens in t.NARROW_CASES]
+    for p in plan_choice.choose(queries):
+        assert all(p[n] == (-1, 1) and not p["by_tile"][n] for n in ("out", "down")), p
+    # more than a workgroup per CU: LDS tiles
+    assert all(plan_choice.choose([(t.case_arch(512, 8, 8, 1792, 301), 1434, 0, 0)])[0][n][0] >= 0 for n in ("out", "down"))
