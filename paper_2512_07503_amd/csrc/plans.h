@@ -205,10 +205,18 @@ struct ForwardPlan {
 // windows32: windows of 32 whose guidance branches the head combines, which needs both row tiles of a sequence in one wavefront
 inline ForwardPlan layer_plan(const ProjShape &s, int M, bool tile_kernels) {
     ForwardPlan f{};
-    f.o = resid_plan(s, M, s.q_dim(), tile_kernels);
-    f.down = resid_plan(s, M, s.d_ff, tile_kernels);
-    f.qkv = norm_plan(s, PLAN_QKV, M, s.qkv_groups(), tile_kernels, f.down);
-    f.gate_up = norm_plan(s, PLAN_SWIGLU, M, s.gate_up_groups(), tile_kernels, f.o);
+    // An output / down projection in row groups touches the weights of the projection behind it, which gains by that: row groups where the
+    // two together are expected to take 2 % less.  70 prompt rows of 1280: down 9.6 us against 9.4 in LDS tiles, QKV then 7.1 against 8.4;
+    // 12 layers 469 -> 418 us, 86 rows of 640 396 -> 363.  (Below 2 % the other side was faster: 88 rows of 2048 193 against 204 us.)
+    auto pair = [&](int K, ProjPlan &first, PlanEpi epi, int groups, ProjPlan &next) {
+        first = resid_plan(s, M, K, tile_kernels);
+        next = norm_plan(s, epi, M, groups, tile_kernels, first);
+        if (s.kernel_flags & SJD_KERNELS_TILES) return;
+        const ProjPlan rg = resid_row_groups(s, M, K), after_rg = norm_plan(s, epi, M, groups, tile_kernels, rg);
+        if (rg.us + after_rg.us < 0.98 * (first.us + next.us)) { first = rg; next = after_rg; }
+    };
+    pair(s.q_dim(), f.o, PLAN_SWIGLU, s.gate_up_groups(), f.gate_up);
+    pair(s.d_ff, f.down, PLAN_QKV, s.qkv_groups(), f.qkv);
     f.tile = f.qkv.tile || f.o.tile || f.gate_up.tile || f.down.tile;
     return f;
 }

@@ -86,3 +86,10 @@ def test_narrow_models_keep_the_row_groups_at_any_number_of_rows():
         assert all(p[n] == (-1, 1) and not p["by_tile"][n] for n in ("out", "down")), p
     # more than a workgroup per CU: LDS tiles
     assert all(plan_choice.choose([(t.case_arch(512, 8, 8, 1792, 301), 1434, 0, 0)])[0][n][0] >= 0 for n in ("out", "down"))
+
+
+def test_row_groups_are_taken_for_what_they_touch_ahead():
+    import test_gpu_lds_tiles as t
+    for d, h, kv, ff, rows in ((1280, 20, 20, 3456, 70), (1280, 20, 5, 3456, 67), (640, 10, 10, 3200, 86)):
+        p = plan_choice.choose([(t.case_arch(d, h, kv, ff, 301), rows, 0, 0)])[0]
+        assert p["down"] == (-1, 1) and p["qkv"] == (-1, 1), p
