@@ -93,3 +93,11 @@ def test_row_groups_are_taken_for_what_they_touch_ahead():
     for d, h, kv, ff, rows in ((1280, 20, 20, 3456, 70), (1280, 20, 5, 3456, 67), (640, 10, 10, 3200, 86)):
         p = plan_choice.choose([(t.case_arch(d, h, kv, ff, 301), rows, 0, 0)])[0]
         assert p["down"] == (-1, 1) and p["qkv"] == (-1, 1), p
+
+
+def test_short_launches_of_narrow_models_stay_out_of_the_tile_kernels():
+    import test_gpu_lds_tiles as t
+    short = [(1024, 16, 16, 3584, 1257), (2048, 32, 32, 5504, 704), (2560, 20, 20, 6400, 1152), (1280, 20, 10, 4480, 931)]
+    longer = [(4096, 32, 32, 11008, 512), (4096, 32, 8, 14336, 2000), (3072, 24, 24, 12288, 1024), (2048, 16, 8, 10240, 1024)]
+    plans = plan_choice.choose([(t.case_arch(d, h, kv, ff, 301), rows, 0, 0) for d, h, kv, ff, rows in short + longer])
+    assert [p["tile"] for p in plans] == [False] * 4 + [True] * 4
