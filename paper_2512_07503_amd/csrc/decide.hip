@@ -18,6 +18,7 @@
 #include <type_traits>
 #include "decide.h"
 
+#include "candidates.h"
 #include "common.hip.h"
 
 #pragma clang fp contract(off)
@@ -195,9 +196,6 @@ struct SampleRowsArgs {
     float cfg_scale, inv_t;
 };
 
-constexpr int kSelBins = 2048;
-constexpr int kBin0Shift = 17;   // round 0 of the select: 2^17 order keys per bin = 64 bins per binade of the logit
-
 // First bin (ascending index) at which the running sum of hist reaches `want` (1 <= want <= total); `before` = the
 // sum of the bins below it.  2048 bins, 1024 threads (two bins each); result in all threads.
 SJD_D void find_bin(const uint32_t *hist, uint32_t want, uint32_t *wsum /* [16] */, uint32_t *out /* [2] */, uint32_t &bin,
@@ -359,15 +357,12 @@ __global__ __launch_bounds__(1024) void sample_rows_sparse_kernel(SampleRowsArgs
     // Rows of many ids: the K kept ones are a few percent, and what follows took 64 steps a thread, each with something to do.  The
     // keys above a bound that 1024 of them (one a thread, spread over the ids) suggest are moved together first, in id order; if
     // they turn out to be the K largest at least and fit, the rest works on them, six a thread, else on all.  The result is the
-    // same.  The bound: rank 1.5 x K / V of the sample and 12 more, some three standard deviations above what K needs.  32 rows of
-    // 65 536 ids, K = 2000: 46.2 -> 25.4 us a launch; 16 rows of 16 384, K = 1000: 19.0 -> 17.6 (the sums over the wavefronts, which
-    // no longer run one by one, included).
-    if constexpr (VPT >= 16) {
-        constexpr int kCand = 6 * 1024;
+    // same.  Which rows, and the bound: candidates.h.  32 rows, K = 2000, without -> with candidates: 65 536 ids 40.8 -> 25.5 us a launch,
+    // 50 000 38.1 -> 24.6, 33 000 34.9 -> 23.6, 20 000 21.7 -> 18.0; 256 rows of 65 536 52.5 -> 45.7, of 32 768 31.7 -> 33.9.
+    if constexpr (VPT > 16) {
         __shared__ uint32_t cand_key[kCand], cand_id[kCand];
-        const uint32_t rank = (uint32_t)((long)a.top_k * 1536 / (ahi - alo > 0 ? ahi - alo : 1)) + 12u;
-        if (a.top_k < ahi - alo && rank < 256u && alo == 0 && ahi == V) {   // block-uniform
-            const int sid = tid + 1024 * ((tid ^ (tid >> 6)) & (VPT - 1)), sv = sid < V ? sid : V - 1;
+        if (alo == 0 && ahi == V && candidates_fit((uint32_t)a.top_k, (uint32_t)V)) {   // block-uniform
+            const uint32_t rank = candidate_rank((uint32_t)a.top_k, (uint32_t)V), sv = sample_id((uint32_t)tid, (uint32_t)V);
             const uint32_t sample = order_key(zrow ? zrow[sv] : guided(lc[sv], lu[sv], a.cfg_scale, a.inv_t));
             hist[2 * tid] = 0u;
             hist[2 * tid + 1] = 0u;
@@ -377,9 +372,7 @@ __global__ __launch_bounds__(1024) void sample_rows_sparse_kernel(SampleRowsArgs
             __syncthreads();
             uint32_t bin, before;
             find_bin(hist, rank, wsum, sel, bin, before);
-            const uint32_t off = (bin + 1u) << kBin0Shift;   // (2048 x 2^17 = 2^28: no overflow)
-            uint32_t bound = bin < (uint32_t)(kSelBins - 1) && kmax > off ? kmax - off + 1u : 1u;   // the bin's lowest key
-            bound = __builtin_amdgcn_readfirstlane(bound);
+            uint32_t bound = __builtin_amdgcn_readfirstlane(candidate_bound(kmax, bin));
             const uint32_t n_cand = ordered_slots(key, bound, base, wsum);
             asm volatile("" : "+s"(bound));   // (as below: nothing is carried from the counting pass in registers)
             int tid_again = tid;

@@ -20,7 +20,8 @@ def _rows(V, K, rng):
 
 
 @pytest.mark.parametrize("V,K", [(16384, 1), (16384, 1000), (16384, 2600), (4097, 500), (16385, 700), (20000, 3000), (32768, 2048),
-                                 (32769, 100), (65535, 6000), (65536, 2000), (65536, 10400)])
+                                 (32769, 100), (65535, 6000), (65536, 2000), (65536, 10400),
+                                 (17000, 2000), (33000, 2000), (50000, 2500), (20000, 2400)])   # (of up to 16384 ids: never candidates)
 def test_rows_on_both_sides_of_the_candidates_conditions(oracle, V, K):
     import torch
     import paper_2512_07503_amd as sjd
