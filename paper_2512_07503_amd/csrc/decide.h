@@ -43,8 +43,7 @@ struct DecideState {
     // Forced-token masks: image position i of sequence s may only take ids in [allow_lo, allow_hi) (relative to
     // sample_lo); every other id has probability 0 there.  [S][max_img]; the whole range by default.
     int32_t *allow_lo, *allow_hi;
-    sjd_step_result *res; // [S]
-    sjd_step_result *res_host; // [S] the same in pinned host memory (every device writes to it directly): no copy behind a step
+    sjd_step_result *res_host; // [S] verdicts, in pinned host memory (the device writes to it directly): no copy behind a step
 };
 
 struct SamplingParams {

@@ -677,7 +677,7 @@ SJD_D uint64_t wave_row_weight(const RowRef &r, int x, int lane) {
 
 // ------------------------------------------------------------------- a11: verification (Eq. 2)
 // One wavefront per draft (4 per block, grid.y = sequence): all drafts are tested in parallel and the first rejection
-// is the minimum over the rejected ones.  the staging of the rows has set acc_len[s] = Le - 1 (no rejection).
+// is the minimum over the rejected ones.  The staging of the rows has set acc_len[s] = Le - 1 (no rejection).
 __global__ __launch_bounds__(256) void verify_kernel(DecideState d, uint64_t seed, int row_width) {
     const int s = blockIdx.y, L = d.L, lane = threadIdx.x & 63;
     const int k = 1 + blockIdx.x * 4 + (threadIdx.x >> 6);   // draft in slot k against row k - 1
@@ -880,10 +880,7 @@ __global__ void draw_kernel(DecideState d, uint64_t seed, float tau, int rows_pe
 __global__ void commit_kernel(DecideState d, uint64_t seed, int init_mode, int row_width) {
     const int s = blockIdx.x, L = d.L;
     const int Le = d.Le[s];
-    auto verdict = [&](const sjd_step_result &r) {
-        d.res[s] = r;
-        d.res_host[s] = r;
-    };
+    auto verdict = [&](const sjd_step_result &r) { d.res_host[s] = r; };
     if (Le == 0) {
         if (threadIdx.x == 0) verdict({0, 0, -1, 1});
         return;

@@ -940,7 +940,6 @@ int alloc_state(sjd_ctx *c) {
     }
     if ((rc = dev_alloc(c, &d.allow_lo, (size_t)S * d.max_img * 4))) return rc;
     if ((rc = dev_alloc(c, &d.allow_hi, (size_t)S * d.max_img * 4))) return rc;
-    if ((rc = dev_alloc(c, &d.res, (size_t)S * sizeof(sjd_step_result)))) return rc;
     hipError_t e = hipHostMalloc((void **)&c->res_host, (size_t)S * sizeof(sjd_step_result), hipHostMallocMapped | hipHostMallocCoherent);
     if (e != hipSuccess) { sjd_set_error(c->err, "hipHostMalloc failed: %s", hipGetErrorString(e)); return SJD_ENOMEM; }
     d.res_host = c->res_host;   // (host and device share the address)
@@ -1433,7 +1432,8 @@ struct SnapshotHeader {
 };
 constexpr uint64_t kSnapshotMagic = 0x31544e53444a53ull;  // "SJDSNT1"
 
-// the per-sequence device arrays of the decoding state: pointer, bytes per sequence
+// the per-sequence device arrays of the decoding state: pointer, bytes per sequence (NULL: a place of the format that nothing uses any
+// more - the last verdicts - written as zeros and not read)
 struct StateArray { void *p; size_t per_seq; };
 std::vector<StateArray> state_arrays(sjd_ctx *c) {
     const DecideState &d = c->ds;
@@ -1444,7 +1444,7 @@ std::vector<StateArray> state_arrays(sjd_ctx *c) {
         {d.out_tok, (size_t)d.max_img * 4}, {d.acc_len, 4}, {d.cand, L * 4}, {d.cand_new, L * 4},
         {d.ids_buf[0], L * cap * 4}, {d.ids_buf[1], L * cap * 4}, {d.e_buf[0], L * cap * 4}, {d.e_buf[1], L * cap * 4},
         {d.cnt_buf[0], L * 4}, {d.cnt_buf[1], L * 4}, {d.Z_buf[0], L * 8}, {d.Z_buf[1], L * 8},
-        {d.allow_lo, (size_t)d.max_img * 4}, {d.allow_hi, (size_t)d.max_img * 4}, {d.res, sizeof(sjd_step_result)}};
+        {d.allow_lo, (size_t)d.max_img * 4}, {d.allow_hi, (size_t)d.max_img * 4}, {nullptr, sizeof(sjd_step_result)}};
     if (c->sp.init_mode == 4) {
         a.push_back({d.hist_ids, (size_t)c->sp.row_width * cap * 4});
         a.push_back({d.hist_e, (size_t)c->sp.row_width * cap * 4});
@@ -1522,7 +1522,8 @@ int sjd_snapshot_save(sjd_ctx *c, void *dst_host, uint64_t cap, uint64_t *writte
     SJD_HIP_TRY(c->err, hipMemcpy(w, c->ds.step, 4, hipMemcpyDeviceToHost));
     w += 16;
     for (const StateArray &a : state_arrays(c)) {
-        SJD_HIP_TRY(c->err, hipMemcpy(w, a.p, a.per_seq * c->n_seqs, hipMemcpyDeviceToHost));
+        if (a.p) SJD_HIP_TRY(c->err, hipMemcpy(w, a.p, a.per_seq * c->n_seqs, hipMemcpyDeviceToHost));
+        else memset(w, 0, a.per_seq * c->n_seqs);
         w += a.per_seq * c->n_seqs;
     }
     const size_t page_bytes = c->pool_layer_bytes / c->n_pages;  // one page of one layer's key (or value) pool, all kv heads
@@ -1633,7 +1634,7 @@ int sjd_snapshot_restore(sjd_ctx *c, const void *src_host, uint64_t bytes) {
     SJD_HIP_TRY(c->err, hipMemcpy(c->ds.step, r, 4, hipMemcpyHostToDevice));
     r += 16;
     for (const StateArray &a : state_arrays(c)) {
-        SJD_HIP_TRY(c->err, hipMemcpy(a.p, r, a.per_seq * n_seqs, hipMemcpyHostToDevice));
+        if (a.p) SJD_HIP_TRY(c->err, hipMemcpy(a.p, r, a.per_seq * n_seqs, hipMemcpyHostToDevice));
         r += a.per_seq * n_seqs;
     }
     const size_t page_bytes = c->pool_layer_bytes / c->n_pages;  // one page of one layer's key (or value) pool, all kv heads
