@@ -233,7 +233,9 @@ inline ForwardPlan forward_plan(const ProjShape &s, int M, bool windows32) {
         if (layer_us(g) < (s.d_model >= 3072 || g.gate_up.us >= 85.0 ? 0.98 : 0.92) * layer_us(f)) f = g;
     }
     const int groups = s.head_groups(), mt = skinny_mt(s, M, groups);
-    f.head = {-1, 1, skinny_us(PLAN_SWIGLU, M, mt, groups, 2, s.d_model / 16, 1, s.n_cus), f.tile};
+    f.head = {-1, 1, skinny_us(PLAN_SWIGLU, M, mt, groups, 2, s.d_model / 16, 1, s.n_cus)};
+    // (by its own time in such forwards, and with weights touched ahead in them: 0.1 % over 60, 2 % at best)
+    if (f.tile) f.head = {-1, 1, tile_us(PLAN_SWIGLU, M, groups * 2, s.d_model / 16, 1, s.n_cus), true};
     if (!f.tile && M > 64 && !(s.kernel_flags & SJD_KERNELS_ROWGROUPS))
         for (int cfg = 0; cfg < kLdsTiles; ++cfg) {
             const double t = lds_us(cfg, PLAN_SWIGLU, M, groups * 2, s.d_model / 16, 1, s.n_cus);
@@ -241,4 +243,42 @@ inline ForwardPlan forward_plan(const ProjShape &s, int M, bool windows32) {
         }
     if (f.head.lds >= 0 && windows32) f.head.lds = kLdsTileHeadZ;
     return f;
+}
+
+// ---- touching weights ahead
+// Launches of row groups and LDS tiles carry workgroups that touch the weights of the projection behind them, so that those are in the
+// L2 of the XCD that will read them (the launches are short and latency-bound, and the chip is mostly idle).
+// Computing workgroups of a launch: LDS tiles over n_blocks column blocks, row groups over `groups` column groups
+inline int lds_wgs(int cfg, int M, int n_blocks) {
+    const LdsTile t = lds_tile(cfg);
+    return 8 * plan_div(plan_div(n_blocks, t.tnb), 8) * plan_div(M, 32 * t.tmt);
+}
+inline int row_group_wgs(int M, int groups, bool rows32, int row_split) {
+    const int m_groups = plan_div(M, 64);
+    if (rows32) return 2 * m_groups * 8 * plan_div(groups, 8);
+    if (row_split == 2) return 16 * plan_div(groups, 8);
+    return m_groups > 1 ? m_groups * 8 * plan_div(groups, 8) : groups;
+}
+// What the launch before needs to know about a projection: n slabs (its column tiles) of nbw column blocks x KB k-blocks
+struct Slabs { int n, nbw, KB; bool whole, lds; };
+inline Slabs slabs_of(const ProjPlan &p, int n_blocks, int KB, int nbw) {
+    if (p.lds < 0) return {plan_div(n_blocks, nbw), nbw, KB, p.ks == 1, false};
+    const int tnb = lds_tile(p.lds).tnb;
+    return {n_blocks / tnb, tnb, KB, p.ks == 1, true};   // whole tiles only: a ragged last one ends with the matrix
+}
+// Workgroups that a launch of cur_wgs, expected to take cur_us, carries, and how many of the next launch's slabs they touch.
+// LDS tiles gain about 1 us where their weights are touched ahead, which a launch of less than 12 us loses and more (500
+// rows of 1280: output projection 11.5 -> 14.8 us, gate/up 15.3 -> 14.0; 948 rows: 18.7 -> 18.2 and 25.0 -> 23.2).
+struct Touch { int wgs, slabs; };
+inline Touch touch(const ProjShape &s, int M, int cur_wgs, double cur_us, const Slabs &next) {
+    if (!next.whole || (next.lds && cur_us < 12.0)) return {0, 0};
+    const size_t slab = (size_t)next.nbw * next.KB * 1024;
+    int fit = (int)std::min<size_t>(next.n, ((size_t)24 << 20) / slab);   // what the L2s hold beside the current weights
+    int wgs = (int)((fit * slab / (96 << 10) + 7) / 8 * 8);
+    wgs = std::min(wgs, (s.n_cus - cur_wgs) / 8 * 8);
+    if (wgs < 8 || (M > 64 && wgs < 32)) return {0, 0};   // long-window launches: a handful of CUs only delays them
+    // few CUs left: touch no more than they get through while the launch computes (a CU streams ~45 GB/s from
+    // HBM, the launches take 7-10 us: 320 KB each), the first slabs
+    fit = (int)std::min<size_t>(fit, (size_t)wgs * (320 << 10) / slab);
+    return fit < 1 ? Touch{0, 0} : Touch{wgs, fit};
 }

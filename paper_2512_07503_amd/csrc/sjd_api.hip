@@ -451,48 +451,22 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     const bool tile = plan.tile;
     // output / down projection: x += A W^T.  One kernel when a workgroup's share is small, else K split over
     // grid.y with the partial sums added by resid_reduce_kernel after the kernel boundary.
-    // Every few-row projection launch carries extra workgroups that touch the weights of the projection after it,
-    // so that those are in the L2 of the XCD that will read them when that launch starts (the launches are short
-    // and latency-bound: first touch from HBM costs 2-3x the time of an L2 hit, and the chip is mostly idle).
-    struct Proj { const void *W; int groups, nbw, KB; bool whole, lds; };
+    // Launches of row groups and LDS tiles touch the weights of the projection behind them (touch, plans.h).
+    struct Proj { const void *W; Slabs slabs; };
     const int groups_d = ceil_div(ceil_div(d, 32), nbw_d), groups_qkv = (H + 2 * Hkv) * (hd / 64);
     // More than 32 rows and so few column groups that a workgroup per group and 32-row tile still finds a CU of its
     // own: row groups of 32 rows instead of 64 (all row groups of a column group on one XCD, whose L2 serves the
     // later readers of the weights).  Each workgroup pulls half the activations, twice as many CUs work.
     auto rows2_for = [&](int groups) { return rows_of_32(c->shape, M, groups); };
-    // computing workgroups of a launch over `groups` column groups
-    auto compute_wgs = [&](int groups, bool r2, int row_split) {
-        if (r2) return 2 * m_groups * 8 * ceil_div(groups, 8);
-        if (row_split == 2) return 16 * ceil_div(groups, 8);
-        return m_groups > 1 ? m_groups * 8 * ceil_div(groups, 8) : groups;
-    };
-    // what the L2 warm-up of the launch before needs to know about a projection: its slabs are column tiles
-    auto proj_of = [&](const void *W, int n_blocks, int KB, int nbw, const ProjPlan &p) {
-        if (p.lds < 0) return Proj{W, ceil_div(n_blocks, nbw), nbw, KB, p.ks == 1, false};
-        const int tnb = lds_tile(p.lds).tnb;
-        return Proj{W, n_blocks / tnb, tnb, KB, p.ks == 1, true};   // whole tiles only: a ragged last one ends with the matrix
-    };
-    auto compute_wgs_lds = [&](int n_blocks, const ProjPlan &p) {
-        const LdsTile t = lds_tile(p.lds);
-        return 8 * ceil_div(ceil_div(n_blocks, t.tnb), 8) * ceil_div(M, 32 * t.tmt);
-    };
+    auto proj_of = [&](const void *W, int n_blocks, int KB, int nbw, const ProjPlan &p) { return Proj{W, slabs_of(p, n_blocks, KB, nbw)}; };
     const int groups_v = c->shape.head_groups();
     const ProjPlan &plan_qkv = plan.qkv, &plan_o = plan.o, &plan_gu = plan.gate_up, &plan_down = plan.down, &plan_head = plan.head;
-    // LDS tiles gain about 1 us where their weights are touched ahead, which a launch of less than 12 us loses and more (500
-    // rows of 1280: output projection 11.5 -> 14.8 us, gate/up 15.3 -> 14.0; 948 rows: 18.7 -> 18.2 and 25.0 -> 23.2).
-    auto warm = [&](int cur_groups, double cur_us, const Proj &nx) {
+    auto warm = [&](int cur_wgs, double cur_us, const Proj &nx) {
         a.pf_wgs = 0;
-        if (!c->l2_warm || tile || !nx.whole || !nx.W || (nx.lds && cur_us < 12.0)) return;
-        const uint32_t slab = (uint32_t)nx.nbw * nx.KB * 1024;
-        int fit = (int)std::min<size_t>(nx.groups, ((size_t)24 << 20) / slab);   // what the L2s hold beside the current weights
-        int wgs = (int)(((size_t)fit * slab / (96 << 10) + 7) / 8 * 8);
-        wgs = std::min(wgs, (n_cus - cur_groups) / 8 * 8);
-        if (wgs < 8 || (m_groups > 1 && wgs < 32)) return;   // long-window launches: a handful of CUs only delays them
-        // few CUs left: touch no more than they get through while the launch computes (a CU streams ~45 GB/s from
-        // HBM, the launches take 7-10 us: 320 KB each), the first slabs
-        fit = (int)std::min<size_t>(fit, (size_t)wgs * (320 << 10) / slab);
-        if (fit < 1) return;
-        a.pf_base = (const char *)nx.W; a.pf_slab_bytes = slab; a.pf_groups = fit; a.pf_wgs = wgs; a.pf_sink = c->pf_sink;
+        if (!c->l2_warm || tile || !nx.W) return;
+        const Touch t = touch(c->shape, M, cur_wgs, cur_us, nx.slabs);
+        if (!t.wgs) return;
+        a.pf_base = (const char *)nx.W; a.pf_slab_bytes = (uint32_t)nx.slabs.nbw * nx.slabs.KB * 1024; a.pf_groups = t.slabs; a.pf_wgs = t.wgs; a.pf_sink = c->pf_sink;
     };
     // The same for the keys and values of the next one-pass attention launch (one workgroup per (head, segment), in
     // that order); call after warm(): takes what is left of the CUs.
@@ -511,7 +485,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     // workgroup; the loop is bound by what a CU's L1 delivers).  Measured on the 36 x 1280 shape: output, down and QKV
     // projections (40-60 groups) gain, gate/up (108 groups: too few CUs left for the warm-up workgroups) loses.
     auto row_split_for = [&](int groups) { return MT == 1 && M > 16 && groups <= 64 && !(md.kernel_flags & SJD_NO_ROW_SPLIT) ? 2 : 1; };
-    const Proj none = {nullptr, 0, 0, 0, false, false};
+    const Proj none = {nullptr, {}};
     const bool mixed_ok = !(md.kernel_flags & SJD_NO_MIXED_WIDTH);
     // LDS-tile and tile kernels (and row groups with the gains in the rows) take the RMSNorm row sums of squares from the kernel
     // that wrote the residual stream: embedding gather, whole-K output / down projection or split-K reduction
@@ -542,7 +516,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             a.ksplit = ceil_div(a.KB, a.kb_per_split);
             if (a.ksplit == 1) {
                 ssq_n = ceil_div(nb, lds_tile(plan.lds).cb);
-                warm(compute_wgs_lds(nb, plan), plan.us, nx);
+                warm(lds_wgs(plan.lds, M, nb), plan.us, nx);
                 SJD_LAUNCH(c, cls, launch_lds<EPI_RESID>(st, a, nb, plan.lds));
                 a.pf_wgs = 0;
                 return SJD_OK;
@@ -571,7 +545,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             a.row_split = row_split_for(groups);
             const bool r2 = rows2_for(groups);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
-            const int n_compute = compute_wgs(groups, r2, a.row_split);
+            const int n_compute = row_group_wgs(M, groups, r2, a.row_split);
             warm(n_compute, plan.us, nx);
             if (kv_next) warm_kv(n_compute, *kv_next);
             ssq_n = groups;
@@ -606,7 +580,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         } else if (plan_qkv.lds >= 0) {
             whole_k();
             use_ssq();
-            warm(compute_wgs_lds(groups_qkv * 2, plan_qkv), plan_qkv.us, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
+            warm(lds_wgs(plan_qkv.lds, M, groups_qkv * 2), plan_qkv.us, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_lds<EPI_QKV>(st, a, groups_qkv * 2, plan_qkv.lds));
             a.pf_wgs = 0;
         } else {
@@ -615,7 +589,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             a.row_split = row_split_for(groups_qkv);
             const bool r2 = rows2_for(groups_qkv);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
-            const int n_compute = compute_wgs(groups_qkv, r2, a.row_split);
+            const int n_compute = row_group_wgs(M, groups_qkv, r2, a.row_split);
             warm(n_compute, plan_qkv.us, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
             if (l == 0) warm_kv(n_compute, pool);  // later layers: requested by the down projection before them
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_skinny<EPI_QKV>(st, a, r2 ? 1 : MT, groups_qkv, 2, nw_for(groups_qkv)));
@@ -636,7 +610,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         } else if (plan_gu.lds >= 0) {
             whole_k();
             use_ssq();
-            warm(compute_wgs_lds(F / 32 * 2, plan_gu), plan_gu.us, with_w(proj_down0, lw.wdown));
+            warm(lds_wgs(plan_gu.lds, M, F / 32 * 2), plan_gu.us, with_w(proj_down0, lw.wdown));
             SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_lds<EPI_SWIGLU>(st, a, F / 32 * 2, plan_gu.lds));
             a.pf_wgs = 0;
         } else {
@@ -645,7 +619,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             a.row_split = row_split_for(F / 32);
             const bool r2 = rows2_for(F / 32);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
-            const int n_compute = compute_wgs(F / 32, r2, a.row_split);
+            const int n_compute = row_group_wgs(M, F / 32, r2, a.row_split);
             warm(n_compute, plan_gu.us, with_w(proj_down0, lw.wdown));
             if (mixed_ok && skinny_mixed_applies(a, F / 32, 2, nw_for(F / 32))) SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_skinny_mixed<EPI_SWIGLU>(st, a, MT, F / 32));
             else SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_skinny<EPI_SWIGLU>(st, a, r2 ? 1 : MT, F / 32, 2, nw_for(F / 32)));

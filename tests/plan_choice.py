@@ -13,24 +13,33 @@ int main() {
     while (scanf("%d %d %d %d %d %d %d %d", &s.d_model, &s.n_heads, &s.n_kv_heads, &s.d_ff, &s.n_sampled, &s.kernel_flags, &M, &win32) == 8) {
         s.n_cus = 256;
         const ForwardPlan f = forward_plan(s, M, win32 != 0);
-        const int d64 = plan_div(s.d_model, 64) * 2;
-        auto mixed = [&](int blocks, int ks) { return (int)tile_two_heights(M, blocks, ks, s.n_cus); };
-        auto rows = [&](int blocks, int ks) { return tile_rows_for(M, blocks, ks, s.n_cus); };
-        const int ko = tile_splits(s, M, s.q_dim() / 16), kd = tile_splits(s, M, s.d_ff / 16);
-        printf("%d %d %d %d %d  ", f.qkv.tile, f.o.tile, f.gate_up.tile, f.down.tile, f.head.tile);
-        printf("%d  %d %d  %d %d  %d %d  %d %d  %d %d  %d %d %d %d  %d %d %d %d  %d %d\n", f.tile, f.qkv.lds, f.qkv.ks, f.o.lds, f.o.ks, f.gate_up.lds,
-               f.gate_up.ks, f.down.lds, f.down.ks, f.head.lds, f.head.ks, rows(s.qkv_groups() * 2, 1), rows(d64, ko), rows(s.gate_up_groups() * 2, 1),
-               rows(d64, kd), mixed(s.qkv_groups() * 2, 1), mixed(d64, ko), mixed(s.gate_up_groups() * 2, 1), mixed(d64, kd), ko, kd);
+        const int nbw = resid_nbw(s.d_model), nd = plan_div(plan_div(s.d_model, 32), nbw) * nbw, tiles_d = plan_div(s.d_model, 64) * 2;
+        const int nq = s.qkv_groups() * 2, ng = s.gate_up_groups() * 2, nh = s.head_groups() * 2, KB = s.d_model / 16, KF = s.d_ff / 16;
+        const ProjPlan *p[5] = {&f.qkv, &f.o, &f.gate_up, &f.down, &f.head};
+        const int blocks[5] = {nq, tiles_d, ng, tiles_d, nh};
+        // workgroups that touch the weights of the projection behind: of launches through LDS tiles
+        auto touches = [&](const ProjPlan &w, int n_blocks, const ProjPlan &next, int next_blocks, int next_KB, int next_nbw) {
+            if (f.tile || w.lds < 0 || w.ks > 1) return 0;
+            return touch(s, M, lds_wgs(w.lds, M, n_blocks), w.us, slabs_of(next, next_blocks, next_KB, next_nbw)).wgs;
+        };
+        const int touched[5] = {touches(f.qkv, nq, f.o, nd, KB, nbw), touches(f.o, plan_div(s.d_model, 32), f.gate_up, ng, KB, 2),
+                                touches(f.gate_up, ng, f.down, nd, KF, nbw), touches(f.down, plan_div(s.d_model, 32), f.qkv, nq, KB, 2), 0};
+        for (int i = 0; i < 5; ++i)
+            printf("%d %d %d %d %d %d  ", p[i]->tile, p[i]->lds, p[i]->ks, p[i]->tile ? tile_rows_for(M, blocks[i], p[i]->ks, s.n_cus) : 0,
+                   p[i]->tile && i < 4 && tile_two_heights(M, blocks[i], p[i]->ks, s.n_cus), touched[i]);
+        printf("\n");
     }
 }
 """
 TILES, ROWGROUPS = 16, 4
+NAMES = ("qkv", "out", "gate_up", "down", "head")
 
 
 def choose(queries):
-    """queries: (arch dict, rows, window of a step with its head fused (0: prompt rows), kernel flags) -> a dict each: tile (every
-    projection through the tile kernels, whose heights, height mixes and K splits come along), by_tile (each projection on its own) and
-    per projection (LDS tile shape or -1, K splits)."""
+    """queries: (arch dict, rows, window of a step with its head fused (0: prompt rows), kernel flags) -> a dict each.  Per projection, by
+    name: (LDS tile shape or -1, K splits).  by_tile: whether it runs through the tile kernels (tile: whether any does), and where it does
+    tile_rows (of a workgroup) and two_heights (in one launch).  touches: how many workgroups of its launch, where that is one through
+    LDS tiles, touch the next projection's weights."""
     with tempfile.TemporaryDirectory() as tmp:
         src, exe = os.path.join(tmp, "main.cpp"), os.path.join(tmp, "main")
         with open(src, "w") as f:
@@ -44,13 +53,12 @@ def choose(queries):
     res = []
     for line in out.splitlines():
         v = [int(x) for x in line.split()]
-        by_tile, v = v[:5], v[5:]
-        names = ("qkv", "out", "gate_up", "down")
-        r = {n: (v[1 + 2 * i], v[2 + 2 * i]) for i, n in enumerate(names + ("head",))}
-        r["tile"] = bool(v[0])
-        r["by_tile"] = {n: bool(t) for n, t in zip(names + ("head",), by_tile)}
-        r["tile_rows"] = dict(zip(names, v[11:15]))
-        r["two_heights"] = {n: bool(m) for n, m in zip(names, v[15:19])}
-        r["tile_splits"] = dict(zip(("out", "down"), v[19:21]))
+        by = {n: v[6 * i:6 * i + 6] for i, n in enumerate(NAMES)}
+        r = {n: (x[1], x[2]) for n, x in by.items()}
+        r["by_tile"] = {n: bool(x[0]) for n, x in by.items()}
+        r["tile"] = any(r["by_tile"][n] for n in NAMES[:4])
+        r["tile_rows"] = {n: x[3] for n, x in by.items() if x[0]}
+        r["two_heights"] = {n: bool(x[4]) for n, x in by.items() if x[0]}
+        r["touches"] = {n: x[5] for n, x in by.items()}
         res.append(r)
     return res

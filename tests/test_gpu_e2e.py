@@ -211,7 +211,8 @@ def _shape_weights(name, layers, random_gains):
     # mixes 256-row and 128-row tiles; 256-row workgroup tiles only; one tile height per launch
     ("cfg4", 2, 64, 3, 3, 0, None), ("cfg4", 2, 64, 2, 5, 0, None), ("cfg4", 2, 64, 2, 5, 16, None), ("cfg4", 2, 64, 2, 5, 16 + 64, None),
     ("cfg4", 2, 64, 2, 5, 16 + 256, None),
-    # 7 sequences: 448 rows, the tile kernels by choice (tests/test_plan_choice.py holds these cases to their kernels)
+    # 7 sequences: 448 rows, gate/up through the tile kernels by choice, beside LDS tiles (tests/test_plan_choice.py holds these cases to
+    # their kernels)
     ("cfg4", 2, 64, 1, 7, 0, None)])
 def test_benchmark_shapes_bf16(oracle, name, layers, prompt, steps, S, flags, window):
     """The benchmark shapes: full depth at short context for cfg1; the 7B-class widths, heads, GQA, vocabulary

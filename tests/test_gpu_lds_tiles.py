@@ -87,7 +87,7 @@ def _forward64(arch, w, tokens, last):
 
 
 @pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens", CASES)
-def test_against_float64(d, heads, kv, ff, ids, window, lens):
+def test_against_float64(d, heads, kv, ff, ids, window, lens, kernels=0):
     import torch
     import paper_2512_07503_amd as sjd
     arch = case_arch(d, heads, kv, ff, ids)
@@ -98,7 +98,7 @@ def test_against_float64(d, heads, kv, ff, ids, window, lens):
     uncond = [rng.integers(0, arch["vocab"], u).astype(np.int32) for _, u in lens]
     out = []
     for flags in (0, sjd.NO_HEAD_FUSION):
-        g = sjd.Decoder(arch, w, "bf16", window, max_ctx, max_seqs=S, top_k=200, seed=5, kernel_flags=flags | sjd.KEEP_LOGITS)
+        g = sjd.Decoder(arch, w, "bf16", window, max_ctx, max_seqs=S, top_k=200, seed=5, kernel_flags=flags | kernels | sjd.KEEP_LOGITS)
         assert g.prefill(cond, uncond, [n] * S) == 0
         windows = [g.window(s)[0] for s in range(S)]
         g.step()
@@ -123,6 +123,7 @@ BIG_CASES = [
     (2048, 16, 16, 5664, 3001, 1, [(1000, 1005)]),   # 2003, beside tile kernels: QKV
     (1280, 20, 20, 6912, 3001, 1, [(480, 480)]),     # 958, 64-wide heads: gate/up
     (3072, 24, 24, 8224, 3001, 2, [(700, 709)]),     # 1407, beside LDS tiles of other shapes: QKV
+    (4096, 32, 8, 5664, 3001, 33, [(1000, 1003)]),   # 2001, gains in the rows, beside tile kernels: QKV
 ]
 
 
@@ -155,14 +156,16 @@ def test_row_groups_of_many_rows_against_float64(d, heads, kv, ff, ids, window, 
 
 
 # Long prompts whose projections run through the tile kernels with K whole: output and down projections of 256-row tiles that
-# leave one partial sum of squares per column tile (32 of them), read by a 256 x 256 QKV and a 256-row gate/up; gains in the
-# weights (window 1) and in the rows (33).  Ragged in rows and in the MLP's columns; same bound.
+# leave one partial sum of squares per column tile (32 of them), read by a 256 x 256 QKV and a 256-row gate/up (by choice: the down
+# projection) or by tile kernels (flag 16: all of them); gains in the weights (window 1) and in the rows (33).  Ragged in rows and in the
+# MLP's columns; same bound.
 WHOLE_K_CASES = [
-    (4096, 32, 8, 5664, 3001, 1, [(1022, 1019)]),    # 2039 prompt rows
-    (4096, 32, 8, 5664, 3001, 33, [(1000, 1003)]),   # 2001
+    (4096, 32, 8, 5664, 3001, 1, [(1022, 1019)], 0),     # 2039 prompt rows
+    (4096, 32, 8, 5664, 3001, 1, [(1022, 1019)], 16),
+    (4096, 32, 8, 5664, 3001, 33, [(1000, 1003)], 16),   # 2001
 ]
 
 
-@pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens", WHOLE_K_CASES)
-def test_whole_k_tiles_against_float64(d, heads, kv, ff, ids, window, lens):
-    test_against_float64(d, heads, kv, ff, ids, window, lens)
+@pytest.mark.parametrize("d,heads,kv,ff,ids,window,lens,kernels", WHOLE_K_CASES)
+def test_whole_k_tiles_against_float64(d, heads, kv, ff, ids, window, lens, kernels):
+    test_against_float64(d, heads, kv, ff, ids, window, lens, kernels)

@@ -6,10 +6,12 @@ EPILOGUE = dict(qkv="QKV", gate_up="SWIGLU", head="HEAD")
 
 
 def _pairs(plan, with_head):
-    """(epilogue, LDS tile shape or -1) of the launches of a forward that does not run through the tile kernels."""
+    """(epilogue, LDS tile shape or -1) of the launches of a forward that do not run through the tile kernels."""
     out = set()
     for proj in ("qkv", "out", "gate_up", "down") + (("head",) if with_head else ()):
         shape, ks = plan[proj]
+        if plan["by_tile"][proj]:
+            continue
         out.add((EPILOGUE.get(proj, "RESID" if ks == 1 else "PARTIAL"), shape))
     return out
 
@@ -23,8 +25,7 @@ def test_the_lds_tile_cases_reach_every_shape_and_epilogue():
         heads += [True, True, False]
     reached = set()
     for plan, head in zip(plan_choice.choose(queries), heads):
-        if not plan["tile"]:
-            reached |= _pairs(plan, head)
+        reached |= _pairs(plan, head)
     shapes = {(e, s) for e in ("QKV", "SWIGLU", "RESID", "PARTIAL", "HEAD") for s in range(4)} | {("HEAD", 4)}
     assert shapes <= reached, shapes - reached
     # the fused head's shape is compared with two of the others: windows of 32 with and without it
@@ -38,11 +39,12 @@ def test_the_benchmark_shape_cases_reach_the_tile_kernels():
     def plan(seqs, flags):
         return plan_choice.choose([(arch, seqs * 64, 32, flags)])[0]
     assert not plan(3, 0)["tile"] and not plan(5, 0)["tile"]
-    p = plan(5, 16)
-    assert p["tile"] and p["two_heights"]["gate_up"] and 128 in p["tile_rows"].values()
-    p = plan(7, 0)
-    assert p["tile"] and p["two_heights"]["gate_up"] and p["tile_splits"]["down"] > 1
-    assert plan(8, 0)["tile"]                 # the benchmark's throughput batch
+    p = plan(5, 16)                           # all through the tile kernels, the down projection with its K split
+    assert all(p["by_tile"].values()) and p["two_heights"]["gate_up"] and 128 in p["tile_rows"].values() and p["down"][1] > 1
+    p = plan(7, 0)                            # gate/up and head alone, beside LDS tiles and a down projection whose K they split
+    assert [n for n, t in p["by_tile"].items() if t] == ["gate_up", "head"] and p["two_heights"]["gate_up"] and p["down"][0] >= 0 and p["down"][1] > 1
+    p = plan(8, 0)                            # the benchmark's throughput batch
+    assert p["by_tile"]["gate_up"] and p["by_tile"]["down"] and p["down"][1] == 4
     assert not plan(8, 4)["tile"]             # row groups only
     import test_gpu_e2e as e
     marks = [m for m in e.test_benchmark_shapes_bf16.pytestmark if m.name == "parametrize"][0]
@@ -60,16 +62,18 @@ def test_few_rows_and_the_row_group_flag_keep_the_row_groups():
 def test_the_big_tile_cases_reach_the_256_x_256_tiles():
     import test_gpu_lds_tiles as t
     queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, 0) for d, h, kv, ff, ids, _, lens in t.BIG_CASES]
-    got = [(n, p["tile"]) for p in plan_choice.choose(queries) for n in ("qkv", "gate_up") if p[n][0] == 5]
-    assert got == [("gate_up", False), ("qkv", True), ("gate_up", False), ("qkv", False)], got
+    got = [(n, p["by_tile"]["gate_up" if n == "qkv" else "qkv"]) for p in plan_choice.choose(queries) for n in ("qkv", "gate_up") if p[n][0] == 5]
+    assert got == [("gate_up", False), ("qkv", True), ("gate_up", False), ("qkv", False), ("qkv", True)], got
 
 
 def test_the_whole_k_cases_reach_the_tile_kernels_with_256_rows():
     import test_gpu_lds_tiles as t
-    queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, 0) for d, h, kv, ff, ids, _, lens in t.WHOLE_K_CASES]
-    for p in plan_choice.choose(queries):
-        assert p["tile"] and p["qkv"][0] == 5 and p["gate_up"][0] == -1 and p["tile_splits"] == dict(out=1, down=1)
-        assert all(p["tile_rows"][n] == 256 and not p["two_heights"][n] for n in ("out", "down")), p
+    assert {(c[5] == 1, c[7]) for c in t.WHOLE_K_CASES} == {(True, 0), (True, 16), (False, 16)}   # gains in the weights, in the rows
+    queries = [(t.case_arch(d, h, kv, ff, ids), sum(c + u - 2 for c, u in lens), 0, flags) for d, h, kv, ff, ids, _, lens, flags in t.WHOLE_K_CASES]
+    for p, q in zip(plan_choice.choose(queries), queries):
+        for n in ("out", "down") if q[3] else ("down",):
+            assert p["by_tile"][n] and p[n][1] == 1 and p["tile_rows"][n] == 256 and not p["two_heights"][n], p
+        assert p["by_tile"]["gate_up"] and p["tile_rows"]["gate_up"] == 256 and (p["by_tile"]["qkv"] if q[3] else p["qkv"][0] == 5), p
 
 
 def test_the_tile_before_row_groups_case_is_one():
@@ -101,3 +105,14 @@ def test_short_launches_of_narrow_models_stay_out_of_the_tile_kernels():
     longer = [(4096, 32, 32, 11008, 512), (4096, 32, 8, 14336, 2000), (3072, 24, 24, 12288, 1024), (2048, 16, 8, 10240, 1024)]
     plans = plan_choice.choose([(t.case_arch(d, h, kv, ff, 301), rows, 0, 0) for d, h, kv, ff, rows in short + longer])
     assert [p["tile"] for p in plans] == [False] * 4 + [True] * 4
+
+
+def test_the_touching_cases_touch():
+    import test_gpu_lds_tiles as t
+    import test_gpu_touched_weights as w
+    queries = []
+    for d, h, kv, ff, ids, window, lens in w.CASES:
+        a = t.case_arch(d, h, kv, ff, ids)
+        queries.append([(a, len(lens) * 2 * window, window, 0), (a, sum(c + u - 2 for c, u in lens), 0, 0)])
+    seen = [{n for p in plan_choice.choose(q) for n, wgs in p["touches"].items() if wgs} for q in queries]
+    assert all(seen) and set.union(*seen) == {"qkv", "out", "gate_up", "down"}, seen
