@@ -34,8 +34,8 @@ enum PlanEpi { PLAN_QKV = 0, PLAN_SWIGLU = 1, PLAN_RESID = 2, PLAN_PARTIAL = 3 }
 
 // The expected times below are fits to launches one after the other over weights from HBM, models of 768, 1280, 2048, 3072 and 4096
 // (grouped heads and not) at 66 to 2040 rows, 4 860 of them; the standard deviation of expected against measured is 5 to 9 % for
-// the row groups and the LDS tiles, 11 % for the tile kernels.  Shapes 2 and 5 and the tile kernels' rates are then set within
-// that, so that near ties fall as whole forwards measured.  Over those models and rows the four projections chosen take 1.021
+// the row groups and the LDS tiles, 11 % for the tile kernels.  Set by hand within that, so that near ties fall as whole forwards
+// measured: t1, t2 and tn of shapes 2, 4 and 5, and the rates in tile_us().  Over those models and rows the four projections chosen take 1.018
 // of the fastest launches' time in the geometric mean; with the rates measured before the kernels had their first arguments in
 // registers, and one family of kernels for a whole layer, it was 1.047.
 struct LdsTile { int tmt, tnb, cb; double t1, t2, tn, fixed[4], hbm, tflops; };
@@ -69,7 +69,8 @@ inline double skinny_us(PlanEpi epi, int M, int mt, int groups, int nbw, int KB,
     const double us = fixed[epi][mt - 1][nbw - 1] + (n - 1) * more[mt - 1][nbw - 1] + n * (double)(nbw + mt) * KB / ks * 1024.0 / 65e3;
     return std::max(us, 4.0 + (double)groups * nbw * KB * 1024.0 / 6e6);
 }
-// ... and of the kernel that adds ks partial sums of M rows of d columns
+// ... and what the kernel that adds ks partial sums of M rows of d columns adds to the launch before it (on its own it takes 2 us more, but with
+// those in here the 33 forwards in which a K split then went were 2.7 % slower)
 inline double reduce_us(int M, int d, int ks) { return 0.3 + (ks + 2.0) * M * d * 4.0 / 3.28e6; }
 
 // ---- fp32
