@@ -23,9 +23,9 @@ static bool own_time(const ProjShape &s, int M, PlanEpi epi, int blocks, int KB,
 }
 int main(int, char **v) {
     const int d = atoi(v[1]), hd = d % 128 ? 64 : 128, flags[] = {0, SJD_KERNELS_ROWGROUPS, SJD_KERNELS_TILES, SJD_NO_ROW_SPLIT, SJD_NO_L2_WARM};
-    for (int ff : {d / 32 * 32 + 32, 2 * d + 96, 7 * d / 2 / 32 * 32}) for (int kv : {1, 4}) for (int fl : flags) for (int M = 1; M <= 2200; ++M) {
+    for (int ff : {d / 32 * 32 + 32, 2 * d + 96, 7 * d / 2 / 32 * 32}) for (int kv : {1, 4}) for (int fl : flags) for (int cus : {256, 304, 64}) for (int M = 1; M <= 2200; M += cus == 256 ? 1 : 9) {
         if (d / hd % kv) continue;
-        const ProjShape s{d, d / hd, d / hd / kv, ff, 16384, 256, fl};
+        const ProjShape s{d, d / hd, d / hd / kv, ff, 16384, cus, fl};
         const ForwardPlan f = forward_plan(s, M, M % 64 == 0);
         if (!own_time(s, M, PLAN_QKV, s.qkv_groups() * 2, d / 16, f.qkv) || !own_time(s, M, PLAN_RESID, plan_div(d, 32), d / 16, f.o) ||
             !own_time(s, M, PLAN_SWIGLU, s.gate_up_groups() * 2, d / 16, f.gate_up) || !own_time(s, M, PLAN_RESID, plan_div(d, 32), ff / 16, f.down)) {
