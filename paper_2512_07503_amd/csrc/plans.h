@@ -169,11 +169,12 @@ inline ProjPlan row_groups(const ProjShape &s, PlanEpi epi, int M, int mt, int g
     return {-1, ks, skinny_us(epi, M, mt, groups, nbw, KB, ks, s.n_cus) + (ks > 1 ? reduce_us(M, s.d_model, ks) : 0.0)};
 }
 // QKV, gate/up: groups of two column blocks, whole K.  Row groups of a CU each whose weights the launch before has touched take
-// about 0.85 of the time (LDS tiles gain a tenth or nothing).
+// about 0.82 of the time (LDS tiles gain a tenth or nothing): 1024 wide, MLP of 3584, 71 and 128 prompt rows, gate/up in row groups 415
+// and 419 us, in LDS tiles 440 and 435.
 inline ProjPlan norm_plan(const ProjShape &s, PlanEpi epi, int M, int groups, bool tile_kernels, const ProjPlan &before) {
     const int KB = s.d_model / 16, mt = skinny_mt(s, M, groups);
     ProjPlan p = row_groups(s, epi, M, mt, groups, 2, KB, 1);
-    if (skinny_per_cu(M, mt, groups, 1, s.n_cus) == 1 && warms(s, M, before, (size_t)groups * 64 * s.d_model * 2)) p.us *= 0.85;
+    if (skinny_per_cu(M, mt, groups, 1, s.n_cus) == 1 && warms(s, M, before, (size_t)groups * 64 * s.d_model * 2)) p.us *= 0.82;
     return with_tiles(s, epi, M, groups * 2, KB, p, tile_kernels);
 }
 inline ProjPlan resid_row_groups(const ProjShape &s, int M, int K) {
@@ -207,14 +208,14 @@ struct ForwardPlan {
 inline ForwardPlan layer_plan(const ProjShape &s, int M, bool tile_kernels) {
     ForwardPlan f{};
     // An output / down projection in row groups touches the weights of the projection behind it, which gains by that: row groups where the
-    // two together are expected to take 2 % less.  70 prompt rows of 1280: down 9.6 us against 9.4 in LDS tiles, QKV then 7.1 against 8.4;
-    // 12 layers 469 -> 418 us, 86 rows of 640 396 -> 363.  (Below 2 % the other side was faster: 88 rows of 2048 193 against 204 us.)
+    // two together are expected to take 3 % less.  70 prompt rows of 1280: down 9.6 us against 9.4 in LDS tiles, QKV then 6.9 against 8.4;
+    // 12 layers 469 -> 418 us, 86 rows of 640 396 -> 363.  (Below 3 % the other side was faster: 88 rows of 2048 193 against 204 us.)
     auto pair = [&](int K, ProjPlan &first, PlanEpi epi, int groups, ProjPlan &next) {
         first = resid_plan(s, M, K, tile_kernels);
         next = norm_plan(s, epi, M, groups, tile_kernels, first);
         if (s.kernel_flags & SJD_KERNELS_TILES) return;
         const ProjPlan rg = resid_row_groups(s, M, K), after_rg = norm_plan(s, epi, M, groups, tile_kernels, rg);
-        if (rg.us + after_rg.us < 0.98 * (first.us + next.us)) { first = rg; next = after_rg; }
+        if (rg.us + after_rg.us < 0.97 * (first.us + next.us)) { first = rg; next = after_rg; }
     };
     pair(s.q_dim(), f.o, PLAN_SWIGLU, s.gate_up_groups(), f.gate_up);
     pair(s.d_ff, f.down, PLAN_QKV, s.qkv_groups(), f.qkv);

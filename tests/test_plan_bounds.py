@@ -11,7 +11,7 @@ _MAIN = r"""
 #include <cstdlib>
 #include <math.h>
 #include "plans.h"
-// the expected time of the kernels that the plan names (whether the weights are touched ahead: row groups, 0.85)
+// the expected time of the kernels that the plan names (whether the weights are touched ahead: row groups, 0.82)
 static bool own_time(const ProjShape &s, int M, PlanEpi epi, int blocks, int KB, const ProjPlan &p) {
     const int nbw = epi == PLAN_RESID ? resid_nbw(s.d_model) : 2, groups = plan_div(blocks, nbw);
     const int mt = p.ks > 1 ? (M <= 32 ? 1 : 2) : skinny_mt(s, M, groups);
@@ -19,7 +19,7 @@ static bool own_time(const ProjShape &s, int M, PlanEpi epi, int blocks, int KB,
     const double reduce = p.ks > 1 ? reduce_us(M, s.d_model, p.ks) : 0.0;
     const double us = (p.tile ? tile_us(e, M, blocks, KB, p.ks, s.n_cus) : p.lds >= 0 ? lds_us(p.lds, e, M, blocks, KB, p.ks, s.n_cus)
                                                                                    : skinny_us(e, M, mt, groups, nbw, KB, p.ks, s.n_cus)) + reduce;
-    return fabs(p.us - us) < 1e-9 * us || (!p.tile && p.lds < 0 && epi != PLAN_RESID && fabs(p.us - 0.85 * us) < 1e-9 * us);
+    return fabs(p.us - us) < 1e-9 * us || (!p.tile && p.lds < 0 && epi != PLAN_RESID && fabs(p.us - 0.82 * us) < 1e-9 * us);
 }
 int main(int, char **v) {
     const int d = atoi(v[1]), hd = d % 128 ? 64 : 128, flags[] = {0, SJD_KERNELS_ROWGROUPS, SJD_KERNELS_TILES, SJD_NO_ROW_SPLIT, SJD_NO_L2_WARM};

@@ -97,6 +97,9 @@ def test_row_groups_are_taken_for_what_they_touch_ahead():
     for d, h, kv, ff, rows in ((1280, 20, 20, 3456, 70), (1280, 20, 5, 3456, 67), (640, 10, 10, 3200, 86)):
         p = plan_choice.choose([(t.case_arch(d, h, kv, ff, 301), rows, 0, 0)])[0]
         assert p["down"] == (-1, 1) and p["qkv"] == (-1, 1), p
+    for rows in (71, 128):
+        p = plan_choice.choose([(t.case_arch(1024, 16, 8, 3584, 301), rows, 0, 0)])[0]
+        assert p["out"] == (-1, 1) and p["gate_up"] == (-1, 1), p
 
 
 def test_short_launches_of_narrow_models_stay_out_of_the_tile_kernels():
