@@ -68,8 +68,9 @@ enum {
     SJD_TILES_256_ROWS = 64,   /* bf16, >= 256 rows: every tile kernel launch uses 256-row
                                 * workgroup tiles (default: 128-row tiles where they
                                 * balance the CUs better)                              */
-    SJD_NO_ROW_SPLIT = 128,    /* bf16, 17..32 rows: projections of at most 64 column groups
-                                * with one workgroup per group (default: two, 16 rows each);
+    SJD_NO_ROW_SPLIT = 128,    /* bf16, up to 64 rows: projections of so few column groups
+                                * that their rows are split as well, with all rows in one
+                                * workgroup (default: 16 or 32 rows each);
                                 * more rows: 64-row groups also for projections of so few
                                 * column groups that 32-row groups would each get a CU     */
     SJD_NO_MIXED_WIDTH = 256,  /* bf16: no launch mixes workgroup shapes.  <= 64 rows: gate/up and

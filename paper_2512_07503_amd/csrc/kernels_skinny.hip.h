@@ -53,7 +53,6 @@ struct SkinnyArgs {
     int n_cus;         // compute units of the device (launch heuristics on the host)
     int groups;        // column groups (set by the launcher)
     int m_groups;      // row groups of MT * 32 rows, each run by its own workgroups over the same weights (M > 64)
-    int row_split;     // 2: (one 32-row tile, whole K) two workgroups per column group, 16 rows each; else 1
     int k_rot;         // 1: workgroup id starts its k-loop (id / 8) iterations in (see skinny_body), 0: all start at k = 0
     int n_heavy;       // mixed-width launch (set by its launcher): workgroups [0, n_heavy) take two column groups each
     float eps;
@@ -283,16 +282,16 @@ SJD_D void l2_warm_kv(const SkinnyArgs &a, int id, int first_id, int tid, int th
     if (sink == 0x9e3779b9u) *a.pf_sink = sink;
 }
 
-template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT, bool ROWS>
-SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0);
+template <int MT, int NBW, int NW, int DEPTH, int EPI, bool ROWS>
+SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int blk0);
 
 // ROWS: the norm gains are in the rows (QKV, SWIGLU, HEAD: sums of squares from row_ssq_part; RESID: gain, ssq_out)
-template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT, bool ROWS>
+template <int MT, int NBW, int NW, int DEPTH, int EPI, bool ROWS>
 __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SJD_HOT_PARAMS, SkinnyArgs a) {
     SJD_HOT_TAKE(a);
     const int tid = threadIdx.x;
-    // computing workgroups come first: one per column group, or (row_split 2) two, listed per XCD like row groups
-    const int n_compute = SPLIT ? 16 * ((a.groups + 7) / 8) : a.m_groups > 1 ? 8 * ((a.groups + 7) / 8) * a.m_groups : a.groups;
+    // computing workgroups come first
+    const int n_compute = a.m_groups > 1 ? 8 * ((a.groups + 7) / 8) * a.m_groups : a.groups;
     if ((int)blockIdx.x >= n_compute && (a.pf_wgs | a.kv_wgs)) {  // whole workgroup: only touches what the next launches read
         if ((int)blockIdx.x < n_compute + a.pf_wgs) l2_warm_next(a, blockIdx.x, n_compute, tid, NW * 64);
         else l2_warm_kv(a, blockIdx.x, n_compute + a.pf_wgs, tid, NW * 64);
@@ -308,16 +307,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(SJD_HOT_PARAMS, Sk
         mg = (blockIdx.x >> 3) % a.m_groups;
         if (g >= a.groups) return;
     }
-    // row_split 2: this workgroup computes rows [16 half, 16 half + 16) of the 32-row tile only.  The loop is bound
-    // by what the CU's L1 delivers, and half the rows are half the activation lines (lane l of a fragment holds row
-    // l % 32, so the other half's lanes simply do not load); the MFMAs run on zeros for them, which costs nothing here.
-    int half = 0;
-    if (SPLIT) {
-        g = (blockIdx.x & 7) + 8 * ((blockIdx.x >> 4));
-        half = (blockIdx.x >> 3) & 1;
-        if (g >= a.groups) return;
-    }
-    skinny_body<MT, NBW, NW, DEPTH, EPI, SPLIT, ROWS>(a, g, mg, half, g * NBW);
+    skinny_body<MT, NBW, NW, DEPTH, EPI, ROWS>(a, g, mg, g * NBW);
 }
 
 // Workgroups of two widths in one launch, for more than 256 column groups of two blocks (gate/up and vocabulary
@@ -332,18 +322,17 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_mixed_kernel(SJD_HOT_PARA
     static_assert(EPI == EPI_SWIGLU || EPI == EPI_HEAD, "epilogues that take any even number of blocks");
     const int w = blockIdx.x;
     // (the wide body's ring has 3/4 of the slots: 6 fragments per slot instead of 4, more bytes in flight all the same)
-    if (w < a.n_heavy) skinny_body<MT, 4, NW, DEPTH * 3 / 4, EPI, false, ROWS>(a, 2 * w, 0, 0, 4 * w);
-    else skinny_body<MT, 2, NW, DEPTH, EPI, false, ROWS>(a, a.n_heavy + w, 0, 0, 2 * (a.n_heavy + w));
+    if (w < a.n_heavy) skinny_body<MT, 4, NW, DEPTH * 3 / 4, EPI, ROWS>(a, 2 * w, 0, 4 * w);
+    else skinny_body<MT, 2, NW, DEPTH, EPI, ROWS>(a, a.n_heavy + w, 0, 2 * (a.n_heavy + w));
 }
 
 // The workgroup's work: column blocks [blk0, blk0 + NBW) (column group g of the QKV epilogue), row group mg.
-template <int MT, int NBW, int NW, int DEPTH, int EPI, bool SPLIT, bool ROWS>
-SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
+template <int MT, int NBW, int NW, int DEPTH, int EPI, bool ROWS>
+SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int blk0) {
     constexpr bool kNorm = EPI != EPI_RESID && EPI != EPI_PARTIAL;
     constexpr bool kSsqLoop = kNorm && !ROWS;   // sums of squares from the operands
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the k-loop control flow scalar
-    const bool a_lane = !SPLIT || ((lane >> 4) & 1) == half;  // SPLIT false: a constant, the loads below stay unconditional
     const int KB = a.KB, m_base = mg * MT * 32;
     const u32x4 *Wp = reinterpret_cast<const u32x4 *>(a.W) + (size_t)blk0 * KB * 64 + lane;
     const u32x4 *Ap = reinterpret_cast<const u32x4 *>(a.A) + (size_t)mg * MT * KB * 64 + lane;
@@ -363,10 +352,9 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
 
     // What the epilogue will need from memory is requested behind the first fragments of the weight stream, so that its
     // latency is not paid after the last MFMA: residual values (RESID), row destination and rotation (QKV).
-    // a tile's accumulators that hold this workgroup's rows (rows 0..15 are registers 0..7), of which a thread adds EPT:
-    // element hh of thread t is register v_of(hh) of lane t % 64
-    constexpr int NV = SPLIT ? 8 : 16, EPT = NV / NW;
-    auto v_of = [&](int hh) { return (SPLIT ? 8 * half : 0) + wave + NW * hh; };
+    // of a tile's 16 accumulators a thread adds EPT: element hh of thread t is register v_of(hh) of lane t % 64
+    constexpr int EPT = 16 / NW;
+    auto v_of = [&](int hh) { return wave + NW * hh; };
     [[maybe_unused]] float xpre[MT][NBW][EPT];
     float gpre[NBW];   // the next norm's gains of this thread's columns
     [[maybe_unused]] QkvRow qrow[MT][EPT];
@@ -425,7 +413,7 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
 #pragma unroll
             for (int i = 0; i < NBW; ++i) bq[s][i] = __builtin_nontemporal_load(Wp + ((size_t)i * KB + kb) * 64);
 #pragma unroll
-            for (int j = 0; j < MT; ++j) aq[s][j] = a_lane ? Ap[((size_t)j * KB + kb) * 64] : u32x4{0u, 0u, 0u, 0u};
+            for (int j = 0; j < MT; ++j) aq[s][j] = Ap[((size_t)j * KB + kb) * 64];
         }
         __builtin_amdgcn_sched_barrier(0);
         request_epilogue();
@@ -454,7 +442,7 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
 #pragma unroll
             for (int i = 0; i < NBW; ++i) bq[s][i] = __builtin_nontemporal_load(Wp + ((size_t)i * KB + kb) * 64);
 #pragma unroll
-            for (int j = 0; j < MT; ++j) aq[s][j] = a_lane ? Ap[((size_t)j * KB + kb) * 64] : u32x4{0u, 0u, 0u, 0u};
+            for (int j = 0; j < MT; ++j) aq[s][j] = Ap[((size_t)j * KB + kb) * 64];
         };
         // Steady state: groups of DEPTH iterations whose refills are all fragments that will be used.  The body is
         // branch-free so that the compiler counts outstanding loads exactly (a slot is consumed while the
@@ -518,10 +506,7 @@ SJD_D void skinny_body(const SkinnyArgs &a, int g, int mg, int half, int blk0) {
             for (int r = 0; r < NW; ++r) {
                 red_t e;
 #pragma unroll
-                for (int hh = 0; hh < EPT; ++hh) {
-                    const int v = r + NW * hh;
-                    e[hh] = SPLIT && half ? acc[j][i][(SPLIT ? 8 : 0) + v] : acc[j][i][v];
-                }
+                for (int hh = 0; hh < EPT; ++hh) e[hh] = acc[j][i][r + NW * hh];
                 red[wave][i][r][lane] = e;
             }
         __syncthreads();
@@ -771,20 +756,17 @@ inline hipError_t launch_skinny_nw(hipStream_t st, const SkinnyArgs &a_in, int M
     SkinnyArgs a = a_in;
     a.groups = groups;
     if (a.ksplit != 1) a.pf_wgs = a.kv_wgs = 0;
-    if (a.row_split == 2 && (MT != 1 || a.m_groups > 1 || a.ksplit != 1 || EPI == EPI_PARTIAL)) return hipErrorInvalidValue;
-    const int n_compute = a.row_split == 2 ? 16 * ((groups + 7) / 8) : a.m_groups > 1 ? 8 * ((groups + 7) / 8) * a.m_groups : groups;
+    const int n_compute = a.m_groups > 1 ? 8 * ((groups + 7) / 8) * a.m_groups : groups;
     const dim3 grid(n_compute + a.pf_wgs + a.kv_wgs, a.ksplit);
     constexpr bool kPair = EPI == EPI_QKV || EPI == EPI_SWIGLU;  // epilogues that need two column blocks
     if (nbw == 2) {
-        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, true, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
-        else if (MT == 1) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, false, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
-        else gemm_skinny_kernel<2, 2, NW, DEPTH, EPI, false, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
+        if (MT == 1) gemm_skinny_kernel<1, 2, NW, DEPTH, EPI, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
+        else gemm_skinny_kernel<2, 2, NW, DEPTH, EPI, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
     } else {
         if (kPair) return hipErrorInvalidValue;
         constexpr int E1 = kPair ? EPI_RESID : EPI;
-        if (MT == 1 && a.row_split == 2) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, true, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
-        else if (MT == 1) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, false, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
-        else gemm_skinny_kernel<2, 1, NW, DEPTH, E1, false, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
+        if (MT == 1) gemm_skinny_kernel<1, 1, NW, DEPTH, E1, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
+        else gemm_skinny_kernel<2, 1, NW, DEPTH, E1, ROWS><<<grid, NW * 64, 0, st>>>(SJD_HOT_PASS(a), a);
     }
     return hipGetLastError();
 }
@@ -792,7 +774,7 @@ inline hipError_t launch_skinny_nw(hipStream_t st, const SkinnyArgs &a_in, int M
 // More column groups (of two blocks) than CUs, one row group, whole K, 4 wavefronts: one workgroup per CU (up to twice as
 // many groups as CUs), the first groups - CUs of them two groups wide; beyond that every workgroup is two groups wide.
 inline bool skinny_mixed_applies(const SkinnyArgs &a, int groups, int nbw, int nw) {
-    return groups > a.n_cus && nbw == 2 && nw == 4 && a.m_groups <= 1 && a.ksplit == 1 && a.row_split != 2;
+    return groups > a.n_cus && nbw == 2 && nw == 4 && a.m_groups <= 1 && a.ksplit == 1;
 }
 template <int EPI>
 inline hipError_t launch_skinny_mixed(hipStream_t st, const SkinnyArgs &a_in, int MT, int groups) {

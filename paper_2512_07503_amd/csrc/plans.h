@@ -122,6 +122,15 @@ inline bool rows_of_32(const ProjShape &s, int M, int groups) {
     return M > 32 && 2 * plan_div(M, 64) * 8 * plan_div(groups, 8) <= s.n_cus && !(s.kernel_flags & SJD_NO_ROW_SPLIT);
 }
 
+// ---- few rows (kernels_few.hip.h): 16-row tiles of a workgroup, 0 where the row-group kernels run.  Wherever two workgroups per column
+// group and 16 or 32 rows still find a CU each; 64 rows of 1280 x 6912 (gate/up), 432 workgroups, took 2 % of a step more than 216
+// of whole groups.  (SJD_NO_ROW_SPLIT: the same sums, all rows in one workgroup.)
+inline int few_wgs(int M, int groups, int rt) { return 16 * plan_div(groups, 8) * plan_div(M, 16 * rt); }
+inline int few_rows(const ProjShape &s, int M, int groups) {
+    if (M > 64) return 0;
+    const int rt = few_wgs(M, groups, 1) <= s.n_cus ? 1 : few_wgs(M, groups, 2) <= s.n_cus ? 2 : 0;
+    return rt && (s.kernel_flags & SJD_NO_ROW_SPLIT) ? (M <= 16 ? 1 : M <= 32 ? 2 : 4) : rt;
+}
 // How a projection runs: row groups (lds < 0, not tile), LDS tiles of shape `lds`, or the tile kernels; ks: splits of
 // K (output / down projections, whose partial sums resid_reduce_kernel adds); us: its expected time, on which the choice rests.
 struct ProjPlan { int lds, ks; double us; bool tile = false; };
@@ -255,10 +264,9 @@ inline int lds_wgs(int cfg, int M, int n_blocks) {
     const LdsTile t = lds_tile(cfg);
     return 8 * plan_div(plan_div(n_blocks, t.tnb), 8) * plan_div(M, 32 * t.tmt);
 }
-inline int row_group_wgs(int M, int groups, bool rows32, int row_split) {
+inline int row_group_wgs(int M, int groups, bool rows32) {
     const int m_groups = plan_div(M, 64);
     if (rows32) return 2 * m_groups * 8 * plan_div(groups, 8);
-    if (row_split == 2) return 16 * plan_div(groups, 8);
     return m_groups > 1 ? m_groups * 8 * plan_div(groups, 8) : groups;
 }
 // What the launch before needs to know about a projection: n slabs (its column tiles) of nbw column blocks x KB k-blocks

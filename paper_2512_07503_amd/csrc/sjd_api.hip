@@ -19,6 +19,7 @@
 #include "kernels_forward.hip.h"
 #include "kernels_gemm.hip.h"
 #include "kernels_skinny.hip.h"
+#include "kernels_few.hip.h"
 #include "kernels_tile.hip.h"
 #include "kernels_lds.hip.h"
 
@@ -481,10 +482,6 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         a.kv_pool = pool;
         a.pf_sink = c->pf_sink;
     };
-    // few column groups and one 32-row tile: two workgroups per group, 16 rows each (half the activation lines per
-    // workgroup; the loop is bound by what a CU's L1 delivers).  Measured on the 36 x 1280 shape: output, down and QKV
-    // projections (40-60 groups) gain, gate/up (108 groups: too few CUs left for the warm-up workgroups) loses.
-    auto row_split_for = [&](int groups) { return MT == 1 && M > 16 && groups <= 64 && !(md.kernel_flags & SJD_NO_ROW_SPLIT) ? 2 : 1; };
     const Proj none = {nullptr, {}};
     const bool mixed_ok = !(md.kernel_flags & SJD_NO_MIXED_WIDTH);
     // LDS-tile and tile kernels (and row groups with the gains in the rows) take the RMSNorm row sums of squares from the kernel
@@ -542,16 +539,22 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
         const int groups = ceil_div(ceil_div(d, 32), nbw_d);
         if (plan.ks == 1) {
             whole_k();
-            a.row_split = row_split_for(groups);
+            // (few rows: no weights are touched ahead, kernels_few.hip.h)
+            if (const int rt = nbw_d == 1 ? few_rows(c->shape, M, groups) : 0) {
+                if (kv_next) warm_kv(few_wgs(M, groups, rt), *kv_next);
+                ssq_n = 2 * groups;
+                SJD_LAUNCH(c, cls, launch_few<EPI_RESID>(st, a, rt, groups));
+                a.kv_wgs = 0;
+                return SJD_OK;
+            }
             const bool r2 = rows2_for(groups);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
-            const int n_compute = row_group_wgs(M, groups, r2, a.row_split);
+            const int n_compute = row_group_wgs(M, groups, r2);
             warm(n_compute, plan.us, nx);
             if (kv_next) warm_kv(n_compute, *kv_next);
             ssq_n = groups;
             SJD_LAUNCH(c, cls, launch_skinny<EPI_RESID>(st, a, r2 ? 1 : MT, groups, nbw_d, nw_for(groups)));
             a.pf_wgs = a.kv_wgs = 0;
-            a.row_split = 1;
             a.m_groups = m_groups;
             return SJD_OK;
         }
@@ -583,18 +586,22 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             warm(lds_wgs(plan_qkv.lds, M, groups_qkv * 2), plan_qkv.us, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_lds<EPI_QKV>(st, a, groups_qkv * 2, plan_qkv.lds));
             a.pf_wgs = 0;
+        } else if (const int rt = few_rows(c->shape, M, groups_qkv)) {
+            whole_k();
+            skinny_ssq();
+            if (l == 0) warm_kv(few_wgs(M, groups_qkv, rt), pool);
+            SJD_LAUNCH(c, KC_GEMM_QKV, launch_few<EPI_QKV>(st, a, rt, groups_qkv));
+            a.kv_wgs = 0;
         } else {
             whole_k();
             skinny_ssq();
-            a.row_split = row_split_for(groups_qkv);
             const bool r2 = rows2_for(groups_qkv);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
-            const int n_compute = row_group_wgs(M, groups_qkv, r2, a.row_split);
+            const int n_compute = row_group_wgs(M, groups_qkv, r2);
             warm(n_compute, plan_qkv.us, with_head || l + 1 < md.n_layers ? with_w(proj_o0, lw.wo) : none);
             if (l == 0) warm_kv(n_compute, pool);  // later layers: requested by the down projection before them
             SJD_LAUNCH(c, KC_GEMM_QKV, launch_skinny<EPI_QKV>(st, a, r2 ? 1 : MT, groups_qkv, 2, nw_for(groups_qkv)));
             a.pf_wgs = a.kv_wgs = 0;
-            a.row_split = 1;
             a.m_groups = m_groups;
         }
         if (!with_head && l + 1 == md.n_layers) return SJD_OK;
@@ -613,18 +620,20 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
             warm(lds_wgs(plan_gu.lds, M, F / 32 * 2), plan_gu.us, with_w(proj_down0, lw.wdown));
             SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_lds<EPI_SWIGLU>(st, a, F / 32 * 2, plan_gu.lds));
             a.pf_wgs = 0;
+        } else if (const int rt = few_rows(c->shape, M, F / 32)) {
+            whole_k();
+            skinny_ssq();
+            SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_few<EPI_SWIGLU>(st, a, rt, F / 32));
         } else {
             whole_k();
             skinny_ssq();
-            a.row_split = row_split_for(F / 32);
             const bool r2 = rows2_for(F / 32);
             a.m_groups = r2 ? 2 * m_groups : m_groups;
-            const int n_compute = row_group_wgs(M, F / 32, r2, a.row_split);
+            const int n_compute = row_group_wgs(M, F / 32, r2);
             warm(n_compute, plan_gu.us, with_w(proj_down0, lw.wdown));
             if (mixed_ok && skinny_mixed_applies(a, F / 32, 2, nw_for(F / 32))) SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_skinny_mixed<EPI_SWIGLU>(st, a, MT, F / 32));
             else SJD_LAUNCH(c, KC_GEMM_GATEUP, launch_skinny<EPI_SWIGLU>(st, a, r2 ? 1 : MT, F / 32, 2, nw_for(F / 32)));
             a.pf_wgs = 0;
-            a.row_split = 1;
             a.m_groups = m_groups;
         }
         const Proj after_down = l + 1 < md.n_layers ? proj_of(c->layers[l + 1].wqkv, groups_qkv * 2, d / 16, 2, plan_qkv)
@@ -853,7 +862,7 @@ template <typename T> int alloc_buffers(sjd_ctx *c) {
         for (int m = 1; m <= c->pre_rows; ++m) cover(m);
         if ((rc = dev_alloc(c, &c->skinny_part, c->skinny_part_elems * sizeof(float)))) return rc;
         if ((rc = dev_alloc(c, &c->pf_sink, 256))) return rc;
-        if ((rc = dev_alloc(c, &c->row_ssq, (size_t)M * ceil_div(d, 32) * sizeof(float)))) return rc;
+        if ((rc = dev_alloc(c, &c->row_ssq, (size_t)std::max(M, 128) * ceil_div(d, 32) * sizeof(float)))) return rc;
         if ((rc = dev_alloc(c, &c->row_meta, (size_t)M * sizeof(QkvRow)))) return rc;
         if ((rc = dev_alloc(c, &c->row_rot, (size_t)M * (hd / 2) * sizeof(float2)))) return rc;
         c->l2_warm = !(md.kernel_flags & SJD_NO_L2_WARM);
