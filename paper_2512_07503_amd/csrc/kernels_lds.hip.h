@@ -5,9 +5,13 @@
 // owns (TMT / WM) x (TNB / WN) of them.  Both operands are stored fragment-major, so a fragment (1 KiB) goes from global
 // memory straight into LDS with one load per lane that never touches a register, lands in the order in which ds_read_b128
 // hands it to the matrix core (no bank conflict, no swizzle), and is read by every wavefront that needs it.
-// A pipeline stage is two k-steps of 16; S stages of LDS, all but the one being read in flight.  Per stage one barrier,
-// placed between the two k-steps: the second k-step's MFMAs run while the next stage's first fragments come out of LDS, the
-// first one's while the second's do.
+// A pipeline stage is two k-steps of 16; S stages of LDS, all but the one being read in flight.  Per stage one barrier; a stage's
+// MFMAs run on registers while the next stage's fragments come out of LDS into a second set.  With one set, read a k-step ahead,
+// every k-step ended in the latency of its last read: six prompts of 948 rows through 36 layers of 1280 and a step of 192
+// 5194 -> 5122 us a pass, the others of these kernels' cases 0 - 1 %.
+// What the epilogue reads (partial sums of squares, destinations of rows, residual values) is asked for ahead of the k-loop, as far
+// as registers go: left to the epilogue it took two or three round trips there, 2.0 of 10.3 us of 238 x 6912 x 1280, now 1.1
+// (a pass as above 5300 -> 5194, a 120-token prompt and a step 3043 -> 3015, 2793 -> 2755).
 //
 // The product is taken transposed (weights as the A operand of the MFMA): a lane then holds 4 consecutive output columns of
 // one row per accumulator quad, which is 8 bytes of the next GEMM's operand layout, 16 bytes of the residual stream or of the
@@ -97,14 +101,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARA
         for (int i = 0; i < NL; ++i) fetch1(i, st, buf);
     };
     const int wm = wave / WN, wn = wave % WN;
-    struct Frags { bf16x8 act[RT], wgt[CB]; };
-    auto read1 = [&](Frags &f, int o, int buf, int kk) {   // operand o of the wavefront: its row tiles, then its column blocks
-        if (o < RT) f.act[o < RT ? o : 0] = __builtin_bit_cast(bf16x8, smem[(buf * FR + (wm * RT + o) * 2 + kk) * 64 + lane]);
-        else f.wgt[o >= RT ? o - RT : 0] = __builtin_bit_cast(bf16x8, smem[(buf * FR + (TMT + wn * CB + o - RT) * 2 + kk) * 64 + lane]);
-    };
-    auto read = [&](Frags &f, int buf, int kk) {
-#pragma unroll
-        for (int o = 0; o < RT + CB; ++o) read1(f, o, buf, kk);
+    struct Frags { bf16x8 act[2][RT], wgt[2][CB]; };   // of a stage: both k-steps
+    constexpr int NR = 2 * (RT + CB);
+    auto read1 = [&](Frags &f, int o, int buf) {   // operand o of the wavefront: k-step by k-step, its row tiles, then its column blocks
+        const int kk = o / (RT + CB), u = o % (RT + CB);
+        if (u < RT) f.act[kk][u < RT ? u : 0] = __builtin_bit_cast(bf16x8, smem[(buf * FR + (wm * RT + u) * 2 + kk) * 64 + lane]);
+        else f.wgt[kk][u >= RT ? u - RT : 0] = __builtin_bit_cast(bf16x8, smem[(buf * FR + (TMT + wn * CB + u - RT) * 2 + kk) * 64 + lane]);
     };
     f32x16 acc[RT][CB];
 #pragma unroll
@@ -113,23 +115,25 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARA
         for (int i = 0; i < CB; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.0f;
-    // One k-step's MFMAs on `f`, with the reads of `nxt` (n_read operands) and the loads of a stage (n_load) spread between
-    // them: issued in a block they would hold the MFMAs behind them back while the load unit takes them one by one.
-    auto k_step = [&](const Frags &f, Frags &nxt, auto n_read, int rbuf, int rkk, auto n_load, int st, int lbuf) {
-        constexpr int NM = RT * CB, NR = decltype(n_read)::value, NO = NR + decltype(n_load)::value;
+    // One stage's MFMAs on `f`, with the reads of the next stage's operands into `nxt` (n_read of them) and the loads of a stage
+    // (n_load) spread between them: issued in a block they would hold the MFMAs behind them back while the load unit takes
+    // them one by one.
+    auto stage_step = [&](const Frags &f, Frags &nxt, auto n_read, int rbuf, auto n_load, int st, int lbuf) {
+        constexpr int NM = 2 * RT * CB, NRD = decltype(n_read)::value, NO = NRD + decltype(n_load)::value;
 #pragma unroll
         for (int u = 0; u < NM; ++u) {
-            acc[u / CB][u % CB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.wgt[u % CB], f.act[u / CB], acc[u / CB][u % CB], 0, 0, 0);
+            const int kk = u / (RT * CB), v = u % (RT * CB);
+            acc[v / CB][v % CB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.wgt[kk][v % CB], f.act[kk][v / CB], acc[v / CB][v % CB], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int o = u * NO / NM; o < (u + 1) * NO / NM; ++o) {
-                if (o < NR) read1(nxt, o, rbuf, rkk);
-                else fetch1(o >= NR ? o - NR : 0, st, lbuf);
+                if (o < NRD) read1(nxt, o, rbuf);
+                else fetch1(o >= NRD ? o - NRD : 0, st, lbuf);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    constexpr std::integral_constant<int, RT + CB> kReads{};
+    constexpr std::integral_constant<int, NR> kReads{};
     constexpr std::integral_constant<int, NL> kLoads{};
     constexpr std::integral_constant<int, 0> kNone{};
     auto barrier = [&]() {
@@ -138,50 +142,93 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARA
         asm volatile("" ::: "memory");
     };
 
+    // What the epilogue needs from memory and one lane can hold is requested ahead of the operands (older loads: the waits below, which
+    // count what is outstanding, cover them): partial sums of squares, even ones in the lower half wavefront, odd ones in the upper;
+    // destinations of the rows; residual values.
+    const int h4 = 4 * (lane >> 5), blk0 = ct * TNB + wn * CB;
+    constexpr int kSsq = !kNorm ? 0 : RT == 1 ? (NW == 8 ? 10 : 20) : RT == 2 ? 10 : RT == 3 ? 8 : 0;
+    constexpr bool kEarlyRow = EPI == EPI_QKV && RT <= 2 && NW < 8, kEarlyX = EPI == EPI_RESID && RT == 1;
+    [[maybe_unused]] float ssq[RT][kSsq + 1];
+    [[maybe_unused]] QkvRow qrow[RT];
+    [[maybe_unused]] float4 xin[CB][4];
+    auto row_m = [&](int j) { return min((rt * TMT + wm * RT + j) * 32 + (lane & 31), a.M - 1); };   // past the end: the last row
+    auto load_x = [&](int m) {
+#pragma unroll
+        for (int i = 0; i < CB; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)   // N is a multiple of 32: a block is inside or past the end as a whole
+                xin[i][q] = *reinterpret_cast<const float4 *>(a.x + (size_t)m * a.N + min(blk0 + i, n_blocks - 1) * 32 + 8 * q + h4);
+    };
+    if constexpr (kNorm) {
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+#pragma unroll
+            for (int u = 0; u < kSsq; ++u) ssq[j][u] = a.row_ssq_part[(size_t)min((lane >> 5) + 2 * u, a.row_ssq_n - 1) * a.M + row_m(j)];
+    }
+    if constexpr (kEarlyRow) {
+#pragma unroll
+        for (int j = 0; j < RT; ++j) qrow[j] = qkv_row(a, row_m(j));
+    }
+    if constexpr (kEarlyX) load_x(row_m(0));
+    __builtin_amdgcn_sched_barrier(0);
+
 #pragma unroll
     for (int s = 0; s < S; ++s)
         if (s < n_st) fetch(s, s);
     // stage 0 has landed once at most the younger stages' loads are outstanding
     wait_stages<NL>(n_st >= S ? S - 1 : 0);
     barrier();
-    Frags f0, f1;
-    if (n_st > 0) read(f0, 0, 0);
+    Frags f, g;
+    if (n_st > 0)
+#pragma unroll
+        for (int o = 0; o < NR; ++o) read1(f, o, 0);
     int it = 0, buf = 0;
-    for (; it + S < n_st; ++it) {
-        k_step(f0, f1, kReads, buf, 1, kNone, 0, 0);
+    auto next_of = [](int b) { return b + 1 == S ? 0 : b + 1; };
+    // stage `it` from cur, while nxt takes stage it + 1 out of LDS and stage it + S takes its buffer, which every wavefront has read
+    auto steady = [&](const Frags &cur, Frags &nxt) {
         wait_stages<NL>(S - 2);   // stage it + 1
         barrier();
-        const int next = buf + 1 == S ? 0 : buf + 1;
-        k_step(f1, f0, kReads, next, 0, kLoads, it + S, buf);
-        buf = next;
+        stage_step(cur, nxt, kReads, next_of(buf), kLoads, it + S, buf);
+        buf = next_of(buf);
+        ++it;
+    };
+    while (it + S + 1 < n_st) {
+        steady(f, g);
+        steady(g, f);
     }
-    // the last S stages: nothing left to fetch (t stages to go, conditions are uniform)
+    if (it + S < n_st) {
+        steady(f, g);
+        f = g;
+    }
+    // the last S stages: nothing left to fetch (t stages to go, conditions are uniform); operands of stage S are in f, of S - 1 in g, ...
+    if (((n_st - it) ^ S) & 1) g = f;
 #pragma unroll
     for (int t = S; t >= 1; --t) {
         if (n_st - it != t) continue;
-        k_step(f0, f1, kReads, buf, 1, kNone, 0, 0);
+        Frags &cur = (t ^ S) & 1 ? g : f, &nxt = (t ^ S) & 1 ? f : g;
         if (t > 1) {
             wait_stages<NL>(t - 2);
             barrier();
-            buf = buf + 1 == S ? 0 : buf + 1;
-            k_step(f1, f0, kReads, buf, 0, kNone, 0, 0);
+            stage_step(cur, nxt, kReads, next_of(buf), kNone, 0, 0);
+            buf = next_of(buf);
         } else {
-            k_step(f1, f0, kNone, 0, 0, kNone, 0, 0);
+            stage_step(cur, nxt, kNone, 0, kNone, 0, 0);
         }
         ++it;
     }
 
     // ---- epilogue: accumulator register v = 4 q + e of lane l is row l % 32 of the row tile, column 8 q + 4 (l / 32) + e of
     //      the column block
-    const int h4 = 4 * (lane >> 5);
     float inv[RT];
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
         inv[j] = 1.0f;
         if constexpr (kNorm) {
-            // 1 / rms: the row's partial sums of squares, even ones in the lower half wavefront, odd ones in the upper
-            const int m = (rt * TMT + wm * RT + j) * 32 + (lane & 31);
-            float t = m < a.M ? row_ssq_sum(a, m, lane >> 5, 2) : 0.0f;
+            // 1 / rms: those requested ahead of the k-loop, then the rest
+            float t = 0.0f;
+#pragma unroll
+            for (int u = 0; u < kSsq; ++u) t += (lane >> 5) + 2 * u < a.row_ssq_n ? ssq[j][u] : 0.0f;
+            if (2 * kSsq < a.row_ssq_n) t += row_ssq_sum(a, row_m(j), (lane >> 5) + 2 * kSsq, 2);
             t += __shfl_xor(t, 32, 64);
             inv[j] = 1.0f / sqrtf(t / (float)(KB * 16) + a.eps);
         }
@@ -231,11 +278,10 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARA
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
         const int m = (rt * TMT + wm * RT + j) * 32 + (lane & 31);
-        const int blk0 = ct * TNB + wn * CB;
         [[maybe_unused]] float sq = 0.0f;
         if (m < a.M) {
             if constexpr (EPI == EPI_QKV) {
-                const QkvRow r = qkv_row(a, m);
+                const QkvRow r = kEarlyRow ? qrow[j] : qkv_row(a, m);
                 const int pairs = a.hd >> 6, half = a.hd >> 1;
 #pragma unroll
                 for (int i = 0; i < CB; i += 2) {
@@ -288,15 +334,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_lds_kernel(SJD_TILE_PARA
                     }
                 }
             } else if constexpr (EPI == EPI_RESID) {
-                // N is a multiple of 32: a block is inside or past the end as a whole
-                float4 xin[CB][4];
-#pragma unroll
-                for (int i = 0; i < CB; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int n = (blk0 + i) * 32 + 8 * q + h4;
-                        if (n < a.N) xin[i][q] = *reinterpret_cast<const float4 *>(a.x + (size_t)m * a.N + n);
-                    }
+                if constexpr (!kEarlyX) load_x(m);
 #pragma unroll
                 for (int i = 0; i < CB; ++i) {
                     float4 gn[4];
