@@ -394,7 +394,7 @@ inline hipError_t launch_lds(hipStream_t st, const SkinnyArgs &a, int n_blocks, 
         (EPI != EPI_PARTIAL && a.ksplit != 1))
         return hipErrorInvalidValue;
 #define SJD_LDS_ONE(I, TMT, TNB, WM, WN, S)                                                                                    \
-    if constexpr (I < kLdsTiles || (I == kLdsTileHeadZ ? EPI == EPI_HEAD : EPI == EPI_QKV || EPI == EPI_SWIGLU))               \
+    if constexpr (I < kLdsTiles || (I == kLdsTileHeadZ ? EPI == EPI_HEAD : I == kLdsTileBig ? EPI == EPI_QKV || EPI == EPI_SWIGLU : EPI == EPI_QKV || EPI == EPI_RESID)) \
         if (cfg == I) {                                                                                                        \
             const int col_tiles = ceil_div(n_blocks, TNB), row_tiles = ceil_div(a.M, 32 * TMT);                                \
             const dim3 grid(8 * ceil_div(col_tiles, 8) * row_tiles + (a.ksplit == 1 ? a.pf_wgs : 0), a.ksplit);                \

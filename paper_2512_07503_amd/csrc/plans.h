@@ -26,9 +26,12 @@ constexpr int TILE_M = 256;   // rows of the larger tile of kernels_tile.hip.h
 // workgroup and its epilogue uncovered: it is for launches of one workgroup per CU at most.  Kernel times in repeated prompt
 // forwards, without -> with it: 2040 x 6144 x 4096 117 -> 101 us (128-row tiles), 900 x 12288 x 4096 110 -> 104 and 1008 x 12288
 // 113 -> 106 (the same), 1280 x 12288 136 -> 113 (192 x 128), 2040 x 6912 x 1280 50 -> 42 (192 x 128); with several per CU it
-// gains nothing (2048 x 28672 x 4096 434 us against 430).
-#define SJD_LDS_TILES(X) X(0, 2, 2, 2, 1, 6) X(1, 4, 2, 4, 1, 6) X(2, 4, 4, 4, 2, 5) X(3, 6, 4, 2, 2, 4) X(4, 4, 4, 2, 2, 4) X(5, 8, 8, 2, 4, 4)
-constexpr int kLdsTiles = 4, kLdsTileHeadZ = 4, kLdsTileBig = 5;
+// gains nothing (2048 x 28672 x 4096 434 us against 430).  Shape 6 (QKV, whole-K output and down), eight wavefronts on 256 x 128 and a
+// workgroup per CU as well, is for launches of one a CU that are long: 512 x 12288 x 4096 84 -> 66 us (128 x 64 tiles), 2048 x 4096 x
+// 4096 86 -> 74 (128 x 128), x 14336 249 -> 220 (tile kernels, whose four wavefronts wait for LDS in turn).  Prompts of 512 to 2048 rows,
+// 2048 to 5120 wide, 42 of them: 1.019 times in the geometric mean, 1.068 to 0.99.
+#define SJD_LDS_TILES(X) X(0, 2, 2, 2, 1, 6) X(1, 4, 2, 4, 1, 6) X(2, 4, 4, 4, 2, 5) X(3, 6, 4, 2, 2, 4) X(4, 4, 4, 2, 2, 4) X(5, 8, 8, 2, 4, 4) X(6, 8, 4, 4, 2, 6)
+constexpr int kLdsTiles = 4, kLdsTileHeadZ = 4, kLdsTileBig = 5, kLdsTileWide = 6;
 // What a projection's epilogue is, as far as its time goes.
 enum PlanEpi { PLAN_QKV = 0, PLAN_SWIGLU = 1, PLAN_RESID = 2, PLAN_PARTIAL = 3 };   // (the head: as SWIGLU)
 
@@ -43,9 +46,10 @@ struct LdsTile { int tmt, tnb, cb; double t1, t2, tn, fixed[4], hbm, tflops; };
 // first operands and epilogue; hbm: MB of weights per microsecond that a launch is held to; tflops: what it sustains at most (long
 // launches run into the power limit; short ones, at higher clocks, do not)
 inline LdsTile lds_tile(int cfg) {
-    static const LdsTile t[6] = {{2, 2, 2, 0.142, 0.228, 0.109, {4.1, 3.5, 4.4, 4.6}, 3.83, 480}, {4, 2, 2, 0.166, 0.316, 0.167, {4.5, 3.5, 5.9, 5.1}, 4.28, 780},
+    static const LdsTile t[7] = {{2, 2, 2, 0.142, 0.228, 0.109, {4.1, 3.5, 4.4, 4.6}, 3.83, 480}, {4, 2, 2, 0.166, 0.316, 0.167, {4.5, 3.5, 5.9, 5.1}, 4.28, 780},
                                  {4, 4, 2, 0.240, 0.511, 0.2634, {5.6, 3.9, 6.5, 5.7}, 4.75, 950}, {6, 4, 2, 0.305, 0.608, 0.328, {11.2, 7.8, 13.9, 6.2}, 4.38, 1090},
-                                 {4, 4, 2, 0.240, 0.511, 0.2634, {5.6, 3.9, 6.5, 5.7}, 4.75, 950}, {8, 8, 2, 0.697, 1e3, 1e3, {11.5, 9.6, 0.0, 0.0}, 5.91, 1110}};
+                                 {4, 4, 2, 0.240, 0.511, 0.2634, {5.6, 3.9, 6.5, 5.7}, 4.75, 950}, {8, 8, 2, 0.697, 1e3, 1e3, {11.5, 9.6, 0.0, 0.0}, 5.91, 1110},
+                                 {8, 4, 2, 0.43, 1e3, 1e3, {13.5, 0.0, 16.3, 0.0}, 5.91, 1170}};
     return t[cfg];
 }
 
@@ -159,6 +163,12 @@ inline ProjPlan with_tiles(const ProjShape &s, PlanEpi epi, int M, int n_blocks,
         const double big = lds_us(kLdsTileBig, epi, M, n_blocks, KB, 1, s.n_cus);
         if (big < p.us) p = {kLdsTileBig, 1, big};
     }
+    // (shape 6 in place of the tile kernels' output and down projections from K = 2 d on: 2000 rows of 4096, K = 14336 249 -> 220 us, a prompt
+    // with K = 8192 2.79 -> 2.71 ms; at 5664 it would be 2.42 -> 2.37 and the tile kernels stay; such projections have been compared from 1280 rows on)
+    if ((epi == PLAN_QKV || (resid && M > 1024)) && !(s.kernel_flags & SJD_KERNELS_TILES)) {
+        const double t = lds_us(kLdsTileWide, epi, M, n_blocks, KB, 1, s.n_cus);
+        if (t < p.us && !(p.tile && resid && KB * 16 < 2 * s.d_model)) p = {kLdsTileWide, 1, t};
+    }
     return p;
 }
 inline int skinny_mt(const ProjShape &s, int M, int groups) { return M <= 32 || rows_of_32(s, M, groups) ? 1 : 2; }   // 32-row tiles per row group
@@ -233,7 +243,7 @@ inline ForwardPlan layer_plan(const ProjShape &s, int M, bool tile_kernels) {
 }
 inline double layer_us(const ForwardPlan &f) { return f.qkv.us + f.o.us + f.gate_up.us + f.down.us; }
 inline ForwardPlan forward_plan(const ProjShape &s, int M, bool windows32) {
-    // The tile kernels are a third set of kernels for the same rows: only where a layer is expected to gain 2 % by them, which is
+    // The tile kernels are a third set of kernels for the same rows: only where a layer is expected to gain 1.5 % by them, which is
     // where the fits tell the sets apart (2000 rows of 1280: expected 0.4 % less, 8 % more as whole prompts), and 8 % in narrow models
     // whose gate/up takes less than 85 us: the fits have launches one by one, and so short ones lose more beside their neighbours than
     // that (84 forwards of 256 to 2040 rows that were expected to gain 2 to 10 %: below 3072 wide and 85 us 42 of 49 were slower, by 2.3 %
@@ -241,7 +251,7 @@ inline ForwardPlan forward_plan(const ProjShape &s, int M, bool windows32) {
     ForwardPlan f = layer_plan(s, M, (s.kernel_flags & SJD_KERNELS_TILES) != 0);
     if (M >= TILE_M && !(s.kernel_flags & (SJD_KERNELS_ROWGROUPS | SJD_KERNELS_TILES))) {
         const ForwardPlan g = layer_plan(s, M, true);
-        if (layer_us(g) < (s.d_model >= 3072 || g.gate_up.us >= 85.0 ? 0.98 : 0.92) * layer_us(f)) f = g;
+        if (layer_us(g) < (s.d_model >= 3072 || g.gate_up.us >= 85.0 ? 0.985 : 0.92) * layer_us(f)) f = g;
     }
     const int groups = s.head_groups(), mt = skinny_mt(s, M, groups);
     f.head = {-1, 1, skinny_us(PLAN_SWIGLU, M, mt, groups, 2, s.d_model / 16, 1, s.n_cus)};

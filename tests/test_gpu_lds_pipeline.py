@@ -25,3 +25,26 @@ def test_the_cases_reach_these_stages():
             if shape >= 0 and ks == 1:
                 seen.add(K // 32)
     assert {2, 3, 5, 6, 7, 10, 11, 12, 33} <= seen, seen
+
+
+# The 256 x 128 tiles of eight wavefronts, ragged in rows and columns: QKV (a last column tile of two blocks), output and down
+# projections of prompts and the QKV of a step; norm gains in the weights and (window 33) in the rows
+WIDE_CASES = [
+    (4096, 32, 32, 8192, 1, [(1022, 1019)], {"out", "down"}),     # 2039 prompt rows
+    (5120, 40, 8, 13824, 33, [(640, 642)], {"out", "down"}),      # 1280
+    (4096, 32, 32, 1024, 32, [(8, 7)] * 8, {"qkv"}),              # 512 rows of a step
+    (3264, 51, 17, 2560, 1, [(570, 567)], {"qkv"}),               # 1135 prompt rows, 170 column blocks
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,heads,kv,ff,window,lens,reached", WIDE_CASES)
+def test_wide_tiles(d, heads, kv, ff, window, lens, reached):
+    _against_float64(d, heads, kv, ff, 301, window, lens)
+
+
+def test_the_wide_cases_reach_the_wide_tiles():
+    for d, h, kv, ff, window, lens, reached in WIDE_CASES:
+        rows = len(lens) * 2 * window if window == 32 else sum(c + u - 2 for c, u in lens)
+        p = plan_choice.choose([(case_arch(d, h, kv, ff, 301), rows, 0, 0)])[0]
+        assert {n for n in ("qkv", "out", "down") if p[n] == (6, 1)} == reached, (d, rows, p)
