@@ -495,7 +495,7 @@ int forward_fused(sjd_ctx *c, const FwdRows &fr, bool with_head) {
     auto skinny_ssq = [&]() { if (!c->fold_gain) use_ssq(); };
     auto reduce = [&]() -> int {
         SJD_LAUNCH(c, KC_ADDNORM, after([&] {
-                       const dim3 grid(ceil_div(d, 1024), M);
+                       const int grid = reduce_grid(M, d);
                        if (a.gain) resid_reduce_kernel<true><<<grid, 256, 0, st>>>(c->skinny_part, a.ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out, a.gain);
                        else resid_reduce_kernel<false><<<grid, 256, 0, st>>>(c->skinny_part, a.ksplit, M, d, c->x, (bf16_t *)c->xn, ssq_out, nullptr);
                    }));
