@@ -13,6 +13,8 @@
 // Touching weights ahead beside these kernels costs what it gains: over 48 divisions of the idle CUs' time between the five launches
 // of a layer the 32-row step took 1.081 to 1.170 ms, 1.083 to 1.099 without.  (With all layers' weights in the memory-side cache
 // touching would pay, 1.053 -> 0.985 ms.)  Keys and values are touched by the launch ahead of the attention as before.
+// Error of the logits against float64 (tests/test_gpu_few_rows.py, 9 models, 22 sequences and branches): 0.9995 of the row-group kernels' in the
+// geometric mean, 0.977 to 1.008.
 // Five steps of loads are under way per wavefront: 2, 3 and 4 take 1 - 2 % longer, 7, 10 and 14 (down) 1 - 2 % as well.
 #pragma once
 #include "kernels_skinny.hip.h"
