@@ -104,7 +104,11 @@ inline int tile_rows_for(int M, int n_blocks, int ksplit, int n_cus) {
 }
 
 // Time of a launch: 32-wide K stages x the busiest CU's tiles (the column tiles of an XCD run on its CUs only): 0.25 us a
-// 128-row tile (0.33 alone on its CU), 0.47 a 256-row tile, 0.25 per 128 x 128 in a launch of both heights.
+// 128-row tile (0.33 alone on its CU), 0.47 a 256-row tile, 0.25 per 128 x 128 in a launch of both heights.  QKV projections, whose
+// epilogue is the longest, take more (medians of 20 launches of 3072 to 5120 wide, all heads their own): 256-row tiles 0.60 (1700 and 1964
+// rows of 4096 250 and 268 us, 1300 and 1900 of 5120 310 and 352), 128-row tiles 0.27 (1300 rows of 4096 185, 1700 of 5120 314), both heights 0.34 (1300 and
+// 1600 rows of 3072 126 and 137).  With the rates of the others, which expected 195 us of 268, 4096 wide prompts took 7 to 8 % longer
+// than with 128 x 128 LDS tiles (1964 rows, 226 us) or 192 x 128 (1300 rows, 153).
 inline bool tile_two_heights(int M, int n_blocks, int ksplit, int n_cus) {
     const int col_tiles = (n_blocks + 3) / 4, rt2 = (M + 255) / 256, rt1 = (M + 127) / 128;
     return ksplit == 1 && rt1 > rt2 && col_tiles * rt2 > n_cus && col_tiles * rt2 < 2 * n_cus && n_cus / rt2 >= 8 && (col_tiles * rt1) % n_cus != 0;
@@ -115,10 +119,10 @@ inline double tile_us(PlanEpi epi, int M, int n_blocks, int KB, int ksplit, int 
     const double stages = KB / (2.0 * ksplit);
     if (tile_two_heights(M, n_blocks, ksplit, n_cus)) {
         const int rt2 = (M + 255) / 256, ct_split = n_cus / rt2 / 8 * 8;
-        return fixed[epi] + stages * 0.25 * (2.0 * ct_split * rt2 + (double)(col_tiles - ct_split) * ((M + 127) / 128)) / n_cus;
+        return fixed[epi] + stages * (epi == PLAN_QKV ? 0.34 : 0.25) * (2.0 * ct_split * rt2 + (double)(col_tiles - ct_split) * ((M + 127) / 128)) / n_cus;
     }
     const int per_xcd = (col_tiles + 7) / 8 * ((M + rows - 1) / rows) * ksplit, cus = n_cus >= 8 ? n_cus / 8 : 1, n = (per_xcd + cus - 1) / cus;
-    return fixed[epi] + stages * (rows == 256 ? 0.465 * n : n == 1 ? 0.328 : 0.25 * n);
+    return fixed[epi] + stages * (rows == 256 ? (epi == PLAN_QKV ? 0.60 : 0.465) * n : n == 1 ? 0.328 : (epi == PLAN_QKV ? 0.27 : 0.25) * n);
 }
 
 // ---- the choice

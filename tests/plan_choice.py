@@ -62,3 +62,15 @@ def choose(queries):
         r["touches"] = {n: x[5] for n, x in by.items()}
         res.append(r)
     return res
+
+
+def evaluate(tmp, expression, queries):
+    """The value of an expression of plans.h in int q[8] (the query's numbers) for each query."""
+    src, exe = os.path.join(str(tmp), "expression.cpp"), os.path.join(str(tmp), "expression")
+    n = len(queries[0])
+    with open(src, "w") as f:
+        f.write('#include <cstdio>\n#include "plans.h"\nint main() {\n    int q[8] = {0}, n = 0;\n    while (scanf("%d", &q[n]) == 1)\n'
+                f'        if (++n == {n}) {{ n = 0; printf("%.9g\\n", (double)({expression})); }}\n}}\n')
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, src, "-o", exe], check=True)
+    out = subprocess.run([exe], input="\n".join(" ".join(map(str, q)) for q in queries), capture_output=True, text=True, check=True).stdout
+    return [float(x) for x in out.split()]
