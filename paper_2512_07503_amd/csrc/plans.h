@@ -169,11 +169,13 @@ inline ProjPlan with_tiles(const ProjShape &s, PlanEpi epi, int M, int n_blocks,
         const double big = lds_us(kLdsTileBig, epi, M, n_blocks, KB, 1, s.n_cus);
         if (big < p.us) p = {kLdsTileBig, 1, big};
     }
-    // (shape 6 in place of the tile kernels' output and down projections from K = 2 d on: 2000 rows of 4096, K = 14336 249 -> 220 us, a prompt
-    // with K = 8192 2.79 -> 2.71 ms; at 5664 it would be 2.42 -> 2.37 and the tile kernels stay; such projections have been compared from 1280 rows on)
+    // Shape 6 in place of the tile kernels' output and down projections: 2000 rows of 4096, K = 14336 249 -> 220 us; prompts of 4096 wide with
+    // MLPs of 5728 to 8032, 1926 to 2042 rows, 13 of them: 0.970 to 0.985 of the time.  (A line at K = 2 d kept these in the tile kernels, and at
+    // 1.75 d to 2 d the whole layer left them for it: MLP 8032, 1980 rows 3478 us, without the line 3376.)  Such projections have been compared from
+    // 1154 rows on: 12 prompts of 5120 wide, 1164 to 1278 rows, were 1.02 to 1.06 times faster with it.
     if ((epi == PLAN_QKV || (resid && M > 1024)) && !(s.kernel_flags & SJD_KERNELS_TILES)) {
         const double t = lds_us(kLdsTileWide, epi, M, n_blocks, KB, 1, s.n_cus);
-        if (t < p.us && !(p.tile && resid && KB * 16 < 2 * s.d_model)) p = {kLdsTileWide, 1, t};
+        if (t < p.us) p = {kLdsTileWide, 1, t};
     }
     return p;
 }

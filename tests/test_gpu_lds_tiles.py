@@ -156,12 +156,11 @@ def test_row_groups_of_many_rows_against_float64(d, heads, kv, ff, ids, window, 
 
 
 # Long prompts whose projections run through the tile kernels with K whole: output and down projections of 256-row tiles that
-# leave one partial sum of squares per column tile (32 of them), read by a 256 x 256 QKV and a 256-row gate/up (by choice: the down
-# projection) or by tile kernels (flag 16: all of them); gains in the weights (window 1) and in the rows (33).  Ragged in rows and in the
+# leave one partial sum of squares per column tile (64 and 32 of them), read by a 256 x 256 QKV and a 256-row gate/up (by choice, 8192 wide) or by tile kernels (flag 16: all of them); gains in the weights (window 1) and in the rows (33).  Ragged in rows and in the
 # MLP's columns; same bound.
 WHOLE_K_CASES = [
-    (4096, 32, 8, 5664, 3001, 1, [(1022, 1019)], 0),     # 2039 prompt rows
-    (4096, 32, 8, 5664, 3001, 1, [(1022, 1019)], 16),
+    (8192, 64, 16, 10912, 3001, 1, [(512, 511)], 0),     # 1021 prompt rows
+    (4096, 32, 8, 5664, 3001, 1, [(1022, 1019)], 16),    # 2039
     (4096, 32, 8, 5664, 3001, 33, [(1000, 1003)], 16),   # 2001
 ]
 
