@@ -59,9 +59,12 @@ inline double lds_us(int cfg, PlanEpi epi, int M, int n_blocks, int KB, int ks, 
     const int wgs_xcd = plan_div(plan_div(n_blocks, t.tnb), 8) * plan_div(M, 32 * t.tmt) * ks;
     const int n = plan_div(wgs_xcd, std::max(1, n_cus / 8));
     const double us = t.fixed[epi] + (double)plan_div(KB, 2 * ks) * (n == 1 ? t.t1 : n == 2 ? t.t2 : n * t.tn);
-    // (a launch of 0.42 TFLOP and more runs at lower clocks still: 1950 x 28672 x 4096 through shape 3 451 us, 1.03 PFLOP/s)
-    const double flops = 1024.0 * M * n_blocks * KB, sustained = t.tflops * (flops > 4.2e11 ? 0.955e6 : 1e6);
-    return std::max({us, 4.0 + n_blocks * (KB * 1024.0) / (t.hbm * 1e6), t.fixed[epi] + flops / sustained});
+    // Launches of shape 3 from 0.3 TFLOP on sustain its rate over whole row tiles, and at no lower clocks as they grow: gate/up of 4096 and 5120 wide, 24
+    // launches of 0.35 to 0.75 TFLOP, 1042 to 1100 TFLOP/s (1500 rows of 28672 x 4096 338 us, 1950 and 2048, 11 tiles of 192 both, 470 and 471; 1900 of
+    // 35840 x 5120 659).  Shorter ones of all shapes were fitted with the rows that are asked for, and the choice among them holds
+    // better with those: counted in whole tiles 61 prompts that would change took 1.017 times as long.
+    const double flops = 1024.0 * M * n_blocks * KB, done = cfg == 3 && flops > 3e11 ? flops * plan_div(M, 192) * 192 / M : flops;
+    return std::max({us, 4.0 + n_blocks * (KB * 1024.0) / (t.hbm * 1e6), t.fixed[epi] + done / (t.tflops * 1e6)});
 }
 // ... of a row-group launch (kernels_skinny.hip.h) over row groups of 32 mt rows and column groups of nbw blocks: a CU moves 65 GB/s
 // of weights and activations, its workgroups but the first cost `more` each on top, and all CUs move 6 TB/s of weights

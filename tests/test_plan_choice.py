@@ -151,3 +151,21 @@ def test_no_projection_leaves_out_a_256_x_128_tile_that_is_expected_to_be_faster
     best = "[&] { const ProjShape s{q[0], q[0] / 128, q[0] / 128 / q[1], q[2], 16384, 256, 0}; const ProjPlan p = forward_plan(s, q[3], false).down; return lds_us(6, PLAN_RESID, q[3], q[0] / 32, q[2] / 16, 1, 256) - p.us; }()"
     for q, slack in zip(queries, plan_choice.evaluate(tmp_path, best, queries)):
         assert slack > -1e-9, (q, slack)
+
+
+def test_no_launch_is_expected_to_slow_down_for_its_size(tmp_path):
+    """Gate/up of 28672 x 4096 and 35840 x 5120 in whole tiles of 192 and of 128 rows: one row tile more never costs more than a tile's share and 1 %
+    (a step of 4.5 % at 0.42 TFLOP once did), and long launches of 192 x 128 tiles take what was measured within 4 %."""
+    for d, blocks in ((4096, 896), (5120, 1120)):
+        for shape, rows in ((2, 128), (3, 192)):
+            tiles = range(4, 2049 // rows)
+            us = plan_choice.evaluate(tmp_path, "lds_us(q[0], PLAN_SWIGLU, q[1], q[2], q[3], 1, 256)", [(shape, rows * n, blocks, d // 16) for n in tiles])
+            share = plan_choice.evaluate(tmp_path, "plan_div(plan_div(plan_div(q[0], 4), 8) * q[1], 32)", [(blocks, n) for n in tiles])   # of the busiest CU
+            for n, a, b, u, v in zip(tiles, us, us[1:], share, share[1:]):
+                if v * n <= u * (n + 1):   # which grows no faster than the rows
+                    assert b <= a * (n + 1) / n * 1.01, (d, shape, n, a, b)
+    measured = [(4096, 14336, 1500, 337.8), (4096, 14336, 1700, 381.7), (4096, 14336, 1780, 425.0), (4096, 14336, 1800, 418.3), (4096, 14336, 1950, 470.3),
+                (4096, 14336, 2048, 470.9), (5120, 13824, 1480, 400.5), (5120, 13824, 1700, 460.3), (5120, 13824, 1900, 514.5), (5120, 13824, 2048, 568.2),
+                (5120, 17920, 1140, 406.2), (5120, 17920, 1300, 468.7), (5120, 17920, 1500, 526.5), (5120, 17920, 1900, 659.0), (5120, 17920, 2048, 747.6)]
+    for m, us in zip(measured, plan_choice.evaluate(tmp_path, "lds_us(3, PLAN_SWIGLU, q[2], q[1] / 16, q[0] / 16, 1, 256)", [m[:3] for m in measured])):
+        assert abs(us - m[3]) < 0.04 * m[3], (m, us)
