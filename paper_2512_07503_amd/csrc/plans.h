@@ -254,15 +254,16 @@ inline ForwardPlan layer_plan(const ProjShape &s, int M, bool tile_kernels) {
 }
 inline double layer_us(const ForwardPlan &f) { return f.qkv.us + f.o.us + f.gate_up.us + f.down.us; }
 inline ForwardPlan forward_plan(const ProjShape &s, int M, bool windows32) {
-    // The tile kernels are a third set of kernels for the same rows: only where a layer is expected to gain 1.5 % by them, which is
-    // where the fits tell the sets apart (2000 rows of 1280: expected 0.4 % less, 8 % more as whole prompts), and 8 % in narrow models
+    // The tile kernels are a third set of kernels for the same rows: only where a layer is expected to gain 2 % by them, which is
+    // where the fits tell the sets apart (2000 rows of 1280: expected 0.4 % less, 8 % more as whole prompts; 34 prompts of 2560 to 5120 wide, 396 to 2044 rows,
+    // that were expected to gain 1.5 to 2 %: 28 of them slower through the tile kernels, all in the mean by 1.3 %, 5.8 % at most), and 8 % in narrow models
     // whose gate/up takes less than 85 us: the fits have launches one by one, and so short ones lose more beside their neighbours than
     // that (84 forwards of 256 to 2040 rows that were expected to gain 2 to 10 %: below 3072 wide and 85 us 42 of 49 were slower, by 2.3 %
     // in the mean; the other 35 were 1.4 % faster).
     ForwardPlan f = layer_plan(s, M, (s.kernel_flags & SJD_KERNELS_TILES) != 0);
     if (M >= TILE_M && !(s.kernel_flags & (SJD_KERNELS_ROWGROUPS | SJD_KERNELS_TILES))) {
         const ForwardPlan g = layer_plan(s, M, true);
-        if (layer_us(g) < (s.d_model >= 3072 || g.gate_up.us >= 85.0 ? 0.985 : 0.92) * layer_us(f)) f = g;
+        if (layer_us(g) < (s.d_model >= 3072 || g.gate_up.us >= 85.0 ? 0.98 : 0.92) * layer_us(f)) f = g;
     }
     const int groups = s.head_groups(), mt = skinny_mt(s, M, groups);
     f.head = {-1, 1, skinny_us(PLAN_SWIGLU, M, mt, groups, 2, s.d_model / 16, 1, s.n_cus)};
