@@ -137,7 +137,8 @@ inline bool rows_of_32(const ProjShape &s, int M, int groups) {
 
 // ---- few rows (kernels_few.hip.h): 16-row tiles of a workgroup, 0 where the row-group kernels run.  Wherever two workgroups per column
 // group and 16 or 32 rows still find a CU each; 64 rows of 1280 x 6912 (gate/up), 432 workgroups, took 2 % of a step more than 216
-// of whole groups.  (SJD_NO_ROW_SPLIT: the same sums, all rows in one workgroup.)
+// of whole groups.  (SJD_NO_ROW_SPLIT: all rows in one workgroup; the same sums together with SJD_NO_K_ROTATION, since a workgroup's number
+// says where its k starts.)
 inline int few_wgs(int M, int groups, int rt) { return 16 * plan_div(groups, 8) * plan_div(M, 16 * rt); }
 inline int few_rows(const ProjShape &s, int M, int groups) {
     if (M > 64) return 0;

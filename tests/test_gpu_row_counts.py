@@ -98,17 +98,18 @@ def test_fewer_sequences_than_the_context_holds(n_seqs, flags):
                 assert err < 1.5e-2
 
 
-@pytest.mark.parametrize("window", [16, 32])
-def test_row_splits_change_no_bit(window):
-    """A 1280-wide model (its MLP narrow enough that K is whole in every projection), 32 rows as two workgroups of 16 a column
-    group against one of 32, and 64 rows as groups of 32 against one of 64 (flag 128; every workgroup walking K from 0): the same
+@pytest.mark.parametrize("window,ff", [(16, 2560), (32, 2560), (24, 2048), (32, 2048)])
+def test_row_splits_change_no_bit(window, ff):
+    """A 1280-wide model (its MLP narrow enough that K is whole in every projection), up to 64 rows in workgroups of 16 and 32 against all of them
+    in one (flag 128; every workgroup walking K from 0, since with the rotation of k the block's number says where it starts).  MLP 2560: gate/up
+    of 64 rows in row groups of 32 and of 64; 2048: in the few-row kernels, four tiles of 16 rows with the flag.  The same
     sums in the same order, and a rotation whose operations the source fixes, so logits, keys and values agree bit for bit.
     (Which of the rotation's products was rounded ahead of the sum was once left to the compiler: one key in some 10^5 moves to
     the next bf16, and the pages hold 24 x 32 x 1280 keys of this step.)"""
     import numpy as np
     import paper_2512_07503_amd as sjd
     from test_gpu_lds_tiles import _weights, case_arch
-    arch = dict(case_arch(1280, 20, 20, 2560, 3001), n_layers=24)
+    arch = dict(case_arch(1280, 20, 20, ff, 3001), n_layers=24)
     w = _weights(arch, 17)
     runs = []
     for flags in (sjd.NO_K_ROTATION, sjd.NO_K_ROTATION | sjd.NO_ROW_SPLIT):
