@@ -10,9 +10,13 @@
 // 5.0 and 0.4 us more between two launches, and the launch in front of each was longer by the touching.
 // Steps of that model, 36 layers: window 16 1.137 -> 1.091 ms, window 1 behind a 120-token prompt 1.14 -> 1.06; 66 steps of models of 512
 // to 4096, 2 to 64 rows: 1.07 times in the geometric mean, none slower (2048 wide, 2 rows 308 -> 272 us; 3072 wide, 64 rows 518 -> 515).
-// Touching weights ahead beside these kernels costs what it gains: over 48 divisions of the idle CUs' time between the five launches
+// Touching weights ahead beside these kernels costs what it gains or more: over 48 divisions of the idle CUs' time between the five launches
 // of a layer the 32-row step took 1.081 to 1.170 ms, 1.083 to 1.099 without.  (With all layers' weights in the memory-side cache
 // touching would pay, 1.053 -> 0.985 ms.)  Keys and values are touched by the launch ahead of the attention as before.
+// That holds where the launch behind is one of row groups that finds its weights cold, too (gate/up of 33 to 64 rows: 7.4 us where the output projection's
+// launch touched them, now 9.1).  Steps with 48 to 200 KB of them touched by each CU that the output projection leaves idle: 1280 wide, 64 rows 1183 -> 1208 to
+// 1227 us, 40 rows 1188 -> 1196 to 1295; 1536 wide, 64 rows 992 -> 999 to 1072; 1024 wide (MLP 5632), 16 rows 758 -> 811 to 822; 2048 wide, 16 rows 991 ->
+// 1031 to 1060, 64 rows 1302 to 1322 -> 1295 to 1338; 1024 wide (MLP 2816), 64 rows 708 -> 703 to 709.  The touching workgroups end after the projection.
 // Error of the logits against float64 (tests/test_gpu_few_rows.py, 9 models, 22 sequences and branches): 0.9995 of the row-group kernels' in the
 // geometric mean, 0.977 to 1.008.
 // Five steps of loads are under way per wavefront: 2, 3 and 4 take 1 - 2 % longer, 7, 10 and 14 (down) 1 - 2 % as well.
