@@ -61,13 +61,13 @@ struct SkinnyArgs {
     bf16_t *xb;        // the same in bf16, fragment-major [M][N]
     int N;             // also the logits row length for HEAD
     // Per-row sums of squares of the input rows, as row_ssq_n partial sums per row written by the kernel that produced the
-    // rows, [row_ssq_n][M] (neighbouring lanes read neighbouring rows); NULL (row-group kernels only): taken from the
+    // rows, [row_ssq_n][M] (neighbouring lanes read neighbouring rows); NULL (row-group and few-row kernels only): taken from the
     // activation fragments inside the k-loop
     const float *row_ssq_part;
     int row_ssq_n;
     // RESID: where a kernel leaves such partial sums for the next one (may be NULL, but not for the tile kernels): one per
-    // column group of the row-group kernels, one per wavefront's columns of the LDS kernels, one per column tile of the tile
-    // kernels
+    // column group of the row-group kernels, two of the few-row kernels (one per half group), one per wavefront's columns of the LDS
+    // kernels, one per column tile of the tile kernels
     float *ssq_out;
     // Gains in the rows: RESID multiplies gain[n] (the next norm's) into the bf16 copy of the stream, and takes ssq_out from
     // the fp32 stream; NULL: the gains are in the weights

@@ -102,7 +102,9 @@ struct sjd_ctx {
     bool attn_onepass = false;             // regime of the launches being enqueued
     std::vector<int32_t> kv_host;          // committed cache positions per segment (sequence * 2 + branch)
     float *part_o = nullptr, *part_ml = nullptr;
-    float *row_ssq = nullptr;              // [up to ceil(d / 32)][M] partial sums of squares of the residual stream's rows
+    // Partial sums of squares of the residual stream's rows, [partial][M]: up to ceil(d / 32) of them per row, 2 ceil(d / 32) where the few-row kernels
+    // leave them (M <= 64), so max(M, 128) x ceil(d / 32) hold both
+    float *row_ssq = nullptr;
     QkvRow *row_meta = nullptr;            // per-row tables of the fused path, rewritten by every forward
     float2 *row_rot = nullptr;
     bool l2_warm = true;                   // projection launches touch the next projection's weights

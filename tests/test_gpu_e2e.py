@@ -46,7 +46,7 @@ def _lockstep(o, g, S, n_steps, tol_abs=None, tol_rel=None):
                                         ("small_tile", 80),
                                         # flag 32: no extra workgroups that warm the next launch's operands into L2
                                         ("small_fused64", 32),
-                                        # flag 128: one workgroup per column group instead of two with 16 rows each
+                                        # flag 128: all rows of a half column group in one workgroup instead of 16 or 32 rows each
                                         ("small_fused64", 128), ("small_fused128", 128),
                                         # flag 512: every workgroup walks K from 0 instead of from its own offset
                                         ("small_fused64", 512), ("small_fused128", 512),
