@@ -16,7 +16,7 @@
 // That holds where the launch behind is one of row groups that finds its weights cold, too (gate/up of 33 to 64 rows: 7.4 us where the output projection's
 // launch touched them, now 9.1).  Steps with 48 to 200 KB of them touched by each CU that the output projection leaves idle: 1280 wide, 64 rows 1183 -> 1208 to
 // 1227 us, 40 rows 1188 -> 1196 to 1295; 1536 wide, 64 rows 992 -> 999 to 1072; 1024 wide (MLP 5632), 16 rows 758 -> 811 to 822; 2048 wide, 16 rows 991 ->
-// 1031 to 1060, 64 rows 1302 to 1322 -> 1295 to 1338; 1024 wide (MLP 2816), 64 rows 708 -> 703 to 709.  The touching workgroups end after the projection.
+// 1031 to 1060, 64 rows 1302 to 1322 -> 1295 to 1338; 1024 wide (MLP 2816), 64 rows 708 -> 703 to 709.
 // Error of the logits against float64 (tests/test_gpu_few_rows.py, 9 models, 22 sequences and branches): 0.9995 of the row-group kernels' in the
 // geometric mean, 0.977 to 1.008.
 // Five steps of loads are under way per wavefront: 2, 3 and 4 take 1 - 2 % longer, 7, 10 and 14 (down) 1 - 2 % as well.
