@@ -714,8 +714,9 @@ SJD_D int block_inverse_cdf(F weight, int n, uint64_t u64, uint64_t *sums /* [20
     const int c0 = tid * per < n ? tid * per : n, c1 = c0 + per < n ? c0 + per : n;
     uint64_t mine = 0;
     // Batches with clamped, unconditional evaluation: their loads go out together.  No wider than a thread's share, since a residual weight
-    // is a search and two divisions: 16 rows of 256 kept pairs 11.8 -> 6.0 us a launch with one evaluation a thread instead of eight.
-    // (Rows in 1024 threads instead of 256: 1000 kept pairs 6.6 -> 7.2 us, 2000 8.8 -> 7.8, 0.1 % of a step; left at 256.)
+    // is a search and two divisions: 16 rows of 256 kept pairs 11.8 -> 6.4 us a launch with one evaluation a thread instead of eight, 1000
+    // 15.0 -> 11.3 with four; from 1025 on as before, but for more code: 2000 17.9 -> 18.2, 3000 30.4 -> 31.0.
+    // (Rows in 1024 threads instead of 256, of another model: 1000 kept pairs 6.6 -> 7.2 us, 2000 8.8 -> 7.8, 0.1 % of a step; left at 256.)
     auto sum = [&](auto batch) {
         constexpr int B = decltype(batch)::value;
         for (int i0 = c0; i0 < c1; i0 += B) {
